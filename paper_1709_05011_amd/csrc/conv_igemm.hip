@@ -1,4 +1,5 @@
-// Implicit-GEMM convolution kernels for gfx950 (fp32 operands, fp32 MFMA accumulation).
+// Implicit-GEMM convolution kernels for gfx950: bf16 forward / backward-data, the filter gradients, and the fallback for fp32
+// operands that the vector paths do not take (fp32 forward / backward-data: conv_split.hip).
 //
 // Forward and backward-data run as  D[m][n] = sum_kg A(m,kg) * B[n][kg]  where row m is an output
 // pixel (img, po, qo), column kg = (r, s, ci) walks the filter window with the channel innermost,
@@ -18,11 +19,10 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include "internal.h"
+#include "conv_common.h"
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 template <int VEC> struct VecT;
 template <> struct VecT<4> {
@@ -36,15 +36,6 @@ template <> struct VecT<1> {
 
 __device__ __forceinline__ float elem(const float4& v, int e) {
     return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-}
-
-// Blocks are dealt round-robin to the 8 XCDs, each with its own L2.  Re-number them so that every
-// XCD works on one contiguous run of tiles (neighbouring tiles share A rows and the whole filter).
-__device__ __forceinline__ int xcd_tile(int bid, int total) {
-    const int per = (total + 7) >> 3, rem = total & 7;
-    const int xcd = bid & 7, idx = bid >> 3;
-    if (rem == 0 || xcd < rem) return xcd * per + idx;
-    return rem * per + (xcd - rem) * (per - 1) + idx;
 }
 
 // Write one wave's accumulators (TM x TN tiles of 32x32) to D: plain rows, or the scatter form used by
@@ -243,15 +234,15 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward / backward-data kernel (channel counts that are multiples of 4, no dilated read).
+// Main forward / backward-data kernel for bf16 operands (channel counts that are multiples of 8, no dilated read).
 //
-// LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
+// LDS tile: [row][64 bytes] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
 // applied on the global side: the lane that owns LDS slot s of a row fetches chunk s ^ swz(row).
 // Positions outside the image, rows past M or N and columns past Kg fetch from a 16-byte block of zeros
 // instead, so every lane always loads and the loop has no branch.
 //
-// Pipeline per 16-wide k-step ("tile"): the tile two steps ahead travels global -> registers, the tile one
+// Pipeline per 32-wide k-step ("tile"): the tile two steps ahead travels global -> registers, the tile one
 // step ahead registers -> LDS (two LDS buffers), fragments are double-buffered in registers so that the LDS
 // reads of the next half-step and the global loads are issued in the shadow of the MFMAs.
 //
@@ -261,24 +252,7 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 // whose range covers only part of a tile's k-steps writes its accumulators to the workspace; a second small
 // kernel adds the parts of each such tile in k order (fixed order: bit-identical reruns) and stores it.
 // ------------------------------------------------------------------------------------------------
-__device__ __attribute__((aligned(16))) const float g_zero_chunk[4] = {0.f, 0.f, 0.f, 0.f};
-
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 2)) & 3; }
-
-// ok ? a : b on pointers by bit masking: never a branch, whatever the cost of computing a
-__device__ __forceinline__ const void* pick(bool ok, const void* a, const void* b) {
-    const uintptr_t m = (uintptr_t)0 - (uintptr_t)ok;
-    return reinterpret_cast<const void*>((reinterpret_cast<uintptr_t>(a) & m) | (reinterpret_cast<uintptr_t>(b) & ~m));
-}
-// 16-byte load through the global (not flat) path: a flat load would also count as an LDS operation
-__device__ __forceinline__ float4 load_global16(const void* ptr) {
-    typedef float gf4 __attribute__((ext_vector_type(4)));
-    const gf4 v = *(const __attribute__((address_space(1))) gf4*)(uintptr_t)ptr;
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-// This wave's LDS writes and reads are complete, then the workgroup barrier.  Global loads stay in flight
-// (__syncthreads() would wait for them too).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
 // Accumulators of one wave <-> a partial-tile slot in the workspace, in register order: every store
 // instruction writes 64 consecutive floats.
@@ -287,20 +261,14 @@ __device__ __forceinline__ size_t partial_index(int wave, int i, int j, int v, i
     return ((((size_t)wave * TM + i) * TN + j) * 16 + v) * 64 + lane;
 }
 
-// BF16: operands are bf16 (8 per 16-byte chunk, k-step 32), multiplied with v_mfma_f32_32x32x16_bf16 (lane l
-// feeds A[row l%32][k 8*(l/32) .. +7], i.e. exactly one LDS chunk per MFMA); the result is stored as bf16.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
+// Operands come 8 to a 16-byte chunk, k-step 32, multiplied with v_mfma_f32_32x32x16_bf16 (lane l feeds A[row l%32][k 8*(l/32) .. +7],
+// i.e. exactly one LDS chunk per MFMA); the result is stored as bf16.
 // UT ("uniform tap"): the channel count is a multiple of the k-step, so a k-step lies inside one filter tap
 // and its (r, s, first channel) are the same for every lane.  They are then tracked in scalar registers, the
 // operands are fetched with buffer loads (tile-relative 32-bit byte offset per lane + scalar offset of the
 // k-step), and a tap outside the image is a bit in a per-row mask that moves the lane's offset past the end
 // of the buffer, where the hardware returns zeros.  That leaves two vector ALU instructions per activation
 // load in the main loop; on this chip every vector ALU instruction displaces MFMA issue time.
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-constexpr unsigned kBufferWords3 = 0x00020000u;       // raw buffer, 32-bit data format
-constexpr unsigned kBufferBytes = 0x80000000u;        // buffer size given to the hardware; offsets with bit 31 set read zeros
-
 // ------------------------------------------------------------------------------------------------
 // Persistent form of the main kernel.  The grid is one round of resident blocks; each block walks its own
 // sequence of segments -- whole tiles (one per round of the launch), then its share of the stream-K
@@ -312,22 +280,18 @@ constexpr unsigned kBufferBytes = 0x80000000u;        // buffer size given to th
 // whose row part of the address is a scalar offset and whose bounds are the buffer's size (rows) and bit 31
 // of the lane offset (columns).
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ int div_by(int n, unsigned mul, unsigned shift) {       // n / d for 0 <= n < 2^31, see magic_for()
-    return mul ? (int)(__umulhi((unsigned)n, mul) >> shift) : n;
-}
-
 // Blocks per compute unit: 3 for tiles up to 128x128 (64 accumulator registers per lane), 2 for the 128x256 tile, 1 for
 // the 256x256 tile (run by eight waves, two per SIMD, each with 128 accumulator registers).
 constexpr int pk_blocks_per_cu(int bm, int bn) { return bm * bn >= 256 * 256 ? 1 : bm * bn > 128 * 128 ? 2 : 3; }
 // Waves along the columns of the tile: 2 (a 2 x 2 block of waves), or 4 for the 256x256 tile (2 x 4 waves of 128 x 64).
 constexpr int pk_waves_n(int bm, int bn) { return bm * bn >= 256 * 256 ? 4 : 2; }
 
-template <int BM, int BN, bool SMALLC, bool BF16, bool UT, bool SCATTER>
+template <int BM, int BN, bool SMALLC, bool UT, bool SCATTER>
 __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64, pk_blocks_per_cu(BM, BN) * pk_waves_n(BM, BN) / 2)
 conv_gemm_pk_kernel(const GemmConv p) {
-    using E = typename OutT<BF16>::type;
-    constexpr int ES = (int)sizeof(E);
-    constexpr int EPC = BF16 ? 8 : 4;
+    using E = uint16_t;
+    constexpr int ES = 2;
+    constexpr int EPC = 8;
     constexpr int BK = 4 * EPC;
     constexpr int WN_ = pk_waves_n(BM, BN), NWV = 2 * WN_;              // waves: 2 along the rows x WN_ along the columns
     constexpr int LA = BM / (16 * NWV), LB = BN / (16 * NWV), LPT = LA + LB;
@@ -547,17 +511,13 @@ conv_gemm_pk_kernel(const GemmConv p) {
         for (int j = 0; j < TN; ++j) fb[slot][j] = *reinterpret_cast<const float4*>(base + b_frag + j * 32 * 16 + ch);
     };
     // one group of MFMAs: every 32x32 tile of the wave advanced by one k-slice
-    auto mfma_group = [&](int slot, int e) __attribute__((always_inline)) {
-        if (BF16 && e != 0) return;
+    auto mfma_group = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                if constexpr (BF16)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
-                                                                        __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(elem(fa[slot][i], e), elem(fb[slot][j], e), acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
+                                                                    __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j], 0, 0, 0);
             }
     };
     auto clear_acc = [&]() __attribute__((always_inline)) {
@@ -597,7 +557,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
                 };
                 const bool hi = lane >= 32;
                 const int odd = lane & 1;
-                const bool pairs = BF16 && ((N_ | ldd_) & 1) == 0;
+                const bool pairs = ((N_ | ldd_) & 1) == 0;
                 if (m0 + BM <= M_) {
                     unsigned colpart[TN];                       // bit 31 past N: stays set after a pixel offset is added
 #pragma unroll
@@ -615,22 +575,17 @@ conv_gemm_pk_kernel(const GemmConv p) {
                             const unsigned row_a = hi ? o4 : o0, row_b = hi ? o5 : o1;     // rows of registers v and v + 1
 #pragma unroll
                             for (int j = 0; j < TN; ++j) {
-                                if constexpr (BF16) {
-                                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                                    typedef float f32x2 __attribute__((ext_vector_type(2)));
-                                    const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
-                                    const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
-                                    if (pairs) {                // as in the plain tile store: a lane stores a column pair of one row
-                                        const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc,
-                                                                              (int)(colpart[j] + (odd ? row_b : row_a)), 0, 0);
-                                    } else {
-                                        __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)(colpart[j] + row_a), 0, 0);
-                                        __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)(colpart[j] + row_b), 0, 0);
-                                    }
+                                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                                const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
+                                const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
+                                if (pairs) {                // as in the plain tile store: a lane stores a column pair of one row
+                                    const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
+                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc,
+                                                                          (int)(colpart[j] + (odd ? row_b : row_a)), 0, 0);
                                 } else {
-                                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)(colpart[j] + row_a), 0, 0);
-                                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v + 1]), d_rsrc, (int)(colpart[j] + row_b), 0, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)(colpart[j] + row_a), 0, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)(colpart[j] + row_b), 0, 0);
                                 }
                             }
                         }
@@ -655,10 +610,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
                                 const int soff = (int)px_off(m);
 #pragma unroll
                                 for (int j = 0; j < TN; ++j) {
-                                    if constexpr (BF16)
-                                        __builtin_amdgcn_raw_buffer_store_b16((short)lc_bf16_rne(acc[i][j][v]), d_rsrc, (int)d_voff[hs][j], soff, 0);
-                                    else
-                                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)d_voff[hs][j], soff, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)lc_bf16_rne(acc[i][j][v]), d_rsrc, (int)d_voff[hs][j], soff, 0);
                                 }
                             }
                 }
@@ -670,7 +622,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
                     (int)kBufferWords3);
                 // bf16 with an even row length: neighbouring lanes (neighbouring columns) trade values so that every
                 // lane stores a pair of columns as one dword -- even lanes for row r0, odd lanes for row r0 + 1.
-                const bool pairs = BF16 && ((N_ | ldd_) & 1) == 0;
+                const bool pairs = ((N_ | ldd_) & 1) == 0;
                 const int odd = lane & 1;
                 unsigned d_voff[TN];
 #pragma unroll
@@ -691,22 +643,17 @@ conv_gemm_pk_kernel(const GemmConv p) {
                         const int soff = r0 * ldd_ * ES;
 #pragma unroll
                         for (int j = 0; j < TN; ++j) {
-                            if constexpr (BF16) {
-                                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                                typedef float f32x2 __attribute__((ext_vector_type(2)));
-                                const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
-                                const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
-                                if (pairs) {
-                                    // u = {row r0 | row r0 + 1} of this lane's column; swap with the neighbouring lane
-                                    const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
-                                } else {
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
-                                }
+                            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                            typedef float f32x2 __attribute__((ext_vector_type(2)));
+                            const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
+                            const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
+                            if (pairs) {
+                                // u = {row r0 | row r0 + 1} of this lane's column; swap with the neighbouring lane
+                                const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
+                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
                             } else {
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)d_voff[j], soff, 0);
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v + 1]), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
+                                __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
+                                __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
                             }
                         }
                     }
@@ -727,11 +674,9 @@ conv_gemm_pk_kernel(const GemmConv p) {
 #pragma unroll
                             for (int v = 0; v < 16; v += 2) {
                                 float x0 = acc[i][j][v], x1 = acc[i][j][v + 1];
-                                if constexpr (BF16) {
-                                    const unsigned u = lc_bf16x2_rne(x0, x1);
-                                    x0 = __uint_as_float(u << 16);
-                                    x1 = __uint_as_float(u & 0xffff0000u);
-                                }
+                                const unsigned u = lc_bf16x2_rne(x0, x1);
+                                x0 = __uint_as_float(u << 16);
+                                x1 = __uint_as_float(u & 0xffff0000u);
                                 if (ragged) {
                                     const int row = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * fhalf + (v & 3);
                                     if (row >= M_) x0 = 0.f;
@@ -771,19 +716,15 @@ conv_gemm_pk_kernel(const GemmConv p) {
     // One k-step out of LDS buffer `cur` (a literal at both calls)
     auto step = [&](int cur, int f) __attribute__((always_inline)) {
         read_frags(cur, 1, 1);
-        mfma_group(0, 0);
-        mfma_group(0, 1);
+        mfma_group(0);
         __builtin_amdgcn_sched_barrier(0);
         sstore(cur ^ 1);                          // k-step f + 1: its buffer was last read one step ago
-        mfma_group(0, 2);
         __builtin_amdgcn_sched_barrier(0);
         if (f + 2 < F) load_step();               // k-step f + 2 into the registers just stored
-        mfma_group(0, 3);
         __builtin_amdgcn_sched_barrier(0);
         lds_barrier();
         read_frags(cur ^ 1, 0, 0);                // first half of k-step f + 1
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mfma_group(1, e);
+        mfma_group(1);
         if (++c_k == c_k1) {                      // the segment is complete: store it, the next step starts a new one
             __builtin_amdgcn_sched_barrier(0);
             epilogue();
@@ -804,10 +745,10 @@ conv_gemm_pk_kernel(const GemmConv p) {
 // Adds the parts of every tile that stream-K blocks split between them, in k order, and stores the tile.
 // Block (t, v) handles accumulator register v of every 32x32 MFMA tile of stream-K tile t, with the thread
 // geometry of the main kernel: 16 blocks per tile keep the whole chip busy on what is a small reduction.
-template <int BM, int BN, bool BF16>
+template <int BM, int BN>
 __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_kernel(const GemmConv p) {
     constexpr int WN_ = pk_waves_n(BM, BN);
-    constexpr int BK = BF16 ? 32 : 16, TM = BM / 64, TN = BN / (32 * WN_);
+    constexpr int BK = 32, TM = BM / 64, TN = BN / (32 * WN_);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / WN_, wn = wave % WN_;
     const int v = blockIdx.y;
@@ -843,7 +784,7 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
             for (int u = 0; u < 16; ++u) out[i][jj][u] = acc[i][jj][0];
     const int tile = p.dp_tiles + blockIdx.x;
     const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * BN;
-    store_tile<TM, TN, BF16>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
+    store_tile<TM, TN, true>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
 }
 
 // The column sums of the tiles that stream-K blocks shared (the main kernel sums the tiles it stores whole): block
@@ -1978,8 +1919,6 @@ __global__ void __launch_bounds__(256, 2) wgrad3x3_slab_kernel(const GemmWgrad p
         }
 }
 
-inline bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) == 0; }
-
 template <int BM, int BN, int BK, int VEC>
 lc_status launch_conv(const GemmConv& p, hipStream_t stream) {
     const long long tiles = (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
@@ -1997,50 +1936,12 @@ lc_status launch_wgrad(const GemmWgrad& p, hipStream_t stream) {
     return lc_end_call();
 }
 
-// Split of the output tiles into whole-tile blocks and stream-K blocks for a BM x BN tiling.
-struct SkPlan {
-    int dp_tiles, sk_blocks;
-    long long sk_iters;
-};
-
-int device_cu_count() {
-    static const int n = [] {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-        (void)hipGetLastError();
-        return cus;
-    }();
-    return n;
-}
-
-SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_split = true) {
-    SkPlan pl;
-    const long long rounds = tiles / resident_blocks;
-    long long dp = rounds * resident_blocks;
-    long long rest = tiles - dp;
-    pl.dp_tiles = (int)dp;
-    pl.sk_blocks = 0;
-    pl.sk_iters = 0;
-    if (rest == 0 || !allow_split || getenv("LARSCONV_NO_STREAMK")) {   // every round is full, or splitting tiles is not wanted
-        pl.dp_tiles = (int)tiles;
-        return pl;
-    }
-    pl.sk_iters = rest * nkt;
-    long long blocks = pl.sk_iters / 8;                      // at least 8 k-steps per stream-K block
-    if (blocks > resident_blocks) blocks = resident_blocks;
-    if (blocks < 1) blocks = 1;
-    pl.sk_blocks = (int)blocks;
-    return pl;
-}
-
 // Blocks of the main kernel that fit on the chip at once (the kernel's launch bounds hold it to this).
 inline int resident_blocks(int bm, int bn) { return pk_blocks_per_cu(bm, bn) * device_cu_count(); }
 
-// Tile of the main kernel for a problem.  fp32: 128 rows, 64 columns for narrow results, otherwise 128.  bf16
-// adds larger tiles, because its loop is bound by what moves through LDS per MFMA, and both the staging writes and
-// the fragment reads per MFMA fall with the tile's sides:
+// Tile of the main kernel for a problem: 128 rows, 64 columns for narrow results, otherwise 128, and larger tiles, because
+// its loop is bound by what moves through LDS per MFMA, and both the staging writes and the fragment reads per MFMA
+// fall with the tile's sides:
 //   128x256 for results at least 256 wide with at least three rounds of such tiles (a quarter fewer LDS and load
 //           instructions per MFMA than 128x128: 5 to 20 % on such layers; with fewer rounds the coarser tiles
 //           leave compute units idle at the end);
@@ -2087,7 +1988,7 @@ inline MainTile main_tile(const GemmConv& p) {
 
 template <int BM, int BN>
 bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
-    const int bk = p.bf16 ? 32 : 16;
+    const int bk = 32;
     *tiles = (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
     *nkt = (p.Kg + bk - 1) / bk;
     return *tiles > 0 && *tiles * *nkt < 0x7fffffffLL;
@@ -2099,27 +2000,13 @@ bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
 template <int BM, int BN>
 bool uniform_tap_ok(const GemmConv& p) {
     static const bool off = getenv("LARSCONV_NO_UNIFORM_TAP") != nullptr;     // comparison runs
-    const int bk = p.bf16 ? 32 : 16, es = p.bf16 ? 2 : 4;
+    const int bk = 32, es = 2;
     if (off || p.Ci % bk != 0 || (long long)p.R * p.S > 32) return false;
     const long long pq = (long long)p.Po * p.Qo;
     const long long images = BM / pq + 2;
     const long long a_span = ((images * p.Hi + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.Wi + p.S + 1) * p.Ci * es;
     const long long b_span = (long long)(BN + 1) * p.Kg * es;
     return a_span < 0x7fff0000LL && b_span < 0x7fff0000LL;
-}
-
-// Constants for div_by(): n / d == umulhi(n, mul) >> shift for 0 <= n < 2^31 (mul == 0 stands for d == 1).
-// With L = ceil(log2 d) and mul = ceil(2^(31+L) / d) the error term n * (mul*d - 2^(31+L)) stays below 2^(31+L).
-void magic_for(int d, unsigned* mul, unsigned* shift) {
-    if (d <= 1) {
-        *mul = 0;
-        *shift = 0;
-        return;
-    }
-    int L = 0;
-    while ((1ll << L) < d) ++L;
-    *mul = (unsigned)((((unsigned long long)1 << (31 + L)) + (unsigned)d - 1) / (unsigned)d);
-    *shift = (unsigned)(L - 1);
 }
 
 }  // namespace
@@ -2147,7 +2034,7 @@ extern "C" int lc_selftest_division(int max_d) {
 
 namespace {
 
-template <int BM, int BN, bool SMALLC, bool BF16>
+template <int BM, int BN, bool SMALLC>
 lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     long long tiles;
     int nkt;
@@ -2176,29 +2063,22 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     const bool ut = !SMALLC && uniform_tap_ok<BM, BN>(p);
     if (p.scatter && p.stats) return LC_ERR_UNSUPPORTED;
     if (p.scatter) {                          // the scatter epilogue addresses the result relative to the tile's first pixel
-        const long long span = ((long long)BM / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * (p.bf16 ? 2 : 4);
+        const long long span = ((long long)BM / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * 2;
         if (span >= 0x7fff0000LL || SMALLC || BN > 128 || BM > 128) return LC_ERR_UNSUPPORTED;   // (1x1 windows never have fewer channels than a k-step)
         if constexpr (BN <= 128 && BM <= 128) {
             if (ut)
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, true>), dim3(grid), threads, 0, stream, p);
+                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, true, true>), dim3(grid), threads, 0, stream, p);
             else
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, false, true>), dim3(grid), threads, 0, stream, p);
+                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, false, true>), dim3(grid), threads, 0, stream, p);
         }
     } else if (ut) {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, false>), dim3(grid), threads, 0, stream, p);
+        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, true, false>), dim3(grid), threads, 0, stream, p);
     } else {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false, false>), dim3(grid), threads, 0, stream, p);
+        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, false, false>), dim3(grid), threads, 0, stream, p);
     }
     if (!whole) {
-        hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
-        if (p.stats) {
-            const dim3 sgrid((unsigned)(tiles - pl.dp_tiles), 2);
-            const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;
-            if (vec4)
-                hipLaunchKernelGGL((tile_stats_kernel<BF16, true>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
-            else
-                hipLaunchKernelGGL((tile_stats_kernel<BF16, false>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
-        }
+        hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
+        if (p.stats) lc_launch_tile_stats(p, BM, BN, pl.dp_tiles, (unsigned)(tiles - pl.dp_tiles), stream);
     }
     return lc_end_call();
 }
@@ -2229,8 +2109,21 @@ auto with_main_tile(const GemmConv& p, F&& f) {
     return f.template operator()<128, 64>();
 }
 
+void lc_launch_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, unsigned rest, hipStream_t stream) {
+    const dim3 grid(rest, 2);
+    const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;
+    if (p.bf16) {
+        if (vec4) hipLaunchKernelGGL((tile_stats_kernel<true, true>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
+        else hipLaunchKernelGGL((tile_stats_kernel<true, false>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
+    } else {
+        if (vec4) hipLaunchKernelGGL((tile_stats_kernel<false, true>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
+        else hipLaunchKernelGGL((tile_stats_kernel<false, false>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
+    }
+}
+
 size_t lc_conv_gemm_workspace(const GemmConv& p) {
     if (!use_main_kernel(p)) return 0;
+    if (!p.bf16) return lc_conv_split_workspace(p);
     return with_main_tile(p, [&]<int BM, int BN>() -> size_t {
         long long tiles;
         int nkt;
@@ -2328,15 +2221,12 @@ lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
     }
     if (p.bf16) {
         if (!use_main_kernel(p)) return LC_ERR_UNSUPPORTED;       // the caller converts to fp32 instead
-        if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
-        return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false, true>(p, stream); });
+        if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true>(p, stream) : launch_conv_sk<128, 64, true>(p, stream);
+        return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false>(p, stream); });
     }
     const bool vec = (p.Ci % 4 == 0) && aligned16(p.a) && aligned16(p.b);
     if (!vec) return launch_conv<64, 64, 16, 1>(p, stream);
-    if (use_main_kernel(p)) {
-        if (p.Ci < 16) return p.N > 64 ? launch_conv_sk<128, 128, true, false>(p, stream) : launch_conv_sk<128, 64, true, false>(p, stream);
-        return p.N > 64 ? launch_conv_sk<128, 128, false, false>(p, stream) : launch_conv_sk<128, 64, false, false>(p, stream);
-    }
+    if (use_main_kernel(p)) return lc_launch_conv_split(p, stream);
     if (p.N > 64) return launch_conv<128, 128, 16, 4>(p, stream);
     return launch_conv<128, 64, 16, 4>(p, stream);
 }

@@ -96,6 +96,11 @@ size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` f
 extern "C" int lc_selftest_division(int max_d);   // host check of the multiply-high division constants (0 = all good)
 bool lc_conv_gemm_bf16_native(const GemmConv& p);   // can the bf16 MFMA kernel take this problem (shape and alignment)?
 bool lc_conv_gemm_scatter_ok(const GemmConv& p);    // can the main kernel's scatter epilogue take this problem?
+// column sums of `rest` tiles of bm x bn from first_tile on, read back from d (stream-K tiles)
+void lc_launch_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, unsigned rest, hipStream_t stream);
+// fp32 problems on the bf16 matrix pipe (conv_split.hip), and the partial-tile bytes they need
+lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream);
+size_t lc_conv_split_workspace(const GemmConv& p);
 size_t lc_conv_gemm_workspace(const GemmConv& p);   // bytes `partial` must hold for this problem (0 = none)
 
 // ResNet's first layer in fp32 (conv_stem.hip): 7x7, stride 2, padding 3, 3 -> 64 channels, NHWC, P and Q multiples of 16.

@@ -1,0 +1,110 @@
+"""GPU parity of the fp32 passes that run on the bf16 matrix pipe, each operand as the sum of three bf16 values.
+
+Checked against float64 torch on the CPU, element by element, with the bound that the arithmetic gives: a product's three dropped parts are
+below 2^-24 of it together, and each of the six kept ones is added with at most one rounding (taken as 2^-23 of the sum of the terms' magnitudes)
+per 32 reduction indices, in which the sums of stream-K pieces or batch splits (at most 64 more) are included:
+|error| <= (6 * ceil(K / 32) + 66) * 2^-23 * sum |a| |b|."""
+import numpy as np
+import pytest
+import torch
+import torch.nn.functional as F
+
+from paper_1709_05011_amd import larsconv as lc
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+NHWC = lc.LC_NHWC
+
+# n, c, h, w, k, r, stride, pad: edges of tiles (128 rows, 64 and 128 columns), reduction remainders (32), channel counts below a k-step,
+# result widths that are not multiples of four, strided results on a grid, stream-K pieces, and one whole tile only
+SHAPES = [
+    (1, 32, 16, 8, 128, 1, 1, 0), (1, 32, 16, 8, 64, 3, 1, 1), (3, 64, 13, 11, 129, 1, 1, 0), (2, 36, 9, 9, 65, 3, 1, 1),
+    (2, 4, 15, 17, 33, 3, 1, 1), (5, 12, 7, 7, 62, 5, 1, 2), (2, 96, 14, 14, 130, 1, 2, 0), (1, 20, 6, 5, 4, 3, 1, 1),
+    (4, 256, 7, 7, 256, 3, 1, 1), (40, 64, 28, 28, 256, 1, 1, 0), (2, 48, 12, 12, 96, 3, 2, 1), (1, 1024, 1, 1, 1000, 1, 1, 0),
+]
+
+
+def _desc(s):
+    n, c, h, w, k, r, stride, pad = s
+    return lc.ConvDesc(n, c, h, w, k, r, r, stride, stride, pad, pad, lc.LC_F32, NHWC)
+
+
+def _conv64(x, w, s):
+    """forward in float64; x, w NHWC / KRSC arrays"""
+    xt, wt = (torch.from_numpy(np.ascontiguousarray(np.transpose(a, (0, 3, 1, 2)))).double() for a in (x, w))
+    return F.conv2d(xt, wt, stride=s[6], padding=s[7]).permute(0, 2, 3, 1).numpy()
+
+
+def _conv64_bwd(dy, w, s):
+    dyt, wt = (torch.from_numpy(np.ascontiguousarray(np.transpose(a, (0, 3, 1, 2)))).double() for a in (dy, w))
+    return torch.nn.grad.conv2d_input((s[0], s[1], s[2], s[3]), wt, dyt, stride=s[6], padding=s[7]).permute(0, 2, 3, 1).numpy()
+
+
+def _data(s, seed, wide=False):
+    """normal values; wide: magnitudes spread over 2^-40 .. 2^40"""
+    rng = np.random.default_rng(seed)
+    d = _desc(s)
+    p, q = lc.conv2d_out_shape(d)
+
+    def make(*shape):
+        a = rng.standard_normal(shape)
+        if wide:
+            a = a * np.exp2(rng.integers(-40, 41, shape))
+        return a.astype(np.float32)
+    return d, make(s[0], s[2], s[3], s[1]), make(s[4], s[5], s[5], s[1]), make(s[0], p, q, s[4])
+
+
+def _within(got, ref, mag, k):
+    bound = (6 * -(-k // 32) + 66) * 2.0 ** -23 * mag
+    bad = ~(np.abs(got.astype(np.float64) - ref) <= bound)
+    assert not bad.any(), (int(bad.sum()), np.max(np.abs(got - ref) / np.maximum(mag, 1e-300)))
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("s", SHAPES, ids=str)
+def test_forward_and_backward_data_within_the_bound(s, wide):
+    d, x, w, dy = _data(s, 11, wide)
+    _within(gu.gpu_fwd(d, x, w), _conv64(x, w, s), _conv64(abs(x), abs(w), s), s[1] * s[5] ** 2)
+    _within(gu.gpu_bwd_data(d, dy, w), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
+
+
+def _same_where_not_finite(got, ref):
+    """ref: float64 with infinities and NaN where fp32 arithmetic has them; the finite rest is compared by the caller"""
+    ref32 = ref.astype(np.float32)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref32))
+    inf = np.isinf(ref32)
+    np.testing.assert_array_equal(got[inf], ref32[inf])
+    return np.isfinite(ref32)
+
+
+@pytest.mark.parametrize("s", [SHAPES[2], SHAPES[3], SHAPES[6], SHAPES[8]], ids=str)
+def test_infinities_nans_and_the_largest_values_come_through_as_in_fp32(s):
+    d, x, w, dy = _data(s, 5)
+    rng = np.random.default_rng(6)
+
+    def plant(a, values):
+        a = a.copy()
+        for v in values:
+            a[tuple(rng.integers(0, m) for m in a.shape)] = v
+        return a
+    top = np.finfo(np.float32).max
+    # +-inf and NaN in the activations (every row or pixel they reach), and a value whose bf16 rounding overflows
+    with np.errstate(over="ignore", invalid="ignore"):
+        for values in ([np.inf], [np.inf, -np.inf, np.nan], [top]):
+            xs, ds = plant(x, values), plant(dy, values)
+            small = (w * np.float32(0.01)).astype(np.float32)         # keeps a sum around the largest value finite
+            ref, mag = _conv64(xs, small, s), _conv64(abs(xs), abs(small), s)
+            got = gu.gpu_fwd(d, xs, small)
+            ok = _same_where_not_finite(got, ref)
+            _within(got[ok], ref[ok], mag[ok], s[1] * s[5] ** 2)
+            ref, mag = _conv64_bwd(ds, small, s), _conv64_bwd(abs(ds), abs(small), s)
+            got = gu.gpu_bwd_data(d, ds, small)
+            ok = _same_where_not_finite(got, ref)
+            _within(got[ok], ref[ok], mag[ok], s[4] * s[5] ** 2)
+        # ... and in a filter: one column of the result
+        ws = plant(w, [np.inf])
+        ref = _conv64(x, ws, s)
+        got = gu.gpu_fwd(d, x, ws)
+        ok = _same_where_not_finite(got, ref)
+        _within(got[ok], ref[ok], _conv64(abs(x), abs(ws), s)[ok], s[1] * s[5] ** 2)
