@@ -106,6 +106,7 @@ GemmConv gemm_bwd_data(const lc_conv_desc* d, int P, int Q) {
     g.dh = g.dw = 1;
     g.sh = g.sw = 1;
     g.bf16 = d->dtype == LC_BF16;
+    g.split = !g.bf16;
     if (d->r == 1 && d->s == 1 && d->pad_h == 0 && d->pad_w == 0) {
         // 1x1 window: one GEMM row per dy pixel; with a stride the result lands on the stride grid
         // of dx and the rest of each stride cell is zero.
@@ -192,6 +193,7 @@ int plan_phases(const lc_conv_desc* d, int P, int Q, Phase* out, bool* all_cover
             g.esh = sh;
             g.esw = sw;
             g.bf16 = d->dtype == LC_BF16;
+            g.split = !g.bf16;
             ph.g = g;
         }
     return n;
@@ -381,7 +383,7 @@ lc_status make_plan(const lc_conv_desc* d, lc_pass pass, Plan* pl) {
         } else if (pl->wgrad_slab) {
             pl->splits = lc_wgrad_slab_splits(d->n, d->h, d->w, pl->cpad, d->k, &pl->m_per_split);
         } else {
-            pl->splits = lc_wgrad_splits(M, d->k, J, pl->bf16);
+            pl->splits = lc_wgrad_splits(M, d->k, J, d->r * d->s, pl->bf16);
             pl->m_per_split = (M + pl->splits - 1) / pl->splits;
         }
         pl->wgrad_direct = pl->splits == 1 && !pad && !pl->stem_wgrad;

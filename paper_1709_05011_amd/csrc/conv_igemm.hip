@@ -1,5 +1,5 @@
-// Implicit-GEMM convolution kernels for gfx950: bf16 forward / backward-data, the filter gradients, and the fallback for fp32
-// operands that the vector paths do not take (fp32 forward / backward-data: conv_split.hip).
+// Implicit-GEMM convolution kernels for gfx950: the forward pass, bf16 backward-data and filter gradients, and the fallbacks of both types
+// (fp32 backward-data and filter gradients: conv_split.hip).
 //
 // Forward and backward-data run as  D[m][n] = sum_kg A(m,kg) * B[n][kg]  where row m is an output
 // pixel (img, po, qo), column kg = (r, s, ci) walks the filter window with the channel innermost,
@@ -14,7 +14,6 @@
 // global -> registers -> LDS with the next tile's global loads in flight while the current tile is
 // multiplied (two LDS buffers, one barrier per k-step).
 #include <hip/hip_runtime.h>
-#include <type_traits>
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
@@ -234,15 +233,15 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward / backward-data kernel for bf16 operands (channel counts that are multiples of 8, no dilated read).
+// Main forward / backward-data kernel (channel counts that are multiples of 4, no dilated read).
 //
-// LDS tile: [row][64 bytes] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
+// LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
 // applied on the global side: the lane that owns LDS slot s of a row fetches chunk s ^ swz(row).
 // Positions outside the image, rows past M or N and columns past Kg fetch from a 16-byte block of zeros
 // instead, so every lane always loads and the loop has no branch.
 //
-// Pipeline per 32-wide k-step ("tile"): the tile two steps ahead travels global -> registers, the tile one
+// Pipeline per 16-wide k-step ("tile"): the tile two steps ahead travels global -> registers, the tile one
 // step ahead registers -> LDS (two LDS buffers), fragments are double-buffered in registers so that the LDS
 // reads of the next half-step and the global loads are issued in the shadow of the MFMAs.
 //
@@ -261,8 +260,8 @@ __device__ __forceinline__ size_t partial_index(int wave, int i, int j, int v, i
     return ((((size_t)wave * TM + i) * TN + j) * 16 + v) * 64 + lane;
 }
 
-// Operands come 8 to a 16-byte chunk, k-step 32, multiplied with v_mfma_f32_32x32x16_bf16 (lane l feeds A[row l%32][k 8*(l/32) .. +7],
-// i.e. exactly one LDS chunk per MFMA); the result is stored as bf16.
+// BF16: operands are bf16 (8 per 16-byte chunk, k-step 32), multiplied with v_mfma_f32_32x32x16_bf16 (lane l
+// feeds A[row l%32][k 8*(l/32) .. +7], i.e. exactly one LDS chunk per MFMA); the result is stored as bf16.
 // UT ("uniform tap"): the channel count is a multiple of the k-step, so a k-step lies inside one filter tap
 // and its (r, s, first channel) are the same for every lane.  They are then tracked in scalar registers, the
 // operands are fetched with buffer loads (tile-relative 32-bit byte offset per lane + scalar offset of the
@@ -286,12 +285,12 @@ constexpr int pk_blocks_per_cu(int bm, int bn) { return bm * bn >= 256 * 256 ? 1
 // Waves along the columns of the tile: 2 (a 2 x 2 block of waves), or 4 for the 256x256 tile (2 x 4 waves of 128 x 64).
 constexpr int pk_waves_n(int bm, int bn) { return bm * bn >= 256 * 256 ? 4 : 2; }
 
-template <int BM, int BN, bool SMALLC, bool UT, bool SCATTER>
+template <int BM, int BN, bool SMALLC, bool BF16, bool UT, bool SCATTER>
 __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64, pk_blocks_per_cu(BM, BN) * pk_waves_n(BM, BN) / 2)
 conv_gemm_pk_kernel(const GemmConv p) {
-    using E = uint16_t;
-    constexpr int ES = 2;
-    constexpr int EPC = 8;
+    using E = typename OutT<BF16>::type;
+    constexpr int ES = (int)sizeof(E);
+    constexpr int EPC = BF16 ? 8 : 4;
     constexpr int BK = 4 * EPC;
     constexpr int WN_ = pk_waves_n(BM, BN), NWV = 2 * WN_;              // waves: 2 along the rows x WN_ along the columns
     constexpr int LA = BM / (16 * NWV), LB = BN / (16 * NWV), LPT = LA + LB;
@@ -511,13 +510,17 @@ conv_gemm_pk_kernel(const GemmConv p) {
         for (int j = 0; j < TN; ++j) fb[slot][j] = *reinterpret_cast<const float4*>(base + b_frag + j * 32 * 16 + ch);
     };
     // one group of MFMAs: every 32x32 tile of the wave advanced by one k-slice
-    auto mfma_group = [&](int slot) __attribute__((always_inline)) {
+    auto mfma_group = [&](int slot, int e) __attribute__((always_inline)) {
+        if (BF16 && e != 0) return;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
-                                                                    __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j], 0, 0, 0);
+                if constexpr (BF16)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
+                                                                        __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j], 0, 0, 0);
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(elem(fa[slot][i], e), elem(fb[slot][j], e), acc[i][j], 0, 0, 0);
             }
     };
     auto clear_acc = [&]() __attribute__((always_inline)) {
@@ -537,7 +540,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
         const int tm = c_tile / nbn;
         const int m0 = tm * BM, n0 = (c_tile - tm * nbn) * BN;
         if (c_k0 == 0 && c_k1 == nkt) {
-            if constexpr (SCATTER) {
+            if constexpr (SCATTER) {                       // (bf16 only: fp32 backward-data runs in conv_split.hip)
                 // Row (img, po, qo) of the GEMM is pixel (po*esh, qo*esw) of image img in the [imgs][Ho][Wo][ldd] result;
                 // the pixels between the stride grid are zero and were cleared by the caller before the launch.  An
                 // accumulator register holds one row in lanes 0..31 and the row four further down in lanes 32..63;
@@ -622,7 +625,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
                     (int)kBufferWords3);
                 // bf16 with an even row length: neighbouring lanes (neighbouring columns) trade values so that every
                 // lane stores a pair of columns as one dword -- even lanes for row r0, odd lanes for row r0 + 1.
-                const bool pairs = ((N_ | ldd_) & 1) == 0;
+                const bool pairs = BF16 && ((N_ | ldd_) & 1) == 0;
                 const int odd = lane & 1;
                 unsigned d_voff[TN];
 #pragma unroll
@@ -643,17 +646,22 @@ conv_gemm_pk_kernel(const GemmConv p) {
                         const int soff = r0 * ldd_ * ES;
 #pragma unroll
                         for (int j = 0; j < TN; ++j) {
-                            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                            typedef float f32x2 __attribute__((ext_vector_type(2)));
-                            const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
-                            const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
-                            if (pairs) {
-                                // u = {row r0 | row r0 + 1} of this lane's column; swap with the neighbouring lane
-                                const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
+                            if constexpr (BF16) {
+                                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                                const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
+                                const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
+                                if (pairs) {
+                                    // u = {row r0 | row r0 + 1} of this lane's column; swap with the neighbouring lane
+                                    const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
+                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
+                                } else {
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
+                                }
                             } else {
-                                __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
-                                __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
+                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)d_voff[j], soff, 0);
+                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v + 1]), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
                             }
                         }
                     }
@@ -674,9 +682,11 @@ conv_gemm_pk_kernel(const GemmConv p) {
 #pragma unroll
                             for (int v = 0; v < 16; v += 2) {
                                 float x0 = acc[i][j][v], x1 = acc[i][j][v + 1];
-                                const unsigned u = lc_bf16x2_rne(x0, x1);
-                                x0 = __uint_as_float(u << 16);
-                                x1 = __uint_as_float(u & 0xffff0000u);
+                                if constexpr (BF16) {
+                                    const unsigned u = lc_bf16x2_rne(x0, x1);
+                                    x0 = __uint_as_float(u << 16);
+                                    x1 = __uint_as_float(u & 0xffff0000u);
+                                }
                                 if (ragged) {
                                     const int row = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * fhalf + (v & 3);
                                     if (row >= M_) x0 = 0.f;
@@ -716,15 +726,19 @@ conv_gemm_pk_kernel(const GemmConv p) {
     // One k-step out of LDS buffer `cur` (a literal at both calls)
     auto step = [&](int cur, int f) __attribute__((always_inline)) {
         read_frags(cur, 1, 1);
-        mfma_group(0);
+        mfma_group(0, 0);
+        mfma_group(0, 1);
         __builtin_amdgcn_sched_barrier(0);
         sstore(cur ^ 1);                          // k-step f + 1: its buffer was last read one step ago
+        mfma_group(0, 2);
         __builtin_amdgcn_sched_barrier(0);
         if (f + 2 < F) load_step();               // k-step f + 2 into the registers just stored
+        mfma_group(0, 3);
         __builtin_amdgcn_sched_barrier(0);
         lds_barrier();
         read_frags(cur ^ 1, 0, 0);                // first half of k-step f + 1
-        mfma_group(1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mfma_group(1, e);
         if (++c_k == c_k1) {                      // the segment is complete: store it, the next step starts a new one
             __builtin_amdgcn_sched_barrier(0);
             epilogue();
@@ -745,10 +759,10 @@ conv_gemm_pk_kernel(const GemmConv p) {
 // Adds the parts of every tile that stream-K blocks split between them, in k order, and stores the tile.
 // Block (t, v) handles accumulator register v of every 32x32 MFMA tile of stream-K tile t, with the thread
 // geometry of the main kernel: 16 blocks per tile keep the whole chip busy on what is a small reduction.
-template <int BM, int BN>
+template <int BM, int BN, bool BF16>
 __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_kernel(const GemmConv p) {
     constexpr int WN_ = pk_waves_n(BM, BN);
-    constexpr int BK = 32, TM = BM / 64, TN = BN / (32 * WN_);
+    constexpr int BK = BF16 ? 32 : 16, TM = BM / 64, TN = BN / (32 * WN_);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / WN_, wn = wave % WN_;
     const int v = blockIdx.y;
@@ -784,7 +798,7 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
             for (int u = 0; u < 16; ++u) out[i][jj][u] = acc[i][jj][0];
     const int tile = p.dp_tiles + blockIdx.x;
     const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * BN;
-    store_tile<TM, TN, true>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
+    store_tile<TM, TN, BF16>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
 }
 
 // The column sums of the tiles that stream-K blocks shared (the main kernel sums the tiles it stores whole): block
@@ -1270,36 +1284,21 @@ __global__ void __launch_bounds__(WGM* WGN * 64) wgrad_f32_kernel(const GemmWgra
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward-weight kernel with scalar addressing (fp32 operands, channel counts multiples of 4, filter
-// windows of at most 32 taps).  Same GEMM, LDS layout, split and fragment reads as wgrad_f32_kernel; the
-// difference is where the address arithmetic runs.  A wave fetches whole reduction rows: one load
-// instruction covers the BN columns of ONE output pixel m, so the pixel's (image, p, q), its byte offset and
-// the set of filter taps that fall inside the image are wave-uniform and are kept in scalar registers
-// (advanced by 16 rows per step with precomputed digits of 16 in the (Q, P) number system).  A lane only
-// holds what depends on its column: the tap's byte offset and the tap's bit position.  A lane whose tap is
-// outside the image for this pixel gets bit 31 of its buffer offset set and the hardware returns zeros.
-// dY rows past the end of the split are cut off by the size of the dY buffer descriptor.
+// backward-weight kernel for a 1x1 window with stride 1 and no padding, bf16 operands, channel counts multiples of 8.  Output pixel m reads
+// input pixel m, X is a plain [M][C] matrix like dY, and both operands are fetched with 16-byte buffer loads at a lane-constant offset
+// plus the step's scalar offset: no per-pixel work at all.  Rows past the end of the split are cut off by the size of the buffer.
+// MFMA operands come from the transposing LDS read, as in wgrad_bf16_kernel.
 // ------------------------------------------------------------------------------------------------
-// BF16: operands are bf16 (reduction step 32, LDS holds bf16, MFMA operands come from the transposing LDS read as
-// in wgrad_bf16_kernel); everything about the addressing is the same with 2-byte elements.
-// PLAIN: a 1x1 window with stride 1 and no padding.  Output pixel m then reads input pixel m, X is a plain
-// [M][C] matrix like dY, and both operands are fetched with 16-byte loads at a lane-constant offset plus the
-// step's scalar offset: no per-pixel work at all.
-template <int BM, int BN, bool BF16, bool PLAIN>
-__global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {   // 4 blocks per compute unit: lc_wgrad_splits()
-    using E = typename OutT<BF16>::type;                          // operand element type (float, or the bits of a bf16)
-    constexpr int ES = (int)sizeof(E);
-    constexpr int EPC = 16 / ES;                                  // elements per 16-byte vector
-    constexpr int BK = BF16 ? 32 : 16;
-    constexpr int AQ = BM / EPC, ARPP = 256 / AQ, LA = BK / ARPP; // dY: 16-byte vectors, ARPP rows per pass
-    constexpr int BV = BN / 64;                                   // X: elements per lane and row (one row per wave and load)
-    constexpr int RW = BK / 4;                                    // X rows per wave and step
-    constexpr int BQ = BN / EPC, BRPP = 256 / BQ, LB = BK / BRPP; // PLAIN: X in 16-byte vectors like dY
-    constexpr int PA = BM + (BF16 ? 32 : 4), PB = BN + (BF16 ? 32 : 4);
+template <int BM, int BN>
+__global__ void __launch_bounds__(256, 4) wgrad_plain_bf16_kernel(const GemmWgrad p) {   // 4 blocks per compute unit: lc_wgrad_splits()
+    using E = uint16_t;
+    constexpr int ES = 2, EPC = 8;                                // element bytes, elements per 16-byte vector
+    constexpr int BK = 32;
+    constexpr int AQ = BM / EPC, ARPP = 256 / AQ, LA = BK / ARPP; // 16-byte vectors per row, rows per pass of the block
+    constexpr int BQ = BN / EPC, BRPP = 256 / BQ, LB = BK / BRPP;
+    constexpr int PA = BM + 32, PB = BN + 32;
     constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
-    static_assert(PLAIN || BV == 2 || (BV == 1 && !BF16), "tile shape");
     static_assert(256 % AQ == 0 && BK % ARPP == 0 && LA >= 1, "tile shape");
-    using BVt = typename std::conditional<BF16, unsigned, typename std::conditional<BV == 2, float2, float>::type>::type;
 
     __shared__ __attribute__((aligned(16))) E As[2][BK * PA];
     __shared__ __attribute__((aligned(16))) E Bs[2][BK * PB];
@@ -1317,10 +1316,9 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
     const int k0 = (tile / nbn) * BM, j0 = (tile % nbn) * BN;
     const int m_begin = z * p.m_per_split;
     const int m_end = min(p.M, m_begin + p.m_per_split);
-    const int H_ = p.H, W_ = p.W, C_ = p.C, P_ = p.P, Q_ = p.Q, R_ = p.R, S_ = p.S, K_ = p.K;
-    const int sh_ = p.sh, sw_ = p.sw, ph_ = p.ph, pw_ = p.pw;
+    const int C_ = p.C, K_ = p.K;
 
-    // dY: lane-constant offset inside a 16-row step; the step's first row is the scalar offset
+    // dY: lane-constant offset inside a step; the step's first row is the scalar offset
     const int a_cq = tid % AQ, a_kr = tid / AQ;
     const int a_col = k0 + a_cq * EPC;
     unsigned a_voff[LA];
@@ -1330,7 +1328,7 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
         (void*)(static_cast<const E*>(p.dy) + (long long)m_begin * K_), 0, (int)((unsigned)(m_end - m_begin) * K_ * (unsigned)ES),
         (int)kBufferWords3);
 
-    // PLAIN: X addressed like dY
+    // X addressed like dY
     const int pb_cq = tid % BQ, pb_kr = tid / BQ;
     unsigned pb_voff[LB];
 #pragma unroll
@@ -1339,104 +1337,26 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
     const __amdgpu_buffer_rsrc_t pb_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(static_cast<const E*>(p.x) + (long long)m_begin * C_), 0, (int)((unsigned)(m_end - m_begin) * C_ * (unsigned)ES),
         (int)kBufferWords3);
-    // X: the lane's column j = (r, s, c): byte offset of the tap relative to the pixel's window origin, bit position
-    const int b_col = j0 + lane * BV;
-    unsigned b_voff = kBufferBytes, b_up = 0;
-    if (b_col < p.J) {
-        const int rs = b_col / C_, fc = b_col - rs * C_;
-        const int fr = rs / S_, fs = rs - fr * S_;
-        b_voff = (unsigned)(((fr * W_ + fs) * C_ + fc) * ES);
-        b_up = 31u - (unsigned)rs;
-    }
-    const int pq = P_ * Q_;
-    const int img_first = m_begin / pq;
-    const int phb = max(ph_, 0), pwb = max(pw_, 0);
-    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(static_cast<const E*>(p.x) + ((long long)img_first * H_ * W_ - ((long long)phb * W_ + pwb)) * C_), 0,
-        (int)kBufferBytes, (int)kBufferWords3);
-    // scalar state of this wave's RW rows: (image - img_first, p, q) of row m_begin + step * 16 + wave * RW + i
-    int s_img[RW], s_p[RW], s_q[RW];
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-        const int m = m_begin + wave * RW + i;
-        const int t = m / Q_;
-        s_q[i] = m - t * Q_;
-        const int im = t / P_;
-        s_p[i] = t - im * P_;
-        s_img[i] = im - img_first;
-    }
-    // 16 rows further: 16 = (d_img * P + d_p) * Q + d_q
-    const int d_q = BK % Q_, d_t = BK / Q_, d_p = d_t % P_, d_img = d_t / P_;
-    const int taps = R_ * S_;
-    const unsigned full = taps >= 32 ? ~0u : (1u << taps) - 1u;
-    unsigned rep = 0;                                             // bit r*S for every r: spreads a mask over s to all rows of the window
-    for (int r = 0; r < R_; ++r) rep |= 1u << (r * S_);
     int mt = m_begin;                                             // first reduction row of the step being loaded
 
     float4 ra[LA];
-    BVt rb[RW];
     float4 prb[LB];
     auto gload = [&]() __attribute__((always_inline)) {
         const int a_soff = (mt - m_begin) * K_ * ES;
 #pragma unroll
         for (int i = 0; i < LA; ++i)
             ra[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)a_voff[i], a_soff, 0));
-        if constexpr (PLAIN) {
-            const int b_soff = (mt - m_begin) * C_ * ES;
+        const int b_soff = (mt - m_begin) * C_ * ES;
 #pragma unroll
-            for (int i = 0; i < LB; ++i)
-                prb[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(pb_rsrc, (int)pb_voff[i], b_soff, 0));
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            const int h0 = s_p[i] * sh_ - ph_, w0 = s_q[i] * sw_ - pw_;
-            int rlo = max(0, -h0), rhi = min(R_ - 1, H_ - 1 - h0);
-            int slo = max(0, -w0), shi = min(S_ - 1, W_ - 1 - w0);
-            const bool ok = (rlo <= rhi) & (slo <= shi) & (mt + wave * RW + i < m_end);
-            rlo = min(rlo, R_ - 1);                              // keep the shifts below in range when the row is dead
-            rhi = max(rhi, 0);
-            slo = min(slo, S_ - 1);
-            const int sspan = max(shi - slo, 0);
-            const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
-            const unsigned wmask = rep * (((2u << sspan) - 1u) << slo);
-            const unsigned inv = ok ? ~(hm & wmask) : ~0u;        // taps outside the image for this pixel
-            const int soff = ok ? (((s_img[i] * H_ + s_p[i] * sh_ + phb - ph_) * W_ + s_q[i] * sw_ + pwb - pw_) * C_) * ES : 0;
-            const unsigned vo = ((inv << b_up) & kBufferBytes) | b_voff;
-            if constexpr (BF16)
-                rb[i] = __builtin_amdgcn_raw_buffer_load_b32(b_rsrc, (int)vo, soff, 0);
-            else if constexpr (BV == 2)
-                rb[i] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, (int)vo, soff, 0));
-            else
-                rb[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b_rsrc, (int)vo, soff, 0));
-        }
+        for (int i = 0; i < LB; ++i)
+            prb[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(pb_rsrc, (int)pb_voff[i], b_soff, 0));
     };
-    auto advance = [&]() __attribute__((always_inline)) {
-        mt += BK;
-        if constexpr (PLAIN) return;
-#pragma unroll
-        for (int i = 0; i < RW; ++i) {
-            int q = s_q[i] + d_q;
-            const bool cq = q >= Q_;
-            q -= cq ? Q_ : 0;
-            int pp = s_p[i] + d_p + (cq ? 1 : 0);
-            const bool cp = pp >= P_;
-            pp -= cp ? P_ : 0;
-            s_q[i] = q;
-            s_p[i] = pp;
-            s_img[i] += d_img + (cp ? 1 : 0);
-        }
-    };
+    auto advance = [&]() __attribute__((always_inline)) { mt += BK; };
     auto sstore = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < LA; ++i) *reinterpret_cast<float4*>(&As[buf][(a_kr + i * ARPP) * PA + a_cq * EPC]) = ra[i];
-        if constexpr (PLAIN) {
 #pragma unroll
-            for (int i = 0; i < LB; ++i) *reinterpret_cast<float4*>(&Bs[buf][(pb_kr + i * BRPP) * PB + pb_cq * EPC]) = prb[i];
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < RW; ++i) *reinterpret_cast<BVt*>(&Bs[buf][(wave * RW + i) * PB + lane * BV]) = rb[i];
+        for (int i = 0; i < LB; ++i) *reinterpret_cast<float4*>(&Bs[buf][(pb_kr + i * BRPP) * PB + pb_cq * EPC]) = prb[i];
     };
 
     f32x16 acc[TM][TN];
@@ -1447,48 +1367,32 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    // Fragments of one group of reduction rows (fp32: 2 rows, one MFMA of k = 2 per tile; bf16: 16 rows, one MFMA of
-    // k = 16 per tile), double-buffered: slot g & 1 holds group g of the step.
-    constexpr int NG = BF16 ? BK / 16 : BK / 2;
-    using Frag = typename std::conditional<BF16, bf16x8, float>::type;
-    Frag fa[2][TM], fb[2][TN];
+    // Fragments of one group of 16 reduction rows (one MFMA of k = 16 per tile), double-buffered: slot g & 1 holds group g of the step.
+    constexpr int NG = BK / 16;
+    bf16x8 fa[2][TM], fb[2][TN];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
-    // bf16: the transposing LDS read (see wgrad_bf16_kernel): this lane's row and column inside a 16-row group
+    // the transposing LDS read (see wgrad_bf16_kernel): this lane's row and column inside a 16-row group
     const int tr_row = 8 * (lane >> 5) + ((lane & 15) >> 2), tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
     auto read_frags = [&](int buf, int g, int slot) __attribute__((always_inline)) {
-        if constexpr (BF16) {
-            auto one = [&](const E* base, int pitch) __attribute__((always_inline)) {
-                const E* q = base + (16 * g + tr_row) * pitch + tr_col;
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)q);
-                const s16x4 hi =
-                    __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(q + 4 * pitch));
-                const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                return __builtin_bit_cast(bf16x8, v);
-            };
+        auto one = [&](const E* base, int pitch) __attribute__((always_inline)) {
+            const E* q = base + (16 * g + tr_row) * pitch + tr_col;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)q);
+            const s16x4 hi =
+                __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(q + 4 * pitch));
+            const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            return __builtin_bit_cast(bf16x8, v);
+        };
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[slot][i] = one(&As[buf][wm * WTM + i * 32], PA);
+        for (int i = 0; i < TM; ++i) fa[slot][i] = one(&As[buf][wm * WTM + i * 32], PA);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) fb[slot][j] = one(&Bs[buf][wn * WTN + j * 32], PB);
-        } else {
-            const E* as = &As[buf][(2 * g + (lane >> 5)) * PA + wm * WTM + (lane & 31)];
-            const E* bs = &Bs[buf][(2 * g + (lane >> 5)) * PB + wn * WTN + (lane & 31)];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) fa[slot][i] = as[i * 32];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[slot][j] = bs[j * 32];
-        }
+        for (int j = 0; j < TN; ++j) fb[slot][j] = one(&Bs[buf][wn * WTN + j * 32], PB);
     };
     auto mfma_group = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if constexpr (BF16)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-            }
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
     };
 
     // One step out of LDS buffer `cur` (a literal at each call).  On entry slot 0 holds the step's first group of
@@ -1497,7 +1401,6 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
     // the first fragments of the next step are read while the last MFMAs run.  Steps past the end of the split
     // are fetched and stored like the others: all of their rows are past m_end, so nothing is read from memory
     // and zeros are stored.
-    constexpr int G_STORE = NG > 2 ? 1 : 0, G_LOAD = NG > 2 ? 3 : 0;
     auto step = [&](int cur) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
@@ -1510,8 +1413,8 @@ __global__ void __launch_bounds__(256, 4) wgrad_ut_kernel(const GemmWgrad p) {  
             __builtin_amdgcn_sched_barrier(0);
             mfma_group(g & 1);
             __builtin_amdgcn_sched_barrier(0);
-            if (g == G_STORE) sstore(cur ^ 1);
-            if (g == G_LOAD) {
+            if (g == 0) {
+                sstore(cur ^ 1);
                 advance();
                 gload();
             }
@@ -1919,6 +1822,8 @@ __global__ void __launch_bounds__(256, 2) wgrad3x3_slab_kernel(const GemmWgrad p
         }
 }
 
+
+
 template <int BM, int BN, int BK, int VEC>
 lc_status launch_conv(const GemmConv& p, hipStream_t stream) {
     const long long tiles = (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
@@ -1939,9 +1844,9 @@ lc_status launch_wgrad(const GemmWgrad& p, hipStream_t stream) {
 // Blocks of the main kernel that fit on the chip at once (the kernel's launch bounds hold it to this).
 inline int resident_blocks(int bm, int bn) { return pk_blocks_per_cu(bm, bn) * device_cu_count(); }
 
-// Tile of the main kernel for a problem: 128 rows, 64 columns for narrow results, otherwise 128, and larger tiles, because
-// its loop is bound by what moves through LDS per MFMA, and both the staging writes and the fragment reads per MFMA
-// fall with the tile's sides:
+// Tile of the main kernel for a problem.  fp32: 128 rows, 64 columns for narrow results, otherwise 128.  bf16
+// adds larger tiles, because its loop is bound by what moves through LDS per MFMA, and both the staging writes and
+// the fragment reads per MFMA fall with the tile's sides:
 //   128x256 for results at least 256 wide with at least three rounds of such tiles (a quarter fewer LDS and load
 //           instructions per MFMA than 128x128: 5 to 20 % on such layers; with fewer rounds the coarser tiles
 //           leave compute units idle at the end);
@@ -1988,7 +1893,7 @@ inline MainTile main_tile(const GemmConv& p) {
 
 template <int BM, int BN>
 bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
-    const int bk = 32;
+    const int bk = p.bf16 ? 32 : 16;
     *tiles = (long long)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
     *nkt = (p.Kg + bk - 1) / bk;
     return *tiles > 0 && *tiles * *nkt < 0x7fffffffLL;
@@ -2000,7 +1905,7 @@ bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
 template <int BM, int BN>
 bool uniform_tap_ok(const GemmConv& p) {
     static const bool off = getenv("LARSCONV_NO_UNIFORM_TAP") != nullptr;     // comparison runs
-    const int bk = 32, es = 2;
+    const int bk = p.bf16 ? 32 : 16, es = p.bf16 ? 2 : 4;
     if (off || p.Ci % bk != 0 || (long long)p.R * p.S > 32) return false;
     const long long pq = (long long)p.Po * p.Qo;
     const long long images = BM / pq + 2;
@@ -2034,7 +1939,7 @@ extern "C" int lc_selftest_division(int max_d) {
 
 namespace {
 
-template <int BM, int BN, bool SMALLC>
+template <int BM, int BN, bool SMALLC, bool BF16>
 lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     long long tiles;
     int nkt;
@@ -2063,22 +1968,29 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     const bool ut = !SMALLC && uniform_tap_ok<BM, BN>(p);
     if (p.scatter && p.stats) return LC_ERR_UNSUPPORTED;
     if (p.scatter) {                          // the scatter epilogue addresses the result relative to the tile's first pixel
-        const long long span = ((long long)BM / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * 2;
-        if (span >= 0x7fff0000LL || SMALLC || BN > 128 || BM > 128) return LC_ERR_UNSUPPORTED;   // (1x1 windows never have fewer channels than a k-step)
-        if constexpr (BN <= 128 && BM <= 128) {
+        const long long span = ((long long)BM / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * (p.bf16 ? 2 : 4);
+        if (span >= 0x7fff0000LL || SMALLC || !BF16 || BN > 128 || BM > 128) return LC_ERR_UNSUPPORTED;   // (1x1 windows never have fewer channels than a k-step)
+        if constexpr (BF16 && BN <= 128 && BM <= 128) {
             if (ut)
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, true, true>), dim3(grid), threads, 0, stream, p);
+                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, true>), dim3(grid), threads, 0, stream, p);
             else
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, false, true>), dim3(grid), threads, 0, stream, p);
+                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, false, true>), dim3(grid), threads, 0, stream, p);
         }
     } else if (ut) {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, true, false>), dim3(grid), threads, 0, stream, p);
+        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, false>), dim3(grid), threads, 0, stream, p);
     } else {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, false, false>), dim3(grid), threads, 0, stream, p);
+        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false, false>), dim3(grid), threads, 0, stream, p);
     }
     if (!whole) {
-        hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
-        if (p.stats) lc_launch_tile_stats(p, BM, BN, pl.dp_tiles, (unsigned)(tiles - pl.dp_tiles), stream);
+        hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
+        if (p.stats) {
+            const dim3 sgrid((unsigned)(tiles - pl.dp_tiles), 2);
+            const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;
+            if (vec4)
+                hipLaunchKernelGGL((tile_stats_kernel<BF16, true>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
+            else
+                hipLaunchKernelGGL((tile_stats_kernel<BF16, false>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
+        }
     }
     return lc_end_call();
 }
@@ -2109,21 +2021,9 @@ auto with_main_tile(const GemmConv& p, F&& f) {
     return f.template operator()<128, 64>();
 }
 
-void lc_launch_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, unsigned rest, hipStream_t stream) {
-    const dim3 grid(rest, 2);
-    const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;
-    if (p.bf16) {
-        if (vec4) hipLaunchKernelGGL((tile_stats_kernel<true, true>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
-        else hipLaunchKernelGGL((tile_stats_kernel<true, false>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
-    } else {
-        if (vec4) hipLaunchKernelGGL((tile_stats_kernel<false, true>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
-        else hipLaunchKernelGGL((tile_stats_kernel<false, false>), grid, dim3(256), 0, stream, p, bm, bn, first_tile);
-    }
-}
-
 size_t lc_conv_gemm_workspace(const GemmConv& p) {
     if (!use_main_kernel(p)) return 0;
-    if (!p.bf16) return lc_conv_split_workspace(p);
+    if (p.split) return lc_conv_split_workspace(p);
     return with_main_tile(p, [&]<int BM, int BN>() -> size_t {
         long long tiles;
         int nkt;
@@ -2221,12 +2121,16 @@ lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
     }
     if (p.bf16) {
         if (!use_main_kernel(p)) return LC_ERR_UNSUPPORTED;       // the caller converts to fp32 instead
-        if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true>(p, stream) : launch_conv_sk<128, 64, true>(p, stream);
-        return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false>(p, stream); });
+        if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
+        return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false, true>(p, stream); });
     }
     const bool vec = (p.Ci % 4 == 0) && aligned16(p.a) && aligned16(p.b);
     if (!vec) return launch_conv<64, 64, 16, 1>(p, stream);
-    if (use_main_kernel(p)) return lc_launch_conv_split(p, stream);
+    if (use_main_kernel(p)) {
+        if (p.split) return lc_launch_conv_split(p, stream);
+        if (p.Ci < 16) return p.N > 64 ? launch_conv_sk<128, 128, true, false>(p, stream) : launch_conv_sk<128, 64, true, false>(p, stream);
+        return p.N > 64 ? launch_conv_sk<128, 128, false, false>(p, stream) : launch_conv_sk<128, 64, false, false>(p, stream);
+    }
     if (p.N > 64) return launch_conv<128, 128, 16, 4>(p, stream);
     return launch_conv<128, 64, 16, 4>(p, stream);
 }
@@ -2237,16 +2141,22 @@ static void wgrad_tile(int K, int J, int* bm, int* bn) {
     *bn = J > 64 ? 128 : 64;
 }
 
-int lc_wgrad_splits(int M, int K, int J, bool bf16) {
+int lc_wgrad_splits(int M, int K, int J, int taps, bool bf16) {
     int bm, bn;
     wgrad_tile(K, J, &bm, &bn);
     const long long tiles = (long long)((K + bm - 1) / bm) * ((J + bn - 1) / bn);
+    const bool split = !bf16 && taps <= 32;               // the kernel of conv_split.hip (lc_wgrad_split_ok)
     // blocks of this tiling that fit on the chip at once (registers and LDS of the kernel instances below):
-    // the split count fills exactly one such round, never spills a few blocks into a second one
-    const int per_cu = (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (bf16 ? 5 : 6);
+    // the split count fills exactly one such round, never spills a few blocks into a second one -- the split kernel fills two, which keeps
+    // its sums short enough for the accuracy of the fp32 instructions (activations behind a ReLU, 1x1 at 56x56, batch 256: error 5.8e-7
+    // with one round, 4.1e-7 with two, 4.2e-7 before)
+    const int per_cu = split ? 2 * lc_wgrad_split_blocks_per_cu(bm, bn) : (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (bf16 ? 5 : 6);
     const long long round = (long long)per_cu * device_cu_count();
     long long want = round / tiles;
-    const long long most = (M + 255) / 256;               // at least 256 reduction rows per split
+    // at least so many reduction rows per split (two images of 14x14 with 256 channels: 29 us at 256, 23.5 at 128, 22 at 64, where sixteen
+    // of 7x7 lose 12 %; bf16 loses 5 % on small layers at 128)
+    const int least = split ? 128 : 256;
+    const long long most = (M + least - 1) / least;
     if (want > most) want = most;
     if (want < 1) want = 1;
     if (want > 8192) want = 8192;
@@ -2302,47 +2212,46 @@ static lc_status launch_wgrad_bf16(const GemmWgrad& p, hipStream_t stream) {
     return lc_end_call();
 }
 
-// Whether wgrad_ut_kernel takes this problem: 16-byte vectors (channel counts multiples of 4, of 8 for bf16), a
-// window of at most 32 taps, and buffer offsets (a split's rows of dY; the images a split touches plus one
-// window of X) below 2^31 bytes.
-static bool wgrad_ut_ok(const GemmWgrad& p) {
-    static const bool off = getenv("LARSCONV_NO_UNIFORM_TAP") != nullptr;     // comparison runs
-    const int epc = p.bf16 ? 8 : 4, es = p.bf16 ? 2 : 4;
-    if (off || p.C % epc != 0 || p.K % epc != 0 || (long long)p.R * p.S > 32) return false;
-    if ((((uintptr_t)p.dy | (uintptr_t)p.x) & 15) != 0) return false;
-    const long long rows = (long long)p.m_per_split + 64;
-    const long long a_span = rows * p.K * es;
+// Whether the split kernel takes this fp32 problem: pairs of columns inside one tap, a window of at most 32 taps, and buffer offsets (a split's
+// rows of dY and of a plain X; the images a split touches plus one window of X) below 2^31 bytes.
+static bool wgrad_split_ok(const GemmWgrad& p) {
+    if (p.bf16 || p.C % 2 != 0 || (long long)p.R * p.S > 32) return false;
+    const long long rows = (long long)p.m_per_split + 64, wide = p.K > p.C ? p.K : p.C;
     const long long images = rows / ((long long)p.P * p.Q) + 2;
-    const long long b_span = ((images * p.H + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.W + p.S + 1) * p.C * es;
-    return a_span < 0x7fff0000LL && b_span < 0x7fff0000LL;
+    const long long b_span = ((images * p.H + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.W + p.S + 1) * p.C * 4;
+    return rows * wide * 4 < 0x7fff0000LL && b_span < 0x7fff0000LL;
 }
 
-template <int BM, int BN, bool BF16, bool PLAIN>
-static lc_status launch_wgrad_ut(const GemmWgrad& p, hipStream_t stream) {
+// Whether the plain 1x1 kernel takes this bf16 problem: 16-byte vectors and buffer offsets (a split's rows of dY and X) below 2^31 bytes.
+static bool wgrad_plain_ok(const GemmWgrad& p) {
+    static const bool off = getenv("LARSCONV_NO_UNIFORM_TAP") != nullptr;     // comparison runs
+    if (off || !p.bf16 || p.C % 8 != 0 || p.K % 8 != 0 || !aligned16(p.dy) || !aligned16(p.x)) return false;
+    if (p.R != 1 || p.S != 1 || p.sh != 1 || p.sw != 1 || p.ph != 0 || p.pw != 0 || p.H != p.P || p.W != p.Q) return false;
+    const long long rows = (long long)p.m_per_split + 64;
+    return rows * (p.K > p.C ? p.K : p.C) * 2 < 0x7fff0000LL;
+}
+
+template <int BM, int BN>
+static lc_status launch_wgrad_plain(const GemmWgrad& p, hipStream_t stream) {
     const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
     if (tiles <= 0 || tiles * p.splits > 0x7fffffffLL) return LC_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((wgrad_ut_kernel<BM, BN, BF16, PLAIN>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((wgrad_plain_bf16_kernel<BM, BN>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
     return lc_end_call();
 }
 
 template <bool BF16>
 static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
     if (p.slab) return BF16 ? launch_wgrad_slab(p, stream) : LC_ERR_UNSUPPORTED;   // (m_per_split counts positions: no other kernel can take it)
-    if (wgrad_ut_ok(p) && !(BF16 && getenv("LARSCONV_WGRAD_WIDEN"))) {
-        // only the 128 x 128 tiling: with narrower tiles a step has too few MFMAs to hide the scalar work and the
-        // narrower loads, and the kernels below measure faster
+    if (!BF16 && wgrad_split_ok(p)) {
         int bm, bn;
         wgrad_tile(p.K, p.J, &bm, &bn);
-        // (bf16: only the plain 1x1 case -- with eight pixels per wave and step and an eighth of the MFMA time the
-        // per-pixel scalar work of the general case does not hide)
-        const bool plain = p.R == 1 && p.S == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 && p.H == p.P && p.W == p.Q;
-        if (bm == 128 && bn == 128 && plain) return launch_wgrad_ut<128, 128, BF16, true>(p, stream);
-        if (plain) {                                  // (no per-pixel work: pays with every tile shape)
-            if (bm == 128) return launch_wgrad_ut<128, 64, BF16, true>(p, stream);
-            if (bn == 128) return launch_wgrad_ut<64, 128, BF16, true>(p, stream);
-            return launch_wgrad_ut<64, 64, BF16, true>(p, stream);
-        }
-        if (bm == 128 && bn == 128 && !BF16) return launch_wgrad_ut<128, 128, false, false>(p, stream);
+        return lc_launch_wgrad_split(p, bm, bn, stream);
+    }
+    if (BF16 && wgrad_plain_ok(p) && !getenv("LARSCONV_WGRAD_WIDEN")) {
+        int bm, bn;
+        wgrad_tile(p.K, p.J, &bm, &bn);
+        if (bm == 128) return bn == 128 ? launch_wgrad_plain<128, 128>(p, stream) : launch_wgrad_plain<128, 64>(p, stream);
+        return bn == 128 ? launch_wgrad_plain<64, 128>(p, stream) : launch_wgrad_plain<64, 64>(p, stream);
     }
     if (BF16 && p.C % 8 == 0 && p.K % 8 == 0 && aligned16(p.dy) && aligned16(p.x) && !getenv("LARSCONV_WGRAD_WIDEN")) {
         int bm, bn;                                   // the bf16 matrix pipe; LARSCONV_WGRAD_WIDEN=1: comparison runs

@@ -1,16 +1,27 @@
-// fp32 forward / backward-data on the bf16 matrix pipe of gfx950: D[m][n] = sum_kg A(m, kg) * B[n][kg], the implicit GEMM of
-// conv_igemm.hip, with every fp32 operand taken apart into three bf16 values.
+// fp32 backward-data and filter gradients on the bf16 matrix pipe of gfx950, with every fp32 operand taken apart into three bf16 values.
+// (The forward pass stays with the fp32 matrix instructions of conv_igemm.hip: its last bits decide ReLUs.)
 //
-// x = h + m + l with h = x rounded to bf16, m = (x - h) rounded to bf16, l the rest: 8 + 8 + 8 significant bits, exact.  Of the nine partial
-// products of a * b the six hh, hm, mh, mm, hl, lh reach the last bit of an fp32 product (the three left out are below 2^-25 of it); each is
-// exact in the matrix pipe and is added to the fp32 accumulator there.  Six v_mfma_f32_16x16x32_bf16 take 96 cycles where the same
-// sums cost v_mfma_f32_32x32x2_f32 256.  The error against 64-bit sums is the fp32 kernel's or smaller (one rounding per 32 terms and
-// product instead of one per two terms): 3x3 over 128 channels 5.2e-7 against 5.9e-7 of the result's norm, 1x1 over 64 channels 1.0e-7 both.
+// x = h + m + l with h = x rounded to bf16, m = (x - h) rounded to bf16, l the rest: 8 + 8 + 8 significant bits, exact for |x| >= 2^-110.  Of the
+// nine partial products of a * b the six hh, hm, mh, mm, hl, lh reach the last bit of an fp32 product (the three left out are below 2^-24 of
+// it together); each is exact in the matrix pipe and is added to the fp32 accumulator there.  Six v_mfma_f32_16x16x32_bf16 take 96 cycles
+// where the same sums cost v_mfma_f32_32x32x2_f32 256.  The kernels are bound by power: over three variants of the loop (0.49 to 0.63 of
+// the cycles with the matrix pipe busy) busy share x clock stayed at 1.08 GHz; without the arithmetic of the split they run 6 % faster,
+// without a third of the LDS reads 7 %.
+// Measured at batch 256 (before: fp32 matrix instructions at 75 to 80 % of their peak), kernel with its reduction:
+//   backward-data    3x3, 128 channels, 28x28: 439 -> 288 us;  1x1, 256 -> 64, 56x56: 268 -> 222 us;  1x1 stride 2, 1024 -> 512: 452 -> 323 us
+//   filter gradient  the same layers: 473 -> 338, 254 -> 235, 417 -> 310 us (with one round of blocks and no turn of the sign 320, 204, 285)
+//
+// Rounding: the matrix instruction rounds to nearest, except that it cuts addends far below the accumulator's last bit downwards: -0.006 ulp
+// per instruction, always the same way.  In one long sum that is nothing; in a filter gradient of 512 splits it adds up to three times the
+// random part (1x1 at 56x56, batch 256: error 1.6e-6 of the norm where fp32 instructions give 4.2e-7).  Long reductions therefore run
+// their last three eighths with the first operand and the accumulator negated -- the point where a sum that grows like a random walk has
+// collected half of the cut -- and every other split starts negated.
 //
 // The split happens once per staged element, on the way from the load registers into LDS.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
+#include <type_traits>
 
 #include "conv_common.h"
 
@@ -21,7 +32,12 @@ namespace {
 struct Split2 {
     unsigned h, m, l;
 };
+template <bool NEG>
 __device__ __forceinline__ Split2 split2(float x0, float x1) {
+    if constexpr (NEG) {                  // (source modifiers: no instruction of its own)
+        x0 = -x0;
+        x1 = -x1;
+    }
     Split2 s;
     s.h = lc_bf16x2_rne(x0, x1);
     const float r0 = x0 - __uint_as_float(s.h << 16), r1 = x1 - __uint_as_float(s.h & 0xffff0000u);
@@ -32,6 +48,8 @@ __device__ __forceinline__ Split2 split2(float x0, float x1) {
 
 constexpr int BK = 32;                     // k-step: 128 bytes of a row, one v_mfma_f32_16x16x32_bf16 deep
 constexpr int kBlock16 = 3072;             // LDS bytes of 16 rows x 32 k: three bf16 planes
+constexpr int kFlipFrom = 16;              // k-steps from which a reduction turns its sign on the way
+__device__ __forceinline__ int flip_step(int k0, int k1) { return k1 - k0 >= kFlipFrom ? k0 + (k1 - k0) * 5 / 8 : -1; }
 
 // Blocks per compute unit (LDS: 48 KB for the 128x128 tile).  The generic addressing needs more registers.
 constexpr int split_blocks_per_cu(int bn, bool ut) { return ut && bn == 64 ? 3 : 2; }
@@ -51,7 +69,8 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
 
     constexpr int kOutPitch = WTN + 4;                     // floats; 16 rows fall on distinct banks
     __shared__ __attribute__((aligned(1024))) unsigned char lds[(BM + BN) / 16 * kBlock16];
-    __shared__ __attribute__((aligned(16))) float out_lds[4 * 16 * kOutPitch];
+    __shared__ __attribute__((aligned(16))) uint2 row_lds[UT ? BM : 1];   // per tile row: byte offset of its pixel's window, taps outside the image
+    static_assert(16 * kOutPitch * 4 * 4 <= sizeof(lds), "output staging");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -97,7 +116,6 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
     int a_h[LA], a_w[LA];
     int l_n0 = 0, kg = 0, c = 0, r = 0, s = 0;
     // uniform-tap addressing: see conv_igemm.hip
-    unsigned a_voff[LA], a_inv[LA];
     __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, 0, (int)kBufferWords3);
     __amdgpu_buffer_rsrc_t b_rsrc = a_rsrc;
     int u_kt = 0, u_c = 0, u_s = 0, u_r = 0;
@@ -115,9 +133,8 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
             const unsigned full = taps >= 32 ? ~0u : (1u << taps) - 1u;
             unsigned rep = 0;
             for (int rr = 0; rr < R_; ++rr) rep |= 1u << (rr * S_);
-#pragma unroll
-            for (int i = 0; i < LA; ++i) {
-                const int m = m0 + (i * 4 + wave) * 8 + lrow;
+            if (lane < LA * 8) {                       // this wave's rows, one per lane; nobody else reads them
+                const int row = ((lane >> 3) * 4 + wave) * 8 + (lane & 7), m = m0 + row;
                 const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
                 const int img = div_by(t, pmul, psh), po = t - img * Po_;
                 const int h0 = po * sh_ - ph_, w0 = qo * sw_ - pw_;
@@ -131,9 +148,10 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
                 const int sspan = max(shi - slo, 0);
                 const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
                 const unsigned wmk = rep * (((2u << sspan) - 1u) << slo);
-                a_inv[i] = ok ? ~(hm & wmk) : ~0u;
-                a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * 4 + kq * 16) : 0u;
+                row_lds[row] = make_uint2(ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * 4) : 0u,
+                                          ok ? ~(hm & wmk) : ~0u);
             }
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
             const long long a_first = ((long long)img0 * Hi_ * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
             a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(A + a_first), 0, (int)kBufferBytes, (int)kBufferWords3);
             // filter rows past N lie past the end of the buffer
@@ -179,7 +197,8 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
             const int b_soff = u_kt * BK * 4;
 #pragma unroll
             for (int l = 0; l < LA; ++l) {
-                const unsigned vo = ((a_inv[l] << up) & kBufferBytes) | a_voff[l];
+                const uint2 row = row_lds[(l * 4 + wave) * 8 + lrow];
+                const unsigned vo = ((row.y << up) & kBufferBytes) | (row.x + (unsigned)kq * 16u);
                 g[l] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)vo, a_soff, 0));
             }
 #pragma unroll
@@ -236,10 +255,12 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         ++l_k;
     };
     unsigned char* const st = lds + (wave >> 1) * kBlock16 + (kq >> 1) * 256 + ((((wave & 1) * 8 + lrow) ^ (kq & 6)) * 16) + (kq & 1) * 8;
-    auto split_store = [&]() __attribute__((always_inline)) {
+    auto split_store = [&](auto neg_a) __attribute__((always_inline)) {
+        constexpr bool NEG = decltype(neg_a)::value;
 #pragma unroll
         for (int l = 0; l < LPT; ++l) {
-            const Split2 a = split2(g[l].x, g[l].y), b = split2(g[l].z, g[l].w);
+            const Split2 a = l < LA ? split2<NEG>(g[l].x, g[l].y) : split2<false>(g[l].x, g[l].y);
+            const Split2 b = l < LA ? split2<NEG>(g[l].z, g[l].w) : split2<false>(g[l].z, g[l].w);
             unsigned char* q = st + (l < LA ? l * 2 : BM / 16 + (l - LA) * 2) * kBlock16;
             *reinterpret_cast<uint2*>(q) = make_uint2(a.h, b.h);
             *reinterpret_cast<uint2*>(q + 1024) = make_uint2(a.m, b.m);
@@ -315,9 +336,17 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         }
     };
 
-    int c_seg = 0, c_tile, c_k0, c_k, c_k1;
+    auto negate_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = -acc[i][j];
+    };
+    int c_seg = 0, c_tile, c_k0, c_k, c_k1, c_flip;
+    bool neg = false;                             // the sum runs with the activations and the accumulators negated
     segment(0, c_tile, c_k0, c_k1);
     c_k = c_k0;
+    c_flip = flip_step(c_k0, c_k1);
     // store (or park) the finished segment
     auto epilogue = [&]() __attribute__((always_inline)) {
         const int tm = c_tile / nbn;
@@ -325,11 +354,15 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         redo_not_finite(m0, n0, c_k0, c_k1);
         if (!(c_k0 == 0 && c_k1 == nkt)) {
             // part of a tile: it is the first piece of this block's stream-K range (slot 2*bid) or the last (2*bid + 1)
-            f32x4* part = reinterpret_cast<f32x4*>(p.partial) + ((size_t)2 * bid + (c_seg == rounds ? 0 : 1)) * (BM * BN / 4);
+            // (a buffer descriptor: 16 lane pointers would be computed ahead of the loop and cost 32 registers in it)
+            const __amdgpu_buffer_rsrc_t part_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(p.partial + ((size_t)2 * bid + (c_seg == rounds ? 0 : 1)) * (BM * BN)), 0, BM * BN * 4, (int)kBufferWords3);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) part[((i * TN + j) * 4 + wave) * 64 + lane] = acc[i][j];
+                for (int j = 0; j < TN; ++j)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), part_rsrc, lane * 16 + wave * 1024,
+                                                           (i * TN + j) * 4096, 0);
             return;
         }
         // 16 rows at a time through the wave's own LDS slice, so that a store covers whole rows of the wave's part (4 x 256 or 8 x 128 bytes, in
@@ -346,7 +379,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         const bool quads = (N_ & 3) == 0;
         constexpr int CPR = WTN / 4, RPI = 64 / CPR;           // lanes per row, rows per store
         const int lr = lane / CPR, col = n0 + wn * WTN + (lane % CPR) * 4;
-        float* const mine = out_lds + wave * (16 * kOutPitch);
+        float* const mine = reinterpret_cast<float*>(lds) + wave * (16 * kOutPitch);     // every wave has read its last fragments of the tile
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -376,58 +409,18 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
                 }
             }
         }
-        if constexpr (!SCATTER) {
-            if (p.stats) {
-                // Per column, the sum and the sum of squares of what this wave has just stored over its WTM rows; rows past M are zero (their
-                // operands were).  A lane holds TM rows of four columns; the other 15 rows of each 16 are in its row of 16 lanes.
-                const int col0 = n0 + wn * WTN + 4 * fgrp;
-                f32x4* st4 = reinterpret_cast<f32x4*>(p.stats + ((size_t)(tm * 2 + wm) * N_ + col0) * 2);
-                auto row_sum = [&](float x) __attribute__((always_inline)) {
-                    x += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x128 /* row_ror:8 */, 0xF, 0xF, true));
-                    x += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x124, 0xF, 0xF, true));
-                    x += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x122, 0xF, 0xF, true));
-                    x += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x121, 0xF, 0xF, true));
-                    return x;
-                };
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    float sum[4], sq[4];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        float a = 0.f, b = 0.f;
-#pragma unroll
-                        for (int i = 0; i < TM; ++i) {
-                            a += acc[i][j][v];
-                            b = fmaf(acc[i][j][v], acc[i][j][v], b);
-                        }
-                        sum[v] = row_sum(a);
-                        sq[v] = row_sum(b);
-                    }
-                    if (frow == 0) {
-                        if (quads) {
-                            if (col0 + j * 16 < N_) {
-                                st4[j * 8] = f32x4{sum[0], sq[0], sum[1], sq[1]};
-                                st4[j * 8 + 1] = f32x4{sum[2], sq[2], sum[3], sq[3]};
-                            }
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                if (col0 + j * 16 + v < N_) {
-                                    reinterpret_cast<float*>(st4)[(j * 16 + v) * 2] = sum[v];
-                                    reinterpret_cast<float*>(st4)[(j * 16 + v) * 2 + 1] = sq[v];
-                                }
-                        }
-                    }
-                }
-            }
-        }
     };
 
     // ---------------- the pipeline ----------------
     load_step();                                  // k-step 0 of the sequence
     clear_acc();
     for (int f = 0; f < F; ++f) {
-        split_store();
+        if (c_k == c_flip) {
+            negate_acc();
+            neg = true;
+        }
+        if (neg) split_store(std::true_type{});
+        else split_store(std::false_type{});
         if (f + 1 < F) load_step();               // stays in flight over the matrix phase
         lds_barrier();
         __builtin_amdgcn_s_setprio(1);
@@ -453,11 +446,15 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         __builtin_amdgcn_s_setprio(0);
         lds_barrier();                            // every wave has read its last fragments
         if (++c_k == c_k1) {                      // the segment is complete: store it, the next step starts a new one
+            if (neg) negate_acc();
+            neg = false;
             epilogue();
+            lds_barrier();                        // the staging of the result is over before the next step is stored
             clear_acc();
             ++c_seg;
             segment(c_seg, c_tile, c_k0, c_k1);
             c_k = c_k0;
+            c_flip = flip_step(c_k0, c_k1);
         }
     }
 }
@@ -512,6 +509,294 @@ __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p)
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Backward-weight: D[k][j] = sum_m dY[m][k] * X(m, j), j = (r, s, c), the same split arithmetic.  The reduction index is the strided one of
+// both operands, and an MFMA wants eight consecutive reduction values of one column from a lane: a wave owns eight of a step's 32 rows, a lane
+// loads its one or two columns of all eight (one row per load instruction), and the packing of value pairs into bf16 pairs along the
+// rows is the transposition -- each column's eight values leave as one 16-byte LDS store per plane.
+//
+// LDS: per 16 columns [plane][row group of 8][16 columns][8 rows]; with two columns per lane a block holds the even columns first, then the odd
+// ones, so that eight lanes store 128 consecutive bytes; the epilogue undoes that.
+// A load covers one output pixel, so its (image, p, q), its byte offset and the set of its taps inside the image are wave-uniform (scalar); a lane
+// holds its column's tap offset and bit, and a tap outside the image moves its offset past the end of the buffer.
+// PLAIN: a 1x1 window with stride 1 and no padding -- pixel m reads pixel m.
+// Three 128x128 blocks per compute unit (168 registers, 48 KB of LDS): 364 us with two of them on the 3x3 layer above, 320 with three.
+// ------------------------------------------------------------------------------------------------
+constexpr int wgrad_split_blocks_per_cu(int bm, int bn) { return bm == 128 && bn == 128 ? 3 : bm == 64 && bn == 64 ? 6 : 4; }
+
+template <int V> struct RowVec;
+template <> struct RowVec<1> { using type = float; };
+template <> struct RowVec<2> { using type = float2; };
+
+template <int BM, int BN, bool PLAIN>
+__global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_split_kernel(const GemmWgrad p) {
+    constexpr int VA = BM / 64, VB = BN / 64;              // columns per lane
+    constexpr int TM = BM / 32, TN = BN / 32;              // 16x16 tiles per wave (2 x 2 waves)
+
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[(BM + BN) / 16 * kBlock16];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int nbn = (p.J + BN - 1) / BN;
+    // split-major, dealt to the XCDs in contiguous runs: the tiles of a split read the same rows and share one L2
+    const int tiles_ = ((p.K + BM - 1) / BM) * nbn;
+    const int work = xcd_tile(blockIdx.x, tiles_ * p.splits);
+    const int z = work / tiles_, tile = work - z * tiles_;
+    const int k0 = (tile / nbn) * BM, j0 = (tile % nbn) * BN;
+    const int m_begin = z * p.m_per_split;
+    const int m_end = min(p.M, m_begin + p.m_per_split);
+    const int H_ = p.H, W_ = p.W, C_ = p.C, P_ = p.P, Q_ = p.Q, R_ = p.R, S_ = p.S, K_ = p.K, J_ = p.J;
+    const int sh_ = p.sh, sw_ = p.sw, ph_ = p.ph, pw_ = p.pw;
+    const int frow = lane & 15, fgrp = lane >> 4;
+
+    // dY: rows past the end of the split lie past the end of the buffer
+    const int a_col = k0 + lane * VA;
+    const unsigned a_voff = a_col < K_ ? (unsigned)a_col * 4u : kBufferBytes;
+    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(static_cast<const float*>(p.dy) + (long long)m_begin * K_), 0, (int)((unsigned)(m_end - m_begin) * (unsigned)K_ * 4u),
+        (int)kBufferWords3);
+    // X: the lane's column j = (r, s, c): byte offset of the tap relative to the pixel's window origin, bit position
+    const int b_col = j0 + lane * VB;
+    unsigned b_voff = kBufferBytes, b_up = 0;
+    if (b_col < J_) {
+        const int rs = b_col / C_, fc = b_col - rs * C_;
+        const int fr = rs / S_, fs = rs - fr * S_;
+        b_voff = PLAIN ? (unsigned)b_col * 4u : (unsigned)(((fr * W_ + fs) * C_ + fc) * 4);
+        b_up = 31u - (unsigned)rs;
+    }
+    const int img_first = m_begin / (P_ * Q_);
+    const int phb = max(ph_, 0), pwb = max(pw_, 0);
+    const float* const X = static_cast<const float*>(p.x);
+    const __amdgpu_buffer_rsrc_t b_rsrc =
+        PLAIN ? __builtin_amdgcn_make_buffer_rsrc((void*)(X + (long long)m_begin * C_), 0, (int)((unsigned)(m_end - m_begin) * (unsigned)C_ * 4u),
+                                                  (int)kBufferWords3)
+              : __builtin_amdgcn_make_buffer_rsrc((void*)(X + ((long long)img_first * H_ * W_ - ((long long)phb * W_ + pwb)) * C_), 0,
+                                                  (int)kBufferBytes, (int)kBufferWords3);
+    // (image - img_first, p, q) of this wave's first row of the step being loaded; 32 rows further: 32 = (d_img * P + d_p) * Q + d_q
+    int mt = m_begin + wave * 8;
+    int s_q, s_p, s_img;
+    {
+        const int t = mt / Q_;
+        s_q = mt - t * Q_;
+        const int im = t / P_;
+        s_p = t - im * P_;
+        s_img = im - img_first;
+    }
+    const int d_q = BK % Q_, d_t = BK / Q_, d_p = d_t % P_, d_img = d_t / P_;
+    const unsigned full = R_ * S_ >= 32 ? ~0u : (1u << (R_ * S_)) - 1u;
+    unsigned rep = 0;                                             // bit r*S for every r: spreads a mask over s to all rows of the window
+    for (int r = 0; r < R_; ++r) rep |= 1u << (r * S_);
+
+    typename RowVec<VA>::type ga[8];
+    typename RowVec<VB>::type gb[8];
+    auto load_row = [&](auto& dst, const __amdgpu_buffer_rsrc_t& rsrc, unsigned vo, int so) __attribute__((always_inline)) {
+        if constexpr (sizeof(dst) == 8)
+            dst = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)vo, so, 0));
+        else
+            dst = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)vo, so, 0));
+    };
+    auto load_step = [&]() __attribute__((always_inline)) {
+        const int row0 = mt - m_begin;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) load_row(ga[i], a_rsrc, a_voff, (row0 + i) * K_ * 4);
+        if constexpr (PLAIN) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) load_row(gb[i], b_rsrc, b_voff, (row0 + i) * C_ * 4);
+        } else {
+            int q = s_q, pp = s_p, im = s_img;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int h0 = pp * sh_ - ph_, w0 = q * sw_ - pw_;
+                unsigned inv = 0;                                 // taps outside the image for this pixel
+                if (mt + i >= m_end) {
+                    inv = ~0u;
+                } else if ((h0 < 0) | (w0 < 0) | (h0 + R_ > H_) | (w0 + S_ > W_)) {
+                    int rlo = max(0, -h0), rhi = min(R_ - 1, H_ - 1 - h0);
+                    int slo = max(0, -w0), shi = min(S_ - 1, W_ - 1 - w0);
+                    const bool some = (rlo <= rhi) & (slo <= shi);
+                    rlo = min(rlo, R_ - 1);                      // keep the shifts in range when no tap is inside
+                    rhi = max(rhi, 0);
+                    slo = min(slo, S_ - 1);
+                    const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
+                    inv = some ? ~(hm & (rep * (((2u << max(shi - slo, 0)) - 1u) << slo))) : ~0u;
+                }
+                const int soff = inv == ~0u ? 0 : ((im * H_ + h0 + phb) * W_ + w0 + pwb) * C_ * 4;
+                load_row(gb[i], b_rsrc, ((inv << b_up) & kBufferBytes) | b_voff, soff);
+                if (++q == Q_) {
+                    q = 0;
+                    if (++pp == P_) {
+                        pp = 0;
+                        ++im;
+                    }
+                }
+            }
+            s_q += d_q;
+            const bool cq = s_q >= Q_;
+            s_q -= cq ? Q_ : 0;
+            s_p += d_p + (cq ? 1 : 0);
+            const bool cp = s_p >= P_;
+            s_p -= cp ? P_ : 0;
+            s_img += d_img + (cp ? 1 : 0);
+        }
+        mt += BK;
+    };
+    // one operand's columns of this lane: eight rows each, three planes
+    auto split_store_cols = [&](auto& g, unsigned char* base, auto neg_g) __attribute__((always_inline)) {
+        constexpr bool NEG = decltype(neg_g)::value;
+        constexpr int V = sizeof(g[0]) / 4;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            Split2 s[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (V == 2) s[u] = e == 0 ? split2<NEG>(g[2 * u].x, g[2 * u + 1].x) : split2<NEG>(g[2 * u].y, g[2 * u + 1].y);
+                else s[u] = split2<NEG>(g[2 * u], g[2 * u + 1]);
+            }
+            unsigned char* q = base + (V == 2 ? (lane >> 3) * kBlock16 + ((lane & 7) + 8 * e) * 16 : (lane >> 4) * kBlock16 + (lane & 15) * 16) + wave * 256;
+            *reinterpret_cast<u32x4*>(q) = u32x4{s[0].h, s[1].h, s[2].h, s[3].h};
+            *reinterpret_cast<u32x4*>(q + 1024) = u32x4{s[0].m, s[1].m, s[2].m, s[3].m};
+            *reinterpret_cast<u32x4*>(q + 2048) = u32x4{s[0].l, s[1].l, s[2].l, s[3].l};
+        }
+    };
+
+    f32x4 acc[TM][TN];
+    bf16x8 fa[3][TM], fb[3][TN];
+    const unsigned char* const fr = lds + fgrp * 256 + frow * 16;
+    auto read_a = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[plane][i] = *reinterpret_cast<const bf16x8*>(fr + (wm * TM + i) * kBlock16 + plane * 1024);
+    };
+    auto read_b = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[plane][j] = *reinterpret_cast<const bf16x8*>(fr + (BM / 16 + wn * TN + j) * kBlock16 + plane * 1024);
+    };
+    auto product = [&](int pa, int pb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pa][i], fb[pb][j], acc[i][j], 0, 0, 0);
+    };
+    auto clear_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    // columns of a 16-block in the order the LDS blocks hold them
+    auto col_of = [](int v, int r) __attribute__((always_inline)) { return v == 2 ? (r < 8 ? 2 * r : 2 * r - 15) : r; };
+
+    clear_acc();
+    const int nkt = (m_end - m_begin + BK - 1) / BK;
+    bool neg = (z & 1) != 0;                          // the sum runs with dY and the accumulators negated
+    const int flip = flip_step(0, nkt);
+    auto negate_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = -acc[i][j];
+    };
+    if (nkt > 0) load_step();
+    for (int kt = 0; kt < nkt; ++kt) {
+        if (kt == flip) {
+            negate_acc();
+            neg = !neg;
+        }
+        if (neg) split_store_cols(ga, lds, std::true_type{});
+        else split_store_cols(ga, lds, std::false_type{});
+        split_store_cols(gb, lds + BM / 16 * kBlock16, std::false_type{});
+        if (kt + 1 < nkt) load_step();                // stays in flight over the matrix phase
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(1);
+        read_b(0);
+        read_a(2);
+        read_a(1);
+        __builtin_amdgcn_sched_barrier(0);
+        product(2, 0);
+        read_a(0);
+        __builtin_amdgcn_sched_barrier(0);
+        product(1, 0);
+        read_b(1);
+        __builtin_amdgcn_sched_barrier(0);
+        product(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        product(1, 1);
+        read_b(2);
+        __builtin_amdgcn_sched_barrier(0);
+        product(0, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        product(0, 2);
+        __builtin_amdgcn_s_setprio(0);
+        lds_barrier();                                // every wave has read its last fragments
+    }
+
+    if (neg) negate_acc();
+    // operands that the split cannot carry (see redo_not_finite above): this wave's part once more with fp32 matrix instructions
+    {
+        float t[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) t[j] = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) t[j] = fmaf(acc[i][j][v], 0.f, t[j]);
+#pragma unroll
+        for (int j = 1; j < TN; ++j) t[0] += t[j];
+        if (__builtin_expect(__ballot(t[0] != t[0]) != 0, 0)) {
+            clear_acc();
+            const float* const DY = static_cast<const float*>(p.dy);
+            for (int m = m_begin + fgrp; m < m_end + fgrp; m += 4) {
+                const int q = m / Q_, qo = m - q * Q_, img = q / P_, po = q - img * P_;
+                float a[TM], b[TN];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int k = k0 + (wm * TM + i) * 16 + col_of(VA, frow);
+                    a[i] = *(const __attribute__((address_space(1))) float*)(uintptr_t)pick((m < m_end) & (k < K_), DY + (long long)m * K_ + k,
+                                                                                            g_zero_chunk);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int jj = j0 + (wn * TN + j) * 16 + col_of(VB, frow);
+                    const int rs = jj / C_, fc = jj - rs * C_, fr_ = rs / S_, fs = rs - fr_ * S_;
+                    const int h = po * sh_ - ph_ + fr_, w = qo * sw_ - pw_ + fs;
+                    const bool ok = (m < m_end) & (jj < J_) & ((unsigned)h < (unsigned)H_) & ((unsigned)w < (unsigned)W_);
+                    b[j] = *(const __attribute__((address_space(1))) float*)(uintptr_t)pick(
+                        ok, X + (((long long)img * H_ + h) * W_ + w) * C_ + fc, g_zero_chunk);
+                }
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        }
+    }
+    float* __restrict__ D = p.d + (long long)z * K_ * J_;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = k0 + (wm * TM + i) * 16 + col_of(VA, 4 * fgrp + v);
+            if (k >= K_) continue;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int jj = j0 + (wn * TN + j) * 16 + col_of(VB, frow);
+                if (jj < J_) D[(long long)k * J_ + jj] = acc[i][j][v];
+            }
+        }
+}
+
+template <int BM, int BN>
+lc_status launch_wgrad_split(const GemmWgrad& p, hipStream_t stream) {
+    const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
+    if (tiles <= 0 || tiles * p.splits > 0x7fffffffLL) return LC_ERR_UNSUPPORTED;
+    const bool plain = p.R == 1 && p.S == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 && p.H == p.P && p.W == p.Q;
+    if (plain) hipLaunchKernelGGL((wgrad_split_kernel<BM, BN, true>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((wgrad_split_kernel<BM, BN, false>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
+    return lc_end_call();
+}
+
 // Whether the uniform-tap variant takes this problem: k-steps that do not straddle taps, a tap mask that fits 32 bits, and tile-relative
 // byte offsets (the images a tile can touch plus one filter window, and the tile's filter rows) that stay below 2^31.
 bool split_uniform_tap(const GemmConv& p) {
@@ -562,7 +847,6 @@ lc_status launch_split_tile(const GemmConv& p, const SplitPlan& s, bool whole, u
     if (!whole) {
         const unsigned rest = (unsigned)(s.tiles - p.dp_tiles);
         hipLaunchKernelGGL((conv_split_fixup_kernel<128, BN>), dim3(rest, 16 * BN / 128), dim3(256), 0, stream, p);
-        if (p.stats) lc_launch_tile_stats(p, 128, BN, p.dp_tiles, rest, stream);
     }
     return lc_end_call();
 }
@@ -578,7 +862,7 @@ size_t lc_conv_split_workspace(const GemmConv& p) {
 lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream) {
     SplitPlan s;
     if (!split_plan(p, &s)) return LC_ERR_UNSUPPORTED;
-    if (p.scatter && p.stats) return LC_ERR_UNSUPPORTED;
+    if (p.stats) return LC_ERR_UNSUPPORTED;
     if (p.scatter) {                          // the scatter epilogue addresses the result relative to the tile's first pixel
         const long long span = (128LL / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * 4;
         if (span >= 0x7fff0000LL) return LC_ERR_UNSUPPORTED;
@@ -600,4 +884,11 @@ lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream) {
     const unsigned grid = p.dp_tiles > 0 ? (unsigned)s.resident : (unsigned)p.sk_blocks;
     const bool whole = p.sk_blocks == 0 || p.sk_iters == (long long)p.sk_blocks * s.nkt;
     return s.bn == 128 ? launch_split_tile<128>(p, s, whole, grid, stream) : launch_split_tile<64>(p, s, whole, grid, stream);
+}
+
+int lc_wgrad_split_blocks_per_cu(int bm, int bn) { return wgrad_split_blocks_per_cu(bm, bn); }
+
+lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream) {
+    if (bm == 128) return bn == 128 ? launch_wgrad_split<128, 128>(p, stream) : launch_wgrad_split<128, 64>(p, stream);
+    return bn == 128 ? launch_wgrad_split<64, 128>(p, stream) : launch_wgrad_split<64, 64>(p, stream);
 }

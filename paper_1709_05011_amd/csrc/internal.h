@@ -87,6 +87,7 @@ struct GemmConv {
     // multiply-high division constants for Qo and Po (filled in by the launcher)
     unsigned qo_mul, qo_shift, po_mul, po_shift;
     int bf16;           // operands a, b and result d are bf16 (sums stay fp32)
+    int split;          // fp32 backward-data: products as sums of bf16 products (conv_split.hip)
     // not null (main and slab kernels, no scatter): [lc_conv_gemm_stats_tiles()][N][2] floats -- per half tile of rows and
     // per column, the sum and the sum of squares of the values stored to d (as stored: after rounding to bf16)
     float* stats;
@@ -96,9 +97,7 @@ size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` f
 extern "C" int lc_selftest_division(int max_d);   // host check of the multiply-high division constants (0 = all good)
 bool lc_conv_gemm_bf16_native(const GemmConv& p);   // can the bf16 MFMA kernel take this problem (shape and alignment)?
 bool lc_conv_gemm_scatter_ok(const GemmConv& p);    // can the main kernel's scatter epilogue take this problem?
-// column sums of `rest` tiles of bm x bn from first_tile on, read back from d (stream-K tiles)
-void lc_launch_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, unsigned rest, hipStream_t stream);
-// fp32 problems on the bf16 matrix pipe (conv_split.hip), and the partial-tile bytes they need
+// fp32 backward-data on the bf16 matrix pipe (conv_split.hip), and the partial-tile bytes they need
 lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream);
 size_t lc_conv_split_workspace(const GemmConv& p);
 size_t lc_conv_gemm_workspace(const GemmConv& p);   // bytes `partial` must hold for this problem (0 = none)
@@ -152,6 +151,9 @@ struct GemmWgrad {
     int slab;           // 3x3 stride-1 pad-1 bf16 layer for wgrad3x3_slab_kernel: m_per_split counts padded positions
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
-int lc_wgrad_splits(int M, int K, int J, bool bf16);   // fixed function of the shape (determinism)
+int lc_wgrad_splits(int M, int K, int J, int taps, bool bf16);   // fixed function of the shape (determinism)
+// fp32 operands on the bf16 matrix pipe (conv_split.hip), output tile bm x bn; and how many of its blocks fit on a compute unit
+lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream);
+int lc_wgrad_split_blocks_per_cu(int bm, int bn);
 bool lc_wgrad_slab_ok(int imgs, int H, int W, int C, int K, int R, int S, int sh, int sw, int ph, int pw, int P, int Q, bool bf16);
 int lc_wgrad_slab_splits(int imgs, int H, int W, int C, int K, int* pos_per_split);

@@ -41,6 +41,11 @@ def _conv64_bwd(dy, w, s):
     return torch.nn.grad.conv2d_input((s[0], s[1], s[2], s[3]), wt, dyt, stride=s[6], padding=s[7]).permute(0, 2, 3, 1).numpy()
 
 
+def _conv64_wgrad(x, dy, s):
+    xt, dyt = (torch.from_numpy(np.ascontiguousarray(np.transpose(a, (0, 3, 1, 2)))).double() for a in (x, dy))
+    return torch.nn.grad.conv2d_weight(xt, (s[4], s[1], s[5], s[5]), dyt, stride=s[6], padding=s[7]).permute(0, 2, 3, 1).numpy()
+
+
 def _data(s, seed, wide=False):
     """normal values; wide: magnitudes spread over 2^-40 .. 2^40"""
     rng = np.random.default_rng(seed)
@@ -63,10 +68,11 @@ def _within(got, ref, mag, k):
 
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("s", SHAPES, ids=str)
-def test_forward_and_backward_data_within_the_bound(s, wide):
+def test_all_three_passes_within_the_bound(s, wide):
     d, x, w, dy = _data(s, 11, wide)
     _within(gu.gpu_fwd(d, x, w), _conv64(x, w, s), _conv64(abs(x), abs(w), s), s[1] * s[5] ** 2)
     _within(gu.gpu_bwd_data(d, dy, w), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
+    _within(gu.gpu_bwd_weight(d, x, dy), _conv64_wgrad(x, dy, s), _conv64_wgrad(abs(x), abs(dy), s), dy.size // s[4])
 
 
 def _same_where_not_finite(got, ref):
@@ -102,6 +108,11 @@ def test_infinities_nans_and_the_largest_values_come_through_as_in_fp32(s):
             got = gu.gpu_bwd_data(d, ds, small)
             ok = _same_where_not_finite(got, ref)
             _within(got[ok], ref[ok], mag[ok], s[4] * s[5] ** 2)
+            xw = (x * np.float32(0.01)).astype(np.float32)
+            ref, mag = _conv64_wgrad(xw, ds, s), _conv64_wgrad(abs(xw), abs(ds), s)
+            got = gu.gpu_bwd_weight(d, xw, ds)
+            ok = _same_where_not_finite(got, ref)
+            _within(got[ok], ref[ok], mag[ok], dy.size // s[4])
         # ... and in a filter: one column of the result
         ws = plant(w, [np.inf])
         ref = _conv64(x, ws, s)
