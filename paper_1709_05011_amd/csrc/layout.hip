@@ -239,32 +239,35 @@ __device__ __forceinline__ double block_sum_double(double x, double* red /* 4 do
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// dw[i] = sum_z part[z][i].  SL lanes of the block share one output: lane j adds the j-th run of
-// consecutive splits (four interleaved partial sums, combined in a fixed tree), then the SL lane sums are
-// added in lane order.  The order depends on (splits, SL) only, never on timing: bit-identical reruns.
+// dw[i] = sum_z part[z][i], memory-bound on the partials.  A thread owns V neighbouring outputs (V = 4: 16-byte loads) and SL lanes of the
+// block share them: lane j adds the j-th run of consecutive splits -- four loads in flight, four interleaved sums combined in a fixed tree --
+// then the SL lane sums are added in lane order.  The order depends on (splits, SL) only, never on timing: bit-identical reruns.
 // sq (may be null) receives, per block, the sum of the squares of the values the block wrote to dw (in double): the
 // filter gradient's squared norm in pieces, for the layer-wise update that follows.
-template <int SL>
+template <int SL, int V>
 __global__ void __launch_bounds__(256) reduce_splits_kernel(const float* __restrict__ part, float* __restrict__ dw, int splits,
                                                             size_t count, int cpad, int c, double* __restrict__ sq) {
+    typedef float vec __attribute__((ext_vector_type(V)));
     constexpr int OUT = 256 / SL;
-    __shared__ float sm[SL][OUT];
+    __shared__ vec sm[SL > 1 ? SL : 1][SL > 1 ? OUT : 1];
     __shared__ double red[4];
     const int o = threadIdx.x % OUT, lane = threadIdx.x / OUT;
-    const size_t i = (size_t)blockIdx.x * OUT + o;
-    float acc = 0.f;
-    if (i < count) {
+    const size_t i = ((size_t)blockIdx.x * OUT + o) * V;
+    vec acc = 0.f;
+    if (i < count) {                                       // (V divides count)
         const int per = (splits + SL - 1) / SL;
         const int z0 = lane * per, z1 = min(splits, z0 + per);
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+        vec a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+        auto at = [&](int z) { return *reinterpret_cast<const vec*>(part + (size_t)z * count + i); };
         int z = z0;
         for (; z + 4 <= z1; z += 4) {
-            a0 += part[(size_t)z * count + i];
-            a1 += part[(size_t)(z + 1) * count + i];
-            a2 += part[(size_t)(z + 2) * count + i];
-            a3 += part[(size_t)(z + 3) * count + i];
+            const vec p0 = at(z), p1 = at(z + 1), p2 = at(z + 2), p3 = at(z + 3);
+            a0 += p0;
+            a1 += p1;
+            a2 += p2;
+            a3 += p3;
         }
-        for (; z < z1; ++z) a0 += part[(size_t)z * count + i];
+        for (; z < z1; ++z) a0 += at(z);
         acc = (a0 + a1) + (a2 + a3);
     }
     if (SL > 1) {
@@ -276,21 +279,27 @@ __global__ void __launch_bounds__(256) reduce_splits_kernel(const float* __restr
             for (int j = 1; j < SL; ++j) acc += sm[j][o];
         }
     }
-    bool wrote = false;
+    double squares = 0.0;
     if (lane == 0 && i < count) {
         if (cpad == c) {
-            dw[i] = acc;
-            wrote = true;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {                  // (dw may be aligned to 4 bytes only)
+                dw[i + v] = acc[v];
+                squares += (double)acc[v] * (double)acc[v];
+            }
         } else {
-            const int ch = (int)(i % cpad);
-            if (ch < c) {
-                dw[(i / cpad) * c + ch] = acc;
-                wrote = true;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int ch = (int)((i + v) % cpad);
+                if (ch < c) {
+                    dw[((i + v) / cpad) * c + ch] = acc[v];
+                    squares += (double)acc[v] * (double)acc[v];
+                }
             }
         }
     }
     if (sq) {
-        const double total = block_sum_double(wrote ? (double)acc * (double)acc : 0.0, red);
+        const double total = block_sum_double(squares, red);
         if (threadIdx.x == 0) sq[blockIdx.x] = total;
     }
 }
@@ -498,22 +507,40 @@ void lc_stem_filter_grad(const float* dwu, float* dw, int k, int r, int s, int c
     hipLaunchKernelGGL(stem_filter_grad_kernel, dim3(grid_for(total, 256)), dim3(256), 0, stream, dwu, dw, k, r, s, c, rb, cu, eh, ew);
 }
 
-// Grid of the split reduction for `count` outputs: few outputs spread each output's splits over more lanes so that the
-// chip still fills.  A fixed function of count (it is also the number of squared-norm pieces the reduction emits).
-static int reduce_splits_lanes(size_t count) { return count >= (size_t)1 << 18 ? 1 : count >= (size_t)1 << 15 ? 4 : 16; }
+// Shape of the split reduction for `count` outputs: four outputs per thread where count allows, and so many lanes per output that the chip still
+// fills.  A fixed function of count (it is also the number of squared-norm pieces the reduction emits).
+static void reduce_splits_shape(size_t count, int* lanes, int* vec) {
+    *vec = count % 4 == 0 ? 4 : 1;
+    const size_t threads = count / *vec;
+    *lanes = threads >= (size_t)1 << 18 ? 1 : threads >= (size_t)1 << 16 ? 4 : threads >= (size_t)1 << 14 ? 8 : 16;
+}
 
 size_t lc_reduce_splits_blocks(size_t count) {
-    const size_t out = 256 / reduce_splits_lanes(count);
+    int lanes, vec;
+    reduce_splits_shape(count, &lanes, &vec);
+    const size_t out = (size_t)(256 / lanes) * vec;
     return (count + out - 1) / out;
 }
 
 void lc_reduce_splits(const float* part, float* dw, int splits, size_t count, int cpad, int c, double* sq, hipStream_t stream) {
     if (!count) return;
-    const unsigned grid = (unsigned)lc_reduce_splits_blocks(count);
-    switch (reduce_splits_lanes(count)) {
-        case 1: hipLaunchKernelGGL(reduce_splits_kernel<1>, dim3(grid), dim3(256), 0, stream, part, dw, splits, count, cpad, c, sq); break;
-        case 4: hipLaunchKernelGGL(reduce_splits_kernel<4>, dim3(grid), dim3(256), 0, stream, part, dw, splits, count, cpad, c, sq); break;
-        default: hipLaunchKernelGGL(reduce_splits_kernel<16>, dim3(grid), dim3(256), 0, stream, part, dw, splits, count, cpad, c, sq);
+    const dim3 grid((unsigned)lc_reduce_splits_blocks(count)), block(256);
+    int lanes, vec;
+    reduce_splits_shape(count, &lanes, &vec);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, part, dw, splits, count, cpad, c, sq); };
+    if (vec == 4) {
+        switch (lanes) {
+            case 1: return go(reduce_splits_kernel<1, 4>);
+            case 4: return go(reduce_splits_kernel<4, 4>);
+            case 8: return go(reduce_splits_kernel<8, 4>);
+            default: return go(reduce_splits_kernel<16, 4>);
+        }
+    }
+    switch (lanes) {
+        case 1: return go(reduce_splits_kernel<1, 1>);
+        case 4: return go(reduce_splits_kernel<4, 1>);
+        case 8: return go(reduce_splits_kernel<8, 1>);
+        default: return go(reduce_splits_kernel<16, 1>);
     }
 }
 
