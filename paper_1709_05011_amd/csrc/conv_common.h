@@ -68,8 +68,7 @@ inline int device_cu_count() {
     return n;
 }
 
-// min_steps: k-steps a stream-K block takes at least
-inline SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_split = true, int min_steps = 8) {
+inline SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_split = true) {
     SkPlan pl;
     const long long rounds = tiles / resident_blocks;
     long long dp = rounds * resident_blocks;
@@ -82,11 +81,60 @@ inline SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_
         return pl;
     }
     pl.sk_iters = rest * nkt;
-    long long blocks = pl.sk_iters / min_steps;
+    long long blocks = pl.sk_iters / 8;                      // at least 8 k-steps per stream-K block
     if (blocks > resident_blocks) blocks = resident_blocks;
     if (blocks < 1) blocks = 1;
     pl.sk_blocks = (int)blocks;
     return pl;
+}
+
+// The same with the number of blocks for the tiles beyond the whole rounds chosen by what they cost.  Candidates: every such tile to S blocks in
+// equal parts -- S = 1 needs no fix-up at all -- or the k-steps end to end over the resident blocks.  The model, in us, fitted to bf16
+// layers of 2 to 64 images: a k-step takes `alone` where a block has its compute unit to itself, `shared` per block where blocks take turns;
+// tiles that several blocks share cost 5 for the fix-up launch and 0.018 per 128x128 part written and read again.  Before, every problem took
+// the last form with 8 k-steps per block or more, which splits tiles that the idle chip could take whole and joins tiles while compute units
+// stand idle (bf16: 1x1 over 512 channels, 16 images of 7x7 20.2 -> 10.4 us; over 64 channels, two of 56x56 22 -> 8.4; 2048 of 512, 64 of 7x7
+// 50 -> 19; 3x3 over 256, 64 of 14x14 46 -> 30).
+struct StepCost {
+    double alone, shared, tile;      // us, us, tile size in 128x128
+    int min_steps;                   // k-steps a block takes of a shared tile at least
+};
+inline SkPlan sk_plan_by_cost(long long tiles, int nkt, int resident_blocks, const StepCost& k) {
+    SkPlan pl = sk_plan(tiles, nkt, resident_blocks);
+    if (pl.sk_blocks == 0) return pl;
+    const long long rest = tiles - pl.dp_tiles, cus = device_cu_count();
+    auto cost = [&](long long blocks, long long steps, bool split) {
+        const double one = (double)steps * k.alone, many = (double)((blocks + cus - 1) / cus) * (double)steps * k.shared;
+        return (one > many ? one : many) + (split ? 5.0 + 0.018 * k.tile * (double)blocks : 0.0);
+    };
+    long long even = pl.sk_iters / k.min_steps;
+    if (even > resident_blocks) even = resident_blocks;
+    if (even < 1) even = 1;
+    pl.sk_blocks = (int)even;
+    double best = cost(even, (pl.sk_iters + even - 1) / even, pl.sk_iters != even * nkt);
+    for (int s = 1; rest * s <= resident_blocks && (s == 1 || nkt >= k.min_steps * s); ++s) {
+        const double c = cost(rest * s, (nkt + s - 1) / s, s > 1);
+        if (c < best) {
+            best = c;
+            pl.sk_blocks = (int)(rest * s);
+        }
+    }
+    return pl;
+}
+
+// First k-step of stream-K block j (j <= sk_blocks), in 32-bit arithmetic: a 64-bit division is some hundred instructions, and every block of
+// the product and of its fix-up starts with several.
+__device__ __forceinline__ int sk_begin(const GemmConv& p, int j) { return j * p.sk_q + div_by(j * p.sk_rem, p.sk_mul, p.sk_shift); }
+// The stream-K blocks [*j0, *j1) with a part of the k-steps [tb, te).
+__device__ __forceinline__ void sk_blocks_of(const GemmConv& p, int tb, int te, int* j0, int* j1) {
+    const float per_step = (float)p.sk_blocks / (float)p.sk_iters;
+    int a = min(p.sk_blocks - 1, (int)((float)tb * per_step)), b = min(p.sk_blocks, (int)((float)te * per_step));
+    while (a > 0 && sk_begin(p, a) > tb) --a;
+    while (sk_begin(p, a + 1) <= tb) ++a;
+    while (b > 0 && sk_begin(p, b - 1) >= te) --b;
+    while (b < p.sk_blocks && sk_begin(p, b) < te) ++b;
+    *j0 = a;
+    *j1 = b;
 }
 
 // Constants for div_by(): n / d == umulhi(n, mul) >> shift for 0 <= n < 2^31 (mul == 0 stands for d == 1).
@@ -101,6 +149,13 @@ inline void magic_for(int d, unsigned* mul, unsigned* shift) {
     while ((1ll << L) < d) ++L;
     *mul = (unsigned)((((unsigned long long)1 << (31 + L)) + (unsigned)d - 1) / (unsigned)d);
     *shift = (unsigned)(L - 1);
+}
+
+// The launcher's part of sk_begin(); sk_blocks and sk_iters are set.
+inline void sk_constants(GemmConv* p) {
+    p->sk_q = p->sk_blocks > 0 ? (int)(p->sk_iters / p->sk_blocks) : 0;
+    p->sk_rem = p->sk_blocks > 0 ? (int)(p->sk_iters % p->sk_blocks) : 0;
+    magic_for(p->sk_blocks, &p->sk_mul, &p->sk_shift);
 }
 
 }  // namespace

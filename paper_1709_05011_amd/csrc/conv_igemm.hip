@@ -17,6 +17,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <type_traits>
 
 #include "conv_common.h"
 
@@ -322,8 +323,8 @@ conv_gemm_pk_kernel(const GemmConv p) {
     const int rounds = p.dp_tiles / G;                     // the launcher makes dp_tiles a multiple of the grid
     int sk_it = 0, sk_len = 0;
     if (bid < p.sk_blocks) {
-        sk_it = (int)((long long)bid * p.sk_iters / p.sk_blocks);
-        sk_len = (int)((long long)(bid + 1) * p.sk_iters / p.sk_blocks) - sk_it;
+        sk_it = sk_begin(p, bid);
+        sk_len = sk_begin(p, bid + 1) - sk_it;
     }
     const int sk_tile = sk_it / nkt, sk_k0 = sk_it - sk_tile * nkt;
     const int F = rounds * nkt + sk_len;                   // k-steps this block runs
@@ -768,26 +769,43 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
     const int v = blockIdx.y;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
-    const long long tb = (long long)blockIdx.x * nkt, te = tb + nkt;      // this tile's k-steps in stream-K positions
-    auto begin_of = [&](long long j) { return j * p.sk_iters / p.sk_blocks; };
-    long long j = tb * p.sk_blocks / p.sk_iters;
-    while (j > 0 && begin_of(j) > tb) --j;
-    while (begin_of(j + 1) <= tb) ++j;
-    if (begin_of(j) <= tb && begin_of(j + 1) >= te) return;              // one block did the whole tile and stored it
+    const int tb = blockIdx.x * nkt, te = tb + nkt;                      // this tile's k-steps in stream-K positions
+    int j, j1;
+    sk_blocks_of(p, tb, te, &j, &j1);
+    if (j1 - j == 1) return;                                             // one block did the whole tile and stored it
 
+    // The first block's piece is the last of its range unless its range starts here (slot 0 or 1); all others start their ranges in this tile.
+    // Four parts are fetched at a time and added one after the other: a chain of dependent loads, and a division per part, made this kernel
+    // a third of the call on small problems (3x3 over 256 channels, two images of 14x14 in fp32: 26.8 -> 23.3 us).
+    const int skip = sk_begin(p, j) >= tb ? 0 : 1;
+    const float* first = p.partial + (size_t)2 * j * (BM * BN) + (size_t)skip * (BM * BN) + partial_index<TM, TN>(wave, 0, 0, v, lane);
+    const float* rest = p.partial + (size_t)2 * (j + 1) * (BM * BN) + partial_index<TM, TN>(wave, 0, 0, v, lane);
+    constexpr size_t kTile = 16 * 64;                                    // floats between the 32x32 tiles of a wave's part
+    const int more = j1 - j - 1;
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] = 0.f;
-    for (; j < p.sk_blocks && begin_of(j) < te; ++j) {
-        const bool first_of_block = begin_of(j) >= tb;                   // the segment starts where the block's range starts
-        const float* part = p.partial + ((size_t)2 * j + (first_of_block ? 0 : 1)) * (BM * BN);
+        for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] = 0.f + first[(i * TN + jj) * kTile];
+    auto add_parts = [&](int t, auto count) __attribute__((always_inline)) {
+        constexpr int U = decltype(count)::value;
+        float part[U][TM][TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] += part[partial_index<TM, TN>(wave, i, jj, v, lane)];
-    }
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jj = 0; jj < TN; ++jj) part[u][i][jj] = rest[(size_t)2 * (t + u) * (BM * BN) + (i * TN + jj) * kTile];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] += part[u][i][jj];
+    };
+    int t = 0;
+    for (; t + 4 <= more; t += 4) add_parts(t, std::integral_constant<int, 4>{});
+    for (; t < more; ++t) add_parts(t, std::integral_constant<int, 1>{});
     // move the sums to register position v, where store_tile expects them
     f32x16 out[TM][TN];
 #pragma unroll
@@ -1899,6 +1917,16 @@ bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
     return *tiles > 0 && *tiles * *nkt < 0x7fffffffLL;
 }
 
+// A 256x256 tile's partial sums are
+// 256 KB per block and piece: writing and re-reading them costs more than the idle end of the last round, which main_tile() has already bounded.
+// fp32 keeps the plain form: the order of a forward sum decides its last bits.
+template <int BM, int BN>
+SkPlan main_sk_plan(const GemmConv& p, long long tiles, int nkt) {
+    if (BM * BN >= 256 * 256 || !p.bf16) return sk_plan(tiles, nkt, resident_blocks(BM, BN), BM * BN < 256 * 256);
+    constexpr double size = BM * BN / 16384.0;
+    return sk_plan_by_cost(tiles, nkt, resident_blocks(BM, BN), StepCost{0.44 * size, 0.3 * size, size, 8});
+}
+
 // Whether the uniform-tap variant of the main kernel takes this problem: k-steps that do not straddle taps,
 // a tap mask that fits 32 bits, and tile-relative byte offsets (the images a tile can touch plus one filter
 // window, and BN filter rows) that stay below 2^31.
@@ -1937,6 +1965,24 @@ extern "C" int lc_selftest_division(int max_d) {
     return 0;
 }
 
+// Host-side check of sk_begin(): j * iters / blocks in 32-bit arithmetic for every block of a spread of work splits; 0, or the failing block count.
+extern "C" int lc_selftest_stream_k(int max_blocks) {
+    for (int blocks = 1; blocks <= max_blocks; ++blocks)
+        for (long long iters : {(long long)blocks, 8LL * blocks + 3, 37LL * blocks - 1, 1000003LL, 0x7fffffffLL / 2}) {
+            if (iters < blocks) continue;
+            GemmConv p = {};
+            p.sk_blocks = blocks;
+            p.sk_iters = iters;
+            sk_constants(&p);
+            for (int j = 0; j <= blocks; ++j) {
+                const unsigned n = (unsigned)(j * p.sk_rem);
+                const unsigned q = p.sk_mul ? (unsigned)(((unsigned long long)n * p.sk_mul) >> 32) >> p.sk_shift : n;
+                if ((long long)j * p.sk_q + q != j * iters / blocks) return blocks;
+            }
+        }
+    return 0;
+}
+
 namespace {
 
 template <int BM, int BN, bool SMALLC, bool BF16>
@@ -1945,9 +1991,7 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     int nkt;
     if (!sk_geometry<BM, BN>(p, &tiles, &nkt)) return LC_ERR_UNSUPPORTED;
     const int resident = resident_blocks(BM, BN);
-    // (a 256x256 tile's partial sums are 256 KB per block and piece: writing and re-reading them costs more than the idle
-    // end of the last round, which main_tile() has already bounded)
-    SkPlan pl = sk_plan(tiles, nkt, resident, BM * BN < 256 * 256);
+    SkPlan pl = main_sk_plan<BM, BN>(p, tiles, nkt);
     // persistent kernel: one round of resident blocks, each taking dp_tiles / grid whole tiles and then its
     // stream-K range; without a workspace for partial tiles the ranges are whole tiles
     if (pl.sk_blocks > 0 && !p.partial) pl.sk_blocks = 0;
@@ -1960,6 +2004,7 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     p.dp_tiles = pl.dp_tiles;
     p.sk_blocks = pl.sk_blocks;
     p.sk_iters = pl.sk_iters;
+    sk_constants(&p);
     magic_for(p.Qo, &p.qo_mul, &p.qo_shift);
     magic_for(p.Po, &p.po_mul, &p.po_shift);
     const unsigned grid = pl.dp_tiles > 0 ? (unsigned)resident : (unsigned)pl.sk_blocks;
@@ -2028,7 +2073,8 @@ size_t lc_conv_gemm_workspace(const GemmConv& p) {
         long long tiles;
         int nkt;
         if (!sk_geometry<BM, BN>(p, &tiles, &nkt)) return 0;
-        const SkPlan pl = sk_plan(tiles, nkt, resident_blocks(BM, BN), BM * BN < 256 * 256);
+        const SkPlan pl = main_sk_plan<BM, BN>(p, tiles, nkt);
+        if (pl.sk_iters == (long long)pl.sk_blocks * nkt) return 0;              // no tile is shared
         return (size_t)2 * pl.sk_blocks * BM * BN * sizeof(float);
     });
 }

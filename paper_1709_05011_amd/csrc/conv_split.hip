@@ -90,8 +90,8 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
     const int rounds = p.dp_tiles / G;                     // the launcher makes dp_tiles a multiple of the grid
     int sk_it = 0, sk_len = 0;
     if (bid < p.sk_blocks) {
-        sk_it = (int)((long long)bid * p.sk_iters / p.sk_blocks);
-        sk_len = (int)((long long)(bid + 1) * p.sk_iters / p.sk_blocks) - sk_it;
+        sk_it = sk_begin(p, bid);
+        sk_len = sk_begin(p, bid + 1) - sk_it;
     }
     const int sk_tile = sk_it / nkt, sk_k0 = sk_it - sk_tile * nkt;
     const int F = rounds * nkt + sk_len;                   // k-steps this block runs
@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
             return;
         }
         // 16 rows at a time through the wave's own LDS slice, so that a store covers whole rows of the wave's part (4 x 256 or 8 x 128 bytes, in
-        // lane order) and not 16 bytes of each of 16 rows per 16 lanes: 1x1 over 64 channels at 56x56, batch 256, 270 -> 23x us.
+        // lane order) and not 16 bytes of each of 16 rows per 16 lanes: 1x1 over 64 channels at 56x56, batch 256, 270 -> 245 us.
         // Rows past M: bit 31 of the lane offset; columns past N likewise, per group of four (value by value where N is not a multiple of
         // four).  Offsets count from the tile's first row (scatter: from its first pixel).
         long long base_px = m0;
@@ -467,27 +467,22 @@ __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
-    const long long tb = (long long)blockIdx.x * nkt, te = tb + nkt;      // this tile's k-steps in stream-K positions
-    auto begin_of = [&](long long j) { return j * p.sk_iters / p.sk_blocks; };
-    long long j = tb * p.sk_blocks / p.sk_iters;
-    while (j > 0 && begin_of(j) > tb) --j;
-    while (begin_of(j + 1) <= tb) ++j;
-    if (begin_of(j) <= tb && begin_of(j + 1) >= te) return;              // one block did the whole tile and stored it
-    long long j1 = te * p.sk_blocks / p.sk_iters;                        // one past the last block with a part of this tile
-    while (j1 > 0 && begin_of(j1 - 1) >= te) --j1;
-    while (j1 < p.sk_blocks && begin_of(j1) < te) ++j1;
+    const int tb = blockIdx.x * nkt, te = tb + nkt;                      // this tile's k-steps in stream-K positions
+    int j, j1;
+    sk_blocks_of(p, tb, te, &j, &j1);
+    if (j1 - j == 1) return;                                             // one block did the whole tile and stored it
     const f32x4* part = reinterpret_cast<const f32x4*>(p.partial) + (blockIdx.y * 4 + wave) * 64 + lane;
     constexpr size_t kSlot = BM * BN / 4;
     // the first block's piece is the last of its range unless its range starts here; all others start their ranges in this tile
-    f32x4 sum = part[((size_t)2 * j + (begin_of(j) >= tb ? 0 : 1)) * kSlot];
-    for (++j; j < j1; j += 4) {
+    f32x4 sum = part[((size_t)2 * j + (sk_begin(p, j) >= tb ? 0 : 1)) * kSlot];
+    for (++j; j + 4 <= j1; j += 4) {
         f32x4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = part[(size_t)2 * (j + u < j1 ? j + u : j) * kSlot];
+        for (int u = 0; u < 4; ++u) v[u] = part[(size_t)2 * (j + u) * kSlot];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j + u < j1) sum += v[u];
+        for (int u = 0; u < 4; ++u) sum += v[u];
     }
+    for (; j < j1; ++j) sum += part[(size_t)2 * j * kSlot];
     const int tile = p.dp_tiles + blockIdx.x, tm = tile / nbn;
     const int ti = blockIdx.y / TN, tj = blockIdx.y - ti * TN;
     const int m = tm * BM + (wave >> 1) * (BM / 2) + ti * 16 + (lane & 15);
@@ -823,7 +818,7 @@ bool split_plan(const GemmConv& p, SplitPlan* s) {
     s->tiles = (long long)((p.M + 127) / 128) * ((p.N + s->bn - 1) / s->bn);
     s->nkt = (p.Kg + BK - 1) / BK;
     if (s->tiles <= 0 || s->tiles * s->nkt >= 0x7fffffffLL) return false;
-    s->sk = sk_plan(s->tiles, s->nkt, s->resident, true, 4);
+    s->sk = sk_plan_by_cost(s->tiles, s->nkt, s->resident, StepCost{s->bn == 128 ? 1.2 : 0.7, s->bn == 128 ? 1.2 : 0.6, s->bn / 128.0, 4});
     return true;
 }
 
@@ -855,7 +850,7 @@ lc_status launch_split_tile(const GemmConv& p, const SplitPlan& s, bool whole, u
 
 size_t lc_conv_split_workspace(const GemmConv& p) {
     SplitPlan s;
-    if (!split_plan(p, &s)) return 0;
+    if (!split_plan(p, &s) || s.sk.sk_iters == (long long)s.sk.sk_blocks * s.nkt) return 0;      // (no tile is shared)
     return (size_t)2 * s.sk.sk_blocks * 128 * s.bn * sizeof(float);
 }
 
@@ -879,6 +874,7 @@ lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream) {
     p.dp_tiles = s.sk.dp_tiles;
     p.sk_blocks = s.sk.sk_blocks;
     p.sk_iters = s.sk.sk_iters;
+    sk_constants(&p);
     magic_for(p.Qo, &p.qo_mul, &p.qo_shift);
     magic_for(p.Po, &p.po_mul, &p.po_shift);
     const unsigned grid = p.dp_tiles > 0 ? (unsigned)s.resident : (unsigned)p.sk_blocks;

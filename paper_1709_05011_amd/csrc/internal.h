@@ -83,6 +83,9 @@ struct GemmConv {
     // remaining tiles, their total k-steps, and the workspace for partial tiles (2 slots per such block)
     int dp_tiles, sk_blocks;
     long long sk_iters;
+    // first k-step of stream-K block j: j * sk_iters / sk_blocks = j * sk_q + j * sk_rem / sk_blocks, the quotient by multiply-high constants
+    int sk_q, sk_rem;
+    unsigned sk_mul, sk_shift;
     float* partial;
     // multiply-high division constants for Qo and Po (filled in by the launcher)
     unsigned qo_mul, qo_shift, po_mul, po_shift;
@@ -94,6 +97,7 @@ struct GemmConv {
 };
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream);
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` for this problem; 0: the kernel that takes it has none
+extern "C" int lc_selftest_stream_k(int max_blocks);   // host check of the work split's 32-bit form (0 = all good)
 extern "C" int lc_selftest_division(int max_d);   // host check of the multiply-high division constants (0 = all good)
 bool lc_conv_gemm_bf16_native(const GemmConv& p);   // can the bf16 MFMA kernel take this problem (shape and alignment)?
 bool lc_conv_gemm_scatter_ok(const GemmConv& p);    // can the main kernel's scatter epilogue take this problem?

@@ -143,6 +143,14 @@ def test_index_division_constants_match_plain_division():
     assert L.lc_selftest_division(20000) == 0
 
 
+def test_work_split_in_32_bits_matches_the_plain_quotients():
+    # first k-step of every block of a shared range: j * iters / blocks, up to four blocks on each of 256 compute units and beyond
+    L = lc.lib()
+    L.lc_selftest_stream_k.restype = ctypes.c_int
+    L.lc_selftest_stream_k.argtypes = [ctypes.c_int]
+    assert L.lc_selftest_stream_k(2048) == 0
+
+
 def test_warmup_poly_lr_host_arithmetic_matches_oracle():
     import oracle
     base, start, W, T = 3.2, 0.1, 195, 3516
