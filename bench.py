@@ -32,6 +32,7 @@ if ROOT not in sys.path:
 
 PEAK_MFMA_F32 = 157.3      # TFLOP/s, MI355X dense fp32 matrix
 PEAK_MFMA_BF16 = 2500.0    # TFLOP/s, MI355X dense bf16 matrix
+PEAK_SPLIT = PEAK_MFMA_BF16 / 6   # fp32 backward-data and filter gradients: six bf16 products per fp32 product
 PEAK_HBM = 8000.0          # GB/s
 LARS_BYTES_PER_PARAM = 28  # norm pass reads w, g (8 B); update reads w, g, v and writes w, v (20 B)
 # HBM-side bytes per launch of the dominant kernel: counters cannot be read from inside this process, so the figure is
@@ -197,6 +198,8 @@ def run_train_step(args):
                 and not os.environ.get("LARSCONV_NO_STEM_DIRECT")):
             return "conv_stem"
         n_gemm = cs.k if pass_ == "fwd" else cs.c
+        if pass_ == "bwd_data" and not bf16:
+            return "conv_split_128x64" if n_gemm <= 64 else "conv_split_128x128"
         k_gemm = cs.c if pass_ == "fwd" else cs.k
         rows = cs.n * cs.p * cs.q if pass_ == "fwd" or cs.stride > 1 else cs.n * cs.h * cs.w
         scatter = pass_ == "bwd_data" and cs.stride > 1
@@ -289,7 +292,10 @@ def run_train_step(args):
     # bf16: all three passes multiply on the bf16 matrix pipe (the filter gradient too, unless the comparison knob
     # LARSCONV_WGRAD_WIDEN sends it through the widening fp32 kernel)
     widened = dom == "wgrad" and os.environ.get("LARSCONV_WGRAD_WIDEN")
-    peak = PEAK_MFMA_BF16 if bf16 and not widened else PEAK_MFMA_F32
+    peak = (PEAK_MFMA_BF16 if bf16 and not widened else PEAK_MFMA_F32 if bf16 or not dom.startswith(("conv_split", "wgrad"))
+            else PEAK_SPLIT)
+    pass_peak = {p: PEAK_MFMA_BF16 if bf16 else PEAK_MFMA_F32 if p == "fwd" else PEAK_SPLIT for p in ("fwd", "bwd_data", "bwd_weight")}
+    conv_ideal_ms = sum(per_pass[p][2] / (pass_peak[p] * 1e9) for p in pass_peak)
     name = {"alexnet_bn": "AlexNet-BN", "alexnet": "AlexNet (grouped)", "resnet50": "ResNet-50"}[args.model]
     n_conv = sum(1 for l in layers if l.cs.h * l.cs.w > 1 and not (l.cs.r == l.cs.h and l.cs.s == l.cs.w and l.cs.pad == 0))
     n_fc = len(layers) - n_conv
@@ -317,7 +323,7 @@ def run_train_step(args):
                      "flops_per_launch": dfl / dn},
         "conv_tflops": {p: round(per_pass[p][2] / (per_pass[p][0] * 1e-3) / 1e12, 2) for p in ("fwd", "bwd_data", "bwd_weight")},
         "conv_tflops_all": round(conv_flops / (conv_ms * 1e-3) / 1e12, 2),
-        "conv_frac_of_mfma_peak": round(conv_flops / (conv_ms * 1e-3) / 1e12 / peak, 4),
+        "conv_frac_of_mfma_peak": round(conv_ideal_ms / conv_ms, 4),      # every pass against the peak of its own instructions
         # lars_step inside the step: its gradients were written a moment ago and part of the 307 MB working set is still
         # in the 256 MB Infinity Cache, so this is an effective rate, not achieved HBM bandwidth ("cold" below is)
         "lars": {"in_step": {"ms": round(lars_ms, 4), "GBps_effective": round(lars_gbps, 1),
@@ -438,7 +444,7 @@ def run_sweep(args):
                 continue                      # the first layer's input gradient is never needed in a training step
             med, mn = time_call(torch, fn, args.iters)
             tf = cs.flops / (med * 1e-3) / 1e12
-            roof = min(peak, cs.flops / min_bytes[p] * PEAK_HBM / 1e3)
+            roof = min(peak if bf16 or p == "fwd" else PEAK_SPLIT, cs.flops / min_bytes[p] * PEAK_HBM / 1e3)
             row[p + "_ms"] = round(med, 4)
             row[p + "_tflops"] = round(tf, 2)
             row[p + "_roof_tflops"] = round(roof, 1)
