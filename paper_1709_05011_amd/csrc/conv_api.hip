@@ -288,6 +288,27 @@ bool stem_direct(const lc_conv_desc* d, const Plan& pl, lc_pass pass) {
     return pass == LC_PASS_FWD || pass == LC_PASS_BWD_WEIGHT;
 }
 
+// The filter-gradient problem of a layer: its shape, without pointers and split.
+GemmWgrad gemm_wgrad(const lc_conv_desc* d, const Plan& pl) {
+    GemmWgrad g = {};
+    g.M = d->n * pl.P * pl.Q;
+    g.K = d->k;
+    g.J = d->r * d->s * pl.cpad;
+    g.H = d->h;
+    g.W = d->w;
+    g.C = pl.cpad;
+    g.P = pl.P;
+    g.Q = pl.Q;
+    g.R = d->r;
+    g.S = d->s;
+    g.sh = d->stride_h;
+    g.sw = d->stride_w;
+    g.ph = d->pad_h;
+    g.pw = d->pad_w;
+    g.bf16 = pl.bf16;
+    return g;
+}
+
 lc_status make_plan(const lc_conv_desc* d, lc_pass pass, Plan* pl) {
     const lc_status st = check_desc(d, &pl->P, &pl->Q);
     if (st != LC_OK) return st;
@@ -383,7 +404,7 @@ lc_status make_plan(const lc_conv_desc* d, lc_pass pass, Plan* pl) {
         } else if (pl->wgrad_slab) {
             pl->splits = lc_wgrad_slab_splits(d->n, d->h, d->w, pl->cpad, d->k, &pl->m_per_split);
         } else {
-            pl->splits = lc_wgrad_splits(M, d->k, J, d->r * d->s, pl->bf16);
+            pl->splits = lc_wgrad_splits(gemm_wgrad(d, *pl));
             pl->m_per_split = (M + pl->splits - 1) / pl->splits;
         }
         pl->wgrad_direct = pl->splits == 1 && !pad && !pl->stem_wgrad;
@@ -807,26 +828,11 @@ lc_status bwd_weight_impl(const lc_conv_desc* d, const void* x, const void* dy, 
         lc_pad_channels(xs, at(workspace, pl.xpad), (size_t)d->n * d->h * d->w, d->c, pl.cpad, pl.esize, stream);
         xs = at(workspace, pl.xpad);
     }
-    GemmWgrad g = {};
+    GemmWgrad g = gemm_wgrad(d, pl);
     g.dy = dys;
     g.x = xs;
-    g.M = d->n * pl.P * pl.Q;
-    g.K = d->k;
-    g.J = d->r * d->s * pl.cpad;
-    g.H = d->h;
-    g.W = d->w;
-    g.C = pl.cpad;
-    g.P = pl.P;
-    g.Q = pl.Q;
-    g.R = d->r;
-    g.S = d->s;
-    g.sh = d->stride_h;
-    g.sw = d->stride_w;
-    g.ph = d->pad_h;
-    g.pw = d->pad_w;
     g.splits = pl.splits;
     g.m_per_split = pl.m_per_split;
-    g.bf16 = pl.bf16;
     g.slab = pl.wgrad_slab;
     g.d = pl.wgrad_direct ? dwdst : reinterpret_cast<float*>(at(workspace, pl.part));
     st = lc_launch_wgrad_f32(g, stream);

@@ -1302,19 +1302,20 @@ __global__ void __launch_bounds__(WGM* WGN * 64) wgrad_f32_kernel(const GemmWgra
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward-weight kernel for a 1x1 window with stride 1 and no padding, bf16 operands, channel counts multiples of 8.  Output pixel m reads
-// input pixel m, X is a plain [M][C] matrix like dY, and both operands are fetched with 16-byte buffer loads at a lane-constant offset
+// backward-weight kernel for a 1x1 window with stride 1 and no padding: bf16 operands with channel counts that are multiples of 8, and fp32
+// (multiples of 4) where wgrad_by_split() leaves it here (64 -> 64, 256 images of 56x56: 92 us, 96 with wgrad_f32_kernel).  Output pixel m
+// reads input pixel m, X is a plain [M][C] matrix like dY, and both operands are fetched with 16-byte buffer loads at a lane-constant offset
 // plus the step's scalar offset: no per-pixel work at all.  Rows past the end of the split are cut off by the size of the buffer.
-// MFMA operands come from the transposing LDS read, as in wgrad_bf16_kernel.
+// bf16 MFMA operands come from the transposing LDS read, as in wgrad_bf16_kernel.
 // ------------------------------------------------------------------------------------------------
-template <int BM, int BN>
-__global__ void __launch_bounds__(256, 4) wgrad_plain_bf16_kernel(const GemmWgrad p) {   // 4 blocks per compute unit: lc_wgrad_splits()
-    using E = uint16_t;
-    constexpr int ES = 2, EPC = 8;                                // element bytes, elements per 16-byte vector
-    constexpr int BK = 32;
+template <int BM, int BN, bool BF16>
+__global__ void __launch_bounds__(256, 4) wgrad_plain_kernel(const GemmWgrad p) {   // 4 blocks per compute unit: lc_wgrad_splits()
+    using E = typename OutT<BF16>::type;                          // operand element type (float, or the bits of a bf16)
+    constexpr int ES = (int)sizeof(E), EPC = 16 / ES;             // element bytes, elements per 16-byte vector
+    constexpr int BK = BF16 ? 32 : 16;
     constexpr int AQ = BM / EPC, ARPP = 256 / AQ, LA = BK / ARPP; // 16-byte vectors per row, rows per pass of the block
     constexpr int BQ = BN / EPC, BRPP = 256 / BQ, LB = BK / BRPP;
-    constexpr int PA = BM + 32, PB = BN + 32;
+    constexpr int PA = BM + (BF16 ? 32 : 4), PB = BN + (BF16 ? 32 : 4);
     constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
     static_assert(256 % AQ == 0 && BK % ARPP == 0 && LA >= 1, "tile shape");
 
@@ -1385,32 +1386,48 @@ __global__ void __launch_bounds__(256, 4) wgrad_plain_bf16_kernel(const GemmWgra
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    // Fragments of one group of 16 reduction rows (one MFMA of k = 16 per tile), double-buffered: slot g & 1 holds group g of the step.
-    constexpr int NG = BK / 16;
-    bf16x8 fa[2][TM], fb[2][TN];
+    // Fragments of one group of reduction rows (fp32: 2 rows, one MFMA of k = 2 per tile; bf16: 16 rows, one MFMA of k = 16 per tile),
+    // double-buffered: slot g & 1 holds group g of the step.
+    constexpr int NG = BF16 ? BK / 16 : BK / 2;
+    using Frag = typename std::conditional<BF16, bf16x8, float>::type;
+    Frag fa[2][TM], fb[2][TN];
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     // the transposing LDS read (see wgrad_bf16_kernel): this lane's row and column inside a 16-row group
     const int tr_row = 8 * (lane >> 5) + ((lane & 15) >> 2), tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
     auto read_frags = [&](int buf, int g, int slot) __attribute__((always_inline)) {
-        auto one = [&](const E* base, int pitch) __attribute__((always_inline)) {
-            const E* q = base + (16 * g + tr_row) * pitch + tr_col;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)q);
-            const s16x4 hi =
-                __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(q + 4 * pitch));
-            const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            return __builtin_bit_cast(bf16x8, v);
-        };
+        if constexpr (BF16) {
+            auto one = [&](const E* base, int pitch) __attribute__((always_inline)) {
+                const E* q = base + (16 * g + tr_row) * pitch + tr_col;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)q);
+                const s16x4 hi =
+                    __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(q + 4 * pitch));
+                const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                return __builtin_bit_cast(bf16x8, v);
+            };
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[slot][i] = one(&As[buf][wm * WTM + i * 32], PA);
+            for (int i = 0; i < TM; ++i) fa[slot][i] = one(&As[buf][wm * WTM + i * 32], PA);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[slot][j] = one(&Bs[buf][wn * WTN + j * 32], PB);
+            for (int j = 0; j < TN; ++j) fb[slot][j] = one(&Bs[buf][wn * WTN + j * 32], PB);
+        } else {
+            const E* as = &As[buf][(2 * g + (lane >> 5)) * PA + wm * WTM + (lane & 31)];
+            const E* bs = &Bs[buf][(2 * g + (lane >> 5)) * PB + wn * WTN + (lane & 31)];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[slot][i] = as[i * 32];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[slot][j] = bs[j * 32];
+        }
     };
     auto mfma_group = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (BF16)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
+            }
     };
 
     // One step out of LDS buffer `cur` (a literal at each call).  On entry slot 0 holds the step's first group of
@@ -1419,6 +1436,7 @@ __global__ void __launch_bounds__(256, 4) wgrad_plain_bf16_kernel(const GemmWgra
     // the first fragments of the next step are read while the last MFMAs run.  Steps past the end of the split
     // are fetched and stored like the others: all of their rows are past m_end, so nothing is read from memory
     // and zeros are stored.
+    constexpr int G_STORE = NG > 2 ? 1 : 0, G_LOAD = NG > 2 ? 3 : 0;
     auto step = [&](int cur) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
@@ -1431,8 +1449,8 @@ __global__ void __launch_bounds__(256, 4) wgrad_plain_bf16_kernel(const GemmWgra
             __builtin_amdgcn_sched_barrier(0);
             mfma_group(g & 1);
             __builtin_amdgcn_sched_barrier(0);
-            if (g == 0) {
-                sstore(cur ^ 1);
+            if (g == G_STORE) sstore(cur ^ 1);
+            if (g == G_LOAD) {
                 advance();
                 gload();
             }
@@ -2187,22 +2205,44 @@ static void wgrad_tile(int K, int J, int* bm, int* bn) {
     *bn = J > 64 ? 128 : 64;
 }
 
-int lc_wgrad_splits(int M, int K, int J, int taps, bool bf16) {
+static bool wgrad_plain_shape(const GemmWgrad& p) {        // output pixel m reads input pixel m
+    return p.R == 1 && p.S == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 && p.H == p.P && p.W == p.Q;
+}
+
+// Whether conv_split.hip's kernel is the one for an fp32 filter gradient (a fixed function of the shape: the split count depends on it).  It takes
+// pairs of columns inside one tap and windows of at most 32 taps.  The fp32 matrix instructions stay the better choice (us: split kernel /
+// fp32 kernel) with filter counts that are multiples of four -- otherwise they have to load value by value, 10.6 / 19.4 -- for
+//   one 64x64 tile, bound by memory and launches: 64 -> 64 1x1, 256 images of 56x56 110 / 92; 24 -> 16 1x1 on 169,756 rows 23.0 / 19.7; 4 -> 24
+//     3x3 on 33,135 rows 16.2 / 13.5; but windows and strides on 1,856 to 4,802 rows 11.7 to 14.6 / 14.1 to 16.9;
+//   at most 64 filters or columns on few rows, a few k-steps of latency: 1x1 on 144 to 224 rows 10.7 to 11.1 / 7.9 to 10.4, on 361 rows 10.9 / 11.6;
+//     windows on 81 to 144 rows 10.3 to 13.5 / 8.6 to 11.6, on 169 rows 12.2 / 12.9;
+// and for a large result on few rows, where the partial sums of a second split cost more than the shorter sums save: 2044 -> 48 5x5 on 198 rows
+// 35.6 / 27.5, 928 -> 496 5x5 on 144 rows 63 / 42, but 172 -> 792 3x3 on 256 rows 24 / 31.
+static bool wgrad_by_split(const GemmWgrad& p) {
+    if (p.bf16 || p.C % 2 != 0 || (long long)p.R * p.S > 32) return false;
+    if (p.M <= 256 && (long long)p.K * p.J >= 1 << 21) return false;
+    if (p.K % 4 != 0 || (p.K > 64 && p.J > 64)) return true;
+    const bool plain = wgrad_plain_shape(p);
+    if (p.K <= 64 && p.J <= 64) return !plain && p.M > 512 && p.M <= 16384;
+    return p.M > (plain ? 256 : 160);
+}
+
+int lc_wgrad_splits(const GemmWgrad& p) {
     int bm, bn;
-    wgrad_tile(K, J, &bm, &bn);
-    const long long tiles = (long long)((K + bm - 1) / bm) * ((J + bn - 1) / bn);
-    const bool split = !bf16 && taps <= 32;               // the kernel of conv_split.hip (lc_wgrad_split_ok)
+    wgrad_tile(p.K, p.J, &bm, &bn);
+    const long long tiles = (long long)((p.K + bm - 1) / bm) * ((p.J + bn - 1) / bn);
+    const bool split = wgrad_by_split(p);
     // blocks of this tiling that fit on the chip at once (registers and LDS of the kernel instances below):
     // the split count fills exactly one such round, never spills a few blocks into a second one -- the split kernel fills two, which keeps
     // its sums short enough for the accuracy of the fp32 instructions (activations behind a ReLU, 1x1 at 56x56, batch 256: error 5.8e-7
     // with one round, 4.1e-7 with two, 4.2e-7 before)
-    const int per_cu = split ? 2 * lc_wgrad_split_blocks_per_cu(bm, bn) : (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (bf16 ? 5 : 6);
+    const int per_cu = split ? 2 * lc_wgrad_split_blocks_per_cu(bm, bn) : (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (p.bf16 ? 5 : 6);
     const long long round = (long long)per_cu * device_cu_count();
     long long want = round / tiles;
     // at least so many reduction rows per split (two images of 14x14 with 256 channels: 29 us at 256, 23.5 at 128, 22 at 64, where sixteen
     // of 7x7 lose 12 %; bf16 loses 5 % on small layers at 128)
     const int least = split ? 128 : 256;
-    const long long most = (M + least - 1) / least;
+    const long long most = (p.M + least - 1) / least;
     if (want > most) want = most;
     if (want < 1) want = 1;
     if (want > 8192) want = 8192;
@@ -2258,30 +2298,31 @@ static lc_status launch_wgrad_bf16(const GemmWgrad& p, hipStream_t stream) {
     return lc_end_call();
 }
 
-// Whether the split kernel takes this fp32 problem: pairs of columns inside one tap, a window of at most 32 taps, and buffer offsets (a split's
-// rows of dY and of a plain X; the images a split touches plus one window of X) below 2^31 bytes.
+// Whether the split kernel takes this problem: wgrad_by_split() and buffer offsets (a split's rows of dY and of a plain X; the images a split
+// touches plus one window of X) below 2^31 bytes.
 static bool wgrad_split_ok(const GemmWgrad& p) {
-    if (p.bf16 || p.C % 2 != 0 || (long long)p.R * p.S > 32) return false;
+    if (!wgrad_by_split(p)) return false;
     const long long rows = (long long)p.m_per_split + 64, wide = p.K > p.C ? p.K : p.C;
     const long long images = rows / ((long long)p.P * p.Q) + 2;
     const long long b_span = ((images * p.H + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.W + p.S + 1) * p.C * 4;
     return rows * wide * 4 < 0x7fff0000LL && b_span < 0x7fff0000LL;
 }
 
-// Whether the plain 1x1 kernel takes this bf16 problem: 16-byte vectors and buffer offsets (a split's rows of dY and X) below 2^31 bytes.
+// Whether the plain 1x1 kernel takes this problem: 16-byte vectors and buffer offsets (a split's rows of dY and X) below 2^31 bytes.
 static bool wgrad_plain_ok(const GemmWgrad& p) {
     static const bool off = getenv("LARSCONV_NO_UNIFORM_TAP") != nullptr;     // comparison runs
-    if (off || !p.bf16 || p.C % 8 != 0 || p.K % 8 != 0 || !aligned16(p.dy) || !aligned16(p.x)) return false;
-    if (p.R != 1 || p.S != 1 || p.sh != 1 || p.sw != 1 || p.ph != 0 || p.pw != 0 || p.H != p.P || p.W != p.Q) return false;
+    const int epc = p.bf16 ? 8 : 4;
+    if (off || p.C % epc != 0 || p.K % epc != 0 || !aligned16(p.dy) || !aligned16(p.x)) return false;
+    if (!wgrad_plain_shape(p)) return false;
     const long long rows = (long long)p.m_per_split + 64;
-    return rows * (p.K > p.C ? p.K : p.C) * 2 < 0x7fff0000LL;
+    return rows * (p.K > p.C ? p.K : p.C) * (p.bf16 ? 2 : 4) < 0x7fff0000LL;
 }
 
-template <int BM, int BN>
+template <int BM, int BN, bool BF16>
 static lc_status launch_wgrad_plain(const GemmWgrad& p, hipStream_t stream) {
     const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
     if (tiles <= 0 || tiles * p.splits > 0x7fffffffLL) return LC_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL((wgrad_plain_bf16_kernel<BM, BN>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL((wgrad_plain_kernel<BM, BN, BF16>), dim3((unsigned)(tiles * p.splits)), dim3(256), 0, stream, p);
     return lc_end_call();
 }
 
@@ -2293,11 +2334,11 @@ static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
         wgrad_tile(p.K, p.J, &bm, &bn);
         return lc_launch_wgrad_split(p, bm, bn, stream);
     }
-    if (BF16 && wgrad_plain_ok(p) && !getenv("LARSCONV_WGRAD_WIDEN")) {
+    if (wgrad_plain_ok(p) && !(BF16 && getenv("LARSCONV_WGRAD_WIDEN"))) {
         int bm, bn;
         wgrad_tile(p.K, p.J, &bm, &bn);
-        if (bm == 128) return bn == 128 ? launch_wgrad_plain<128, 128>(p, stream) : launch_wgrad_plain<128, 64>(p, stream);
-        return bn == 128 ? launch_wgrad_plain<64, 128>(p, stream) : launch_wgrad_plain<64, 64>(p, stream);
+        if (bm == 128) return bn == 128 ? launch_wgrad_plain<128, 128, BF16>(p, stream) : launch_wgrad_plain<128, 64, BF16>(p, stream);
+        return bn == 128 ? launch_wgrad_plain<64, 128, BF16>(p, stream) : launch_wgrad_plain<64, 64, BF16>(p, stream);
     }
     if (BF16 && p.C % 8 == 0 && p.K % 8 == 0 && aligned16(p.dy) && aligned16(p.x) && !getenv("LARSCONV_WGRAD_WIDEN")) {
         int bm, bn;                                   // the bf16 matrix pipe; LARSCONV_WGRAD_WIDEN=1: comparison runs

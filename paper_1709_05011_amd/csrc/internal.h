@@ -155,7 +155,7 @@ struct GemmWgrad {
     int slab;           // 3x3 stride-1 pad-1 bf16 layer for wgrad3x3_slab_kernel: m_per_split counts padded positions
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
-int lc_wgrad_splits(int M, int K, int J, int taps, bool bf16);   // fixed function of the shape (determinism)
+int lc_wgrad_splits(const GemmWgrad& p);   // fixed function of the shape (determinism)
 // fp32 operands on the bf16 matrix pipe (conv_split.hip), output tile bm x bn; and how many of its blocks fit on a compute unit
 lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream);
 int lc_wgrad_split_blocks_per_cu(int bm, int bn);

@@ -151,6 +151,24 @@ def test_work_split_in_32_bits_matches_the_plain_quotients():
     assert L.lc_selftest_stream_k(2048) == 0
 
 
+def test_filter_gradients_bound_by_memory_or_latency_plan_for_the_fp32_kernels():
+    # the plan's partial sums tell the kernel: one round of blocks with 256 rows each at least for the fp32 kernels, two rounds with 128 rows for
+    # the kernel with split operands (no GPU in sight: the plan counts 256 compute units)
+    def partials(n, c, hw, k, r=1, stride=1):
+        d = lc.ConvDesc(n, c, hw, hw, k, r, r, stride, stride, r // 2, r // 2)
+        return lc.conv2d_workspace_bytes(d, lc.LC_PASS_BWD_WEIGHT) / (4.0 * k * r * r * c)
+
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("block counts of a chip with 256 compute units")
+    assert partials(256, 64, 56, 64) == 8 * 256            # ResNet-50's 64 -> 64 layer
+    assert partials(64, 4, 56, 64, 3) == -(-64 * 56 * 56 // 256)
+    assert partials(256, 16, 28, 48) == -(-256 * 28 * 28 // 256)
+    assert partials(1, 232, 13, 8) == 0 and partials(3, 92, 6, 8, 5) == 0 and partials(22, 2044, 6, 48, 5, 2) == 0      # few rows: one split
+    assert partials(2, 256, 14, 256, 3) == 4               # ... and the split kernel's 128 rows
+    assert partials(2, 64, 37, 42) == -(-2 * 37 * 37 // 128)
+
+
 def test_warmup_poly_lr_host_arithmetic_matches_oracle():
     import oracle
     base, start, W, T = 3.2, 0.1, 195, 3516

@@ -60,8 +60,9 @@ def _data(s, seed, wide=False):
     return d, make(s[0], s[2], s[3], s[1]), make(s[4], s[5], s[5], s[1]), make(s[0], p, q, s[4])
 
 
-def _within(got, ref, mag, k):
-    bound = (6 * -(-k // 32) + 66) * 2.0 ** -23 * mag
+def _within(got, ref, mag, k, step=None):
+    """step: reduction indices per rounding where the fp32 instructions may run (two of them per instruction)"""
+    bound = (max(6 * -(-k // 32), -(-k // step) if step else 0) + 66) * 2.0 ** -23 * mag
     bad = ~(np.abs(got.astype(np.float64) - ref) <= bound)
     assert not bad.any(), (int(bad.sum()), np.max(np.abs(got - ref) / np.maximum(mag, 1e-300)))
 
@@ -73,6 +74,23 @@ def test_all_three_passes_within_the_bound(s, wide):
     _within(gu.gpu_fwd(d, x, w), _conv64(x, w, s), _conv64(abs(x), abs(w), s), s[1] * s[5] ** 2)
     _within(gu.gpu_bwd_data(d, dy, w), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
     _within(gu.gpu_bwd_weight(d, x, dy), _conv64_wgrad(x, dy, s), _conv64_wgrad(abs(x), abs(dy), s), dy.size // s[4])
+
+
+# The rows, filters and columns at which a filter gradient changes kernels (wide results, one 64x64 tile, few rows, filter counts that are not
+# multiples of four), both sides of each line; n, c, hw, k, window, stride.
+ROUTES = [
+    (1, 64, 23, 64, 1, 1), (1, 64, 23, 62, 1, 1), (1, 32, 46, 64, 1, 2), (1, 32, 44, 64, 1, 2), (4, 32, 128, 64, 1, 2), (5, 32, 128, 64, 1, 2),
+    (1, 68, 16, 64, 1, 1), (1, 68, 17, 64, 1, 1), (1, 64, 16, 68, 1, 1), (1, 64, 17, 66, 1, 1), (1, 8, 12, 64, 3, 1), (1, 8, 13, 64, 3, 1),
+    (1, 2048, 16, 1024, 1, 1), (1, 2048, 15, 1028, 1, 1), (1, 2048, 17, 1024, 1, 1), (2, 4, 56, 64, 3, 1), (1, 7, 28, 64, 1, 1), (3, 64, 56, 64, 1, 1),
+]
+
+
+@pytest.mark.parametrize("s", ROUTES, ids=str)
+def test_filter_gradients_on_either_side_of_every_line(s):
+    n, c, hw, k, r, stride = s
+    d, x, _, dy = _data((n, c, hw, hw, k, r, stride, r // 2), 17)
+    t = (n, c, hw, hw, k, r, stride, r // 2)
+    _within(gu.gpu_bwd_weight(d, x, dy), _conv64_wgrad(x, dy, t), _conv64_wgrad(abs(x), abs(dy), t), dy.size // k, step=2)
 
 
 def _same_where_not_finite(got, ref):
