@@ -2233,12 +2233,11 @@ int lc_wgrad_splits(const GemmWgrad& p) {
     const long long tiles = (long long)((p.K + bm - 1) / bm) * ((p.J + bn - 1) / bn);
     const bool split = wgrad_by_split(p);
     // blocks of this tiling that fit on the chip at once (registers and LDS of the kernel instances below):
-    // the split count fills exactly one such round, never spills a few blocks into a second one -- the split kernel fills two, which keeps
-    // its sums short enough for the accuracy of the fp32 instructions (activations behind a ReLU, 1x1 at 56x56, batch 256: error 5.8e-7
-    // with one round, 4.1e-7 with two, 4.2e-7 before)
-    const int per_cu = split ? 2 * lc_wgrad_split_blocks_per_cu(bm, bn) : (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (p.bf16 ? 5 : 6);
+    // the split count fills exactly one such round, never spills a few blocks into a second one
+    const int per_cu = split ? lc_wgrad_split_blocks_per_cu(bm, bn) : (bm == 128 && bn == 128) ? 4 : (bm == 64 && bn == 64) ? 8 : (p.bf16 ? 5 : 6);
     const long long round = (long long)per_cu * device_cu_count();
     long long want = round / tiles;
+    if (split && want * tiles * 8 < round * 7) want = 2 * round / tiles;      // (many tiles: where one round would leave an eighth of the chip idle, two)
     // at least so many reduction rows per split (two images of 14x14 with 256 channels: 29 us at 256, 23.5 at 128, 22 at 64, where sixteen
     // of 7x7 lose 12 %; bf16 loses 5 % on small layers at 128)
     const int least = split ? 128 : 256;

@@ -1,9 +1,12 @@
 """GPU parity of the fp32 passes that run on the bf16 matrix pipe, each operand as the sum of three bf16 values.
 
 Checked against float64 torch on the CPU, element by element, with the bound that the arithmetic gives: a product's three dropped parts are
-below 2^-24 of it together, and each of the six kept ones is added with at most one rounding (taken as 2^-23 of the sum of the terms' magnitudes)
-per 32 reduction indices, in which the sums of stream-K pieces or batch splits (at most 64 more) are included:
-|error| <= (6 * ceil(K / 32) + 66) * 2^-23 * sum |a| |b|."""
+below 2^-24 of it together; each of the six kept ones is added with four roundings (one after eight terms, taken as 2^-24 each) to a sum over one
+k-step of 32 reduction indices, and that sum with one rounding to the accumulator.  With the sums of stream-K pieces or batch splits (at most 64 more)
+that is below (ceil(K / 32) + 90) * 2^-23 of the sum of magnitudes; _within() allows six roundings per k-step and 66:
+|error| <= (6 * ceil(K / 32) + 66) * 2^-23 * sum |a| |b|, which the fp32 instructions of the forward pass (and of filter counts that are not multiples
+of four, in backward-data) keep in practice as well.  Worst-case bounds are loose by the square root of the number of roundings, so the errors'
+norm and mean are bounded too, over long reductions."""
 import numpy as np
 import pytest
 import torch
@@ -75,6 +78,51 @@ def test_all_three_passes_within_the_bound(s, wide):
     _within(gu.gpu_bwd_data(d, dy, w), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
     _within(gu.gpu_bwd_weight(d, x, dy), _conv64_wgrad(x, dy, s), _conv64_wgrad(abs(x), abs(dy), s), dy.size // s[4])
 
+
+
+def _norm_and_mean(got, ref):
+    e = got.astype(np.float64) - ref
+    return np.linalg.norm(e) / np.linalg.norm(ref), abs(e.mean()) / np.sqrt((ref * ref).mean())
+
+
+def test_long_sums_round_once_per_k_step():
+    """Whole tiles of 16 k-steps (784 of them on 256 compute units) and splits of 8 and 16.  A sum of n k-steps rounded once each to nearest (rms
+    0.41 * 2^-24 of the running sum, which grows like a random walk) is off by sqrt(n / 2) * 0.41 * 2^-24 of its size, 0.7e-7 for n = 16, plus the roundings
+    inside a k-step, 0.5e-7; six times four roundings per step give 3.2e-7.  The mean: what the instruction cuts always the same way, 24 times
+    0.006 * 2^-24 of a k-step's sum, would be -5e-7 of the result for 6272 steps without the alternating sign."""
+    s = (32, 64, 56, 56, 512, 1, 1, 0)
+    d, x, w, dy = _data(s, 23)
+    err, mean = _norm_and_mean(gu.gpu_bwd_data(d, dy, w), (dy.reshape(-1, 512).astype(np.float64) @ w.reshape(512, 64)).reshape(x.shape))
+    assert err < 2e-7 and mean < 2e-8, (err, mean)
+    for s, limit in (((64, 64, 56, 56, 256, 1, 1, 0), 2.5e-7), ((1, 1536, 64, 64, 1024, 1, 1, 0), 2e-7)):
+        d, x, w, dy = _data(s, 29)
+        x = np.maximum(x, 0)                                          # behind a ReLU
+        ref = dy.reshape(-1, s[4]).T.astype(np.float64) @ x.reshape(-1, s[1])
+        err, mean = _norm_and_mean(gu.gpu_bwd_weight(d, x, dy), ref.reshape(w.shape))
+        assert err < limit and mean < 5e-8, (s, err, mean)
+
+
+@pytest.mark.parametrize("c,k", [(128, 128), (60, 64), (68, 132)])
+def test_each_of_the_six_products_counts(c, k):
+    """Results that are one product each: all 24 bits of both operands matter (without the smallest of the kept products the error is above 2^-19)."""
+    rng = np.random.default_rng(31)
+
+    def full(*shape):                                                 # 24 significant bits, the lowest always set
+        m = rng.integers(1 << 23, 1 << 24, shape) | 1
+        return (m * np.exp2(rng.integers(-30, 10, shape))).astype(np.float32)
+    n = 300
+    d = lc.ConvDesc(n, c, 1, 1, k, 1, 1, 1, 1, 0, 0, lc.LC_F32, NHWC)
+    w, v, at = full(k, 1, 1, c), full(n), rng.integers(0, k, n)
+    dy = np.zeros((n, 1, 1, k), np.float32)
+    dy[np.arange(n), 0, 0, at] = v
+    ref = v[:, None].astype(np.float64) * w[at, 0, 0, :]
+    got = gu.gpu_bwd_data(d, dy, w).reshape(n, c)
+    assert (np.abs(got - ref) <= 2.0 ** -22 * np.abs(ref)).all(), np.max(np.abs(got / ref - 1))
+    x, dy = np.zeros((n, 1, 1, c), np.float32), np.zeros((n, 1, 1, k), np.float32)
+    x[7], dy[7] = full(1, 1, c), full(1, 1, k)
+    ref = dy[7].reshape(k, 1).astype(np.float64) * x[7].reshape(1, c)
+    got = gu.gpu_bwd_weight(d, x, dy).reshape(k, c)
+    assert (np.abs(got - ref) <= 2.0 ** -22 * np.abs(ref)).all(), np.max(np.abs(got / ref - 1))
 
 # The rows, filters and columns at which a filter gradient changes kernels (wide results, one 64x64 tile, few rows, filter counts that are not
 # multiples of four), both sides of each line; n, c, hw, k, window, stride.
