@@ -1,7 +1,8 @@
 // fp32 backward-data and filter gradients on the bf16 matrix pipe of gfx950, with every fp32 operand taken apart into three bf16 values.
 // (The forward pass stays with the fp32 matrix instructions of conv_igemm.hip: its last bits decide ReLUs.)
 //
-// x = h + m + l with h = x rounded to bf16, m = (x - h) rounded to bf16, l the rest: 8 + 8 + 8 significant bits, exact for |x| >= 2^-110.  Of the
+// x = h + m + l with h = x rounded to bf16, m = (x - h) rounded to bf16, l the rest: 8 + 8 + 8 significant bits.  Operands are scaled by 2^16 first,
+// so that the parts of the smallest fp32 number are above bf16's smallest (2^-133) and the three parts are exact down to 2^-149.  Of the
 // nine partial products of a * b the six hh, hm, mh, mm, hl, lh reach the last bit of an fp32 product (the three left out are below 2^-24 of
 // it together); each is exact in the matrix pipe.  Six v_mfma_f32_16x16x32_bf16 take 96 cycles
 // where the same sums cost v_mfma_f32_32x32x2_f32 256.  The products of one k-step are summed by themselves and then added to the accumulators with
@@ -22,12 +23,13 @@ namespace {
 
 // Two values at a time.  (v_dot2_f32_bf16 would take the widening and the subtraction in one instruction, but it runs on the matrix pipe's
 // time: a loop of one MFMA and four of them takes 25 ns per MFMA, with subtractions 19.)
+constexpr float kScale = 65536.f;
 struct Split2 {
     unsigned h, m, l;
 };
-__device__ __forceinline__ Split2 split2(float x0, float x1, float turn) {      // turn: 1 or -1, see sum_products()
-    x0 *= turn;
-    x1 *= turn;
+__device__ __forceinline__ Split2 split2(float x0, float x1, float scale) {      // kScale or -kScale, see sum_products()
+    x0 *= scale;
+    x1 *= scale;
     Split2 s;
     s.h = lc_bf16x2_rne(x0, x1);
     const float r0 = x0 - __uint_as_float(s.h << 16), r1 = x1 - __uint_as_float(s.h & 0xffff0000u);
@@ -56,9 +58,10 @@ __device__ __forceinline__ void sum_products(f32x4 (&t)[N], F&& mfma) {
         for (int n = 0; n < N; ++n) t[n] = mfma(n, kParts[q][0], kParts[q][1], q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : t[n]);
 }
 __device__ __forceinline__ float turn_of(int k_step) { return (k_step & 1) ? -1.f : 1.f; }
-__device__ __forceinline__ void add_sums(f32x4& acc, const f32x4& t, float turn) {
+// unscale: the k-step's turn over the scales of both operands
+__device__ __forceinline__ void add_sums(f32x4& acc, const f32x4& t, float unscale) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = fmaf(t[v], turn, acc[v]);
+    for (int v = 0; v < 4; ++v) acc[v] = fmaf(t[v], unscale, acc[v]);
 }
 
 // Blocks per compute unit (LDS: 48 KB for the 128x128 tile).  The generic addressing needs more registers.
@@ -265,11 +268,11 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
         ++l_k;
     };
     unsigned char* const st = lds + (wave >> 1) * kBlock16 + (kq >> 1) * 256 + ((((wave & 1) * 8 + lrow) ^ (kq & 6)) * 16) + (kq & 1) * 8;
-    auto split_store = [&](float turn) __attribute__((always_inline)) {
+    auto split_store = [&](float scale_a) __attribute__((always_inline)) {
 #pragma unroll
         for (int l = 0; l < LPT; ++l) {
-            const float sign = l < LA ? turn : 1.f;
-            const Split2 a = split2(g[l].x, g[l].y, sign), b = split2(g[l].z, g[l].w, sign);
+            const float scale = l < LA ? scale_a : kScale;
+            const Split2 a = split2(g[l].x, g[l].y, scale), b = split2(g[l].z, g[l].w, scale);
             unsigned char* q = st + (l < LA ? l * 2 : BM / 16 + (l - LA) * 2) * kBlock16;
             *reinterpret_cast<uint2*>(q) = make_uint2(a.h, b.h);
             *reinterpret_cast<uint2*>(q + 1024) = make_uint2(a.m, b.m);
@@ -285,7 +288,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
     };
     // one k-step out of LDS: the filter's fragments are held, the activations' fetched one row of tiles ahead, and a row's sums are added between
     // the next row's matrix instructions (behind them: 3 % slower)
-    auto matrix_phase = [&](float turn) __attribute__((always_inline)) {
+    auto matrix_phase = [&](float unscale) __attribute__((always_inline)) {
         bf16x8 fa[2][3], fb[3][TN];
         f32x4 t[2][TN];
 #pragma unroll
@@ -306,7 +309,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
                 });
             if (i > 0) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) add_sums(acc[i - 1][j], t[(i - 1) & 1][j], turn);
+                for (int j = 0; j < TN; ++j) add_sums(acc[i - 1][j], t[(i - 1) & 1][j], unscale);
             }
             if (i > 0 && i < TM) {
 #pragma unroll
@@ -324,7 +327,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    // An infinity or a NaN does not survive the split (inf - inf), nor does a value that rounds past the largest bf16: this wave's part of
+    // An infinity or a NaN does not survive the split (inf - inf), nor does a value past 2^112 or a product past 2^96 (the scale): this wave's part of
     // the segment [k0, k1) once more with fp32 matrix instructions straight from memory, where the split's result is not finite.  Every such
     // operand makes its whole row or column of the split's result NaN, so looking at the result finds them all; a sum that overflows by
     // itself comes here too and leaves as fp32 arithmetic has it.
@@ -440,11 +443,11 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
     clear_acc();
     for (int f = 0; f < F; ++f) {
         const float turn = turn_of(c_k);
-        split_store(turn);
+        split_store(turn * kScale);
         if (f + 1 < F) load_step();               // stays in flight over the matrix phase
         lds_barrier();
         __builtin_amdgcn_s_setprio(1);
-        matrix_phase(turn);
+        matrix_phase(turn / (kScale * kScale));
         __builtin_amdgcn_s_setprio(0);
         lds_barrier();                            // every wave has read its last fragments
         if (++c_k == c_k1) {                      // the segment is complete: store it, the next step starts a new one
@@ -636,15 +639,15 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
         mt += BK;
     };
     // one operand's columns of this lane: eight rows each, three planes
-    auto split_store_cols = [&](auto& g, unsigned char* base, float turn) __attribute__((always_inline)) {
+    auto split_store_cols = [&](auto& g, unsigned char* base, float scale) __attribute__((always_inline)) {
         constexpr int V = sizeof(g[0]) / 4;
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             Split2 s[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                if constexpr (V == 2) s[u] = e == 0 ? split2(g[2 * u].x, g[2 * u + 1].x, turn) : split2(g[2 * u].y, g[2 * u + 1].y, turn);
-                else s[u] = split2(g[2 * u], g[2 * u + 1], turn);
+                if constexpr (V == 2) s[u] = e == 0 ? split2(g[2 * u].x, g[2 * u + 1].x, scale) : split2(g[2 * u].y, g[2 * u + 1].y, scale);
+                else s[u] = split2(g[2 * u], g[2 * u + 1], scale);
             }
             unsigned char* q = base + (V == 2 ? (lane >> 3) * kBlock16 + ((lane & 7) + 8 * e) * 16 : (lane >> 4) * kBlock16 + (lane & 15) * 16) + wave * 256;
             *reinterpret_cast<u32x4*>(q) = u32x4{s[0].h, s[1].h, s[2].h, s[3].h};
@@ -660,7 +663,7 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
     };
     // one k-step out of LDS, in blocks of 2 x 2 tiles -- four sums in flight with 64 registers for fragments and sums, which leaves room for three
     // blocks per compute unit; neighbouring blocks keep one operand's fragments
-    auto matrix_phase = [&](float turn) __attribute__((always_inline)) {
+    auto matrix_phase = [&](float unscale) __attribute__((always_inline)) {
         bf16x8 fa[3][2], fb[3][2];
         auto read_a = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
@@ -687,7 +690,7 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
                     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pa][n >> 1], fb[pb][n & 1], c, 0, 0, 0);
                 });
 #pragma unroll
-                for (int n = 0; n < 4; ++n) add_sums(acc[i0 + (n >> 1)][j0 + (n & 1)], t[n], turn);
+                for (int n = 0; n < 4; ++n) add_sums(acc[i0 + (n >> 1)][j0 + (n & 1)], t[n], unscale);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -706,12 +709,12 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
     if (nkt > 0) load_step();
     for (int kt = 0; kt < nkt; ++kt) {
         const float turn = turn_of(kt);
-        split_store_cols(ga, lds, turn);
-        split_store_cols(gb, lds + BM / 16 * kBlock16, 1.f);
+        split_store_cols(ga, lds, turn * kScale);
+        split_store_cols(gb, lds + BM / 16 * kBlock16, kScale);
         if (kt + 1 < nkt) load_step();                // stays in flight over the matrix phase
         lds_barrier();
         __builtin_amdgcn_s_setprio(1);
-        matrix_phase(turn);
+        matrix_phase(turn / (kScale * kScale));
         __builtin_amdgcn_s_setprio(0);
         lds_barrier();                                // every wave has read its last fragments
     }

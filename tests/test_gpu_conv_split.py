@@ -124,6 +124,25 @@ def test_each_of_the_six_products_counts(c, k):
     got = gu.gpu_bwd_weight(d, x, dy).reshape(k, c)
     assert (np.abs(got - ref) <= 2.0 ** -22 * np.abs(ref)).all(), np.max(np.abs(got / ref - 1))
 
+
+@pytest.mark.parametrize("e", [-112, -118, -124, -130])
+@pytest.mark.parametrize("s", [(3, 64, 13, 11, 128, 1, 1, 0), (2, 36, 9, 9, 68, 3, 1, 1), (2, 96, 14, 14, 132, 1, 2, 0), (2, 20, 12, 12, 96, 3, 2, 1)], ids=str)
+def test_the_smallest_numbers_keep_their_bits(s, e):
+    """One operand of magnitude 2^e, down into fp32's subnormal numbers -- unscaled, the lower parts of its split fall below the smallest bf16, 2^-133 --
+    against partners that keep the results normal.  As accurate as elsewhere: at most 20 k-steps, so below 1.5e-7 of the norm as derived above."""
+    d, x, w, dy = _data(s, 41)
+
+    def tiny(a):
+        return (a * 2.0 ** e).astype(np.float32)
+    up = np.float32(2.0 ** 60)
+    for dy_, w_ in ((tiny(dy), w * up), (dy * up, tiny(w))):
+        err, _ = _norm_and_mean(gu.gpu_bwd_data(d, dy_, w_), _conv64_bwd(dy_, w_, s))
+        assert err < 1.5e-7, err
+    for x_, dy_ in ((tiny(x), dy * up), (x * up, tiny(dy))):
+        err, _ = _norm_and_mean(gu.gpu_bwd_weight(d, x_, dy_), _conv64_wgrad(x_, dy_, s))
+        assert err < 1.5e-7, err
+
+
 # The rows, filters and columns at which a filter gradient changes kernels (wide results, one 64x64 tile, few rows, filter counts that are not
 # multiples of four), both sides of each line; n, c, hw, k, window, stride.
 ROUTES = [
