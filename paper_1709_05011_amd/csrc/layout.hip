@@ -508,9 +508,11 @@ void lc_stem_filter_grad(const float* dwu, float* dw, int k, int r, int s, int c
 }
 
 // Shape of the split reduction for `count` outputs: four outputs per thread where count allows, and so many lanes per output that the chip still
-// fills.  A fixed function of count (it is also the number of squared-norm pieces the reduction emits).
+// fills.  Up to 4096 outputs single ones, 16 lanes each: that is one block per compute unit, with four outputs per thread a quarter of
+// them would work (64 -> 64 1x1, 256 images of 56x56 95 -> 92 us; 16 -> 16, 484 of 20x20 20.8 -> 19.7).  A fixed function of count (it is also the
+// number of squared-norm pieces the reduction emits).
 static void reduce_splits_shape(size_t count, int* lanes, int* vec) {
-    *vec = count % 4 == 0 ? 4 : 1;
+    *vec = count % 4 == 0 && count > 4096 ? 4 : 1;
     const size_t threads = count / *vec;
     *lanes = threads >= (size_t)1 << 18 ? 1 : threads >= (size_t)1 << 16 ? 4 : threads >= (size_t)1 << 14 ? 8 : 16;
 }

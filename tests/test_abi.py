@@ -169,6 +169,13 @@ def test_filter_gradients_bound_by_memory_or_latency_plan_for_the_fp32_kernels()
     assert partials(2, 64, 37, 42) == -(-2 * 37 * 37 // 128)
 
 
+def test_small_filter_gradients_are_reduced_by_a_block_per_sixteen_outputs():
+    # (a piece of the squared norm per block of the reduction)
+    for c, k in ((64, 64), (16, 48), (16, 16)):
+        assert lc.conv2d_bwd_weight_sq_count(lc.ConvDesc(64, c, 28, 28, k, 1, 1, 1, 1, 0, 0)) == c * k // 16
+    assert lc.conv2d_bwd_weight_sq_count(lc.ConvDesc(64, 64, 28, 28, 256, 1, 1, 1, 1, 0, 0)) == 64 * 256 // 64
+
+
 def test_warmup_poly_lr_host_arithmetic_matches_oracle():
     import oracle
     base, start, W, T = 3.2, 0.1, 195, 3516
