@@ -127,8 +127,7 @@ inline SkPlan sk_plan_by_cost(long long tiles, int nkt, int resident_blocks, con
 __device__ __forceinline__ int sk_begin(const GemmConv& p, int j) { return j * p.sk_q + div_by(j * p.sk_rem, p.sk_mul, p.sk_shift); }
 // The stream-K blocks [*j0, *j1) with a part of the k-steps [tb, te).
 __device__ __forceinline__ void sk_blocks_of(const GemmConv& p, int tb, int te, int* j0, int* j1) {
-    const float per_step = (float)p.sk_blocks / (float)p.sk_iters;
-    int a = min(p.sk_blocks - 1, (int)((float)tb * per_step)), b = min(p.sk_blocks, (int)((float)te * per_step));
+    int a = min(p.sk_blocks - 1, (int)((float)tb * p.sk_per_step)), b = min(p.sk_blocks, (int)((float)te * p.sk_per_step));      // within one of them
     while (a > 0 && sk_begin(p, a) > tb) --a;
     while (sk_begin(p, a + 1) <= tb) ++a;
     while (b > 0 && sk_begin(p, b - 1) >= te) --b;
@@ -137,6 +136,25 @@ __device__ __forceinline__ void sk_blocks_of(const GemmConv& p, int tb, int te, 
     *j1 = b;
 }
 
+// The shared tile that row x of a fix-up's grid adds up: the tile (counted from the first stream-K tile) and the blocks
+// [*j0, *j1) with parts of it; false: the tile that row x stands for was stored whole.  Ranges of a tile's k-steps and more meet in at most one point
+// inside a tile: a row per meeting point (MEET).  Shorter ones share nearly every tile: a row per tile.  (1x1 over 32 channels, two k-steps per tile, 17 images
+// of 44x44 in fp32: a row per tile and its search for the blocks made 8,352 blocks of which most had nothing to do, 19 us; this way 4.)
+template <bool MEET>
+__device__ __forceinline__ bool sk_shared_tile(const GemmConv& p, int nkt, int x, int* tile, int* j0, int* j1) {
+    if constexpr (MEET) {
+        const int b = sk_begin(p, x + 1);
+        *tile = b / nkt;
+        *j0 = x;
+        *j1 = x + 2;
+        return b != *tile * nkt;
+    } else {
+        *tile = x;
+        sk_blocks_of(p, x * nkt, x * nkt + nkt, j0, j1);
+        return *j1 - *j0 > 1;
+    }
+}
+inline bool sk_ranges_meet(const GemmConv& p, int nkt) { return p.sk_q >= nkt; }
 // Constants for div_by(): n / d == umulhi(n, mul) >> shift for 0 <= n < 2^31 (mul == 0 stands for d == 1).
 // With L = ceil(log2 d) and mul = ceil(2^(31+L) / d) the error term n * (mul*d - 2^(31+L)) stays below 2^(31+L).
 inline void magic_for(int d, unsigned* mul, unsigned* shift) {
@@ -156,6 +174,7 @@ inline void sk_constants(GemmConv* p) {
     p->sk_q = p->sk_blocks > 0 ? (int)(p->sk_iters / p->sk_blocks) : 0;
     p->sk_rem = p->sk_blocks > 0 ? (int)(p->sk_iters % p->sk_blocks) : 0;
     magic_for(p->sk_blocks, &p->sk_mul, &p->sk_shift);
+    p->sk_per_step = p->sk_iters > 0 ? (float)p->sk_blocks / (float)p->sk_iters : 0.f;
 }
 
 }  // namespace

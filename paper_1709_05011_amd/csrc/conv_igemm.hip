@@ -17,6 +17,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 #include <type_traits>
 
 #include "conv_common.h"
@@ -760,7 +761,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
 // Adds the parts of every tile that stream-K blocks split between them, in k order, and stores the tile.
 // Block (t, v) handles accumulator register v of every 32x32 MFMA tile of stream-K tile t, with the thread
 // geometry of the main kernel: 16 blocks per tile keep the whole chip busy on what is a small reduction.
-template <int BM, int BN, bool BF16>
+template <int BM, int BN, bool BF16, bool MEET>
 __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_kernel(const GemmConv p) {
     constexpr int WN_ = pk_waves_n(BM, BN);
     constexpr int BK = BF16 ? 32 : 16, TM = BM / 64, TN = BN / (32 * WN_);
@@ -769,10 +770,9 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
     const int v = blockIdx.y;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
-    const int tb = blockIdx.x * nkt, te = tb + nkt;                      // this tile's k-steps in stream-K positions
-    int j, j1;
-    sk_blocks_of(p, tb, te, &j, &j1);
-    if (j1 - j == 1) return;                                             // one block did the whole tile and stored it
+    int sk_tile, j, j1;
+    if (!sk_shared_tile<MEET>(p, nkt, blockIdx.x, &sk_tile, &j, &j1)) return;  // one block did the whole tile and stored it
+    const int tb = sk_tile * nkt;                                        // this tile's first k-step in stream-K positions
 
     // The first block's piece is the last of its range unless its range starts here (slot 0 or 1); all others start their ranges in this tile.
     // Four parts are fetched at a time and added one after the other: a chain of dependent loads, and a division per part, made this kernel
@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
         for (int jj = 0; jj < TN; ++jj)
 #pragma unroll
             for (int u = 0; u < 16; ++u) out[i][jj][u] = acc[i][jj][0];
-    const int tile = p.dp_tiles + blockIdx.x;
+    const int tile = p.dp_tiles + sk_tile;
     const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * BN;
     store_tile<TM, TN, BF16>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
 }
@@ -1997,6 +1997,17 @@ extern "C" int lc_selftest_stream_k(int max_blocks) {
                 const unsigned q = p.sk_mul ? (unsigned)(((unsigned long long)n * p.sk_mul) >> 32) >> p.sk_shift : n;
                 if ((long long)j * p.sk_q + q != j * iters / blocks) return blocks;
             }
+            // ranges of a tile and more: the rows of sk_shared_tile<true>() are the tiles with several parts, each once, and the parts are two
+            for (int nkt : {1, 2, 3, 7, 64}) {
+                if (p.sk_q < nkt || iters > 1000000) continue;
+                long long last = -1;
+                for (long long x = 0; x + 1 < blocks; ++x) {
+                    const long long b = (x + 1) * iters / blocks, tile = b / nkt;
+                    if (b == tile * nkt) continue;
+                    if (tile == last || x * iters / blocks > tile * nkt || (x + 2) * iters / blocks < std::min(iters, (tile + 1) * nkt)) return blocks;
+                    last = tile;
+                }
+            }
         }
     return 0;
 }
@@ -2045,7 +2056,10 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
         hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false, false>), dim3(grid), threads, 0, stream, p);
     }
     if (!whole) {
-        hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
+        if (!sk_ranges_meet(p, nkt))
+            hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16, false>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
+        else if (pl.sk_blocks > 1)
+            hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16, true>), dim3((unsigned)pl.sk_blocks - 1, 16), threads, 0, stream, p);
         if (p.stats) {
             const dim3 sgrid((unsigned)(tiles - pl.dp_tiles), 2);
             const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;

@@ -463,16 +463,15 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
 
 // Adds the parts of every tile that stream-K blocks split between them, in k order, and stores the tile: block (t, y) handles the 16x16
 // tile y of each of the four waves of stream-K tile t.  Four parts are fetched at a time.
-template <int BM, int BN>
+template <int BM, int BN, bool MEET>
 __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p) {
     constexpr int TN = BN / 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
-    const int tb = blockIdx.x * nkt, te = tb + nkt;                      // this tile's k-steps in stream-K positions
-    int j, j1;
-    sk_blocks_of(p, tb, te, &j, &j1);
-    if (j1 - j == 1) return;                                             // one block did the whole tile and stored it
+    int sk_tile, j, j1;
+    if (!sk_shared_tile<MEET>(p, nkt, blockIdx.x, &sk_tile, &j, &j1)) return;  // one block did the whole tile and stored it
+    const int tb = sk_tile * nkt;                                        // this tile's first k-step in stream-K positions
     const f32x4* part = reinterpret_cast<const f32x4*>(p.partial) + (blockIdx.y * 4 + wave) * 64 + lane;
     constexpr size_t kSlot = BM * BN / 4;
     // the first block's piece is the last of its range unless its range starts here; all others start their ranges in this tile
@@ -485,7 +484,7 @@ __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p)
         for (int u = 0; u < 4; ++u) sum += v[u];
     }
     for (; j < j1; ++j) sum += part[(size_t)2 * j * kSlot];
-    const int tile = p.dp_tiles + blockIdx.x, tm = tile / nbn;
+    const int tile = p.dp_tiles + sk_tile, tm = tile / nbn;
     const int ti = blockIdx.y / TN, tj = blockIdx.y - ti * TN;
     const int m = tm * BM + (wave >> 1) * (BM / 2) + ti * 16 + (lane & 15);
     const int col = (tile - tm * nbn) * BN + (wave & 1) * (BN / 2) + tj * 16 + 4 * (lane >> 4);
@@ -837,8 +836,10 @@ lc_status launch_split_tile(const GemmConv& p, const SplitPlan& s, bool whole, u
         else launch_split<BN, true, false, false>(p, grid, stream);
     }
     if (!whole) {
-        const unsigned rest = (unsigned)(s.tiles - p.dp_tiles);
-        hipLaunchKernelGGL((conv_split_fixup_kernel<128, BN>), dim3(rest, 16 * BN / 128), dim3(256), 0, stream, p);
+        if (!sk_ranges_meet(p, s.nkt))
+            hipLaunchKernelGGL((conv_split_fixup_kernel<128, BN, false>), dim3((unsigned)(s.tiles - p.dp_tiles), 16 * BN / 128), dim3(256), 0, stream, p);
+        else if (p.sk_blocks > 1)
+            hipLaunchKernelGGL((conv_split_fixup_kernel<128, BN, true>), dim3((unsigned)p.sk_blocks - 1, 16 * BN / 128), dim3(256), 0, stream, p);
     }
     return lc_end_call();
 }

@@ -86,6 +86,7 @@ struct GemmConv {
     // first k-step of stream-K block j: j * sk_iters / sk_blocks = j * sk_q + j * sk_rem / sk_blocks, the quotient by multiply-high constants
     int sk_q, sk_rem;
     unsigned sk_mul, sk_shift;
+    float sk_per_step;  // sk_blocks / sk_iters, about
     float* partial;
     // multiply-high division constants for Qo and Po (filled in by the launcher)
     unsigned qo_mul, qo_shift, po_mul, po_shift;

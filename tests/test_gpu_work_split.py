@@ -48,3 +48,18 @@ def test_every_form_of_the_split_adds_up(s):
     bwd = lambda a, b: torch.nn.grad.conv2d_input(xn.shape, b, a, padding=r // 2).permute(0, 2, 3, 1)                # noqa: E731
     check(run(lc.conv2d_fwd, lc.LC_PASS_FWD, x, w, dy.shape), fwd(xn, wn), fwd(xn.abs(), wn.abs()), c * r * r)
     check(run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, w, x.shape), bwd(dyn, wn), bwd(dyn.abs(), wn.abs()), k * r * r)
+
+
+@pytest.mark.parametrize("s", [(41, 48, 7, 520), (17, 32, 44, 544), (40, 16, 7, 640), (3, 80, 28, 192), (2, 40, 31, 33)], ids=str)
+def test_ranges_of_several_tiles_meet_inside_tiles(s):
+    """fp32 forward 1x1 with one to five k-steps of 16 per tile: blocks of eight k-steps take whole tiles and share the ones their ranges meet in.  The bound
+    of the fp32 sums, a rounding every two terms."""
+    n, c, hw, k = s
+    g = torch.Generator().manual_seed(5)
+    x, w = torch.randn((n, hw, hw, c), generator=g), torch.randn((k, 1, 1, c), generator=g)
+    d = lc.ConvDesc(n, c, hw, hw, k, 1, 1, 1, 1, 0, 0, lc.LC_F32, lc.LC_NHWC)
+    y = torch.full((n, hw, hw, k), float("nan"), device=gu.DEV)
+    lc.conv2d_fwd(d, x.to(gu.DEV), w.to(gu.DEV), y, gu.workspace(lc.conv2d_workspace_bytes(d, lc.LC_PASS_FWD)))
+    torch.cuda.synchronize()
+    ref, mag = x.double() @ w.double().view(k, c).t(), x.double().abs() @ w.double().abs().view(k, c).t()
+    assert bool(((y.cpu().double() - ref).abs() <= (c // 2 + 4) * 2.0 ** -23 * mag).all())
