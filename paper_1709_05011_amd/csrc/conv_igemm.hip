@@ -2223,22 +2223,23 @@ static bool wgrad_plain_shape(const GemmWgrad& p) {        // output pixel m rea
     return p.R == 1 && p.S == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 && p.H == p.P && p.W == p.Q;
 }
 
+// A result so large and so few rows that the partial sums of a second split cost more than the shorter sums save: 372 -> 800 3x3 on 196 rows 33 us
+// with two splits, 25 with one; 928 -> 496 5x5 on 144 rows 63 / 42; but 172 -> 792 3x3 (1.2 M results) on 256 rows 24 / 31.
+static bool wgrad_large_on_few_rows(const GemmWgrad& p) { return p.M <= 256 && (long long)p.K * p.J >= 3 << 19; }
+
 // Whether conv_split.hip's kernel is the one for an fp32 filter gradient (a fixed function of the shape: the split count depends on it).  It takes
 // pairs of columns inside one tap and windows of at most 32 taps.  The fp32 matrix instructions stay the better choice (us: split kernel /
 // fp32 kernel) with filter counts that are multiples of four -- otherwise they have to load value by value, 10.6 / 19.4 -- for
 //   one 64x64 tile, bound by memory and launches: 64 -> 64 1x1, 256 images of 56x56 110 / 92; 24 -> 16 1x1 on 169,756 rows 23.0 / 19.7; 4 -> 24
 //     3x3 on 33,135 rows 16.2 / 13.5; but windows and strides on 1,856 to 4,802 rows 11.7 to 14.6 / 14.1 to 16.9;
 //   at most 64 filters or columns on few rows, a few k-steps of latency: 1x1 on 144 to 224 rows 10.7 to 11.1 / 7.9 to 10.4, on 361 rows 10.9 / 11.6;
-//     windows on 81 to 144 rows 10.3 to 13.5 / 8.6 to 11.6, on 169 rows 12.2 / 12.9;
-// and for a large result on few rows, where the partial sums of a second split cost more than the shorter sums save: 2044 -> 48 5x5 on 198 rows
-// 35.6 / 27.5, 928 -> 496 5x5 on 144 rows 63 / 42, but 172 -> 792 3x3 on 256 rows 24 / 31.
+//     windows on 81 to 144 rows 10.3 to 13.5 / 8.6 to 11.6, on 169 rows 12.2 / 12.9; 2044 -> 48 5x5 on 198 rows 35.6 / 27.5.
 static bool wgrad_by_split(const GemmWgrad& p) {
     if (p.bf16 || p.C % 2 != 0 || (long long)p.R * p.S > 32) return false;
-    if (p.M <= 256 && (long long)p.K * p.J >= 1 << 21) return false;
     if (p.K % 4 != 0 || (p.K > 64 && p.J > 64)) return true;
     const bool plain = wgrad_plain_shape(p);
     if (p.K <= 64 && p.J <= 64) return !plain && p.M > 512 && p.M <= 16384;
-    return p.M > (plain ? 256 : 160);
+    return p.M > (plain || wgrad_large_on_few_rows(p) ? 256 : 160);
 }
 
 int lc_wgrad_splits(const GemmWgrad& p) {
@@ -2254,7 +2255,7 @@ int lc_wgrad_splits(const GemmWgrad& p) {
     if (split && want * tiles * 8 < round * 7) want = 2 * round / tiles;      // (many tiles: where one round would leave an eighth of the chip idle, two)
     // at least so many reduction rows per split (two images of 14x14 with 256 channels: 29 us at 256, 23.5 at 128, 22 at 64, where sixteen
     // of 7x7 lose 12 %; bf16 loses 5 % on small layers at 128)
-    const int least = split ? 128 : 256;
+    const int least = split && !wgrad_large_on_few_rows(p) ? 128 : 256;
     const long long most = (p.M + least - 1) / least;
     if (want > most) want = most;
     if (want < 1) want = 1;

@@ -148,7 +148,7 @@ def test_the_smallest_numbers_keep_their_bits(s, e):
 ROUTES = [
     (1, 64, 23, 64, 1, 1), (1, 64, 23, 62, 1, 1), (1, 32, 46, 64, 1, 2), (1, 32, 44, 64, 1, 2), (4, 32, 128, 64, 1, 2), (5, 32, 128, 64, 1, 2),
     (1, 68, 16, 64, 1, 1), (1, 68, 17, 64, 1, 1), (1, 64, 16, 68, 1, 1), (1, 64, 17, 66, 1, 1), (1, 8, 12, 64, 3, 1), (1, 8, 13, 64, 3, 1),
-    (1, 2048, 16, 1024, 1, 1), (1, 2048, 15, 1028, 1, 1), (1, 2048, 17, 1024, 1, 1), (2, 4, 56, 64, 3, 1), (1, 7, 28, 64, 1, 1), (3, 64, 56, 64, 1, 1),
+    (1, 2048, 16, 768, 1, 1), (1, 2048, 16, 764, 1, 1), (1, 2048, 17, 768, 1, 1), (1, 2732, 14, 64, 3, 1), (1, 2728, 14, 64, 3, 1), (2, 4, 56, 64, 3, 1), (1, 7, 28, 64, 1, 1), (3, 64, 56, 64, 1, 1),
 ]
 
 
