@@ -176,6 +176,20 @@ def test_small_filter_gradients_are_reduced_by_a_block_per_sixteen_outputs():
     assert lc.conv2d_bwd_weight_sq_count(lc.ConvDesc(64, 64, 28, 28, 256, 1, 1, 1, 1, 0, 0)) == 64 * 256 // 64
 
 
+def test_narrow_tiles_with_many_k_steps_are_shared():
+    # tiles that one block each would sit on while the chip idles: partial sums in the plan (1x1 over 1248 channels to 29 in bf16, 39 k-steps;
+    # fp32 backward-data of 53 to 392 channels, 13 k-steps of a result 53 wide, and of 128 channels at 28x28, 32 images, 36 k-steps)
+    def parts(n, c, hw, k, r, dtype, which):
+        d = lc.ConvDesc(n, c, hw, hw, k, r, r, 1, 1, r // 2, r // 2, dtype)
+        filters = 0 if which == lc.LC_PASS_FWD else -(-k * r * r * c * 4 // 256) * 256
+        return lc.conv2d_workspace_bytes(d, which) - filters
+
+    assert parts(258, 1248, 20, 29, 1, lc.LC_BF16, lc.LC_PASS_FWD) > 0
+    assert parts(2, 53, 47, 392, 1, lc.LC_F32, lc.LC_PASS_BWD_DATA) > 0
+    assert parts(32, 128, 28, 128, 3, lc.LC_F32, lc.LC_PASS_BWD_DATA) > 0
+    assert parts(1, 256, 8, 32, 3, lc.LC_F32, lc.LC_PASS_BWD_DATA) > 0
+
+
 def test_warmup_poly_lr_host_arithmetic_matches_oracle():
     import oracle
     base, start, W, T = 3.2, 0.1, 195, 3516
