@@ -204,3 +204,87 @@ def test_infinities_nans_and_the_largest_values_come_through_as_in_fp32(s):
         got = gu.gpu_fwd(d, x, ws)
         ok = _same_where_not_finite(got, ref)
         _within(got[ok], ref[ok], _conv64(abs(x), abs(ws), s)[ok], s[1] * s[5] ** 2)
+
+
+# Backward-data on the split kernel (the gathered channels, k, are a multiple of four) with results that are c wide: tile edges, widths that are not
+# multiples of four, and every addressing it has -- k-steps inside one tap (k a multiple of 32), k-steps across taps, fewer channels than a k-step --
+# each plain and with the result of a strided 1x1 on its grid, strided windows in phases, and tiles shared between blocks (long reductions).
+RAGGED = [
+    (2, 130, 9, 9, 32, 3, 1, 1), (3, 65, 13, 11, 64, 1, 1, 0), (2, 33, 9, 9, 36, 3, 1, 1), (2, 129, 7, 7, 20, 3, 1, 1), (1, 128, 11, 12, 4, 3, 1, 1),
+    (2, 62, 14, 14, 64, 1, 2, 0), (2, 130, 14, 14, 20, 1, 2, 0), (2, 70, 14, 14, 100, 1, 2, 0), (2, 256, 10, 10, 32, 1, 2, 0), (2, 50, 12, 12, 96, 3, 2, 1),
+    (1, 130, 10, 10, 512, 3, 1, 1), (1, 61, 9, 9, 640, 1, 1, 0), (2, 97, 13, 13, 324, 1, 2, 0),
+]
+
+
+@pytest.mark.parametrize("s", RAGGED, ids=str)
+def test_ragged_results_of_every_addressing(s):
+    d, x, w, dy = _data(s, 43)
+    _within(gu.gpu_bwd_data(d, dy, w), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
+    _within(gu.gpu_bwd_weight(d, x, dy), _conv64_wgrad(x, dy, s), _conv64_wgrad(abs(x), abs(dy), s), dy.size // s[4])
+
+
+def _plant(a, values, seed):
+    a, rng = a.copy(), np.random.default_rng(seed)
+    for v in values:
+        a[tuple(rng.integers(0, m) for m in a.shape)] = v
+    return a
+
+
+NOT_FINITE = ([np.inf], [np.inf, -np.inf, np.nan], [np.finfo(np.float32).max], [np.float32(2.0 ** 120), np.float32(-2.0 ** 113)])
+
+
+@pytest.mark.parametrize("s", RAGGED, ids=str)
+def test_infinities_nans_and_the_largest_values_in_either_operand(s):
+    """... of both passes: planted infinities, NaN, and values that the scaled split cannot carry come through as in fp32 arithmetic."""
+    d, x, w, dy = _data(s, 47)
+    x, w, dy = (a * np.float32(0.01) for a in (x, w, dy))             # keeps a sum around the largest value finite
+    with np.errstate(over="ignore", invalid="ignore"):
+        for i, values in enumerate(NOT_FINITE):
+            for dy_, w_ in ((_plant(dy, values, i), w), (dy, _plant(w, values, i))):
+                if s[5] > 1 and not np.isfinite(w_).all():
+                    continue                # (taps outside the image: zero times the filter here, left out by the reference)
+                ref, mag = _conv64_bwd(dy_, w_, s), _conv64_bwd(abs(dy_), abs(w_), s)
+                got = gu.gpu_bwd_data(d, dy_, w_)
+                ok = _same_where_not_finite(got, ref)
+                _within(got[ok], ref[ok], mag[ok], s[4] * s[5] ** 2)
+            for x_, dy_ in ((_plant(x, values, i), dy), (x, _plant(dy, values, i))):
+                ref, mag = _conv64_wgrad(x_, dy_, s), _conv64_wgrad(abs(x_), abs(dy_), s)
+                got = gu.gpu_bwd_weight(d, x_, dy_)
+                ok = _same_where_not_finite(got, ref)
+                _within(got[ok], ref[ok], mag[ok], dy.size // s[4], step=2)
+
+
+def test_an_infinity_in_a_long_segment():
+    """Whole tiles of 16 k-steps and splits of 16: the wave that meets the infinity computes its part again, the others keep theirs."""
+    with np.errstate(over="ignore", invalid="ignore"):
+        s = (32, 64, 56, 56, 512, 1, 1, 0)
+        d, x, w, dy = _data(s, 53)
+        dy = _plant(dy, [np.inf, -np.inf, np.nan], 1)
+        a, b = dy.reshape(-1, 512).astype(np.float64), w.reshape(512, 64).astype(np.float64)
+        ref, got = (a @ b).reshape(x.shape), gu.gpu_bwd_data(d, dy, w)
+        ok = _same_where_not_finite(got, ref)
+        _within(got[ok], ref[ok], (abs(a) @ abs(b)).reshape(x.shape)[ok], 512)
+        s = (1, 1536, 64, 64, 1024, 1, 1, 0)
+        d, x, w, dy = _data(s, 59)
+        x = _plant(x, [np.inf, -np.inf, np.nan], 1)
+        a, b = dy.reshape(-1, 1024).T.astype(np.float64), x.reshape(-1, 1536).astype(np.float64)
+        ref, got = (a @ b).reshape(w.shape), gu.gpu_bwd_weight(d, x, dy)
+        ok = _same_where_not_finite(got, ref)
+        _within(got[ok], ref[ok], (abs(a) @ abs(b)).reshape(w.shape)[ok], 4096)
+
+
+@pytest.mark.parametrize("s", [(3, 64, 13, 11, 128, 1, 1, 0), (2, 36, 9, 9, 65, 3, 1, 1), (2, 96, 14, 14, 132, 1, 2, 0)], ids=str)
+def test_tensors_aligned_to_four_bytes_only(s):
+    """The filter gradient's 8-byte loads and the 16-byte stores of backward-data's result on tensors that start 4 bytes past a 16-byte boundary."""
+    d, x, w, dy = _data(s, 61)
+
+    def off(a):
+        t = torch.empty(a.size + 1, dtype=torch.float32, device=gu.DEV)
+        t[1:].copy_(torch.from_numpy(a.reshape(-1)))
+        return t[1:].view(a.shape)
+    dw, dx = off(np.full_like(w, np.nan)), off(np.full_like(x, np.nan))
+    lc.conv2d_bwd_weight(d, off(x), off(dy), dw, gu.workspace(lc.conv2d_workspace_bytes(d, lc.LC_PASS_BWD_WEIGHT)))
+    lc.conv2d_bwd_data(d, gu.dev(dy), gu.dev(w), dx, gu.workspace(lc.conv2d_workspace_bytes(d, lc.LC_PASS_BWD_DATA)))
+    torch.cuda.synchronize()
+    _within(dw.cpu().numpy(), _conv64_wgrad(x, dy, s), _conv64_wgrad(abs(x), abs(dy), s), dy.size // s[4])
+    _within(dx.cpu().numpy(), _conv64_bwd(dy, w, s), _conv64_bwd(abs(dy), abs(w), s), s[4] * s[5] ** 2)
