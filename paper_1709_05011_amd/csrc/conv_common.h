@@ -16,7 +16,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kBufferWords3 = 0x00020000u;       // raw buffer, 32-bit data format
 constexpr unsigned kBufferBytes = 0x80000000u;        // buffer size given to the hardware; offsets with bit 31 set read zeros
 
-
 // Blocks are dealt round-robin to the 8 XCDs, each with its own L2.  Re-number them so that every
 // XCD works on one contiguous run of tiles (neighbouring tiles share A rows and the whole filter).
 __device__ __forceinline__ int xcd_tile(int bid, int total) {
@@ -27,7 +26,6 @@ __device__ __forceinline__ int xcd_tile(int bid, int total) {
 }
 
 __device__ __attribute__((aligned(16))) const float g_zero_chunk[4] = {0.f, 0.f, 0.f, 0.f};
-
 
 // ok ? a : b on pointers by bit masking: never a branch, whatever the cost of computing a
 __device__ __forceinline__ const void* pick(bool ok, const void* a, const void* b) {
@@ -157,6 +155,56 @@ __device__ __forceinline__ bool sk_shared_tile(const GemmConv& p, int nkt, int x
     }
 }
 inline bool sk_ranges_meet(const GemmConv& p, int nkt) { return p.sk_q >= nkt; }
+// The segments of one block of a persistent product kernel: its whole tiles, one per round, then its stream-K range cut at the tile boundaries.
+struct SkWalk {
+    int G, bid, nkt, dp_tiles, rounds, it, len, tile0, k00;
+    __device__ __forceinline__ SkWalk(const GemmConv& p, int k_steps) : G(gridDim.x), bid(blockIdx.x), nkt(k_steps), dp_tiles(p.dp_tiles) {
+        rounds = dp_tiles / G;                             // the launcher makes dp_tiles a multiple of the grid
+        it = len = 0;
+        if (bid < p.sk_blocks) {
+            it = sk_begin(p, bid);
+            len = sk_begin(p, bid + 1) - it;
+        }
+        tile0 = it / nkt;
+        k00 = it - tile0 * nkt;
+    }
+    __device__ __forceinline__ int steps() const { return rounds * nkt + len; }      // k-steps this block runs
+    __device__ __forceinline__ void segment(int s, int& tile, int& k0, int& k1) const {
+        if (s < rounds) {
+            tile = xcd_tile(s * G + bid, dp_tiles);
+            k0 = 0;
+            k1 = nkt;
+        } else {                                           // piece s - rounds of the stream-K range
+            const int t = tile0 + (s - rounds);
+            tile = dp_tiles + t;
+            k0 = s == rounds ? k00 : 0;
+            k1 = min(nkt, it + len - t * nkt);
+        }
+    }
+};
+
+// The taps of an R x S window (at most 32) as bits r * S + s, and which of them lie outside an H x W image for a window whose first tap is at
+// (h0, w0): all bits set where none lies inside.
+struct WindowTaps {
+    unsigned full, rep;                                    // every tap; bit r * S of every r, which spreads a mask over s to all rows
+    __device__ __forceinline__ WindowTaps(int R, int S) {
+        full = R * S >= 32 ? ~0u : (1u << (R * S)) - 1u;
+        rep = 0;
+        for (int r = 0; r < R; ++r) rep |= 1u << (r * S);
+    }
+    __device__ __forceinline__ unsigned outside(int h0, int w0, int H, int W, int R, int S) const {
+        int rlo = max(0, -h0), rhi = min(R - 1, H - 1 - h0);      // rows and columns of the window inside the image
+        int slo = max(0, -w0), shi = min(S - 1, W - 1 - w0);
+        const bool some = (rlo <= rhi) & (slo <= shi);
+        rlo = min(rlo, R - 1);                                    // keep the shifts in range when no tap is inside
+        rhi = max(rhi, 0);
+        slo = min(slo, S - 1);
+        const unsigned rows = (full << (rlo * S)) & (full >> ((R - 1 - rhi) * S));
+        const unsigned cols = rep * (((2u << max(shi - slo, 0)) - 1u) << slo);
+        return some ? ~(rows & cols) : ~0u;
+    }
+};
+
 // Constants for div_by(): n / d == umulhi(n, mul) >> shift for 0 <= n < 2^31 (mul == 0 stands for d == 1).
 // With L = ceil(log2 d) and mul = ceil(2^(31+L) / d) the error term n * (mul*d - 2^(31+L)) stays below 2^(31+L).
 inline void magic_for(int d, unsigned* mul, unsigned* shift) {

@@ -24,7 +24,6 @@
 
 namespace {
 
-
 template <int VEC> struct VecT;
 template <> struct VecT<4> {
     using type = float4;
@@ -320,28 +319,10 @@ conv_gemm_pk_kernel(const GemmConv p) {
     const int a_frag = (wm * WTM + frow) * 16, b_frag = BM * 16 + (wn * WTN + frow) * 16;
 
     // ---- this block's segments: `rounds` whole tiles, then its stream-K range cut at the tile boundaries ----
-    const int G = gridDim.x, bid = blockIdx.x;
-    const int rounds = p.dp_tiles / G;                     // the launcher makes dp_tiles a multiple of the grid
-    int sk_it = 0, sk_len = 0;
-    if (bid < p.sk_blocks) {
-        sk_it = sk_begin(p, bid);
-        sk_len = sk_begin(p, bid + 1) - sk_it;
-    }
-    const int sk_tile = sk_it / nkt, sk_k0 = sk_it - sk_tile * nkt;
-    const int F = rounds * nkt + sk_len;                   // k-steps this block runs
+    const SkWalk walk(p, nkt);
+    const int F = walk.steps(), rounds = walk.rounds, bid = walk.bid;
     if (F == 0) return;
-    auto segment = [&](int s, int& tile, int& k0, int& k1) __attribute__((always_inline)) {
-        if (s < rounds) {
-            tile = xcd_tile(s * G + bid, p.dp_tiles);
-            k0 = 0;
-            k1 = nkt;
-        } else {                                           // piece s - rounds of the stream-K range
-            const int t = sk_tile + (s - rounds);
-            tile = p.dp_tiles + t;
-            k0 = s == rounds ? sk_k0 : 0;
-            k1 = min(nkt, sk_it + sk_len - t * nkt);
-        }
-    };
+    auto segment = [&](int s, int& tile, int& k0, int& k1) __attribute__((always_inline)) { walk.segment(s, tile, k0, k1); };
 
     // ---------------- load side ----------------
     int l_seg = -1, l_k = 0, l_k1 = 0;                     // segment being loaded, next k-step, end
@@ -363,27 +344,16 @@ conv_gemm_pk_kernel(const GemmConv p) {
             const int pq = Po_ * Qo_;
             const int img0 = m0 / pq;
             const int phb = max(ph_, 0), pwb = max(pw_, 0);
-            const int taps = R_ * S_;
-            const unsigned full = taps >= 32 ? ~0u : (1u << taps) - 1u;
-            unsigned rep = 0;
-            for (int rr = 0; rr < R_; ++rr) rep |= 1u << (rr * S_);
+            const WindowTaps window(R_, S_);
 #pragma unroll
             for (int i = 0; i < LA; ++i) {
                 const int m = m0 + (i * NWV + wave) * 16 + lrow;
                 const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
                 const int img = div_by(t, pmul, psh), po = t - img * Po_;
                 const int h0 = po * sh_ - ph_, w0 = qo * sw_ - pw_;
-                // taps of this pixel's window inside the image: rows rlo..rhi, columns slo..shi
-                int rlo = max(0, -h0), rhi = min(R_ - 1, Hi_ - 1 - h0);
-                int slo = max(0, -w0), shi = min(S_ - 1, Wi_ - 1 - w0);
-                const bool ok = (m < M_) & (rlo <= rhi) & (slo <= shi);
-                rlo = min(rlo, R_ - 1);
-                rhi = max(rhi, 0);
-                slo = min(slo, S_ - 1);
-                const int sspan = max(shi - slo, 0);
-                const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
-                const unsigned wmk = rep * (((2u << sspan) - 1u) << slo);
-                a_inv[i] = ok ? ~(hm & wmk) : ~0u;
+                const unsigned inv = window.outside(h0, w0, Hi_, Wi_, R_, S_);
+                const bool ok = (m < M_) & (inv != ~0u);
+                a_inv[i] = ok ? inv : ~0u;
                 a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * ES + kq * 16) : 0u;
             }
 #pragma unroll
@@ -1857,8 +1827,6 @@ __global__ void __launch_bounds__(256, 2) wgrad3x3_slab_kernel(const GemmWgrad p
             D[(long long)row * p.J + col] = acc[tap][v];
         }
 }
-
-
 
 template <int BM, int BN, int BK, int VEC>
 lc_status launch_conv(const GemmConv& p, hipStream_t stream) {

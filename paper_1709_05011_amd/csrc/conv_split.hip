@@ -74,7 +74,8 @@ constexpr int split_blocks_per_cu(int bn, bool ut) { return ut && bn == 64 ? 3 :
 // LDS (one stage): per 16 rows [plane h, m, l][k 0-7, 8-15, 16-23, 24-31][16 rows][8 bf16]; a fragment is 1 KB read in lane order.  Row r of
 // k group g sits at r ^ 2g, which puts the 16 lanes that a store serves per cycle (two rows x eight 4-value pieces) on 128 distinct bytes.
 //
-// A block is in its matrix phase or in its split-and-store phase; the other two blocks of the compute unit fill the pipe meanwhile.
+// A block is in its matrix phase or in its split-and-store phase; the other block of the compute unit (of the narrow tile with uniform taps: the other
+// two) fills the pipe meanwhile.
 template <int BM, int BN, bool SMALLC, bool UT, bool SCATTER>
 __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_split_kernel(const GemmConv p) {
     constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 16, TN = WTN / 16;
@@ -99,28 +100,10 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
     const int frow = lane & 15, fgrp = lane >> 4;
 
     // ---- this block's segments: `rounds` whole tiles, then its stream-K range cut at the tile boundaries ----
-    const int G = gridDim.x, bid = blockIdx.x;
-    const int rounds = p.dp_tiles / G;                     // the launcher makes dp_tiles a multiple of the grid
-    int sk_it = 0, sk_len = 0;
-    if (bid < p.sk_blocks) {
-        sk_it = sk_begin(p, bid);
-        sk_len = sk_begin(p, bid + 1) - sk_it;
-    }
-    const int sk_tile = sk_it / nkt, sk_k0 = sk_it - sk_tile * nkt;
-    const int F = rounds * nkt + sk_len;                   // k-steps this block runs
+    const SkWalk walk(p, nkt);
+    const int F = walk.steps(), rounds = walk.rounds, bid = walk.bid;
     if (F == 0) return;
-    auto segment = [&](int s, int& tile, int& k0, int& k1) __attribute__((always_inline)) {
-        if (s < rounds) {
-            tile = xcd_tile(s * G + bid, p.dp_tiles);
-            k0 = 0;
-            k1 = nkt;
-        } else {                                           // piece s - rounds of the stream-K range
-            const int t = sk_tile + (s - rounds);
-            tile = p.dp_tiles + t;
-            k0 = s == rounds ? sk_k0 : 0;
-            k1 = min(nkt, sk_it + sk_len - t * nkt);
-        }
-    };
+    auto segment = [&](int s, int& tile, int& k0, int& k1) __attribute__((always_inline)) { walk.segment(s, tile, k0, k1); };
 
     // ---------------- load side ----------------
     int l_seg = -1, l_k = 0, l_k1 = 0;                     // segment being loaded, next k-step, end
@@ -142,27 +125,16 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
             const int pq = Po_ * Qo_;
             const int img0 = m0 / pq;
             const int phb = max(ph_, 0), pwb = max(pw_, 0);
-            const int taps = R_ * S_;
-            const unsigned full = taps >= 32 ? ~0u : (1u << taps) - 1u;
-            unsigned rep = 0;
-            for (int rr = 0; rr < R_; ++rr) rep |= 1u << (rr * S_);
+            const WindowTaps window(R_, S_);
             if (lane < LA * 8) {                       // this wave's rows, one per lane; nobody else reads them
                 const int row = ((lane >> 3) * 4 + wave) * 8 + (lane & 7), m = m0 + row;
                 const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
                 const int img = div_by(t, pmul, psh), po = t - img * Po_;
                 const int h0 = po * sh_ - ph_, w0 = qo * sw_ - pw_;
-                // taps of this pixel's window inside the image: rows rlo..rhi, columns slo..shi
-                int rlo = max(0, -h0), rhi = min(R_ - 1, Hi_ - 1 - h0);
-                int slo = max(0, -w0), shi = min(S_ - 1, Wi_ - 1 - w0);
-                const bool ok = (m < M_) & (rlo <= rhi) & (slo <= shi);
-                rlo = min(rlo, R_ - 1);
-                rhi = max(rhi, 0);
-                slo = min(slo, S_ - 1);
-                const int sspan = max(shi - slo, 0);
-                const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
-                const unsigned wmk = rep * (((2u << sspan) - 1u) << slo);
+                const unsigned inv = window.outside(h0, w0, Hi_, Wi_, R_, S_);
+                const bool ok = (m < M_) & (inv != ~0u);
                 row_lds[row] = make_uint2(ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * 4) : 0u,
-                                          ok ? ~(hm & wmk) : ~0u);
+                                          ok ? inv : ~0u);
             }
             asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
             const long long a_first = ((long long)img0 * Hi_ * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
@@ -580,9 +552,7 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
         s_img = im - img_first;
     }
     const int d_q = BK % Q_, d_t = BK / Q_, d_p = d_t % P_, d_img = d_t / P_;
-    const unsigned full = R_ * S_ >= 32 ? ~0u : (1u << (R_ * S_)) - 1u;
-    unsigned rep = 0;                                             // bit r*S for every r: spreads a mask over s to all rows of the window
-    for (int r = 0; r < R_; ++r) rep |= 1u << (r * S_);
+    const WindowTaps window(R_, S_);
 
     typename RowVec<VA>::type ga[8];
     typename RowVec<VB>::type gb[8];
@@ -608,14 +578,7 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
                 if (mt + i >= m_end) {
                     inv = ~0u;
                 } else if ((h0 < 0) | (w0 < 0) | (h0 + R_ > H_) | (w0 + S_ > W_)) {
-                    int rlo = max(0, -h0), rhi = min(R_ - 1, H_ - 1 - h0);
-                    int slo = max(0, -w0), shi = min(S_ - 1, W_ - 1 - w0);
-                    const bool some = (rlo <= rhi) & (slo <= shi);
-                    rlo = min(rlo, R_ - 1);                      // keep the shifts in range when no tap is inside
-                    rhi = max(rhi, 0);
-                    slo = min(slo, S_ - 1);
-                    const unsigned hm = (full << (rlo * S_)) & (full >> ((R_ - 1 - rhi) * S_));
-                    inv = some ? ~(hm & (rep * (((2u << max(shi - slo, 0)) - 1u) << slo))) : ~0u;
+                    inv = window.outside(h0, w0, H_, W_, R_, S_);
                 }
                 const int soff = inv == ~0u ? 0 : ((im * H_ + h0 + phb) * W_ + w0 + pwb) * C_ * 4;
                 load_row(gb[i], b_rsrc, ((inv << b_up) & kBufferBytes) | b_voff, soff);
