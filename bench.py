@@ -444,7 +444,9 @@ def run_sweep(args):
                 continue                      # the first layer's input gradient is never needed in a training step
             med, mn = time_call(torch, fn, args.iters)
             tf = cs.flops / (med * 1e-3) / 1e12
-            roof = min(peak if bf16 or p == "fwd" else PEAK_SPLIT, cs.flops / min_bytes[p] * PEAK_HBM / 1e3)
+            # (filter gradients that stay on the fp32 instructions: the first layer's kernel, and one 64x64 tile)
+            fp32_pipe = p == "fwd" or (p == "bwd_weight" and (idx == 1 or (cs.k <= 64 and cs.c * cs.r * cs.s <= 64)))
+            roof = min(peak if bf16 or fp32_pipe else PEAK_SPLIT, cs.flops / min_bytes[p] * PEAK_HBM / 1e3)
             row[p + "_ms"] = round(med, 4)
             row[p + "_tflops"] = round(tf, 2)
             row[p + "_roof_tflops"] = round(roof, 1)
