@@ -8,8 +8,10 @@
 // where the same sums cost v_mfma_f32_32x32x2_f32 256.  The products of one k-step are summed by themselves and then added to the accumulators with
 // one rounding, which leaves errors of a fifth to a half of those of fp32 instructions (see sum_products()).
 // Measured at batch 256, whole calls, fp32 matrix instructions at 75 to 80 % of their peak -> this kernel:
-//   backward-data    3x3, 128 channels, 28x28: 504 -> 305 us;  1x1, 256 -> 64, 56x56: 295 -> 227 us;  1x1 stride 2, 1024 -> 512: 498 -> 344 us
-//   filter gradient  the same layers: 510 -> 380, 277 -> 208, 430 -> 323 us
+//   backward-data    3x3, 128 channels, 28x28: 498 -> 310 us;  1x1, 256 -> 64, 56x56: 297 -> 238 us;  1x1 stride 2, 1024 -> 512: 514 -> 346 us
+//   filter gradient  the same layers: 489 -> 371, 264 -> 209, 423 -> 327 us
+// Backward-data is bound by power (3x3: matrix pipe busy in 60 % of the cycles at 1.77 GHz), the filter gradient by the split's arithmetic, its scalar
+// work per pixel and the chains of six products (44 % at 1.92 GHz).
 //
 // The split happens once per staged element, on the way from the load registers into LDS.
 #include <hip/hip_runtime.h>
