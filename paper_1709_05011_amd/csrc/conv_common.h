@@ -96,7 +96,7 @@ inline SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_
 // stand idle (bf16: 1x1 over 512 channels, 16 images of 7x7 20.2 -> 10.4 us; over 64 channels, two of 56x56 22 -> 7.5; backward of 512 to 2048, 64 of
 // 7x7 39 -> 28; 3x3 over 256, 64 of 14x14 46 -> 30).
 struct StepCost {
-    double alone, shared, tile;      // us, us, tile size in 128x128
+    double alone, shared, tile;      // us, us, what a part costs in parts of 128x128
     int min_steps;                   // k-steps a block takes of a shared tile at least
 };
 inline SkPlan sk_plan_by_cost(long long tiles, int nkt, int resident_blocks, const StepCost& k) {

@@ -1905,13 +1905,14 @@ bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
 
 // How the tiles beyond the whole rounds are shared out.  A 256x256 tile's partial sums are 256 KB per block and piece: writing and re-reading them
 // costs more than the idle end of the last round, which main_tile() has already bounded.  fp32 keeps the plain form: the order of a forward sum
-// decides its last bits.  bf16: 128x64 tiles take more than half a 128x128 tile's time per k-step where a block is alone (0.22 us instead of 0.35
-// left tiles whole that should be shared: 1x1 over 1248 channels to 29, 258 images of 20x20 54 -> 64 us).
+// decides its last bits.  bf16, 128x64 tiles: a lone block's k-step takes nearly as long as a 128x128 tile's, and a part costs the fix-up as much (with half
+// of both, tiles stayed whole that should be shared: 1x1 over 1248 channels to 29, 258 images of 20x20 54 -> 64 us; of 454 drawn
+// narrow layers 32 were more than 3 % behind the plain form, now 6, and the form chosen is 1.5 % off the best one in the mean).
 template <int BM, int BN>
 SkPlan main_sk_plan(const GemmConv& p, long long tiles, int nkt) {
     if (BM * BN >= 256 * 256 || !p.bf16) return sk_plan(tiles, nkt, resident_blocks(BM, BN), BM * BN < 256 * 256);
     constexpr double size = BM * BN / 16384.0;
-    return sk_plan_by_cost(tiles, nkt, resident_blocks(BM, BN), StepCost{size < 1.0 ? 0.35 : 0.44 * size, 0.3 * size, size, 8});
+    return sk_plan_by_cost(tiles, nkt, resident_blocks(BM, BN), StepCost{size < 1.0 ? 0.4 : 0.44 * size, 0.3 * size, size < 1.0 ? 1.0 : size, 8});
 }
 
 // Whether the uniform-tap variant of the main kernel takes this problem: k-steps that do not straddle taps,
