@@ -32,6 +32,7 @@ struct Plan {
     int splits = 1, m_per_split = 0;
     bool wgrad_direct = true;
     bool stem_wgrad = false;         // ResNet's first layer: the filter-gradient kernels of conv_stem.hip
+    int wgrad_bm = 0, wgrad_bn = 0;  // bf16: the tile of wgrad_dma_kernel (0: another kernel)
     bool wgrad_slab = false;         // bf16 3x3 stride-1 pad-1 layer: the kernel that stages the activations once for all taps
     // bf16 problems the bf16 MFMA kernel does not take (backward-data with k not a multiple of 8, or a strided
     // window other than 1x1): operands are widened to fp32 copies, the fp32 pass runs on them, the result is
@@ -404,7 +405,10 @@ lc_status make_plan(const lc_conv_desc* d, lc_pass pass, Plan* pl) {
         } else if (pl->wgrad_slab) {
             pl->splits = lc_wgrad_slab_splits(d->n, d->h, d->w, pl->cpad, d->k, &pl->m_per_split);
         } else {
-            pl->splits = lc_wgrad_splits(gemm_wgrad(d, *pl));
+            GemmWgrad g = gemm_wgrad(d, *pl);
+            pl->splits = lc_wgrad_splits(&g);
+            pl->wgrad_bm = g.dma_bm;
+            pl->wgrad_bn = g.dma_bn;
             pl->m_per_split = (M + pl->splits - 1) / pl->splits;
         }
         pl->wgrad_direct = pl->splits == 1 && !pad && !pl->stem_wgrad;
@@ -834,6 +838,8 @@ lc_status bwd_weight_impl(const lc_conv_desc* d, const void* x, const void* dy, 
     g.splits = pl.splits;
     g.m_per_split = pl.m_per_split;
     g.slab = pl.wgrad_slab;
+    g.dma_bm = pl.wgrad_bm;
+    g.dma_bn = pl.wgrad_bn;
     g.d = pl.wgrad_direct ? dwdst : reinterpret_cast<float*>(at(workspace, pl.part));
     st = lc_launch_wgrad_f32(g, stream);
     if (st != LC_OK) return st;

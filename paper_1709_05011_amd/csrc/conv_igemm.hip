@@ -2212,8 +2212,11 @@ static bool wgrad_by_split(const GemmWgrad& p) {
     return p.M > (plain || wgrad_large_on_few_rows(p) ? 256 : 160);
 }
 
-int lc_wgrad_splits(const GemmWgrad& p) {
-    int bm, bn;
+int lc_wgrad_splits(GemmWgrad* g) {
+    const GemmWgrad& p = *g;
+    int bm, bn, dma_splits;
+    if (lc_wgrad_dma_plan(p, &g->dma_bm, &g->dma_bn, &dma_splits)) return dma_splits;
+    g->dma_bm = g->dma_bn = 0;
     wgrad_tile(p.K, p.J, &bm, &bn);
     const long long tiles = (long long)((p.K + bm - 1) / bm) * ((p.J + bn - 1) / bn);
     const bool split = wgrad_by_split(p);
@@ -2238,10 +2241,11 @@ bool lc_wgrad_slab_ok(int imgs, int H, int W, int C, int K, int R, int S, int sh
     if (getenv("LARSCONV_NO_WGRAD_SLAB")) return false;                    // comparison runs
     if (!bf16 || R != 3 || S != 3 || sh != 1 || sw != 1 || ph != 1 || pw != 1 || P != H || Q != W) return false;
     if (C % 64 != 0 || K % 64 != 0 || W < 6 || (W + 3 + 31) / 32 > kWsMaxL) return false;
-    // narrow images spend too many MFMAs on halo positions (2 of every W + 2) and the 128-wide tiles of
-    // wgrad_bf16_kernel are as fast from 14 x 14 down; tests lower the threshold to send small shapes here
+    // 64 channels and 64 filters only: nine taps of 64 columns fill two and a quarter of wgrad_dma_kernel's tiles (512 images of 56x56 161 us here, 178
+    // there; but 128 -> 128 at 28x28 188 / 113, 64 -> 128 at 56x56 303 / 260, 192 -> 64 at 28x28 135 / 103).  Narrow images spend too many
+    // MFMAs on halo positions (2 of every W + 2).  Tests lower the threshold to send small shapes here, of any number of channels.
     const char* e = getenv("LARSCONV_WGRAD_SLAB_MIN_W");
-    if (W < (e ? atoi(e) : 24)) return false;
+    if (W < (e ? atoi(e) : 24) || (!e && (C != 64 || K != 64))) return false;
     const long long pixels = (long long)imgs * H * W, positions = (long long)imgs * (H + 1) * (W + 2);
     return pixels * (C > K ? C : K) * 2 < 0x7fff0000LL && positions < 0x7ff00000LL;
 }
@@ -2313,6 +2317,7 @@ static lc_status launch_wgrad_plain(const GemmWgrad& p, hipStream_t stream) {
 template <bool BF16>
 static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
     if (p.slab) return BF16 ? launch_wgrad_slab(p, stream) : LC_ERR_UNSUPPORTED;   // (m_per_split counts positions: no other kernel can take it)
+    if (BF16 && p.dma_bm) return lc_launch_wgrad_dma(p, stream);
     if (!BF16 && wgrad_split_ok(p)) {
         int bm, bn;
         wgrad_tile(p.K, p.J, &bm, &bn);
@@ -2321,8 +2326,12 @@ static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
     if (wgrad_plain_ok(p) && !(BF16 && getenv("LARSCONV_WGRAD_WIDEN"))) {
         int bm, bn;
         wgrad_tile(p.K, p.J, &bm, &bn);
-        if (bm == 128) return bn == 128 ? launch_wgrad_plain<128, 128, BF16>(p, stream) : launch_wgrad_plain<128, 64, BF16>(p, stream);
-        return bn == 128 ? launch_wgrad_plain<64, 128, BF16>(p, stream) : launch_wgrad_plain<64, 64, BF16>(p, stream);
+        if constexpr (BF16) {
+            return launch_wgrad_plain<64, 64, true>(p, stream);
+        } else {
+            if (bm == 128) return bn == 128 ? launch_wgrad_plain<128, 128, BF16>(p, stream) : launch_wgrad_plain<128, 64, BF16>(p, stream);
+            return bn == 128 ? launch_wgrad_plain<64, 128, BF16>(p, stream) : launch_wgrad_plain<64, 64, BF16>(p, stream);
+        }
     }
     if (BF16 && p.C % 8 == 0 && p.K % 8 == 0 && aligned16(p.dy) && aligned16(p.x) && !getenv("LARSCONV_WGRAD_WIDEN")) {
         int bm, bn;                                   // the bf16 matrix pipe; LARSCONV_WGRAD_WIDEN=1: comparison runs

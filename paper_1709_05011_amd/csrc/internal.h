@@ -154,9 +154,13 @@ struct GemmWgrad {
     int splits, m_per_split;
     int bf16;           // dy and x are bf16 (widened on the fly; the sums and d stay fp32)
     int slab;           // 3x3 stride-1 pad-1 bf16 layer for wgrad3x3_slab_kernel: m_per_split counts padded positions
+    int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (conv_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
-int lc_wgrad_splits(const GemmWgrad& p);   // fixed function of the shape (determinism)
+int lc_wgrad_splits(GemmWgrad* p);   // fixed function of the shape (determinism); chooses the tile of wgrad_dma_kernel where that takes the layer
+// bf16 operands straight into LDS (conv_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
+bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits);
+lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream);
 // fp32 operands on the bf16 matrix pipe (conv_split.hip), output tile bm x bn; and how many of its blocks fit on a compute unit
 lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream);
 int lc_wgrad_split_blocks_per_cu(int bm, int bn);
