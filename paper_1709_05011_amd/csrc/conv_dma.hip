@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "conv_common.h"
 
@@ -31,6 +32,552 @@ __device__ __forceinline__ void wait_loads_and_barrier() {
 }
 __device__ __forceinline__ unsigned lds_address(const void* ptr) {
     return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)(uintptr_t)ptr;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Forward and backward-data.  A k-step is 64 values of the reduction: 128 bytes of a row, so that a load of 64 lanes covers eight whole lines.  LDS holds a
+// stage as [row][128 bytes] with the 16-byte pieces of a row at piece ^ (row / 2 % 8) -- the lanes fetch them in that order -- and a fragment of sixteen rows then
+// meets every bank once.  Two stages; while one is multiplied the other arrives, across tile boundaries (persistent blocks, segments as in SkWalk).
+//
+// A wave owns 16 TM x 16 TN of the tile in 16x16 pieces, the filter being the matrix instruction's first operand: a lane holds four neighbouring columns of a
+// pixel.  TMA and TMB: rows of pieces of the first and the second row of waves; each SIMD runs one wave of either kind, so a tile may have any
+// multiple of 16 rows.
+//
+// Bound: windows by the matrix pipe and power (3x3 over 256 channels, 512 images of 14x14: 98 to 106 us by the card's temperature, 1,110 to 1,200 TFLOP/s where a large
+// product reaches 1,377), 1x1 layers by memory (512 to 128 at 28x28 131 -> 108 us, 4.8 TB/s; 64 to 256 at 56x56 225 -> 197, 5.2).  With staging registers and k-steps of 32, half
+// a line of a row per load, the same layers took 147, 131 and 225.  Measured and left out: the loads spread over the following step, wave priorities around
+// the matrix instructions (both equal or slower).
+//
+// kChunks: the channels are a multiple of 64, a k-step is 64 channels of one tap of the window and its place is scalar.  (The taps run fastest: the rows of a tile are read
+// again soon.)  kPadded: the same with the last 64 channels filled up with zeros.  kPieces: the reduction as it lies in the filter, a lane's piece of it has a tap
+// of its own.
+// ------------------------------------------------------------------------------------------------
+struct ConvDma {
+    GemmConv g;
+    int nkt;                      // k-steps of a tile
+    unsigned ci_mul, ci_shift, s_mul, s_shift;
+};
+
+// The sum over the 16 lanes of a row of lanes, in each of them.
+__device__ __forceinline__ float sum_of_16(float x) {
+    x += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), 0x128 /* row_ror 8 */, 0xF, 0xF, true));
+    x += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), 0x124, 0xF, 0xF, true));
+    x += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), 0x122, 0xF, 0xF, true));
+    x += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), 0x121, 0xF, 0xF, true));
+    return x;
+}
+
+// What leaves with a tile: whole 16-byte pieces of rows (columns a multiple of 8); the same and the statistics, any number of columns; any number of columns, or
+// the pixels of a stride grid.
+enum ConvDmaOut { kRows, kStats, kAny };
+enum ConvDmaIn { kChunks, kPadded, kPieces };
+
+template <int TMA, int TMB, int TN, int WN, ConvDmaIn IN, ConvDmaOut OUT>
+__global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma pp) {
+    const GemmConv& p = pp.g;
+    constexpr int BM = 16 * (TMA + TMB), BN = 16 * TN * WN, NW = 2 * WN;
+    constexpr int NA = BM / 8, NB = BN / 8;                // loads of a stage
+    constexpr int LA = (NA + NW - 1) / NW, LB = NB / NW;
+    constexpr int STAGE = (BM + BN) * 128;
+    constexpr int kOutPitch = TN * 32 + 16;                // bytes
+    static_assert(NB % NW == 0, "tile shape");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    unsigned char* const bounce = smem + 2 * STAGE;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int nbn = (p.N + BN - 1) / BN;
+    const int nkt = pp.nkt;
+    const uint16_t* const A = static_cast<const uint16_t*>(p.a);
+    const uint16_t* const B = static_cast<const uint16_t*>(p.b);
+    const int Hi_ = p.Hi, Wi_ = p.Wi, Ci_ = p.Ci, R_ = p.R, S_ = p.S, M_ = p.M, N_ = p.N, Kg_ = p.Kg, ldd_ = p.ldd;
+    const int sh_ = p.sh, sw_ = p.sw, ph_ = p.ph, pw_ = p.pw, Po_ = p.Po, Qo_ = p.Qo;
+    const unsigned qmul = p.qo_mul, qsh = p.qo_shift, pmul = p.po_mul, psh = p.po_shift;
+    const int taps = R_ * S_;
+
+    const SkWalk walk(p, nkt);
+    const int F = walk.steps(), rounds = walk.rounds, bid = walk.bid;
+    if (F == 0) return;
+
+    // ---------------- load side ----------------
+    int l_seg = -1, l_k = 0, l_k1 = 0;                     // segment being loaded, next k-step, end
+    const int lrow = lane >> 3;
+    const int piece = (lane & 7) ^ (((wave & 1) * 4 + (lrow >> 1)) & 7);     // row / 2 % 8 of every row this lane loads: 8 * (i * NW + wave) + lrow
+    unsigned a_voff[LA], a_inv[LA];
+    u32x4 a_rsrc = {0, 0, 0, 0}, b_rsrc = a_rsrc;
+    const unsigned b_voff = (unsigned)((wave * 8 + lrow) * Kg_ * 2 + piece * 16);
+    int u_c = 0, u_tap = 0, u_r = 0, u_s = 0;              // first channel and tap; kPieces: u_c is the k-step
+    const unsigned lds0 = lds_address(smem);
+    unsigned l_lds = lds0;
+    auto loader_setup = [&](int tile, int k0) __attribute__((always_inline)) {
+        const int tm = tile / nbn;
+        const int m0 = tm * BM, n0 = (tile - tm * nbn) * BN;
+        const int img0 = div_by(div_by(m0, qmul, qsh), pmul, psh);
+        const int phb = max(ph_, 0), pwb = max(pw_, 0);
+        const WindowTaps window(R_, S_);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int row = (i * NW + wave) * 8 + lrow, m = m0 + row;
+            const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
+            const int img = div_by(t, pmul, psh), po = t - img * Po_;
+            const int h0 = po * sh_ - ph_, w0 = qo * sw_ - pw_;
+            const unsigned inv = window.outside(h0, w0, Hi_, Wi_, R_, S_);
+            const bool ok = (m < M_) & (inv != ~0u);
+            a_inv[i] = ok ? inv : ~0u;
+            a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * 2 + (IN != kPieces ? piece * 16 : 0)) : 0u;
+        }
+        const long long a_first = ((long long)img0 * Hi_ * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
+        a_rsrc = buffer_words(A + a_first, kBufferBytes);
+        const long long b_left = (long long)(N_ - n0) * Kg_ * 2;       // rows past N lie past the end of the buffer
+        b_rsrc = buffer_words(B + (long long)n0 * Kg_, b_left > 0x7fffffffLL ? 0x7fffffffu : (unsigned)b_left);
+        if constexpr (IN != kPieces) {
+            const int chunk = k0 / taps;
+            u_tap = k0 - chunk * taps;
+            u_c = chunk * 64;
+            u_r = u_tap / S_;
+            u_s = u_tap - u_r * S_;
+        } else {
+            u_c = k0;
+        }
+    };
+    // the next k-step of the block's sequence (past its end: nothing)
+    unsigned v_off = 0, v_up = 0, v_bad = 0;               // this lane's piece: byte offset from the window's first value, tap; bit 31: no such channel
+    auto load_begin = [&]() __attribute__((always_inline)) {
+        if (l_k == l_k1) {
+            int tile;
+            ++l_seg;
+            walk.segment(l_seg, tile, l_k, l_k1);
+            loader_setup(tile, l_k);
+        }
+        if constexpr (IN == kPadded) v_bad = u_c + piece * 8 < Ci_ ? 0u : kBufferBytes;
+        if constexpr (IN == kPieces) {
+            const int kg = u_c * 64 + piece * 8;
+            const int rs = div_by(kg, pp.ci_mul, pp.ci_shift), c = kg - rs * Ci_;
+            const int r = div_by(rs, pp.s_mul, pp.s_shift), s = rs - r * S_;
+            v_off = (unsigned)(((r * Wi_ + s) * Ci_ + c) * 2);
+            v_bad = kg < Kg_ ? 0u : kBufferBytes;
+            v_up = (unsigned)max(31 - rs, 0);
+        }
+    };
+    auto load_one = [&](int l) __attribute__((always_inline)) {
+        if (l < LA) {
+            const int load = l * NW + wave;
+            if (NA % NW != 0 && load >= NA) return;
+            if constexpr (IN != kPieces) {
+                const unsigned vo = (((a_inv[l] << (31 - u_tap)) & kBufferBytes) | a_voff[l]) | v_bad;
+                load_to_lds(a_rsrc, vo, ((u_r * Wi_ + u_s) * Ci_ + u_c) * 2, l_lds + load * 1024);
+            } else {
+                load_to_lds(a_rsrc, ((a_inv[l] << v_up) & kBufferBytes) | v_bad | (a_voff[l] + v_off), 0, l_lds + load * 1024);
+            }
+        } else {
+            const int load = (l - LA) * NW + wave;
+            const int rows = (l - LA) * NW * 8 * Kg_ * 2;
+            load_to_lds(b_rsrc, b_voff | v_bad, rows + (IN != kPieces ? (u_tap * Ci_ + u_c) * 2 : u_c * 128), l_lds + BM * 128 + load * 1024);
+        }
+    };
+    auto load_end = [&]() __attribute__((always_inline)) {
+        if constexpr (IN != kPieces) {
+            ++u_tap;
+            ++u_s;
+            const bool row = u_s == S_;
+            u_s = row ? 0 : u_s;
+            u_r += row ? 1 : 0;
+            const bool chunk = u_tap == taps;
+            u_tap = chunk ? 0 : u_tap;
+            u_r = chunk ? 0 : u_r;
+            u_c += chunk ? 64 : 0;
+        } else {
+            ++u_c;
+        }
+        ++l_k;
+        l_lds = l_lds == lds0 ? lds0 + STAGE : lds0;
+    };
+
+    // ---------------- compute side ----------------
+    auto run = [&]<int TM>(std::integral_constant<int, TM>) __attribute__((always_inline)) {
+        const int row0 = wm * TMA * 16;                    // this wave's first row of the tile
+        f32x4 acc[TM][TN];
+        bf16x8 fa[4], fb[2][TN];
+        // fragment: row lane % 16, pieces lane / 16 (first half of the k-step) and 4 + lane / 16
+        const int sw = ((lane & 15) >> 1), fp = lane >> 4;
+        const unsigned char* const a_lane = smem + (row0 + (lane & 15)) * 128;
+        const unsigned char* const b_lane = smem + BM * 128 + (wn * TN * 16 + (lane & 15)) * 128;
+        const int half0 = ((fp ^ sw) & 7) * 16, half1 = (((4 + fp) ^ sw) & 7) * 16;
+        auto read_a = [&](int stage, int h, int i, int slot) __attribute__((always_inline)) {
+            fa[slot] = *reinterpret_cast<const bf16x8*>(a_lane + stage + (h ? half1 : half0) + i * 2048);
+        };
+        auto read_b = [&](int stage, int h, int j) __attribute__((always_inline)) {
+            fb[h][j] = *reinterpret_cast<const bf16x8*>(b_lane + stage + (h ? half1 : half0) + j * 2048);
+        };
+        auto clear_acc = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        };
+        int c_seg = 0, c_tile, c_k0, c_k, c_k1;
+        walk.segment(0, c_tile, c_k0, c_k1);
+        c_k = c_k0;
+        unsigned char* const mine = bounce + wave * (16 * kOutPitch);
+        const bool whole_rows = OUT == kRows || ((N_ | ldd_) & 7) == 0;
+        auto epilogue = [&]() __attribute__((always_inline)) {
+            const int tm = c_tile / nbn;
+            const int m0 = tm * BM, n0 = (c_tile - tm * nbn) * BN;
+            if (!(c_k0 == 0 && c_k1 == nkt)) {
+                // part of a tile: the first piece of this block's stream-K range (slot 2 * bid) or the last (2 * bid + 1)
+                const __amdgpu_buffer_rsrc_t part_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    (void*)(p.partial + ((size_t)2 * bid + (c_seg == rounds ? 0 : 1)) * (BM * BN)), 0, BM * BN * 4, (int)kBufferWords3);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), part_rsrc, lane * 16 + wave * 1024,
+                                                               (i * TN + j) * NW * 1024, 0);
+                return;
+            }
+            // 16 rows at a time through the wave's own LDS, so that a store covers whole rows of the wave's part.  Rows past M lie past the end of the buffer
+            // or have bit 31 of the offset set, columns past N the latter.
+            constexpr int CPR = TN * 2, RPI = 64 / CPR;    // lanes per row, rows per store
+            const int mw = m0 + row0, lr = lane / CPR, col = n0 + wn * TN * 16 + lane % CPR * 8;
+            const bool scatter = OUT == kAny && p.scatter != 0;
+            long long first_px = mw;
+            if (scatter) {
+                const int t0 = div_by(mw, qmul, qsh), i0 = div_by(t0, pmul, psh);
+                first_px = ((long long)i0 * p.Ho + (t0 - i0 * Po_) * p.esh) * p.Wo + (mw - t0 * Qo_) * p.esw;
+            }
+            const long long left = scatter ? 0x7fffffffLL : (long long)(M_ - mw) * ldd_ * 2;
+            const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(static_cast<uint16_t*>(p.d) + first_px * ldd_), 0, (int)(left > 0x7fffffffLL ? 0x7fffffffLL : left > 0 ? left : 0), (int)kBufferWords3);
+            const unsigned d_voff = col < N_ ? (unsigned)(lr * ldd_ + col) * 2u : kBufferBytes;
+            float sum[TN][4], sq[TN][4];
+            constexpr bool stats = OUT == kStats;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[j][e] = sq[j][e] = 0.f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const uint2 u = make_uint2(lc_bf16x2_rne(acc[i][j][0], acc[i][j][1]), lc_bf16x2_rne(acc[i][j][2], acc[i][j][3]));
+                    *reinterpret_cast<uint2*>(mine + (lane & 15) * kOutPitch + j * 32 + (lane >> 4) * 8) = u;
+                    if (stats) {                           // of the values as stored; rows past M are zeros
+                        const float x[4] = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                                            __uint_as_float(u.y & 0xffff0000u)};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            sum[j][e] += x[e];
+                            sq[j][e] = fmaf(x[e], x[e], sq[j][e]);
+                        }
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+                u32x4 out[16 / RPI];
+#pragma unroll
+                for (int e = 0; e < 16 / RPI; ++e) out[e] = *reinterpret_cast<const u32x4*>(mine + (e * RPI + lr) * kOutPitch + lane % CPR * 16);
+                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+                if (OUT == kRows || (whole_rows & !scatter)) {
+#pragma unroll
+                    for (int e = 0; e < 16 / RPI; ++e)
+                        __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 16 / RPI; ++e) {
+                        const int m = mw + i * 16 + e * RPI + lr;
+                        int px = m - mw;
+                        if (scatter) {
+                            const int t = div_by(m, qmul, qsh), img = div_by(t, pmul, psh);
+                            px = (int)(((long long)img * p.Ho + (t - img * Po_) * p.esh) * p.Wo + (m - t * Qo_) * p.esw - first_px);
+                        }
+                        const unsigned off = m < M_ ? (unsigned)(px * ldd_ + col) * 2u : kBufferBytes;
+                        if (whole_rows) {
+                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off : kBufferBytes), 0, 0);
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 8; ++v)
+                                __builtin_amdgcn_raw_buffer_store_b16((short)(out[e][v >> 1] >> (16 * (v & 1))), d_rsrc,
+                                                                      (int)(col + v < N_ ? off : kBufferBytes), v * 2, 0);
+                        }
+                    }
+                }
+            }
+            if (stats) {                                   // the 16 lanes of a group hold the sums of a piece's pixels
+                typedef float flt2 __attribute__((ext_vector_type(2)));
+                flt2* const st = reinterpret_cast<flt2*>(p.stats) + ((size_t)tm * 2 + wm) * N_;
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float a = sum_of_16(sum[j][e]), b = sum_of_16(sq[j][e]);
+                        const int c = n0 + (wn * TN + j) * 16 + 4 * (lane >> 4) + e;
+                        if ((lane & 15) == 0 && c < N_) st[c] = flt2{a, b};
+                    }
+            }
+        };
+
+        load_begin();
+#pragma unroll
+        for (int l = 0; l < LA + LB; ++l) load_one(l);
+        load_end();
+        if (F > 1) {
+            load_begin();
+#pragma unroll
+            for (int l = 0; l < LA + LB; ++l) load_one(l);
+            load_end();
+        }
+        clear_acc();
+        if (F > 1 && wave < NA - (LA - 1) * NW) wait_loads_and_barrier<LA + LB>();
+        else if (F > 1) wait_loads_and_barrier<LA - 1 + LB>();
+        else wait_loads_and_barrier<0>();
+        read_a(0, 0, 0, 0);
+        read_a(0, 0, 1, 1);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) read_b(0, 0, j);
+        bool stored = false;                               // the last step ended in stores that may still be under way
+        auto step = [&]<int BUF>(std::integral_constant<int, BUF>, int f) __attribute__((always_inline)) {
+            constexpr int stage = BUF * STAGE, other = STAGE - stage, OFF = (BUF * 2 * TM) & 3;
+#pragma unroll
+            for (int q = 0; q < 2 * TM; ++q) {
+                const int h = q / TM;
+                if (q + 2 < 2 * TM) {
+                    read_a(stage, (q + 2) / TM, (q + 2) % TM, (q + 2 + OFF) & 3);
+                    if (q < TN) read_b(stage, 1, q);
+                } else if (q + 2 == 2 * TM) {
+                    // this stage has been read, the next has arrived
+                    if (stored) wait_loads_and_barrier<TM * 16 * TN * 32 / 1024>();
+                    else wait_loads_and_barrier<0>();
+                    stored = false;
+                    read_a(other, 0, 0, (q + 2 + OFF) & 3);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) read_b(other, 0, j);
+                } else {
+                    read_a(other, 0, 1, (q + 2 + OFF) & 3);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[q % TM][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[h][j], fa[(q + OFF) & 3], acc[q % TM][j], 0, 0, 0);
+                if (q + 2 >= 2 * TM && f + 2 < F) {        // k-step f + 2 into the stage just read
+                    constexpr int half = (LA + LB + 1) / 2;
+                    if (q + 2 == 2 * TM) load_begin();
+#pragma unroll
+                    for (int l = 0; l < LA + LB; ++l)
+                        if ((l < half) == (q + 2 == 2 * TM)) load_one(l);
+                    if (q + 1 == 2 * TM) load_end();
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (++c_k == c_k1) {
+                epilogue();
+                stored = c_k0 == 0 && c_k1 == nkt && OUT != kStats && whole_rows;
+                clear_acc();
+                ++c_seg;
+                walk.segment(c_seg, c_tile, c_k0, c_k1);
+                c_k = c_k0;
+            }
+        };
+        // (the last step reads fragments that are never used)
+        for (int f = 0; f < F; f += 2) {
+            step(std::integral_constant<int, 0>{}, f);
+            if (f + 1 < F) step(std::integral_constant<int, 1>{}, f + 1);
+        }
+    };
+    if constexpr (TMA == TMB) {
+        run(std::integral_constant<int, TMA>{});
+    } else {
+        if (wm == 0) run(std::integral_constant<int, TMA>{});
+        else run(std::integral_constant<int, TMB>{});
+    }
+}
+
+// Adds the parts of every tile that stream-K blocks share, in k order, and stores the tile: block (t, y) takes piece y of each wave's part.
+template <int TM, int TN, int WN, bool MEET>
+__global__ void __launch_bounds__(2 * WN * 64) conv_dma_fixup_kernel(const GemmConv p, int nkt) {
+    constexpr int BM = 32 * TM, BN = 16 * TN * WN, NW = 2 * WN;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nbn = (p.N + BN - 1) / BN;
+    int sk_tile, j, j1;
+    if (!sk_shared_tile<MEET>(p, nkt, blockIdx.x, &sk_tile, &j, &j1)) return;  // one block did the whole tile and stored it
+    const int tb = sk_tile * nkt;                                        // this tile's first k-step in stream-K positions
+    const f32x4* part = reinterpret_cast<const f32x4*>(p.partial) + (blockIdx.y * NW + wave) * 64 + lane;
+    constexpr size_t kSlot = BM * BN / 4;
+    // the first block's piece is the last of its range unless its range starts here; all others start their ranges in this tile
+    f32x4 sum = part[((size_t)2 * j + (sk_begin(p, j) >= tb ? 0 : 1)) * kSlot];
+    for (++j; j + 4 <= j1; j += 4) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = part[(size_t)2 * (j + u) * kSlot];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += v[u];
+    }
+    for (; j < j1; ++j) sum += part[(size_t)2 * j * kSlot];
+    const int tile = p.dp_tiles + sk_tile, tm = tile / nbn;
+    const int ti = blockIdx.y / TN, tj = blockIdx.y - ti * TN;
+    const int m = tm * BM + (wave / WN) * TM * 16 + ti * 16 + (lane & 15);
+    const int col = (tile - tm * nbn) * BN + (wave % WN) * TN * 16 + tj * 16 + 4 * (lane >> 4);
+    if (m >= p.M || col >= p.N) return;
+    long long px = m;
+    if (p.scatter) {
+        const int qo = m % p.Qo, t = m / p.Qo;
+        const int po = t % p.Po, img = t / p.Po;
+        px = ((long long)img * p.Ho + (long long)po * p.esh) * p.Wo + (long long)qo * p.esw;
+    }
+    uint16_t* d = static_cast<uint16_t*>(p.d) + px * p.ldd + col;
+    const uint2 u = make_uint2(lc_bf16x2_rne(sum[0], sum[1]), lc_bf16x2_rne(sum[2], sum[3]));
+    if (((p.N | p.ldd) & 3) == 0 && (reinterpret_cast<uintptr_t>(p.d) & 7) == 0) {
+        *reinterpret_cast<uint2*>(d) = u;
+    } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (col + v < p.N) d[v] = (uint16_t)((v < 2 ? u.x : u.y) >> (16 * (v & 1)));
+    }
+}
+
+// Windows over channels that are nearly a multiple of 64: chunk by chunk all the same, also where that leaves up to a 32nd of the products to zeros.  With all
+// channels of a tap before the next tap, a tile's rows come from beyond L2 once per tap (3x3, us, pieces / padded: 1120 to 64 253 / 175, 1272 to 96 212 / 161,
+// 696 to 1984 439 / 417; but with a ninth of zeros 288 to 1048 380 / 407).
+ConvDmaIn conv_dma_in(const GemmConv& p) {
+    if (p.Ci % 64 == 0) return kChunks;
+    return p.R * p.S > 1 && (p.Ci + 63) / 64 * 64 * 32LL <= p.Ci * 33LL ? kPadded : kPieces;
+}
+int conv_dma_steps(const GemmConv& p) { return conv_dma_in(p) != kPieces ? (p.Ci + 63) / 64 * p.R * p.S : (p.Kg + 63) / 64; }
+
+// Tiles, and what a k-step of them takes in us where a block has its compute unit to itself, per block where `per_cu` take turns, and the same for what a tile costs
+// beyond its k-steps.
+struct ConvTile {
+    int bm, bn, per_cu;
+    float alone, shared, tile;
+};
+constexpr int kWide = 0, kSquare = 1, kNarrow = 2, kNarrowTwoWaves = 3;
+constexpr ConvTile kConvTiles[] = {{256, 256, 1, 1.4f, 1.065f, 1.9f}, {128, 128, 2, 0.41f, 0.2f, 0.8f}, {128, 64, 3, 0.355f, 0.181f, 0.7f}, {128, 64, 3, 0.545f, 0.17f, 0.62f},
+                                   {240, 256, 1, 1.2f, 1.0f, 2.2f},   {224, 256, 1, 1.1f, 0.915f, 2.05f}, {208, 256, 1, 0.88f, 0.86f, 2.2f}, {192, 256, 1, 0.72f, 0.8f, 2.2f}};
+
+struct ConvDmaPlan {
+    int tile;                     // of kConvTiles
+    int nkt;
+    long long tiles;
+    SkPlan sk;
+};
+
+// Tile and work split by cost, in us: rounds of whole tiles, then the rest whole to one block each, to S blocks each in equal parts, or end to end over the resident
+// blocks; shared tiles cost the fix-up's launch and their parts.  Memory (4.2 MB per us) and what the tiles read from the L2s (15 MB) are taken in by the
+// fourth-power mean, since none hides behind another entirely.  Fitted to 178 layers of 1 to 512 images, forward, every tile with up to nine splits: the choice is 1.7 %
+// off the best in the mean, 6 % or more in one of ten, and 1.3 times as fast in the mean as the kernels with staging registers that took these layers before
+// (3x3 over 256 channels, 512 images of 14x14: 147 -> 106 us).
+// Row counts other than 128 and 256 fill the rounds of wide results (that layer has 392 tiles of 256 rows: two rounds for one and a half; 483 of 208: 116 -> 106).  They
+// replace a tile that no blocks share, where every sum is the same: so the result does not depend on whether statistics, which come in pieces of 64 or 128 rows, are wanted.
+bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
+    const int cus = device_cu_count(), nkt = conv_dma_steps(p);
+    const float pixels = p.R == 1 && p.S == 1 ? (float)p.M : (float)p.M / ((float)p.Po * (float)p.Qo) * (float)p.Hi * (float)p.Wi;
+    const float memory = (pixels * (float)p.Ci + (float)p.M * (float)p.N) * (2e-6f / 4.2f);
+    auto fourth = [](float x) { return x * x * x * x; };
+    const bool rows = !p.scatter && p.N % 8 == 0 && p.ldd % 8 == 0;
+    float best = 1e30f;
+    out->nkt = nkt;
+    auto tile_cost = [&](int i) {
+        const ConvTile& t = kConvTiles[i];
+        const long long tiles = (long long)((p.M + t.bm - 1) / t.bm) * ((p.N + t.bn - 1) / t.bn);
+        if (tiles * nkt >= 0x7fffffffLL) return;
+        const int resident = t.per_cu * cus, rest = (int)(tiles % resident);
+        const float whole = (float)(tiles / resident * t.per_cu) * ((float)nkt * t.shared + t.tile);
+        const float others = fourth(memory) + fourth((float)tiles * (float)nkt * (float)(t.bm + t.bn) * (128e-6f / 15.f));
+        auto consider = [&](int blocks, bool even) {
+            const int steps = rest ? (int)(((long long)rest * nkt + blocks - 1) / blocks) : 0;
+            float us = whole;
+            if (rest) {
+                const float turns = (float)((blocks + cus - 1) / cus);
+                float r = std::max((float)steps * t.alone + t.tile, turns * ((float)steps * t.shared + t.tile));
+                if (!even) r *= 1.15f;                     // (unequal parts: blocks no longer read the same rows together)
+                us += r;
+                if (blocks != rest) us += 5.f + 0.021f * (float)blocks * (float)(t.bm * t.bn) / 16384.f;
+            }
+            us = sqrtf(sqrtf(fourth(us) + others));
+            // (a last round of narrow tiles on fewer than half of the compute units also leaves memory idle: 1x1 over 1248 channels to 29 or 32, 258 images of 20x20
+            // 50.5 and 47.2 us, with the last 39 tiles shared out 49.7 and 46.4; square ones 109 / 112: 512 to 128, 512 images of 28x28)
+            if (t.bn == 64 && whole > 0.f && blocks == rest && 2 * rest < cus) us *= 1.01f;
+            if (us < best) {
+                best = us;
+                out->tile = i;
+                out->tiles = tiles;
+                out->sk.dp_tiles = (int)(tiles - rest);
+                out->sk.sk_blocks = rest ? blocks : 0;
+                out->sk.sk_iters = (long long)rest * nkt;
+            }
+        };
+        consider(rest ? rest : 1, true);
+        if (rest == 0 || i == kWide || i > kNarrowTwoWaves) return;
+        for (int s = 2; s <= 16 && rest * s <= resident && nkt >= 2 * s; s += s < 4 ? 1 : s < 8 ? 2 : 4) consider(rest * s, true);
+        const int all = (int)std::min<long long>(resident, (long long)rest * nkt / 2);
+        if (all > rest) consider(all, false);
+    };
+    if (p.N > 128 && rows) tile_cost(kWide);
+    if (p.N > 64) tile_cost(kSquare);
+    tile_cost(kNarrow);
+    tile_cost(kNarrowTwoWaves);
+    if (best >= 1e30f) return false;
+    if (any_rows && p.N > 128 && rows && out->sk.sk_iters == (long long)out->sk.sk_blocks * nkt)
+        for (int i = kNarrowTwoWaves + 1; i < (int)(sizeof(kConvTiles) / sizeof(kConvTiles[0])); ++i) tile_cost(i);
+    return true;
+}
+bool conv_dma_shares(const ConvDmaPlan& c) { return c.sk.sk_iters != (long long)c.sk.sk_blocks * c.nkt; }
+
+template <int TMA, int TMB, int TN, int WN>
+lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_t stream) {
+    constexpr int BM = 16 * (TMA + TMB), BN = 16 * TN * WN, threads = 2 * WN * 64;
+    constexpr int lds = 2 * (BM + BN) * 128 + 2 * WN * 16 * (TN * 32 + 16);
+    ConvDma c = {q, plan.nkt, 0, 0, 0, 0};
+    GemmConv& p = c.g;
+    const long long tiles = plan.tiles;
+    const int nkt = plan.nkt, resident = kConvTiles[plan.tile].per_cu * device_cu_count();
+    SkPlan pl = plan.sk;
+    if (pl.sk_blocks > 0 && !p.partial) pl.sk_blocks = 0;
+    if (pl.sk_blocks == 0) {
+        const long long rest = tiles % resident;
+        pl.dp_tiles = (int)(tiles - rest);
+        pl.sk_blocks = (int)rest;
+        pl.sk_iters = rest * nkt;
+    }
+    p.dp_tiles = pl.dp_tiles;
+    p.sk_blocks = pl.sk_blocks;
+    p.sk_iters = pl.sk_iters;
+    sk_constants(&p);
+    magic_for(p.Qo, &p.qo_mul, &p.qo_shift);
+    magic_for(p.Po, &p.po_mul, &p.po_shift);
+    magic_for(p.Ci, &c.ci_mul, &c.ci_shift);
+    magic_for(p.S, &c.s_mul, &c.s_shift);
+    const unsigned grid = pl.dp_tiles > 0 ? (unsigned)resident : (unsigned)pl.sk_blocks;
+    lc_status st = LC_OK;
+    auto launch = [&]<ConvDmaIn IN, ConvDmaOut OUT>() {
+        static const bool once = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_dma_kernel<TMA, TMB, TN, WN, IN, OUT>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
+        if (!once) st = LC_ERR_LAUNCH;
+        else hipLaunchKernelGGL((conv_dma_kernel<TMA, TMB, TN, WN, IN, OUT>), dim3(grid), dim3(threads), lds, stream, c);
+    };
+    auto out = [&]<ConvDmaIn IN>() {
+        if constexpr (WN != 4 || (TMA == 8 && TMB == 8)) {
+            if (p.stats) return launch.template operator()<IN, kStats>();
+        }
+        if constexpr (WN != 4) {
+            if (p.scatter || ((p.N | p.ldd) & 7) != 0) return launch.template operator()<IN, kAny>();
+        }
+        launch.template operator()<IN, kRows>();
+    };
+    switch (conv_dma_in(p)) {
+        case kChunks: out.template operator()<kChunks>(); break;
+        case kPadded: out.template operator()<kPadded>(); break;
+        case kPieces: out.template operator()<kPieces>(); break;
+    }
+    if (st != LC_OK) return st;
+    if constexpr (TMA == TMB) {
+        if (pl.sk_blocks > 0 && pl.sk_iters != (long long)pl.sk_blocks * nkt) {
+            if (!sk_ranges_meet(p, nkt))
+                hipLaunchKernelGGL((conv_dma_fixup_kernel<TMA, TN, WN, false>), dim3((unsigned)(tiles - pl.dp_tiles), TMA * TN), dim3(threads), 0, stream, p, nkt);
+            else if (pl.sk_blocks > 1)
+                hipLaunchKernelGGL((conv_dma_fixup_kernel<TMA, TN, WN, true>), dim3((unsigned)pl.sk_blocks - 1, TMA * TN), dim3(threads), 0, stream, p, nkt);
+        }
+    }
+    return lc_end_call();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -331,6 +878,53 @@ constexpr WgradTile kWgradTiles[] = {{256, 256, 1, 0.70f, 0.787f}, {256, 128, 1,
 
 }  // namespace
 
+// bf16 operands of 16-byte pieces, windows of at most 32 taps, byte offsets within a tile (the images it can touch plus a window; its filters; its result) below 2^31.
+bool lc_conv_dma_ok(const GemmConv& p) {
+    static const bool off = getenv("LARSCONV_NO_CONV_DMA") != nullptr;       // comparison runs
+    if (off || !p.bf16 || p.Ci % 8 != 0 || !aligned16(p.a) || !aligned16(p.b) || p.dh > 1 || p.dw > 1) return false;
+    if ((long long)p.R * p.S > 32 || p.M >= 0x7fff0000) return false;
+    const long long images = 256LL / ((long long)p.Po * p.Qo) + 2;
+    const long long a_span = ((images * p.Hi + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.Wi + p.S + 1) * p.Ci * 2;
+    const long long d_span = p.scatter ? images * p.Ho * p.Wo * p.ldd * 2 : 288LL * p.ldd * 2;
+    return a_span < 0x7fff0000LL && 257LL * p.Kg * 2 < 0x7fff0000LL && d_span < 0x7fff0000LL;
+}
+
+size_t lc_conv_dma_workspace(const GemmConv& p) {
+    ConvDmaPlan c;
+    if (!conv_dma_plan(p, true, &c) || !conv_dma_shares(c)) return 0;
+    return (size_t)2 * c.sk.sk_blocks * kConvTiles[c.tile].bm * kConvTiles[c.tile].bn * sizeof(float);
+}
+
+size_t lc_conv_dma_stats_tiles(const GemmConv& p) {
+    ConvDmaPlan c;
+    if (!conv_dma_plan(p, false, &c)) return 0;
+    const int bm = kConvTiles[c.tile].bm;
+    return (size_t)2 * ((p.M + bm - 1) / bm);
+}
+
+lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream) {
+    ConvDmaPlan c;
+    if (!conv_dma_plan(p, p.stats == nullptr, &c)) return LC_ERR_UNSUPPORTED;
+    if (p.scatter && p.stats) return LC_ERR_UNSUPPORTED;
+    auto go = [&]<int TMA, int TMB, int TN, int WN>() { return launch_conv_dma<TMA, TMB, TN, WN>(p, c, stream); };
+    lc_status st = LC_ERR_UNSUPPORTED;
+    switch (c.tile) {
+        case kWide: st = go.template operator()<8, 8, 4, 4>(); break;
+        case kSquare: st = go.template operator()<4, 4, 4, 2>(); break;
+        case kNarrow: st = go.template operator()<4, 4, 2, 2>(); break;
+        case kNarrowTwoWaves: st = go.template operator()<4, 4, 4, 1>(); break;
+        case 4: st = go.template operator()<8, 7, 4, 4>(); break;
+        case 5: st = go.template operator()<7, 7, 4, 4>(); break;
+        case 6: st = go.template operator()<7, 6, 4, 4>(); break;
+        case 7: st = go.template operator()<6, 6, 4, 4>(); break;
+    }
+    if (st == LC_OK && p.stats && conv_dma_shares(c) && p.partial) {
+        lc_tile_stats(p, kConvTiles[c.tile].bm, kConvTiles[c.tile].bn, c.sk.dp_tiles, c.tiles, stream);
+        st = lc_end_call();
+    }
+    return st;
+}
+
 // Tile and splits by cost, in us: the stages of a block alone on its compute unit, of blocks that take turns, the operands' bytes at 3.85 MB (as
 // few as 23 blocks reach that from what is cached) and what the tiles read from the L2s at 21.5 MB, in the fourth-power mean, since none hides behind
 // another entirely; partial sums of several splits cost 0.3 a MB to write and to read again, and the launch that adds them 3.1.  Fitted to 188 layers of 1
@@ -402,3 +996,4 @@ lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
     }
     return LC_ERR_UNSUPPORTED;
 }
+

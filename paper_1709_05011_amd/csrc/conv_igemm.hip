@@ -1,5 +1,5 @@
-// Implicit-GEMM convolution kernels for gfx950: the forward pass, bf16 backward-data and filter gradients, and the fallbacks of both types
-// (fp32 backward-data and filter gradients: conv_split.hip).
+// Implicit-GEMM convolution kernels for gfx950: the fp32 forward pass, bf16 layers of 64 channels with a 3x3 window, and the fallbacks of both types
+// (bf16: conv_dma.hip; fp32 backward-data and filter gradients: conv_split.hip).
 //
 // Forward and backward-data run as  D[m][n] = sum_kg A(m,kg) * B[n][kg]  where row m is an output
 // pixel (img, po, qo), column kg = (r, s, ci) walks the filter window with the channel innermost,
@@ -234,7 +234,8 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward / backward-data kernel (channel counts that are multiples of 4, no dilated read).
+// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with windows of more than 32 taps and
+// tensors of spans that conv_dma.hip does not take.
 //
 // LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
@@ -280,22 +281,17 @@ __device__ __forceinline__ size_t partial_index(int wave, int i, int j, int v, i
 // whose row part of the address is a scalar offset and whose bounds are the buffer's size (rows) and bit 31
 // of the lane offset (columns).
 // ------------------------------------------------------------------------------------------------
-// Blocks per compute unit: 3 for tiles up to 128x128 (64 accumulator registers per lane), 2 for the 128x256 tile, 1 for
-// the 256x256 tile (run by eight waves, two per SIMD, each with 128 accumulator registers).
-constexpr int pk_blocks_per_cu(int bm, int bn) { return bm * bn >= 256 * 256 ? 1 : bm * bn > 128 * 128 ? 2 : 3; }
-// Waves along the columns of the tile: 2 (a 2 x 2 block of waves), or 4 for the 256x256 tile (2 x 4 waves of 128 x 64).
-constexpr int pk_waves_n(int bm, int bn) { return bm * bn >= 256 * 256 ? 4 : 2; }
+constexpr int kPkBlocksPerCu = 3;        // tiles up to 128x128: 64 accumulator registers per lane
 
-template <int BM, int BN, bool SMALLC, bool BF16, bool UT, bool SCATTER>
-__global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64, pk_blocks_per_cu(BM, BN) * pk_waves_n(BM, BN) / 2)
-conv_gemm_pk_kernel(const GemmConv p) {
+template <int BM, int BN, bool SMALLC, bool BF16, bool UT>
+__global__ void __launch_bounds__(256, kPkBlocksPerCu) conv_gemm_pk_kernel(const GemmConv p) {
     using E = typename OutT<BF16>::type;
     constexpr int ES = (int)sizeof(E);
     constexpr int EPC = BF16 ? 8 : 4;
     constexpr int BK = 4 * EPC;
-    constexpr int WN_ = pk_waves_n(BM, BN), NWV = 2 * WN_;              // waves: 2 along the rows x WN_ along the columns
+    constexpr int NWV = 4;                                             // waves, 2 x 2
     constexpr int LA = BM / (16 * NWV), LB = BN / (16 * NWV), LPT = LA + LB;
-    constexpr int WTM = BM / 2, WTN = BN / WN_, TM = WTM / 32, TN = WTN / 32;
+    constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
     constexpr int STAGE = (BM + BN) * 16;
     static_assert(BM % (16 * NWV) == 0 && BN % (16 * NWV) == 0 && WTM % 32 == 0 && WTN % 32 == 0, "tile shape");
 
@@ -303,7 +299,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN_, wn = wave % WN_;
+    const int wm = wave >> 1, wn = wave & 1;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
     const E* __restrict__ A = static_cast<const E*>(p.a);
@@ -512,84 +508,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
         const int tm = c_tile / nbn;
         const int m0 = tm * BM, n0 = (c_tile - tm * nbn) * BN;
         if (c_k0 == 0 && c_k1 == nkt) {
-            if constexpr (SCATTER) {                       // (bf16 only: fp32 backward-data runs in conv_split.hip)
-                // Row (img, po, qo) of the GEMM is pixel (po*esh, qo*esw) of image img in the [imgs][Ho][Wo][ldd] result;
-                // the pixels between the stride grid are zero and were cleared by the caller before the launch.  An
-                // accumulator register holds one row in lanes 0..31 and the row four further down in lanes 32..63;
-                // rows are wave-uniform, so their pixel offsets (relative to the tile's first pixel) are computed
-                // on the scalar unit and each lane picks its own.
-                const int Ho_ = p.Ho, Wo_ = p.Wo, esh_ = p.esh, esw_ = p.esw;
-                int t0 = div_by(m0, qmul, qsh);
-                const int q0 = m0 - t0 * Qo_, i0 = div_by(t0, pmul, psh), p0 = t0 - i0 * Po_;
-                const long long first_px = ((long long)i0 * Ho_ + p0 * esh_) * Wo_ + q0 * esw_;
-                const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-                    (void*)(static_cast<E*>(p.d) + first_px * ldd_), 0, (int)kBufferBytes, (int)kBufferWords3);
-                auto px_off = [&](int m) __attribute__((always_inline)) {        // scalar: byte offset of row m's pixel
-                    const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
-                    const int img = div_by(t, pmul, psh), po = t - img * Po_;
-                    const long long px = ((long long)img * Ho_ + po * esh_) * Wo_ + qo * esw_;
-                    return (unsigned)((int)(px - first_px) * ldd_ * ES);
-                };
-                const bool hi = lane >= 32;
-                const int odd = lane & 1;
-                const bool pairs = ((N_ | ldd_) & 1) == 0;
-                if (m0 + BM <= M_) {
-                    unsigned colpart[TN];                       // bit 31 past N: stays set after a pixel offset is added
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int col = n0 + wn * WTN + j * 32 + (lane & 31);
-                        colpart[j] = col < N_ ? (unsigned)((pairs ? (col & ~1) : col) * ES) : kBufferBytes;
-                    }
-                    const unsigned perm_sel = odd ? 0x03020706u : 0x05040100u;
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int v = 0; v < 16; v += 2) {
-                            const int m = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + (v & 3);
-                            const unsigned o0 = px_off(m), o1 = px_off(m + 1), o4 = px_off(m + 4), o5 = px_off(m + 5);
-                            const unsigned row_a = hi ? o4 : o0, row_b = hi ? o5 : o1;     // rows of registers v and v + 1
-#pragma unroll
-                            for (int j = 0; j < TN; ++j) {
-                                typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                                typedef float f32x2 __attribute__((ext_vector_type(2)));
-                                const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
-                                const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
-                                if (pairs) {                // as in the plain tile store: a lane stores a column pair of one row
-                                    const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc,
-                                                                          (int)(colpart[j] + (odd ? row_b : row_a)), 0, 0);
-                                } else {
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)(colpart[j] + row_a), 0, 0);
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)(colpart[j] + row_b), 0, 0);
-                                }
-                            }
-                        }
-                } else {
-                    // the last tile along M: rows are checked one by one on the scalar unit, each half of the wave is
-                    // stored by its own instruction with the other half's lanes parked past the end of the buffer
-                    unsigned d_voff[2][TN];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int col = n0 + wn * WTN + j * 32 + (lane & 31);
-                        d_voff[0][j] = (col < N_ && !hi) ? (unsigned)(col * ES) : kBufferBytes;
-                        d_voff[1][j] = (col < N_ && hi) ? (unsigned)(col * ES) : kBufferBytes;
-                    }
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v)
-#pragma unroll
-                            for (int hs = 0; hs < 2; ++hs) {
-                                const int m = m0 + wm * WTM + i * 32 + 8 * (v >> 2) + 4 * hs + (v & 3);
-                                if (m >= M_) continue;
-                                const int soff = (int)px_off(m);
-#pragma unroll
-                                for (int j = 0; j < TN; ++j) {
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)lc_bf16_rne(acc[i][j][v]), d_rsrc, (int)d_voff[hs][j], soff, 0);
-                                }
-                            }
-                }
-            } else {
+            {
                 // rows: scalar offset, cut off at M by the size of the buffer; columns: lane offset, bit 31 past N
                 const long long rows_left = (long long)(M_ - m0) * ldd_ * ES;
                 const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -638,7 +557,7 @@ conv_gemm_pk_kernel(const GemmConv p) {
                         }
                     }
             }
-            if constexpr (!SCATTER) {
+            {
                 if (p.stats) {
                     // Per column, the sum and the sum of squares of what this wave has just stored (the values as stored:
                     // rounded where the result is bf16) over its WTM rows; rows past M count as zero.  A lane holds 16 rows
@@ -732,11 +651,10 @@ conv_gemm_pk_kernel(const GemmConv p) {
 // Block (t, v) handles accumulator register v of every 32x32 MFMA tile of stream-K tile t, with the thread
 // geometry of the main kernel: 16 blocks per tile keep the whole chip busy on what is a small reduction.
 template <int BM, int BN, bool BF16, bool MEET>
-__global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_kernel(const GemmConv p) {
-    constexpr int WN_ = pk_waves_n(BM, BN);
-    constexpr int BK = BF16 ? 32 : 16, TM = BM / 64, TN = BN / (32 * WN_);
+__global__ void __launch_bounds__(256) conv_gemm_fixup_kernel(const GemmConv p) {
+    constexpr int BK = BF16 ? 32 : 16, TM = BM / 64, TN = BN / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave / WN_, wn = wave % WN_;
+    const int wm = wave >> 1, wn = wave & 1;
     const int v = blockIdx.y;
     const int nbn = (p.N + BN - 1) / BN;
     const int nkt = (p.Kg + BK - 1) / BK;
@@ -786,7 +704,7 @@ __global__ void __launch_bounds__(2 * pk_waves_n(BM, BN) * 64) conv_gemm_fixup_k
             for (int u = 0; u < 16; ++u) out[i][jj][u] = acc[i][jj][0];
     const int tile = p.dp_tiles + sk_tile;
     const int m0 = (tile / nbn) * BM, n0 = (tile % nbn) * BN;
-    store_tile<TM, TN, BF16>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, v);
+    store_tile<TM, TN, BF16>(p, out, m0 + wm * (BM / 2), n0 + wn * (BN / 2), lane, v);
 }
 
 // The column sums of the tiles that stream-K blocks shared (the main kernel sums the tiles it stores whole): block
@@ -875,9 +793,8 @@ __global__ void __launch_bounds__(256) tile_stats_kernel(const GemmConv p, int b
 constexpr int kSlabPitch = 80;         // bytes between slab pixels
 constexpr int kSlabMaxVec = 8;         // 16-byte slab vectors per thread: slabs of up to 512 pixels
 
-template <int BN>
 __global__ void __launch_bounds__(256, 2) conv3x3_slab_kernel(const GemmConv p) {
-    constexpr int BM = 128, WTM = 64, WTN = BN / 2, TM = 2, TN = WTN / 32, LB = BN * 4 / 256;
+    constexpr int BM = 128, BN = 64, WTM = 64, WTN = BN / 2, TM = 2, TN = WTN / 32, LB = BN * 4 / 256;
     extern __shared__ __attribute__((aligned(1024))) unsigned char slab_smem[];
     float* bl = reinterpret_cast<float*>(slab_smem);                 // filter tile, two stages of BN rows x 64 bytes
     unsigned char* slab = slab_smem + 2 * BN * 64;
@@ -1846,54 +1763,7 @@ lc_status launch_wgrad(const GemmWgrad& p, hipStream_t stream) {
 }
 
 // Blocks of the main kernel that fit on the chip at once (the kernel's launch bounds hold it to this).
-inline int resident_blocks(int bm, int bn) { return pk_blocks_per_cu(bm, bn) * device_cu_count(); }
-
-// Tile of the main kernel for a problem.  fp32: 128 rows, 64 columns for narrow results, otherwise 128.  bf16
-// adds larger tiles, because its loop is bound by what moves through LDS per MFMA, and both the staging writes and
-// the fragment reads per MFMA fall with the tile's sides:
-//   128x256 for results at least 256 wide with at least three rounds of such tiles (a quarter fewer LDS and load
-//           instructions per MFMA than 128x128: 5 to 20 % on such layers; with fewer rounds the coarser tiles
-//           leave compute units idle at the end);
-//   256x256 (eight waves) for results at least 256 wide whose tiles fill whole rounds of the chip well enough;
-//   256x64  for results at most 64 wide with at least three rounds of such tiles: a wave then owns 128 x 32 and
-//           issues as many MFMAs per load as in the 128x128 tile (4 to 7 % on the 56x56 layers with 64 filters
-//           or channels).
-// The few-channels and scatter variants are built for 128 rows and 64 or 128 columns only.
-struct MainTile {
-    int bm, bn;
-};
-inline MainTile main_tile(const GemmConv& p) {
-    static const bool no_wide = getenv("LARSCONV_NO_WIDE_TILE") != nullptr;    // comparison runs
-    static const bool no_tall = getenv("LARSCONV_NO_TALL_TILE") != nullptr;
-    static const bool no_big = getenv("LARSCONV_NO_BIG_TILE") != nullptr;
-    MainTile t{128, p.N <= 64 ? 64 : 128};
-    if (!p.bf16 || p.Ci < 32 || p.scatter) return t;
-    if (p.N <= 64) {
-        if (!no_tall && (p.M + 255) / 256 >= 3LL * resident_blocks(256, 64)) t.bm = 256;
-        return t;
-    }
-    if (p.N >= 256 && !no_big) {
-        // 256x256, eight waves: half the operand bytes per MFMA through the vector-memory path and LDS of the 128x128 tile.
-        // Taken when its tiles fill the chip at least once and the last, partly filled round wastes less than the tile
-        // gains (measured over ResNet-50's layers at batch 512: results up to 512 wide gain 5 to 20 % from 70 % fill on;
-        // wider results only with at least 16 k-steps per tile and 85 % fill, otherwise the 128x256 tile is faster).
-        const long long tiles = (long long)((p.M + 255) / 256) * ((p.N + 255) / 256);
-        const long long res = resident_blocks(256, 256);
-        const long long rounds = (tiles + res - 1) / res;
-        const int nkt = (p.Kg + 31) / 32;
-        static const int fill_env = [] {
-            const char* e = getenv("LARSCONV_BIG_TILE_FILL");                  // comparison runs: another threshold
-            return e ? atoi(e) : 0;
-        }();
-        const int fill = fill_env ? fill_env : (p.N <= 512 ? 70 : 85);
-        if (tiles >= res && tiles * 100 >= rounds * res * fill && (fill_env || p.N <= 512 || nkt >= 16)) return MainTile{256, 256};
-    }
-    if (p.N >= 256 && !no_wide) {
-        const long long tiles = (long long)((p.M + 127) / 128) * ((p.N + 255) / 256);
-        if (tiles >= 3LL * resident_blocks(128, 256)) t.bn = 256;
-    }
-    return t;
-}
+inline int resident_blocks() { return kPkBlocksPerCu * device_cu_count(); }
 
 template <int BM, int BN>
 bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
@@ -1903,16 +1773,12 @@ bool sk_geometry(const GemmConv& p, long long* tiles, int* nkt) {
     return *tiles > 0 && *tiles * *nkt < 0x7fffffffLL;
 }
 
-// How the tiles beyond the whole rounds are shared out.  A 256x256 tile's partial sums are 256 KB per block and piece: writing and re-reading them
-// costs more than the idle end of the last round, which main_tile() has already bounded.  fp32 keeps the plain form: the order of a forward sum
-// decides its last bits.  bf16, 128x64 tiles: a lone block's k-step takes nearly as long as a 128x128 tile's, and a part costs the fix-up as much (with half
-// of both, tiles stayed whole that should be shared: 1x1 over 1248 channels to 29, 258 images of 20x20 54 -> 64 us; of 454 drawn
-// narrow layers 32 were more than 3 % behind the plain form, now 6, and the form chosen is 1.5 % off the best one in the mean).
+// How the tiles beyond the whole rounds are shared out.  fp32 keeps the plain form: the order of a forward sum decides its last bits.
 template <int BM, int BN>
 SkPlan main_sk_plan(const GemmConv& p, long long tiles, int nkt) {
-    if (BM * BN >= 256 * 256 || !p.bf16) return sk_plan(tiles, nkt, resident_blocks(BM, BN), BM * BN < 256 * 256);
+    if (!p.bf16) return sk_plan(tiles, nkt, resident_blocks());
     constexpr double size = BM * BN / 16384.0;
-    return sk_plan_by_cost(tiles, nkt, resident_blocks(BM, BN), StepCost{size < 1.0 ? 0.4 : 0.44 * size, 0.3 * size, size < 1.0 ? 1.0 : size, 8});
+    return sk_plan_by_cost(tiles, nkt, resident_blocks(), StepCost{size < 1.0 ? 0.4 : 0.44, 0.3 * size, 1.0, 8});
 }
 
 // Whether the uniform-tap variant of the main kernel takes this problem: k-steps that do not straddle taps,
@@ -1989,7 +1855,7 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     long long tiles;
     int nkt;
     if (!sk_geometry<BM, BN>(p, &tiles, &nkt)) return LC_ERR_UNSUPPORTED;
-    const int resident = resident_blocks(BM, BN);
+    const int resident = resident_blocks();
     SkPlan pl = main_sk_plan<BM, BN>(p, tiles, nkt);
     // persistent kernel: one round of resident blocks, each taking dp_tiles / grid whole tiles and then its
     // stream-K range; without a workspace for partial tiles the ranges are whole tiles
@@ -2007,37 +1873,18 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     magic_for(p.Qo, &p.qo_mul, &p.qo_shift);
     magic_for(p.Po, &p.po_mul, &p.po_shift);
     const unsigned grid = pl.dp_tiles > 0 ? (unsigned)resident : (unsigned)pl.sk_blocks;
-    const dim3 threads(2 * pk_waves_n(BM, BN) * 64);
+    const dim3 threads(256);
     const bool whole = pl.sk_blocks == 0 || pl.sk_iters == (long long)pl.sk_blocks * nkt;
     const bool ut = !SMALLC && uniform_tap_ok<BM, BN>(p);
-    if (p.scatter && p.stats) return LC_ERR_UNSUPPORTED;
-    if (p.scatter) {                          // the scatter epilogue addresses the result relative to the tile's first pixel
-        const long long span = ((long long)BM / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * (p.bf16 ? 2 : 4);
-        if (span >= 0x7fff0000LL || SMALLC || !BF16 || BN > 128 || BM > 128) return LC_ERR_UNSUPPORTED;   // (1x1 windows never have fewer channels than a k-step)
-        if constexpr (BF16 && BN <= 128 && BM <= 128) {
-            if (ut)
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, true>), dim3(grid), threads, 0, stream, p);
-            else
-                hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, false, true>), dim3(grid), threads, 0, stream, p);
-        }
-    } else if (ut) {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true, false>), dim3(grid), threads, 0, stream, p);
-    } else {
-        hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false, false>), dim3(grid), threads, 0, stream, p);
-    }
+    if (p.scatter) return LC_ERR_UNSUPPORTED;
+    if (ut) hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true>), dim3(grid), threads, 0, stream, p);
+    else hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false>), dim3(grid), threads, 0, stream, p);
     if (!whole) {
         if (!sk_ranges_meet(p, nkt))
             hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16, false>), dim3((unsigned)(tiles - pl.dp_tiles), 16), threads, 0, stream, p);
         else if (pl.sk_blocks > 1)
             hipLaunchKernelGGL((conv_gemm_fixup_kernel<BM, BN, BF16, true>), dim3((unsigned)pl.sk_blocks - 1, 16), threads, 0, stream, p);
-        if (p.stats) {
-            const dim3 sgrid((unsigned)(tiles - pl.dp_tiles), 2);
-            const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && (reinterpret_cast<uintptr_t>(p.d) & 15) == 0;
-            if (vec4)
-                hipLaunchKernelGGL((tile_stats_kernel<BF16, true>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
-            else
-                hipLaunchKernelGGL((tile_stats_kernel<BF16, false>), sgrid, dim3(256), 0, stream, p, BM, BN, pl.dp_tiles);
-        }
+        if (p.stats) lc_tile_stats(p, BM, BN, pl.dp_tiles, tiles, stream);
     }
     return lc_end_call();
 }
@@ -2048,8 +1895,8 @@ inline bool use_main_kernel(const GemmConv& p) {
         return e && strcmp(e, "classic") == 0;
     }();
     const bool vec = (p.Ci % (p.bf16 ? 8 : 4) == 0) && aligned16(p.a) && aligned16(p.b);
-    // (the scatter epilogue of the main kernel is not built for its few-channels variant)
-    const bool few_scatter = p.scatter && p.Ci < (p.bf16 ? 32 : 16);
+    // (the scatter form is for conv_dma.hip and conv_split.hip)
+    const bool few_scatter = p.scatter && (p.bf16 || p.Ci < 16);
     // (its tile store addresses a tile's rows with 32-bit byte offsets)
     const bool wide_rows = (long long)288 * p.ldd * (p.bf16 ? 2 : 4) >= 0x7fff0000LL;
     return vec && !(p.dh > 1 || p.dw > 1) && !(classic && !p.bf16) && !few_scatter && !wide_rows;
@@ -2057,18 +1904,61 @@ inline bool use_main_kernel(const GemmConv& p) {
 
 }  // namespace
 
-// Calls f.template operator()<BM, BN>() for the tile main_tile() picks.
+// The slab kernel's conditions: bf16, 3x3 window with stride 1 and padding 1 (so the output has the input's size),
+// whole 32-channel chunks, byte offsets that fit 31 bits, a slab of at most 512 pixels, and enough tiles to fill the chip
+// (below that the work split of conv_dma.hip is worth more).  At most 64 filters: there a tile of conv_dma.hip reads its pixels nine times for few products (64 to 64,
+// 512 images of 56x56: 174 us here, 189 there; 128 to 128 at 28x28 148 / 113).  Returns the LDS bytes of the launch in *lds.
+static bool slab_kernel_ok(const GemmConv& p, size_t* lds) {
+    static const bool off = getenv("LARSCONV_NO_SLAB") != nullptr;       // comparison runs
+    if (off || !p.bf16 || p.N > 64 || p.scatter || p.R != 3 || p.S != 3 || p.sh != 1 || p.sw != 1 || p.ph != 1 || p.pw != 1 || p.dh > 1 || p.dw > 1)
+        return false;
+    if (p.Po != p.Hi || p.Qo != p.Wi || p.Ci % 32 != 0 || p.Kg != 9 * p.Ci) return false;
+    if (!aligned16(p.a) || !aligned16(p.b) || (reinterpret_cast<uintptr_t>(p.d) & 3)) return false;
+    const long long hw = (long long)p.Hi * p.Wi;
+    if (p.M % hw != 0) return false;
+    if ((long long)p.M * p.Ci * 2 >= 0x7fff0000LL || (long long)p.N * 9 * p.Ci * 2 >= 0x7fff0000LL || (long long)288 * p.ldd * 2 >= 0x7fff0000LL)
+        return false;
+    // rows a tile's 128 consecutive pixels can span, the empty rows between the images it can touch, and the two halo rows
+    const long long rows = (128 + p.Wi - 2) / p.Wi + (128 + hw - 2) / hw + 3;
+    const long long px = rows * (p.Wi + 2);
+    if (px > (long long)kSlabMaxVec * 64) return false;
+    *lds = (size_t)2 * 64 * 64 + (size_t)px * kSlabPitch;
+    const char* e = getenv("LARSCONV_SLAB_MIN_TILES");                      // tests lower it to send small shapes here
+    const long long min_tiles = e ? atoll(e) : device_cu_count();
+    return (p.M + 127) / 128 >= min_tiles;
+}
+
+static lc_status launch_slab(const GemmConv& p, size_t lds, hipStream_t stream) {
+    constexpr int BN = 64;
+    static bool once = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(conv3x3_slab_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   2 * BN * 64 + kSlabMaxVec * 64 * kSlabPitch) == hipSuccess;
+    }();
+    if (!once) return LC_ERR_LAUNCH;
+    const long long tiles = (p.M + 127) / 128;
+    hipLaunchKernelGGL((conv3x3_slab_kernel), dim3((unsigned)tiles), dim3(256), lds, stream, p);
+    return lc_end_call();
+}
+
+void lc_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, long long tiles, hipStream_t stream) {
+    const dim3 grid((unsigned)(tiles - first_tile), 2);
+    const bool vec4 = p.N % 4 == 0 && p.ldd % 4 == 0 && aligned16(p.d);
+    auto kernel = p.bf16 ? (vec4 ? tile_stats_kernel<true, true> : tile_stats_kernel<true, false>)
+                         : (vec4 ? tile_stats_kernel<false, true> : tile_stats_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, bm, bn, first_tile);
+}
+
+// Calls f.template operator()<BM, BN>() for the main kernel's tile.
 template <typename F>
 auto with_main_tile(const GemmConv& p, F&& f) {
-    const MainTile t = main_tile(p);
-    if (t.bm == 256 && t.bn == 256) return f.template operator()<256, 256>();
-    if (t.bm == 256) return f.template operator()<256, 64>();
-    if (t.bn == 256) return f.template operator()<128, 256>();
-    if (t.bn == 128) return f.template operator()<128, 128>();
+    if (p.N > 64) return f.template operator()<128, 128>();
     return f.template operator()<128, 64>();
 }
 
 size_t lc_conv_gemm_workspace(const GemmConv& p) {
+    size_t lds;
+    if (slab_kernel_ok(p, &lds)) return 0;
+    if (lc_conv_dma_ok(p)) return lc_conv_dma_workspace(p);
     if (!use_main_kernel(p)) return 0;
     if (p.split) return lc_conv_split_workspace(p);
     return with_main_tile(p, [&]<int BM, int BN>() -> size_t {
@@ -2081,96 +1971,35 @@ size_t lc_conv_gemm_workspace(const GemmConv& p) {
     });
 }
 
-bool lc_conv_gemm_bf16_native(const GemmConv& p) { return p.bf16 && use_main_kernel(p); }
+bool lc_conv_gemm_bf16_native(const GemmConv& p) { return p.bf16 && (lc_conv_dma_ok(p) || use_main_kernel(p)); }
 
 bool lc_conv_gemm_scatter_ok(const GemmConv& p) {
-    if (!p.scatter || !use_main_kernel(p) || p.Ci < (p.bf16 ? 32 : 16)) return false;
+    if (p.scatter && p.bf16) return lc_conv_dma_ok(p);
+    if (!p.scatter || !use_main_kernel(p) || p.Ci < 16) return false;
     // (the scatter epilogue addresses the result relative to the tile's first pixel with 32-bit byte offsets)
     const long long span = (128LL / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * (p.bf16 ? 2 : 4);
     return span < 0x7fff0000LL;
 }
 
-// The slab kernel's conditions: bf16, 3x3 window with stride 1 and padding 1 (so the output has the input's size),
-// whole 32-channel chunks, byte offsets that fit 31 bits, a slab of at most 512 pixels, and enough tiles to fill the chip
-// (below that the main kernel's stream-K split is worth more).  Returns the LDS bytes of the launch in *lds.
-static bool slab_kernel_ok(const GemmConv& p, int bn, size_t* lds) {
-    static const bool off = getenv("LARSCONV_NO_SLAB") != nullptr;       // comparison runs
-    if (off || !p.bf16 || p.scatter || p.R != 3 || p.S != 3 || p.sh != 1 || p.sw != 1 || p.ph != 1 || p.pw != 1 || p.dh > 1 || p.dw > 1)
-        return false;
-    if (p.Po != p.Hi || p.Qo != p.Wi || p.Ci % 32 != 0 || p.Kg != 9 * p.Ci) return false;
-    if (!aligned16(p.a) || !aligned16(p.b) || (reinterpret_cast<uintptr_t>(p.d) & 3)) return false;
-    const long long hw = (long long)p.Hi * p.Wi;
-    if (p.M % hw != 0) return false;
-    if ((long long)p.M * p.Ci * 2 >= 0x7fff0000LL || (long long)p.N * 9 * p.Ci * 2 >= 0x7fff0000LL || (long long)288 * p.ldd * 2 >= 0x7fff0000LL)
-        return false;
-    // rows a tile's 128 consecutive pixels can span, the empty rows between the images it can touch, and the two halo rows
-    const long long rows = (128 + p.Wi - 2) / p.Wi + (128 + hw - 2) / hw + 3;
-    const long long px = rows * (p.Wi + 2);
-    if (px > (long long)kSlabMaxVec * 64) return false;
-    *lds = (size_t)2 * bn * 64 + (size_t)px * kSlabPitch;
-    const char* e = getenv("LARSCONV_SLAB_MIN_TILES");                      // tests lower it to send small shapes here
-    const long long min_tiles = e ? atoll(e) : device_cu_count();
-    const long long tiles = (long long)((p.M + 127) / 128) * ((p.N + bn - 1) / bn);
-    if (tiles < min_tiles) return false;
-    // where the main kernel runs its 256x256 tile (half the filter bytes per MFMA as well) it measures 4-6 % faster
-    const MainTile t = main_tile(p);
-    return e != nullptr || !(t.bm == 256 && t.bn == 256);
-}
-
-template <int BN>
-static lc_status launch_slab(const GemmConv& p, size_t lds, hipStream_t stream) {
-    static bool once = [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(conv3x3_slab_kernel<BN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   2 * BN * 64 + kSlabMaxVec * 64 * kSlabPitch) == hipSuccess;
-    }();
-    if (!once) return LC_ERR_LAUNCH;
-    const long long tiles = (long long)((p.M + 127) / 128) * ((p.N + BN - 1) / BN);
-    hipLaunchKernelGGL((conv3x3_slab_kernel<BN>), dim3((unsigned)tiles), dim3(256), lds, stream, p);
-    return lc_end_call();
-}
-
-// The tile the main kernel runs a problem with (0 x 0: another kernel takes it); mirrors lc_launch_conv_gemm.
-static void main_kernel_tile(const GemmConv& p, int* bm, int* bn) {
-    *bm = *bn = 0;
-    size_t lds;
-    if (p.bf16 && slab_kernel_ok(p, p.N > 64 ? 128 : 64, &lds)) {       // the slab kernel: 128 rows
-        *bm = 128;
-        *bn = p.N > 64 ? 128 : 64;
-        return;
-    }
-    if (!use_main_kernel(p) || p.scatter) return;
-    if (p.bf16) {
-        if (p.Ci < 32) {
-            *bm = 128;
-            *bn = p.N > 64 ? 128 : 64;
-        } else {
-            const MainTile t = main_tile(p);
-            *bm = t.bm;
-            *bn = t.bn;
-        }
-        return;
-    }
-    *bm = 128;
-    *bn = p.N > 64 ? 128 : 64;
-}
-
+// Row pieces of the statistics: half a tile of the kernel that takes the problem (mirrors lc_launch_conv_gemm).
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
-    int bm, bn;
-    main_kernel_tile(p, &bm, &bn);
-    return bm ? (size_t)2 * ((p.M + bm - 1) / bm) : 0;
+    size_t lds;
+    if (!slab_kernel_ok(p, &lds)) {
+        if (lc_conv_dma_ok(p)) return p.scatter ? 0 : lc_conv_dma_stats_tiles(p);
+        if (!use_main_kernel(p) || p.scatter) return 0;
+    }
+    return (size_t)2 * ((p.M + 127) / 128);
 }
 
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
     if (p.stats && lc_conv_gemm_stats_tiles(p) == 0) return LC_ERR_UNSUPPORTED;
     if (p.bf16) {
         size_t lds;
-        const int bn = p.N > 64 ? 128 : 64;
-        if (slab_kernel_ok(p, bn, &lds)) return bn == 128 ? launch_slab<128>(p, lds, stream) : launch_slab<64>(p, lds, stream);
-    }
-    if (p.bf16) {
+        if (slab_kernel_ok(p, &lds)) return launch_slab(p, lds, stream);
+        if (lc_conv_dma_ok(p)) return lc_launch_conv_dma(p, stream);
         if (!use_main_kernel(p)) return LC_ERR_UNSUPPORTED;       // the caller converts to fp32 instead
         if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
-        return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false, true>(p, stream); });
+        return p.N > 64 ? launch_conv_sk<128, 128, false, true>(p, stream) : launch_conv_sk<128, 64, false, true>(p, stream);
     }
     const bool vec = (p.Ci % 4 == 0) && aligned16(p.a) && aligned16(p.b);
     if (!vec) return launch_conv<64, 64, 16, 1>(p, stream);

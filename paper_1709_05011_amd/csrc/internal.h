@@ -105,6 +105,13 @@ bool lc_conv_gemm_scatter_ok(const GemmConv& p);    // can the main kernel's sca
 // fp32 backward-data on the bf16 matrix pipe (conv_split.hip), and the partial-tile bytes they need
 lc_status lc_launch_conv_split(GemmConv p, hipStream_t stream);
 size_t lc_conv_split_workspace(const GemmConv& p);
+// bf16 operands straight into LDS (conv_dma.hip): whether the kernel takes a problem, partial-tile bytes, row pieces of `stats`
+bool lc_conv_dma_ok(const GemmConv& p);
+size_t lc_conv_dma_workspace(const GemmConv& p);
+size_t lc_conv_dma_stats_tiles(const GemmConv& p);
+lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream);
+// the column sums of the tiles first_tile .. tiles - 1 of bm x bn, read back from p.d (conv_igemm.hip)
+void lc_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, long long tiles, hipStream_t stream);
 size_t lc_conv_gemm_workspace(const GemmConv& p);   // bytes `partial` must hold for this problem (0 = none)
 
 // ResNet's first layer in fp32 (conv_stem.hip): 7x7, stride 2, padding 3, 3 -> 64 channels, NHWC, P and Q multiples of 16.
