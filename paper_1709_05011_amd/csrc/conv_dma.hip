@@ -67,9 +67,9 @@ __device__ __forceinline__ float sum_of_16(float x) {
     return x;
 }
 
-// What leaves with a tile: whole 16-byte pieces of rows (columns a multiple of 8); the same and the statistics, any number of columns; any number of columns, or
-// the pixels of a stride grid.
-enum ConvDmaOut { kRows, kStats, kAny };
+// What leaves with a tile: whole 16-byte pieces of rows (columns a multiple of 8); any number of columns and the statistics; any number of columns; the pixels
+// of a stride grid.
+enum ConvDmaOut { kRows, kStats, kAny, kGrid };
 enum ConvDmaIn { kChunks, kPadded, kPieces };
 
 template <int TMA, int TMB, int TN, int WN, ConvDmaIn IN, ConvDmaOut OUT>
@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             // or have bit 31 of the offset set, columns past N the latter.
             constexpr int CPR = TN * 2, RPI = 64 / CPR;    // lanes per row, rows per store
             const int mw = m0 + row0, lr = lane / CPR, col = n0 + wn * TN * 16 + lane % CPR * 8;
-            const bool scatter = OUT == kAny && p.scatter != 0;
+            constexpr bool scatter = OUT == kGrid;
             long long first_px = mw;
             if (scatter) {
                 const int t0 = div_by(mw, qmul, qsh), i0 = div_by(t0, pmul, psh);
@@ -250,6 +250,14 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             const __amdgpu_buffer_rsrc_t d_rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 (void*)(static_cast<uint16_t*>(p.d) + first_px * ldd_), 0, (int)(left > 0x7fffffffLL ? 0x7fffffffLL : left > 0 ? left : 0), (int)kBufferWords3);
             const unsigned d_voff = col < N_ ? (unsigned)(lr * ldd_ + col) * 2u : kBufferBytes;
+            auto row_off = [&](int m) __attribute__((always_inline)) {       // byte offset of a row of the result; bit 31 past M
+                int px = m - mw;
+                if (scatter) {
+                    const int t = div_by(m, qmul, qsh), img = div_by(t, pmul, psh);
+                    px = (int)(((long long)img * p.Ho + (t - img * Po_) * p.esh) * p.Wo + (m - t * Qo_) * p.esw - first_px);
+                }
+                return m < M_ ? (unsigned)(px * ldd_) * 2u : kBufferBytes;
+            };
             float sum[TN][4], sq[TN][4];
             constexpr bool stats = OUT == kStats;
 #pragma unroll
@@ -273,33 +281,45 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
                     }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-                u32x4 out[16 / RPI];
+                if (whole_rows) {
+                    u32x4 out[16 / RPI];
 #pragma unroll
-                for (int e = 0; e < 16 / RPI; ++e) out[e] = *reinterpret_cast<const u32x4*>(mine + (e * RPI + lr) * kOutPitch + lane % CPR * 16);
-                asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-                if (OUT == kRows || (whole_rows & !scatter)) {
-#pragma unroll
-                    for (int e = 0; e < 16 / RPI; ++e)
-                        __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
-                } else {
+                    for (int e = 0; e < 16 / RPI; ++e) out[e] = *reinterpret_cast<const u32x4*>(mine + (e * RPI + lr) * kOutPitch + lane % CPR * 16);
+                    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
 #pragma unroll
                     for (int e = 0; e < 16 / RPI; ++e) {
-                        const int m = mw + i * 16 + e * RPI + lr;
-                        int px = m - mw;
-                        if (scatter) {
-                            const int t = div_by(m, qmul, qsh), img = div_by(t, pmul, psh);
-                            px = (int)(((long long)img * p.Ho + (t - img * Po_) * p.esh) * p.Wo + (m - t * Qo_) * p.esw - first_px);
-                        }
-                        const unsigned off = m < M_ ? (unsigned)(px * ldd_ + col) * 2u : kBufferBytes;
-                        if (whole_rows) {
-                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off : kBufferBytes), 0, 0);
+                        if constexpr (!scatter) {
+                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
                         } else {
-#pragma unroll
-                            for (int v = 0; v < 8; ++v)
-                                __builtin_amdgcn_raw_buffer_store_b16((short)(out[e][v >> 1] >> (16 * (v & 1))), d_rsrc,
-                                                                      (int)(col + v < N_ ? off : kBufferBytes), v * 2, 0);
+                            const unsigned off = row_off(mw + i * 16 + e * RPI + lr);
+                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, 0);
                         }
                     }
+                } else {
+                    // rows that start anywhere: neighbouring lanes store neighbouring columns, in pairs where there is an even number of them
+                    // (a loop: unrolled, the two forms for every row of pieces are more code than the instruction cache holds)
+                    auto store = [&](auto pair) __attribute__((always_inline)) {
+                        constexpr int V = decltype(pair)::value, PER = TN * 16 / V, RWS = 64 / PER;      // columns per lane; lanes per row, rows per store
+                        const int c = lane % PER * V, cc = n0 + wn * TN * 16 + c;
+                        const unsigned char* q = mine + lane / PER * kOutPitch + c * 2;
+                        const unsigned voff = cc < N_ ? (unsigned)(lane / PER * ldd_ + cc) * 2u : kBufferBytes;
+                        int so = i * 16 * ldd_ * 2;
+#pragma unroll 4
+                        for (int e = 0; e < 16 / RWS; ++e) {
+                            const unsigned v = V == 2 ? *reinterpret_cast<const unsigned*>(q) : *reinterpret_cast<const unsigned short*>(q);
+                            int o = (int)voff, at = so;
+                            if constexpr (OUT == kGrid) {
+                                o = (int)(cc < N_ ? row_off(mw + i * 16 + e * RWS + lane / PER) + (unsigned)cc * 2u : kBufferBytes);
+                                at = 0;
+                            }
+                            if constexpr (V == 2) __builtin_amdgcn_raw_buffer_store_b32(v, d_rsrc, o, at, 0);
+                            else __builtin_amdgcn_raw_buffer_store_b16((short)v, d_rsrc, o, at, 0);
+                            q += RWS * kOutPitch;
+                            so += RWS * ldd_ * 2;
+                        }
+                    };
+                    if (((N_ | ldd_) & 1) == 0) store(std::integral_constant<int, 2>{});
+                    else store(std::integral_constant<int, 1>{});
                 }
             }
             if (stats) {                                   // the 16 lanes of a group hold the sums of a piece's pixels
@@ -449,8 +469,9 @@ struct ConvTile {
     int bm, bn, per_cu;
     float alone, shared, tile;
 };
-constexpr int kWide = 0, kSquare = 1, kNarrow = 2, kNarrowTwoWaves = 3;
+constexpr int kWide = 0, kSquare = 1, kNarrow = 2, kNarrowTwoWaves = 3, kSlim = 4, kOtherRows = 5;
 constexpr ConvTile kConvTiles[] = {{256, 256, 1, 1.4f, 1.065f, 1.9f}, {128, 128, 2, 0.41f, 0.2f, 0.8f}, {128, 64, 3, 0.355f, 0.181f, 0.7f}, {128, 64, 3, 0.545f, 0.17f, 0.62f},
+                                   {128, 32, 3, 0.36f, 0.115f, 0.45f},
                                    {240, 256, 1, 1.2f, 1.0f, 2.2f},   {224, 256, 1, 1.1f, 0.915f, 2.05f}, {208, 256, 1, 0.88f, 0.86f, 2.2f}, {192, 256, 1, 0.72f, 0.8f, 2.2f}};
 
 struct ConvDmaPlan {
@@ -461,10 +482,10 @@ struct ConvDmaPlan {
 };
 
 // Tile and work split by cost, in us: rounds of whole tiles, then the rest whole to one block each, to S blocks each in equal parts, or end to end over the resident
-// blocks; shared tiles cost the fix-up's launch and their parts.  Memory (4.2 MB per us) and what the tiles read from the L2s (15 MB) are taken in by the
+// blocks; shared tiles cost the fix-up's launch, each of a tile's parts in its turn, and what the parts move.  Memory (4.2 MB per us) and what the tiles read from the L2s (15 MB) are taken in by the
 // fourth-power mean, since none hides behind another entirely.  Fitted to 178 layers of 1 to 512 images, forward, every tile with up to nine splits: the choice is 1.7 %
 // off the best in the mean, 6 % or more in one of ten, and 1.3 times as fast in the mean as the kernels with staging registers that took these layers before
-// (3x3 over 256 channels, 512 images of 14x14: 147 -> 106 us).
+// (3x3 over 256 channels, 512 images of 14x14: 147 -> 106 us).  Results of at most 32 columns have a tile of their own (64 to 32 1x1, 512 images of 56x56: 61 us, 83 with 64 columns).
 // Row counts other than 128 and 256 fill the rounds of wide results (that layer has 392 tiles of 256 rows: two rounds for one and a half; 483 of 208: 116 -> 106).  They
 // replace a tile that no blocks share, where every sum is the same: so the result does not depend on whether statistics, which come in pieces of 64 or 128 rows, are wanted.
 bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
@@ -490,12 +511,9 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
                 float r = std::max((float)steps * t.alone + t.tile, turns * ((float)steps * t.shared + t.tile));
                 if (!even) r *= 1.15f;                     // (unequal parts: blocks no longer read the same rows together)
                 us += r;
-                if (blocks != rest) us += 5.f + 0.021f * (float)blocks * (float)(t.bm * t.bn) / 16384.f;
+                if (blocks != rest) us += 3.2f + 0.35f * (float)((blocks + rest - 1) / rest) + 0.016f * (float)blocks * (float)(t.bm * t.bn) / 16384.f;
             }
             us = sqrtf(sqrtf(fourth(us) + others));
-            // (a last round of narrow tiles on fewer than half of the compute units also leaves memory idle: 1x1 over 1248 channels to 29 or 32, 258 images of 20x20
-            // 50.5 and 47.2 us, with the last 39 tiles shared out 49.7 and 46.4; square ones 109 / 112: 512 to 128, 512 images of 28x28)
-            if (t.bn == 64 && whole > 0.f && blocks == rest && 2 * rest < cus) us *= 1.01f;
             if (us < best) {
                 best = us;
                 out->tile = i;
@@ -506,7 +524,7 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
             }
         };
         consider(rest ? rest : 1, true);
-        if (rest == 0 || i == kWide || i > kNarrowTwoWaves) return;
+        if (rest == 0 || i == kWide || i >= kOtherRows) return;
         for (int s = 2; s <= 16 && rest * s <= resident && nkt >= 2 * s; s += s < 4 ? 1 : s < 8 ? 2 : 4) consider(rest * s, true);
         const int all = (int)std::min<long long>(resident, (long long)rest * nkt / 2);
         if (all > rest) consider(all, false);
@@ -515,9 +533,10 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
     if (p.N > 64) tile_cost(kSquare);
     tile_cost(kNarrow);
     tile_cost(kNarrowTwoWaves);
+    if (p.N <= 32) tile_cost(kSlim);
     if (best >= 1e30f) return false;
     if (any_rows && p.N > 128 && rows && out->sk.sk_iters == (long long)out->sk.sk_blocks * nkt)
-        for (int i = kNarrowTwoWaves + 1; i < (int)(sizeof(kConvTiles) / sizeof(kConvTiles[0])); ++i) tile_cost(i);
+        for (int i = kOtherRows; i < (int)(sizeof(kConvTiles) / sizeof(kConvTiles[0])); ++i) tile_cost(i);
     return true;
 }
 bool conv_dma_shares(const ConvDmaPlan& c) { return c.sk.sk_iters != (long long)c.sk.sk_blocks * c.nkt; }
@@ -559,7 +578,8 @@ lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_
             if (p.stats) return launch.template operator()<IN, kStats>();
         }
         if constexpr (WN != 4) {
-            if (p.scatter || ((p.N | p.ldd) & 7) != 0) return launch.template operator()<IN, kAny>();
+            if (p.scatter) return launch.template operator()<IN, kGrid>();
+            if (((p.N | p.ldd) & 7) != 0) return launch.template operator()<IN, kAny>();
         }
         launch.template operator()<IN, kRows>();
     };
@@ -913,10 +933,11 @@ lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream) {
         case kSquare: st = go.template operator()<4, 4, 4, 2>(); break;
         case kNarrow: st = go.template operator()<4, 4, 2, 2>(); break;
         case kNarrowTwoWaves: st = go.template operator()<4, 4, 4, 1>(); break;
-        case 4: st = go.template operator()<8, 7, 4, 4>(); break;
-        case 5: st = go.template operator()<7, 7, 4, 4>(); break;
-        case 6: st = go.template operator()<7, 6, 4, 4>(); break;
-        case 7: st = go.template operator()<6, 6, 4, 4>(); break;
+        case kSlim: st = go.template operator()<4, 4, 2, 1>(); break;
+        case kOtherRows: st = go.template operator()<8, 7, 4, 4>(); break;
+        case kOtherRows + 1: st = go.template operator()<7, 7, 4, 4>(); break;
+        case kOtherRows + 2: st = go.template operator()<7, 6, 4, 4>(); break;
+        case kOtherRows + 3: st = go.template operator()<6, 6, 4, 4>(); break;
     }
     if (st == LC_OK && p.stats && conv_dma_shares(c) && p.partial) {
         lc_tile_stats(p, kConvTiles[c.tile].bm, kConvTiles[c.tile].bn, c.sk.dp_tiles, c.tiles, stream);
@@ -955,6 +976,7 @@ bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits) {
             const int stages = ((p.M + s - 1) / s + 31) / 32;
             if (t.bm * t.bn == 256 * 256 && stages > chain + chain / 8) return;      // (it has no second set of sums)
             const float steps = (float)stages, blocks = (float)(tiles * s), turns = (float)((tiles * s + cus - 1) / cus);
+            if (steps * t.alone >= best || turns * steps * t.shared >= best) return;
             float us = sqrtf(sqrtf(fourth(steps * t.alone) + fourth(turns * steps * t.shared) + fourth(operands / std::min(3.85f, 0.167f * blocks)) +
                                    fourth(blocks * steps * read)));
             if (s > 1) us += 3.1f + 0.3f * mb * (float)s;

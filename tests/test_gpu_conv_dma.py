@@ -1,5 +1,5 @@
 """GPU parity of the bf16 forward / backward-data kernel whose operands go from memory straight into LDS: every tile it is built for (192 to 256 rows of wide
-results, 128x128, 128x64 with four and with two waves), channels that are multiples of 64, nearly so (filled up with zeros) and any multiple of 8, tiles taken
+results, 128x128, 128x64 with four and with two waves, 128x32), channels that are multiples of 64, nearly so (filled up with zeros) and any multiple of 8, tiles taken
 whole and shared by blocks, filter counts that are no multiple of 8, and the stride grids of strided layers.  Against float64 on the same bf16 operands.  Bound
 per element: one rounding to bf16 (2^-8 of the value, in which the fp32 sum on the other side of a rounding boundary is included) and the fp32
 sums, a rounding every eight terms and the additions of parts, 2^-23 of the sum of magnitudes apiece."""
@@ -34,7 +34,8 @@ SHAPES = [
     (7, 208, 5, 16, 3, 1),
     (2, 128, 5, 16, 3, 1),
     (62, 8, 26, 40, 1, 1),         # two waves
-    (57, 64, 24, 16, 1, 1),
+    (57, 64, 24, 16, 1, 1),        # 128x32
+    (40, 32, 31, 32, 3, 1),
     (112, 544, 30, 56, 1, 1),
     (3, 64, 1, 1000, 1, 1),        # a fully connected layer of a few rows
     (5, 72, 9, 33, 3, 1),          # filter counts off the vector stores
@@ -44,6 +45,8 @@ SHAPES = [
     (5, 72, 11, 40, 3, 2),
     (3, 16, 12, 264, 3, 2),
     (2, 256, 9, 8, 5, 3),
+    (4, 37, 10, 64, 1, 2),         # stride grids of odd and of even counts of channels
+    (3, 38, 9, 64, 3, 2),
 ]
 
 
