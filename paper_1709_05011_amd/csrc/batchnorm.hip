@@ -419,12 +419,36 @@ __global__ void __launch_bounds__(kThreads) bn_fold_pieces_kernel(const float* _
 // each, so that loads overlap), then the first lane adds the 64 lane sums in lane order.  Returns true in the thread
 // that holds the channel's totals.  Few channels per block: the layers with 64 channels still start 16 blocks.
 constexpr int kFinChannels = 4, kFinLanes = 64;
-__device__ __forceinline__ bool channel_totals(const BnWorkspace& ws, const BnGeom& g, int* ch_out, double* t0, double* t1) {
+// PIECES: straight from the fp32 pieces of a convolution's statistics; the sums are bn_fold_pieces_kernel's and then the same, in the same order, bit for bit.
+template <bool PIECES>
+__device__ __forceinline__ bool channel_totals(const BnWorkspace& ws, const float* pieces, int n_pieces, const BnGeom& g, int* ch_out, double* t0, double* t1) {
     __shared__ double red[kFinLanes][kFinChannels][2];
     const int cl = threadIdx.x % kFinChannels, sl = threadIdx.x / kFinChannels;
     const int ch = blockIdx.x * kFinChannels + cl;
     double s0 = 0.0, s1 = 0.0, u0 = 0.0, u1 = 0.0;
-    if (ch < g.C) {
+    if (PIECES && ch < g.C) {
+        const float2* part = reinterpret_cast<const float2*>(pieces) + ch;
+        const int slabs = min(g.slabs, n_pieces);
+        for (int k = sl; k < slabs; k += 8 * kFinLanes) {
+            float2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k + u * kFinLanes < slabs ? part[(size_t)(k + u * kFinLanes) * g.C] : make_float2(0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                double x0 = (double)v[u].x, x1 = (double)v[u].y, y0 = 0.0, y1 = 0.0;      // the slab's pieces, every other one by itself
+                if (n_pieces > g.slabs) {
+                    bool odd = true;
+                    for (int t = k + u * kFinLanes + g.slabs; k + u * kFinLanes < slabs && t < n_pieces; t += g.slabs, odd = !odd) {
+                        const float2 w = part[(size_t)t * g.C];
+                        if (odd) { y0 += (double)w.x; y1 += (double)w.y; }
+                        else { x0 += (double)w.x; x1 += (double)w.y; }
+                    }
+                }
+                if (u & 1) { u0 += x0 + y0; u1 += x1 + y1; }
+                else { s0 += x0 + y0; s1 += x1 + y1; }
+            }
+        }
+    } else if (ch < g.C) {
         const double2* part = reinterpret_cast<const double2*>(ws.partial);
         int k = sl;
         for (; k + kFinLanes < g.slabs; k += 2 * kFinLanes) {
@@ -461,14 +485,17 @@ struct BnSecond {
     const float* inv_std = nullptr;
 };
 
-template <typename T>
+// A launch less for layers of few pieces: ResNet-50's layers at 32 images have 25 to 1568, and folding them was 5 us of launch each.  Beyond kFusedPieces the
+// fold's many blocks read faster than these few.
+constexpr int kFusedPieces = 2048;
+template <typename T, bool PIECES>
 __global__ void __launch_bounds__(kFinChannels* kFinLanes)
-bn_finalize_fwd_kernel(BnWorkspace ws, const T* __restrict__ x, size_t pivot_stride, const float* __restrict__ gamma,
+bn_finalize_fwd_kernel(BnWorkspace ws, const float* __restrict__ pieces, int n_pieces, const T* __restrict__ x, size_t pivot_stride, const float* __restrict__ gamma,
                        const float* __restrict__ beta, float* __restrict__ save_mean, float* __restrict__ save_invstd, BnGeom g, float eps,
                        BnSecond second) {
     int ch;
     double s0, s1;
-    if (!channel_totals(ws, g, &ch, &s0, &s1)) return;
+    if (!channel_totals<PIECES>(ws, pieces, n_pieces, g, &ch, &s0, &s1)) return;
     const double m = (double)g.M;
     const double off = s0 / m;                                  // mean of x - pivot
     const double mean = (x ? (double)widen<T>(x[ch * pivot_stride]) : 0.0) + off;      // x null: plain sums, no pivot
@@ -497,7 +524,7 @@ bn_finalize_bwd_kernel(BnWorkspace ws, const float* __restrict__ gamma, const fl
                        const float* __restrict__ inv_std, float* __restrict__ dgamma, float* __restrict__ dbeta, BnGeom g) {
     int ch;
     double s0, s1;
-    if (!channel_totals(ws, g, &ch, &s0, &s1)) return;
+    if (!channel_totals<false>(ws, nullptr, 0, g, &ch, &s0, &s1)) return;
     dbeta[ch] = (float)s0;
     dgamma[ch] = (float)s1;
     const double m = (double)g.M, is = (double)inv_std[ch], mu = (double)mean[ch];
@@ -643,16 +670,19 @@ lc_status bn_fwd_impl(const T* x, const float* gamma, const float* beta, const T
     } while (0)
 #define LC_BN_FWD(VEC)                                                                                                                  \
     do {                                                                                                                                \
-        if (stats) {                                                                                                                    \
+        if (stats && stats_tiles <= (size_t)kFusedPieces) {                                                                             \
+            hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, true>), fin_grid, fin_block, 0, stream, ws, stats, (int)stats_tiles, none,    \
+                               pivot_stride, gamma, beta, save_mean, save_invstd, g, eps, second);                                      \
+        } else if (stats) {                                                                                                             \
             hipLaunchKernelGGL(bn_fold_pieces_kernel, dim3((unsigned)g.slabs, (unsigned)((2 * c + kThreads - 1) / kThreads)),           \
                                dim3(kThreads), 0, stream, stats, (int)stats_tiles, ws.partial, g.slabs, 2 * c);                         \
-            hipLaunchKernelGGL(bn_finalize_fwd_kernel<T>, fin_grid, fin_block, 0, stream, ws, none, pivot_stride, gamma, beta,          \
-                               save_mean, save_invstd, g, eps, second);                                                                 \
+            hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, false>), fin_grid, fin_block, 0, stream, ws, nonef, 0, none, pivot_stride,    \
+                               gamma, beta, save_mean, save_invstd, g, eps, second);                                                    \
         } else {                                                                                                                        \
             hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, kStats>), grid, dim3(kThreads), 0, stream, x, none, nonef, nonef, nonef,  \
                                nonef, g, ws);                                                                                           \
-            hipLaunchKernelGGL(bn_finalize_fwd_kernel<T>, fin_grid, fin_block, 0, stream, ws, x, pivot_stride, gamma, beta, save_mean,  \
-                               save_invstd, g, eps, second);                                                                            \
+            hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, false>), fin_grid, fin_block, 0, stream, ws, nonef, 0, x, pivot_stride,       \
+                               gamma, beta, save_mean, save_invstd, g, eps, second);                                                    \
         }                                                                                                                               \
         if (stats_only) break;                                                                                                          \
         if (two) { if (clamp) LC_BN_APPLY(VEC, true, true); else LC_BN_APPLY(VEC, true, false); }                                       \
@@ -669,7 +699,7 @@ lc_status bn_fwd_impl(const T* x, const float* gamma, const float* beta, const T
         if constexpr (kF32) {
             hipLaunchKernelGGL((bn_reduce_nchw_kernel<kStats>), dim3((unsigned)g.slabs, (unsigned)c), dim3(kThreads), 0, stream, x, none, nonef,
                                nonef, nonef, nonef, g, ws);
-            hipLaunchKernelGGL(bn_finalize_fwd_kernel<T>, fin_grid, fin_block, 0, stream, ws, x, pivot_stride, gamma, beta, save_mean,
+            hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, false>), fin_grid, fin_block, 0, stream, ws, nonef, 0, x, pivot_stride, gamma, beta, save_mean,
                                save_invstd, g, eps, second);
             const dim3 agrid(stream_blocks(total));
 #define LC_BN_APPLY(TWO, RELU) \
