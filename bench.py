@@ -39,15 +39,14 @@ LARS_BYTES_PER_PARAM = 28  # norm pass reads w, g (8 B); update reads w, g, v an
 # parsed from the tracked rocprofv3 summaries (two --pmc runs, FETCH_SIZE then WRITE_SIZE, scaled by what the same
 # counters read for a 1 GiB copy; the commands are in the files).  None when the file or the kernel's row is missing.
 TRAFFIC_PROFILES = {("resnet50", "f32"): "resnet50_step_fp32_b256_hbm_traffic_and_mfma.txt",
-                    ("alexnet_bn", "f32"): "alexnet_bn_step_fp32_b256_kernel_trace.txt",
-                    ("resnet50", "bf16"): "resnet50_step_bf16_b512_kernel_trace.txt"}
+                    ("alexnet_bn", "f32"): "alexnet_bn_step_fp32_b256_kernel_trace.txt"}
 TRAFFIC_BATCH = {"f32": 256, "bf16": 512}
 
 
-def kernel_instance_name(label: str, bf16: bool) -> str:
-    """Name rocprofv3 prints for the main-kernel instance behind one of this file's labels (conv_gemm_128x128 ...)."""
+def kernel_instance_name(label: str) -> str:
+    """What rocprofv3's names of the fp32 main-kernel instance behind one of this file's labels (conv_gemm_128x128 ...) begin with."""
     bm, bn = label.rsplit("_", 1)[1].split("x")
-    return f"conv_gemm_pk_kernel<{bm}, {bn}, false, {'true' if bf16 else 'false'}, true, false>"
+    return f"conv_gemm_pk_kernel<{bm}, {bn}, false, false, true"
 
 
 def profile_traffic(model: str, dtype: str, label: str, batch: int):
@@ -58,7 +57,7 @@ def profile_traffic(model: str, dtype: str, label: str, batch: int):
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
-    want = kernel_instance_name(label, dtype == "bf16")
+    want = kernel_instance_name(label)
     section, found = None, {}
     for line in open(path):
         head = line.strip()
@@ -202,28 +201,13 @@ def run_train_step(args):
             return "conv_split_128x64" if n_gemm <= 64 else "conv_split_128x128"
         k_gemm = cs.c if pass_ == "fwd" else cs.k
         rows = cs.n * cs.p * cs.q if pass_ == "fwd" or cs.stride > 1 else cs.n * cs.h * cs.w
-        scatter = pass_ == "bwd_data" and cs.stride > 1
-        # bf16 has two more tiles, each taken with three or more rounds of such tiles (and not by the strided 1x1
-        # backward-data layers, whose scatter epilogue exists for the 128-row tiles of 64 and 128 columns only)
-        special = bf16 and k_gemm >= 32 and not scatter
-        big = False
-        if special and n_gemm >= 256:
-            tiles = -(-rows // 256) * -(-n_gemm // 256)            # 256x256 (eight waves): one block per compute unit
-            rounds = -(-tiles // 256)
-            nkt = -(-(k_gemm * cs.r * cs.s) // 32)
-            fill = 70 if n_gemm <= 512 else 85
-            big = tiles >= 256 and tiles * 100 >= rounds * 256 * fill and (n_gemm <= 512 or nkt >= 16)
-        # 3x3 stride-1 pad-1 layers in bf16: the kernel that stages the activation slab once for all nine taps
-        if (bf16 and cs.r == 3 and cs.s == 3 and cs.stride == 1 and cs.pad == 1 and k_gemm % 32 == 0 and not big
-                and -(-rows // 128) * -(-n_gemm // (128 if n_gemm > 64 else 64)) >= 256):
-            return "conv3x3_slab"
+        if bf16:
+            # 3x3 stride-1 pad-1 layers of at most 64 columns: the kernel that stages the activation slab once for all nine taps
+            slab = (cs.r == 3 and cs.s == 3 and cs.stride == 1 and cs.pad == 1 and k_gemm % 32 == 0 and n_gemm <= 64
+                    and -(-rows // 128) >= 256)
+            return "conv3x3_slab" if slab else "conv_dma"
         if n_gemm <= 64:
-            return "conv_gemm_256x64" if special and -(-rows // 256) >= 3 * 3 * 256 else "conv_gemm_128x64"
-        if special and n_gemm >= 256:
-            if big:
-                return "conv_gemm_256x256"
-            if -(-rows // 128) * -(-n_gemm // 256) >= 3 * 2 * 256:
-                return "conv_gemm_128x256"
+            return "conv_gemm_128x64"
         return "conv_gemm_128x128"
 
     def step(timer=None):
