@@ -36,6 +36,11 @@ SHAPES = {
     "stem_7x7_s2_c3": (4, 3, 32, 32, 64, 7, 7, 2, 3),
     "resnet_14_stage": (8, 256, 14, 14, 256, 3, 3, 1, 1),
 }
+SHAPES_F32_ONLY = {
+    "stream_k_64_columns": (2, 512, 7, 7, 64, 3, 3, 1, 1),             # one fix-up for tile and sums: 64 columns, ragged ones, and two tiles of columns
+    "stream_k_36_columns": (3, 256, 9, 9, 36, 3, 3, 1, 1),
+    "stream_k_132_columns": (3, 256, 9, 9, 132, 3, 3, 1, 1),
+}
 SHAPES_BF16_ONLY = {
     "big_tile_256x256": (64, 128, 28, 28, 512, 1, 1, 1, 0),
 }
@@ -134,6 +139,11 @@ def _case(name, shape, bf16):
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_statistics_out_of_the_convolution(name, bf16):
     _case(name, SHAPES[name], bf16)
+
+
+@pytest.mark.parametrize("name", list(SHAPES_F32_ONLY))
+def test_statistics_with_the_fixup(name):
+    _case(name, SHAPES_F32_ONLY[name], False)
 
 
 @pytest.mark.parametrize("name", list(SHAPES_BF16_ONLY))
@@ -236,3 +246,32 @@ def test_statistics_at_full_size_bf16():
     want = np.maximum((ys - mean_ref) / np.sqrt(var_ref + EPS) * gamma.cpu().numpy().astype(np.float64) + beta.cpu().numpy(), 0.0)
     gots = out.view(m, k)[idx].to(torch.float32).cpu().numpy()
     assert np.all(np.abs(gots - want) <= np.abs(want) * 2.0 ** -8 + 2e-4 * float(np.max(np.abs(want))))
+
+
+@pytest.mark.parametrize("pieces", [1, 2, 63, 513, 1024, 1025, 2047, 2048])
+@pytest.mark.parametrize("shape", [(2, 8, 5, 5), (4, 68, 9, 9), (16, 512, 28, 28)], ids=str)      # few, some and the most slabs of partial sums
+def test_few_pieces_give_the_bits_of_many(shape, pieces):
+    """Up to 2048 pieces the finalize kernel adds them itself; beyond that they are folded first.  Pieces of zeros behind the others send the same sums the
+    second way, and every sum keeps its order: the same bits, and the float64 sums of the host (1e-6: results are stored in fp32)."""
+    n, c, h, w = shape
+    m = n * h * w
+    gen = torch.Generator().manual_seed(31 * pieces + c)
+    sums = torch.randn((pieces, c), generator=gen) * (m / pieces) ** 0.5
+    squares = (torch.rand((pieces, c), generator=gen) + 0.5) * (m / pieces)
+    stats = torch.zeros((2049, c, 2))
+    stats[:pieces, :, 0], stats[:pieces, :, 1] = sums, squares
+    x = torch.randn((n, h, w, c), generator=gen).to(gu.DEV)
+    gamma, beta, st = torch.ones(c, device=gu.DEV), torch.zeros(c, device=gu.DEV), stats.to(gu.DEV)
+    ws = gu.workspace(lc.batchnorm_workspace_bytes(n, c, h, w, NHWC))
+    got = []
+    for count in (pieces, 2049):
+        y, mean, inv = torch.empty_like(x), torch.empty(c, device=gu.DEV), torch.empty(c, device=gu.DEV)
+        lc.batchnorm_fwd_pre(lc.LC_F32, x, gamma, beta, None, y, mean, inv, n, c, h, w, EPS, False, NHWC, st[:count], count, ws)
+        torch.cuda.synchronize()
+        got.append((y.cpu(), mean.cpu(), inv.cpu()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    want = sums.double().sum(0) / m
+    var = squares.double().sum(0) / m - want.square()
+    assert ((got[0][1].double() - want).abs() <= 1e-6 * (want.abs() + var.sqrt())).all()
+    assert ((got[0][2].double() * (var + EPS).sqrt() - 1).abs() <= 1e-6).all()
