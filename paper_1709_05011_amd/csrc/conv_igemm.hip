@@ -2049,7 +2049,7 @@ auto with_main_tile(const GemmConv& p, F&& f) {
 
 size_t lc_conv_gemm_workspace(const GemmConv& p) {
     size_t lds;
-    if (slab_kernel_ok(p, &lds)) return 0;
+    if (slab_kernel_ok(p, &lds) || lc_conv_held_ok(p, true)) return 0;
     if (lc_conv_dma_ok(p)) return lc_conv_dma_workspace(p);
     if (!use_main_kernel(p)) return 0;
     if (p.split) return lc_conv_split_workspace(p);
@@ -2076,6 +2076,7 @@ bool lc_conv_gemm_scatter_ok(const GemmConv& p) {
 // Row pieces of the statistics: half a tile of the kernel that takes the problem (mirrors lc_launch_conv_gemm).
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
     size_t lds;
+    if (const size_t pieces = lc_conv_held_stats_tiles(p)) return pieces;
     if (!slab_kernel_ok(p, &lds)) {
         if (lc_conv_dma_ok(p)) return p.scatter ? 0 : lc_conv_dma_stats_tiles(p);
         if (!use_main_kernel(p) || p.scatter) return 0;
@@ -2087,6 +2088,7 @@ lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
     if (p.stats && lc_conv_gemm_stats_tiles(p) == 0) return LC_ERR_UNSUPPORTED;
     if (p.bf16) {
         size_t lds;
+        if (lc_conv_held_ok(p, p.stats != nullptr)) return lc_launch_conv_held(p, stream);
         if (slab_kernel_ok(p, &lds)) return launch_slab(p, lds, stream);
         if (lc_conv_dma_ok(p)) return lc_launch_conv_dma(p, stream);
         if (!use_main_kernel(p)) return LC_ERR_UNSUPPORTED;       // the caller converts to fp32 instead

@@ -110,6 +110,10 @@ bool lc_conv_dma_ok(const GemmConv& p);
 size_t lc_conv_dma_workspace(const GemmConv& p);
 size_t lc_conv_dma_stats_tiles(const GemmConv& p);
 lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream);
+// bf16 3x3 layers from 64 channels to 33 to 64 filters whose filter a wave holds in registers (conv_dma.hip)
+bool lc_conv_held_ok(const GemmConv& p, bool stats);
+size_t lc_conv_held_stats_tiles(const GemmConv& p);
+lc_status lc_launch_conv_held(const GemmConv& p, hipStream_t stream);
 // the column sums of the tiles first_tile .. tiles - 1 of bm x bn, read back from p.d (conv_igemm.hip)
 void lc_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, long long tiles, hipStream_t stream);
 size_t lc_conv_gemm_workspace(const GemmConv& p);   // bytes `partial` must hold for this problem (0 = none)
