@@ -880,6 +880,48 @@ extern "C" lc_status conv2d_bwd_weight_sq(const lc_conv_desc* d, const void* x, 
 }
 
 
+// Which kernel a pass of a layer ends in, in words (tests and the benchmark's labels); 0 and the text, or an error.  stats: conv2d_fwd_stats.  A layer
+// with groups: that of one group; backward-data by stride phases: that of the first phase.
+extern "C" int lc_selftest_conv_route(const lc_conv_desc* d, int pass, int stats, char* text, size_t size) {
+    lc_conv_desc canon, one;
+    if (!d || !text || size < 8) return LC_ERR_NULL;
+    if (d->groups > 1) {
+        one = *d;
+        one.c /= d->groups;
+        one.k /= d->groups;
+        one.groups = 1;
+        d = &one;
+    }
+    d = whole_window_as_1x1(d, &canon);
+    Plan pl;
+    const lc_status st = make_plan(d, (lc_pass)pass, &pl);
+    if (st != LC_OK) return st;
+    if (pl.blocks) return lc_selftest_conv_route(&pl.inner, pass, stats, text, size);
+    if (pl.via_f32) {
+        const lc_conv_desc f = as_f32(d);
+        return lc_selftest_conv_route(&f, pass, stats, text, size);
+    }
+    if (stem_direct(d, pl, (lc_pass)pass)) {
+        snprintf(text, size, pass == LC_PASS_FWD ? "conv_stem" : "conv_stem_wgrad");
+    } else if (pass == LC_PASS_BWD_WEIGHT) {
+        GemmWgrad g = gemm_wgrad(d, pl);
+        g.splits = pl.splits;
+        g.m_per_split = pl.m_per_split;
+        g.slab = pl.wgrad_slab;
+        g.dma_bm = pl.wgrad_bm;
+        g.dma_bn = pl.wgrad_bn;
+        lc_wgrad_describe(g, text, size);
+    } else if (pl.phases) {
+        Phase ph[kMaxPhases];
+        bool covered;
+        plan_phases(d, pl.P, pl.Q, ph, &covered);
+        lc_conv_gemm_describe(ph[0].g, false, text, size);
+    } else {
+        lc_conv_gemm_describe(pass == LC_PASS_FWD ? gemm_fwd(d, pl.P, pl.Q, pl.cpad) : gemm_bwd_data(d, pl.P, pl.Q), stats != 0, text, size);
+    }
+    return LC_OK;
+}
+
 extern "C" const char* lc_status_string(lc_status status) {
     switch (status) {
         case LC_OK: return "ok";

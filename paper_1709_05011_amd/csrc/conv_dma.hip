@@ -2,6 +2,7 @@
 // instructions, and several k-steps in flight per compute unit.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <stdio.h>
 #include <stdlib.h>
 #include <algorithm>
 #include <cmath>
@@ -50,13 +51,19 @@ __device__ __forceinline__ unsigned lds_address(const void* ptr) {
 //
 // kChunks: the channels are a multiple of 64, a k-step is 64 channels of one tap of the window and its place is scalar.  (The taps run fastest: the rows of a tile are read
 // again soon.)  kPadded: the same with the last 64 channels filled up with zeros.  kPieces: the reduction as it lies in the filter, a lane's piece of it has a tap
-// of its own.
+// of its own.  Which taps of a row's window lie outside the image is a 32-bit mask.  Windows of more than 32 taps: kRuns is kPadded in runs of at most 32 taps (whole rows of
+// the window, or parts of one that is wider), the masks set up anew for each; kTaps is kPieces with a piece's row and column compared with the image's size, two 16-bit
+// numbers at a time.  us, staging registers with half lines / here, forward, then backward-data: 7x7 over 256 channels, 256 images of 28x28 1462 / 1091 and 1464 / 1100; 11x11 96
+// to 128, 64 of 28x28 203 / 146 and 246 / 203; 13x13 with stride 2 64 to 128, 32 of 56x56 113 / 79 and 210 / 180; 7x7 24 to 40, 64 of 56x56 57 / 49 and 83 / 84.
 // ------------------------------------------------------------------------------------------------
 struct ConvDma {
     GemmConv g;
     int nkt;                      // k-steps of a tile
     unsigned ci_mul, ci_shift, s_mul, s_shift;
+    int run_rows;                 // kRuns: rows of a window in a run; 0: parts of a row
 };
+
+constexpr unsigned kNoRow = 0x80000000u;                   // row -2^15: outside under every tap's row (below 2^14)
 
 // The sum over the 16 lanes of a row of lanes, in each of them.
 __device__ __forceinline__ float sum_of_16(float x) {
@@ -70,7 +77,7 @@ __device__ __forceinline__ float sum_of_16(float x) {
 // What leaves with a tile: whole 16-byte pieces of rows (columns a multiple of 8); any number of columns and the statistics; any number of columns; the pixels
 // of a stride grid.
 enum ConvDmaOut { kRows, kStats, kAny, kGrid };
-enum ConvDmaIn { kChunks, kPadded, kPieces };
+enum ConvDmaIn { kChunks, kPadded, kPieces, kRuns, kTaps };
 
 template <int TMA, int TMB, int TN, int WN, ConvDmaIn IN, ConvDmaOut OUT>
 __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma pp) {
@@ -104,10 +111,12 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
     int l_seg = -1, l_k = 0, l_k1 = 0;                     // segment being loaded, next k-step, end
     const int lrow = lane >> 3;
     const int piece = (lane & 7) ^ (((wave & 1) * 4 + (lrow >> 1)) & 7);     // row / 2 % 8 of every row this lane loads: 8 * (i * NW + wave) + lrow
-    unsigned a_voff[LA], a_inv[LA];
+    unsigned a_voff[LA], a_inv[LA];                        // kTaps: a_inv is the place of the window's first tap in the image, row in the upper half
     u32x4 a_rsrc = {0, 0, 0, 0}, b_rsrc = a_rsrc;
+    constexpr bool by_tap = IN == kChunks || IN == kPadded || IN == kRuns;
     const unsigned b_voff = (unsigned)((wave * 8 + lrow) * Kg_ * 2 + piece * 16);
-    int u_c = 0, u_tap = 0, u_r = 0, u_s = 0;              // first channel and tap; kPieces: u_c is the k-step
+    int u_c = 0, u_tap = 0, u_r = 0, u_s = 0;              // first channel and tap; kPieces, kTaps: u_c is the k-step
+    int u_first = 0, l_stop = 0;                           // kRuns: the run's first tap; the k-step behind the run or the segment
     const unsigned lds0 = lds_address(smem);
     unsigned l_lds = lds0;
     auto loader_setup = [&](int tile, int k0) __attribute__((always_inline)) {
@@ -115,69 +124,108 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
         const int m0 = tm * BM, n0 = (tile - tm * nbn) * BN;
         const int img0 = div_by(div_by(m0, qmul, qsh), pmul, psh);
         const int phb = max(ph_, 0), pwb = max(pw_, 0);
-        const WindowTaps window(R_, S_);
+        auto place = [&]() __attribute__((always_inline)) {
+            if constexpr (by_tap) {
+                const int chunk = k0 / taps;
+                u_tap = k0 - chunk * taps;
+                u_c = chunk * 64;
+                u_r = u_tap / S_;
+                u_s = u_tap - u_r * S_;
+            } else {
+                u_c = k0;
+            }
+        };
+        int run_r = 0, run_s = 0, rows = R_, cols = S_;    // the part of the window that the masks are for
+        if constexpr (IN == kRuns) {
+            place();
+            if (pp.run_rows > 0) {
+                run_r = u_r / pp.run_rows * pp.run_rows;
+                rows = min(pp.run_rows, R_ - run_r);
+            } else {
+                run_r = u_r;
+                run_s = u_s & ~31;
+                rows = 1;
+                cols = min(32, S_ - run_s);
+            }
+            u_first = run_r * S_ + run_s;
+            l_stop = min(l_k1, k0 + (u_first + rows * cols - u_tap));
+        }
+        const int run_h = ph_ - run_r, run_w = pw_ - run_s, first_h = phb - run_r, first_w = pwb - run_s;
+        const WindowTaps window(IN != kTaps ? rows : 1, IN != kTaps ? cols : 1);
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int row = (i * NW + wave) * 8 + lrow, m = m0 + row;
             const int t = div_by(m, qmul, qsh), qo = m - t * Qo_;
             const int img = div_by(t, pmul, psh), po = t - img * Po_;
-            const int h0 = po * sh_ - ph_, w0 = qo * sw_ - pw_;
-            const unsigned inv = window.outside(h0, w0, Hi_, Wi_, R_, S_);
-            const bool ok = (m < M_) & (inv != ~0u);
-            a_inv[i] = ok ? inv : ~0u;
-            a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + phb) * Wi_) + w0 + pwb) * Ci_ * 2 + (IN != kPieces ? piece * 16 : 0)) : 0u;
+            const int h0 = po * sh_ - run_h, w0 = qo * sw_ - run_w;      // the run's first row and column in the image
+            bool ok;
+            if constexpr (IN == kTaps) {
+                ok = (m < M_) & (h0 < Hi_) & (h0 + R_ > 0) & (w0 < Wi_) & (w0 + S_ > 0);
+                a_inv[i] = ok ? (unsigned)h0 << 16 | ((unsigned)w0 & 0xffffu) : kNoRow;
+            } else {
+                const unsigned inv = window.outside(h0, w0, Hi_, Wi_, rows, cols);
+                ok = (m < M_) & (inv != ~0u);
+                a_inv[i] = ok ? inv : ~0u;
+            }
+            a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + first_h) * Wi_) + w0 + first_w) * Ci_ * 2 + (by_tap ? piece * 16 : 0)) : 0u;
         }
         const long long a_first = ((long long)img0 * Hi_ * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
         a_rsrc = buffer_words(A + a_first, kBufferBytes);
         const long long b_left = (long long)(N_ - n0) * Kg_ * 2;       // rows past N lie past the end of the buffer
         b_rsrc = buffer_words(B + (long long)n0 * Kg_, b_left > 0x7fffffffLL ? 0x7fffffffu : (unsigned)b_left);
-        if constexpr (IN != kPieces) {
-            const int chunk = k0 / taps;
-            u_tap = k0 - chunk * taps;
-            u_c = chunk * 64;
-            u_r = u_tap / S_;
-            u_s = u_tap - u_r * S_;
-        } else {
-            u_c = k0;
-        }
+        if constexpr (IN != kRuns) place();
     };
     // the next k-step of the block's sequence (past its end: nothing)
     unsigned v_off = 0, v_up = 0, v_bad = 0;               // this lane's piece: byte offset from the window's first value, tap; bit 31: no such channel
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    s16x2 v_rs = {0, 0};                                   // kTaps: the tap's column and row
+    const s16x2 last = {(short)(Wi_ - 1), (short)(Hi_ - 1)};
+    int l_tile = 0;
     auto load_begin = [&]() __attribute__((always_inline)) {
-        if (l_k == l_k1) {
+        if constexpr (IN == kRuns) {
+            if (l_k == l_stop) {
+                if (l_k == l_k1) walk.segment(++l_seg, l_tile, l_k, l_k1);
+                loader_setup(l_tile, l_k);
+            }
+        } else if (l_k == l_k1) {
             int tile;
             ++l_seg;
             walk.segment(l_seg, tile, l_k, l_k1);
             loader_setup(tile, l_k);
         }
-        if constexpr (IN == kPadded) v_bad = u_c + piece * 8 < Ci_ ? 0u : kBufferBytes;
-        if constexpr (IN == kPieces) {
+        if constexpr (IN == kPadded || IN == kRuns) v_bad = u_c + piece * 8 < Ci_ ? 0u : kBufferBytes;
+        if constexpr (!by_tap) {
             const int kg = u_c * 64 + piece * 8;
             const int rs = div_by(kg, pp.ci_mul, pp.ci_shift), c = kg - rs * Ci_;
             const int r = div_by(rs, pp.s_mul, pp.s_shift), s = rs - r * S_;
             v_off = (unsigned)(((r * Wi_ + s) * Ci_ + c) * 2);
             v_bad = kg < Kg_ ? 0u : kBufferBytes;
             v_up = (unsigned)max(31 - rs, 0);
+            v_rs = s16x2{(short)s, (short)r};
         }
     };
     auto load_one = [&](int l) __attribute__((always_inline)) {
         if (l < LA) {
             const int load = l * NW + wave;
             if (NA % NW != 0 && load >= NA) return;
-            if constexpr (IN != kPieces) {
-                const unsigned vo = (((a_inv[l] << (31 - u_tap)) & kBufferBytes) | a_voff[l]) | v_bad;
+            if constexpr (by_tap) {
+                const unsigned vo = (((a_inv[l] << (31 - (u_tap - u_first))) & kBufferBytes) | a_voff[l]) | v_bad;
                 load_to_lds(a_rsrc, vo, ((u_r * Wi_ + u_s) * Ci_ + u_c) * 2, l_lds + load * 1024);
+            } else if constexpr (IN == kTaps) {            // a sign bit of the place, or of what is left to the last row and column: outside
+                const s16x2 at = __builtin_bit_cast(s16x2, a_inv[l]) + v_rs;
+                const unsigned out = __builtin_bit_cast(unsigned, at) | __builtin_bit_cast(unsigned, last - at);
+                load_to_lds(a_rsrc, ((out << 16 | out) & kBufferBytes) | v_bad | (a_voff[l] + v_off), 0, l_lds + load * 1024);
             } else {
                 load_to_lds(a_rsrc, ((a_inv[l] << v_up) & kBufferBytes) | v_bad | (a_voff[l] + v_off), 0, l_lds + load * 1024);
             }
         } else {
             const int load = (l - LA) * NW + wave;
             const int rows = (l - LA) * NW * 8 * Kg_ * 2;
-            load_to_lds(b_rsrc, b_voff | v_bad, rows + (IN != kPieces ? (u_tap * Ci_ + u_c) * 2 : u_c * 128), l_lds + BM * 128 + load * 1024);
+            load_to_lds(b_rsrc, b_voff | v_bad, rows + (by_tap ? (u_tap * Ci_ + u_c) * 2 : u_c * 128), l_lds + BM * 128 + load * 1024);
         }
     };
     auto load_end = [&]() __attribute__((always_inline)) {
-        if constexpr (IN != kPieces) {
+        if constexpr (by_tap) {
             ++u_tap;
             ++u_s;
             const bool row = u_s == S_;
@@ -457,11 +505,12 @@ __global__ void __launch_bounds__(2 * WN * 64) conv_dma_fixup_kernel(const GemmC
 // Windows over channels that are nearly a multiple of 64: chunk by chunk all the same, also where that leaves up to a 32nd of the products to zeros.  With all
 // channels of a tap before the next tap, a tile's rows come from beyond L2 once per tap (3x3, us, pieces / padded: 1120 to 64 253 / 175, 1272 to 96 212 / 161,
 // 696 to 1984 439 / 417; but with a ninth of zeros 288 to 1048 380 / 407).
+bool conv_dma_by_tap(const GemmConv& p) { return p.Ci % 64 == 0 || (p.R * p.S > 1 && (p.Ci + 63) / 64 * 64 * 32LL <= p.Ci * 33LL); }
 ConvDmaIn conv_dma_in(const GemmConv& p) {
-    if (p.Ci % 64 == 0) return kChunks;
-    return p.R * p.S > 1 && (p.Ci + 63) / 64 * 64 * 32LL <= p.Ci * 33LL ? kPadded : kPieces;
+    if ((long long)p.R * p.S > 32) return conv_dma_by_tap(p) ? kRuns : kTaps;
+    return p.Ci % 64 == 0 ? kChunks : conv_dma_by_tap(p) ? kPadded : kPieces;
 }
-int conv_dma_steps(const GemmConv& p) { return conv_dma_in(p) != kPieces ? (p.Ci + 63) / 64 * p.R * p.S : (p.Kg + 63) / 64; }
+int conv_dma_steps(const GemmConv& p) { return conv_dma_by_tap(p) ? (p.Ci + 63) / 64 * p.R * p.S : (p.Kg + 63) / 64; }
 
 // Tiles, and what a k-step of them takes in us where a block has its compute unit to itself, per block where `per_cu` take turns, and the same for what a tile costs
 // beyond its k-steps.
@@ -493,7 +542,7 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
     const float pixels = p.R == 1 && p.S == 1 ? (float)p.M : (float)p.M / ((float)p.Po * (float)p.Qo) * (float)p.Hi * (float)p.Wi;
     const float memory = (pixels * (float)p.Ci + (float)p.M * (float)p.N) * (2e-6f / 4.2f);
     auto fourth = [](float x) { return x * x * x * x; };
-    const bool rows = !p.scatter && p.N % 8 == 0 && p.ldd % 8 == 0;
+    const bool rows = !p.scatter && p.N % 8 == 0 && p.ldd % 8 == 0, large = (long long)p.R * p.S > 32;
     float best = 1e30f;
     out->nkt = nkt;
     auto tile_cost = [&](int i) {
@@ -525,17 +574,18 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
         };
         consider(rest ? rest : 1, true);
         if (rest == 0 || i == kWide || i >= kOtherRows) return;
-        for (int s = 2; s <= 16 && rest * s <= resident && nkt >= 2 * s; s += s < 4 ? 1 : s < 8 ? 2 : 4) consider(rest * s, true);
+        // (windows of more than 32 taps: every number of parts; 512 to 512 7x7, 64 images of 7x7, 392 k-steps: five parts 85 us, end to end 117, staging registers 111)
+        for (int s = 2; s <= 16 && rest * s <= resident && nkt >= 2 * s; s += large || s < 4 ? 1 : s < 8 ? 2 : 4) consider(rest * s, true);
         const int all = (int)std::min<long long>(resident, (long long)rest * nkt / 2);
         if (all > rest) consider(all, false);
     };
     if (p.N > 128 && rows) tile_cost(kWide);
     if (p.N > 64) tile_cost(kSquare);
     tile_cost(kNarrow);
-    tile_cost(kNarrowTwoWaves);
-    if (p.N <= 32) tile_cost(kSlim);
+    if (!large) tile_cost(kNarrowTwoWaves);               // (kRuns and kTaps are built for three of the tiles)
+    if (!large && p.N <= 32) tile_cost(kSlim);
     if (best >= 1e30f) return false;
-    if (any_rows && p.N > 128 && rows && out->sk.sk_iters == (long long)out->sk.sk_blocks * nkt)
+    if (any_rows && !large && p.N > 128 && rows && out->sk.sk_iters == (long long)out->sk.sk_blocks * nkt)
         for (int i = kOtherRows; i < (int)(sizeof(kConvTiles) / sizeof(kConvTiles[0])); ++i) tile_cost(i);
     return true;
 }
@@ -545,7 +595,7 @@ template <int TMA, int TMB, int TN, int WN>
 lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_t stream) {
     constexpr int BM = 16 * (TMA + TMB), BN = 16 * TN * WN, threads = 2 * WN * 64;
     constexpr int lds = 2 * (BM + BN) * 128 + 2 * WN * 16 * (TN * 32 + 16);
-    ConvDma c = {q, plan.nkt, 0, 0, 0, 0};
+    ConvDma c = {q, plan.nkt, 0, 0, 0, 0, 32 / q.S};
     GemmConv& p = c.g;
     const long long tiles = plan.tiles;
     const int nkt = plan.nkt, resident = kConvTiles[plan.tile].per_cu * device_cu_count();
@@ -587,6 +637,9 @@ lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_
         case kChunks: out.template operator()<kChunks>(); break;
         case kPadded: out.template operator()<kPadded>(); break;
         case kPieces: out.template operator()<kPieces>(); break;
+        default:
+            if constexpr (TMA == TMB && TMA != 7 && TMA != 6 && WN != 1) conv_dma_in(p) == kRuns ? out.template operator()<kRuns>() : out.template operator()<kTaps>();
+            else st = LC_ERR_UNSUPPORTED;
     }
     if (st != LC_OK) return st;
     if constexpr (TMA == TMB) {
@@ -1137,12 +1190,14 @@ constexpr WgradTile kWgradTiles[] = {{256, 256, 1, 0.70f, 0.787f}, {256, 128, 1,
 
 }  // namespace
 
-// bf16 operands of 16-byte pieces, windows of at most 32 taps, byte offsets within a tile (the images it can touch plus a window; its filters; its result) below 2^31.
+// bf16 operands of 16-byte pieces, byte offsets within a tile (the images it can touch plus a window; its filters; its result) below 2^31.
 bool lc_conv_dma_ok(const GemmConv& p) {
     static const bool off = getenv("LARSCONV_NO_CONV_DMA") != nullptr;       // comparison runs
     if (off || !p.bf16 || p.Ci % 8 != 0 || !aligned16(p.a) || !aligned16(p.b) || p.dh > 1 || p.dw > 1) return false;
-    if ((long long)p.R * p.S > 32 || p.M >= 0x7fff0000) return false;
-    const long long images = 256LL / ((long long)p.Po * p.Qo) + 2;
+    if (p.M >= 0x7fff0000) return false;
+    constexpr int k16 = 1 << 14;                           // kTaps: rows, columns and taps in 16 bits
+    if ((long long)p.R * p.S > 32 && !conv_dma_by_tap(p) && (p.Hi >= k16 || p.Wi >= k16 || p.R >= k16 || p.S >= k16)) return false;
+    const long long images = (p.scatter ? 128LL : 256LL) / ((long long)p.Po * p.Qo) + 2;       // (stride grids have tiles of 128 rows)
     const long long a_span = ((images * p.Hi + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.Wi + p.S + 1) * p.Ci * 2;
     const long long d_span = p.scatter ? images * p.Ho * p.Wo * p.ldd * 2 : 288LL * p.ldd * 2;
     return a_span < 0x7fff0000LL && 257LL * p.Kg * 2 < 0x7fff0000LL && d_span < 0x7fff0000LL;
@@ -1159,6 +1214,15 @@ size_t lc_conv_dma_stats_tiles(const GemmConv& p) {
     if (!conv_dma_plan(p, false, &c)) return 0;
     const int bm = kConvTiles[c.tile].bm;
     return (size_t)2 * ((p.M + bm - 1) / bm);
+}
+
+void lc_conv_dma_describe(const GemmConv& p, bool stats, char* text, size_t size) {
+    ConvDmaPlan c;
+    static const char* const in[] = {"chunks", "padded", "pieces", "runs", "taps"};
+    if (!conv_dma_plan(p, !stats, &c)) snprintf(text, size, "none");
+    else
+        snprintf(text, size, "conv_dma %dx%d%s %s%s", kConvTiles[c.tile].bm, kConvTiles[c.tile].bn, c.tile == kNarrowTwoWaves ? " two waves" : "",
+                 in[conv_dma_in(p)], conv_dma_shares(c) ? " shared" : "");
 }
 
 lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream) {

@@ -15,6 +15,7 @@
 // multiplied (two LDS buffers, one barrier per k-step).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 #include <algorithm>
@@ -234,8 +235,8 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with windows of more than 32 taps and
-// tensors of spans that conv_dma.hip does not take.
+// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with tensors of spans that conv_dma.hip
+// does not take.
 //
 // LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
@@ -2047,12 +2048,34 @@ auto with_main_tile(const GemmConv& p, F&& f) {
     return f.template operator()<128, 64>();
 }
 
+// The kernel that takes a problem; with the statistics (stats) another may.
+enum class ConvKernel { kHeld, kSlab, kDma, kMain, kSplit, kGeneral, kNone };
+static ConvKernel conv_kernel(const GemmConv& p, bool stats, size_t* slab_lds) {
+    if (p.bf16) {
+        if (lc_conv_held_ok(p, stats)) return ConvKernel::kHeld;
+        if (slab_kernel_ok(p, slab_lds)) return ConvKernel::kSlab;
+        if (lc_conv_dma_ok(p)) return ConvKernel::kDma;
+        return use_main_kernel(p) ? ConvKernel::kMain : ConvKernel::kNone;       // kNone: the caller converts to fp32 instead
+    }
+    if (!use_main_kernel(p)) return ConvKernel::kGeneral;
+    return p.split ? ConvKernel::kSplit : ConvKernel::kMain;
+}
+
+void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t size) {
+    size_t lds;
+    const ConvKernel k = conv_kernel(p, stats, &lds);
+    if (k == ConvKernel::kDma) return lc_conv_dma_describe(p, stats, text, size);
+    static const char* const names[] = {"conv3x3_held", "conv3x3_slab", "", "conv_gemm_pk", "conv_gemm_split", "conv_gemm", "none"};
+    snprintf(text, size, "%s", names[(int)k]);
+}
+
+// (asked for the call with statistics, which the kernels without partial tiles take no more often than the call without)
 size_t lc_conv_gemm_workspace(const GemmConv& p) {
     size_t lds;
-    if (slab_kernel_ok(p, &lds) || lc_conv_held_ok(p, true)) return 0;
-    if (lc_conv_dma_ok(p)) return lc_conv_dma_workspace(p);
-    if (!use_main_kernel(p)) return 0;
-    if (p.split) return lc_conv_split_workspace(p);
+    const ConvKernel k = conv_kernel(p, true, &lds);
+    if (k == ConvKernel::kDma) return lc_conv_dma_workspace(p);
+    if (k == ConvKernel::kSplit) return lc_conv_split_workspace(p);
+    if (k != ConvKernel::kMain) return 0;
     return with_main_tile(p, [&]<int BM, int BN>() -> size_t {
         long long tiles;
         int nkt;
@@ -2073,35 +2096,40 @@ bool lc_conv_gemm_scatter_ok(const GemmConv& p) {
     return span < 0x7fff0000LL;
 }
 
-// Row pieces of the statistics: half a tile of the kernel that takes the problem (mirrors lc_launch_conv_gemm).
+// Row pieces of the statistics: half a tile of the kernel that takes the problem.
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
     size_t lds;
-    if (const size_t pieces = lc_conv_held_stats_tiles(p)) return pieces;
-    if (!slab_kernel_ok(p, &lds)) {
-        if (lc_conv_dma_ok(p)) return p.scatter ? 0 : lc_conv_dma_stats_tiles(p);
-        if (!use_main_kernel(p) || p.scatter) return 0;
+    if (p.scatter) return 0;
+    switch (conv_kernel(p, true, &lds)) {
+        case ConvKernel::kHeld: return lc_conv_held_stats_tiles(p);
+        case ConvKernel::kDma: return lc_conv_dma_stats_tiles(p);
+        case ConvKernel::kSlab:
+        case ConvKernel::kMain:
+        case ConvKernel::kSplit: return (size_t)2 * ((p.M + 127) / 128);
+        default: return 0;
     }
-    return (size_t)2 * ((p.M + 127) / 128);
 }
 
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
     if (p.stats && lc_conv_gemm_stats_tiles(p) == 0) return LC_ERR_UNSUPPORTED;
-    if (p.bf16) {
-        size_t lds;
-        if (lc_conv_held_ok(p, p.stats != nullptr)) return lc_launch_conv_held(p, stream);
-        if (slab_kernel_ok(p, &lds)) return launch_slab(p, lds, stream);
-        if (lc_conv_dma_ok(p)) return lc_launch_conv_dma(p, stream);
-        if (!use_main_kernel(p)) return LC_ERR_UNSUPPORTED;       // the caller converts to fp32 instead
-        if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
-        return p.N > 64 ? launch_conv_sk<128, 128, false, true>(p, stream) : launch_conv_sk<128, 64, false, true>(p, stream);
+    size_t lds;
+    switch (conv_kernel(p, p.stats != nullptr, &lds)) {
+        case ConvKernel::kHeld: return lc_launch_conv_held(p, stream);
+        case ConvKernel::kSlab: return launch_slab(p, lds, stream);
+        case ConvKernel::kDma: return lc_launch_conv_dma(p, stream);
+        case ConvKernel::kSplit: return lc_launch_conv_split(p, stream);
+        case ConvKernel::kNone: return LC_ERR_UNSUPPORTED;
+        case ConvKernel::kMain:
+            if (p.bf16) {
+                if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
+                return p.N > 64 ? launch_conv_sk<128, 128, false, true>(p, stream) : launch_conv_sk<128, 64, false, true>(p, stream);
+            }
+            if (p.Ci < 16) return p.N > 64 ? launch_conv_sk<128, 128, true, false>(p, stream) : launch_conv_sk<128, 64, true, false>(p, stream);
+            return p.N > 64 ? launch_conv_sk<128, 128, false, false>(p, stream) : launch_conv_sk<128, 64, false, false>(p, stream);
+        case ConvKernel::kGeneral: break;
     }
     const bool vec = (p.Ci % 4 == 0) && aligned16(p.a) && aligned16(p.b);
     if (!vec) return launch_conv<64, 64, 16, 1>(p, stream);
-    if (use_main_kernel(p)) {
-        if (p.split) return lc_launch_conv_split(p, stream);
-        if (p.Ci < 16) return p.N > 64 ? launch_conv_sk<128, 128, true, false>(p, stream) : launch_conv_sk<128, 64, true, false>(p, stream);
-        return p.N > 64 ? launch_conv_sk<128, 128, false, false>(p, stream) : launch_conv_sk<128, 64, false, false>(p, stream);
-    }
     if (p.N > 64) return launch_conv<128, 128, 16, 4>(p, stream);
     return launch_conv<128, 64, 16, 4>(p, stream);
 }
@@ -2274,6 +2302,18 @@ static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
     if (bm == 128) return launch_wgrad<128, 64, 16, 4, BF16>(p, stream);
     if (bn == 128) return launch_wgrad<64, 128, 16, 4, BF16>(p, stream);
     return launch_wgrad<64, 64, 16, 4, BF16>(p, stream);
+}
+
+// (mirrors dispatch_wgrad)
+void lc_wgrad_describe(const GemmWgrad& p, char* text, size_t size) {
+    const char* kernel = "wgrad";
+    if (p.slab) kernel = "wgrad3x3_slab";
+    else if (p.bf16 && p.dma_bm) kernel = "wgrad_dma";
+    else if (!p.bf16 && wgrad_split_ok(p)) kernel = "wgrad_split";
+    else if (wgrad_plain_ok(p)) kernel = "wgrad_plain";
+    else if (p.bf16 && p.C % 8 == 0 && p.K % 8 == 0) kernel = "wgrad_bf16";
+    if (p.dma_bm) snprintf(text, size, "%s %dx%d splits %d", kernel, p.dma_bm, p.dma_bn, p.splits);
+    else snprintf(text, size, "%s splits %d", kernel, p.splits);
 }
 
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream) {

@@ -110,6 +110,9 @@ bool lc_conv_dma_ok(const GemmConv& p);
 size_t lc_conv_dma_workspace(const GemmConv& p);
 size_t lc_conv_dma_stats_tiles(const GemmConv& p);
 lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream);
+// the kernel (tile, addressing, whether blocks share tiles) that takes a problem, in words
+void lc_conv_dma_describe(const GemmConv& p, bool stats, char* text, size_t size);
+void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t size);
 // bf16 3x3 layers from 64 channels to 33 to 64 filters whose filter a wave holds in registers (conv_dma.hip)
 bool lc_conv_held_ok(const GemmConv& p, bool stats);
 size_t lc_conv_held_stats_tiles(const GemmConv& p);
@@ -168,6 +171,7 @@ struct GemmWgrad {
     int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (conv_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
+void lc_wgrad_describe(const GemmWgrad& p, char* text, size_t size);     // the kernel that takes a planned problem, in words
 int lc_wgrad_splits(GemmWgrad* p);   // fixed function of the shape (determinism); chooses the tile of wgrad_dma_kernel where that takes the layer
 // bf16 operands straight into LDS (conv_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
 bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits);

@@ -1,5 +1,7 @@
 """Helpers for the GPU parity tests: move seeded numpy inputs to the device, call the C ABI through
 the binding, bring results back.  torch is used for device memory only."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -71,3 +73,22 @@ def scaled_err(got: np.ndarray, ref: np.ndarray) -> float:
     assert np.all(np.isfinite(got)), "output has NaN/Inf (unwritten element?)"
     scale = float(np.max(np.abs(ref))) if ref.size else 1.0
     return float(np.max(np.abs(got - ref))) / (scale if scale > 0 else 1.0) if ref.size else 0.0
+
+
+def route(d: lc.ConvDesc, which: int, stats: bool = False) -> str:
+    """The kernel a pass of a layer ends in, in the library's words (host only)."""
+    text, c = ctypes.create_string_buffer(96), d.c_struct()
+    assert lc.lib().lc_selftest_conv_route(ctypes.byref(c), ctypes.c_int(which), ctypes.c_int(stats), text, ctypes.c_size_t(96)) == 0
+    return text.value.decode()
+
+
+def guarded(shape, dtype, guard_bytes=4096):
+    """A result filled with NaN between guard bytes, and a function that checks that the guard bytes still hold what they held."""
+    size = torch.Size(shape).numel() * torch.empty((), dtype=dtype).element_size()
+    raw = torch.full((guard_bytes + (size + 255) // 256 * 256 + guard_bytes,), 0x5A, dtype=torch.uint8, device=DEV)
+    out = raw[guard_bytes:guard_bytes + size].view(dtype).view(shape)
+    out.fill_(float("nan"))
+
+    def check():
+        assert bool((raw[:guard_bytes] == 0x5A).all()) and bool((raw[guard_bytes + size:] == 0x5A).all()), "written outside the result"
+    return out, check

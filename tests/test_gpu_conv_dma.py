@@ -48,24 +48,39 @@ SHAPES = [
     (4, 37, 10, 64, 1, 2),         # stride grids of odd and of even counts of channels
     (3, 38, 9, 64, 3, 2),
 ]
+# windows of more than 32 taps: n, c, h, w, k, r, s, stride, pad_h, pad_w; the kernel of forward and of backward-data
+LARGE_WINDOWS = [
+    ((3, 64, 15, 14, 136, 7, 7, 1, 3, 3), "conv_dma 128x64 runs shared", "conv_dma 128x64 taps shared"),       # runs of 28 and 21 taps, split between blocks
+    ((1, 504, 7, 7, 72, 7, 7, 1, 3, 3), "conv_dma 128x64 runs shared", "conv_dma 128x64 taps shared"),
+    ((2, 40, 12, 13, 72, 7, 7, 1, 3, 3), "conv_dma 128x64 taps shared", "conv_dma 128x64 taps shared"),          # pieces of several taps in a k-step
+    ((60, 64, 31, 31, 136, 3, 11, 1, 1, 5), "conv_dma 256x256 runs", "conv_dma 128x64 taps"),
+    ((60, 8, 33, 33, 264, 6, 6, 1, 2, 3), "conv_dma 256x256 taps", "conv_dma 128x64 taps"),
+    ((20, 128, 20, 20, 128, 7, 7, 1, 3, 3), "conv_dma 128x128 runs shared", "conv_dma 128x128 runs shared"),
+    ((2, 64, 3, 50, 72, 1, 35, 1, 0, 20), "conv_dma 128x64 runs shared", "conv_dma 128x64 taps shared"),       # runs of 32 and 3 taps of a row; more padding than half of it
+    ((2, 64, 6, 90, 64, 2, 70, 1, 1, 30), "conv_dma 128x64 runs shared", "conv_dma 128x64 runs shared"),
+    ((2, 64, 50, 3, 64, 37, 1, 1, 18, 0), "conv_dma 128x64 runs shared", "conv_dma 128x64 runs shared"),
+    ((2, 24, 50, 3, 40, 37, 1, 1, 18, 0), "conv_dma 128x64 taps", "conv_dma 128x64 taps shared"),
+    ((3, 64, 5, 4, 72, 9, 9, 1, 4, 4), "conv_dma 128x64 runs shared", "conv_dma 128x64 taps shared"),          # larger than the image
+    ((3, 16, 21, 19, 40, 13, 13, 2, 6, 6), "conv_dma 128x64 taps shared", "conv_dma 128x64 taps shared"),        # four phases of up to 49 taps
+    ((2, 37, 16, 16, 64, 13, 12, 2, 5, 6), "conv_dma 128x64 taps shared", "conv_dma 128x64 runs shared"),      # odd counts of columns
+    ((2, 64, 11, 11, 33, 7, 7, 1, 3, 3), "conv_dma 128x64 runs shared", "conv_gemm"),
+]
 
 
-@pytest.mark.parametrize("s", SHAPES, ids=str)
-def test_matches_float64(s):
-    n, c, hw, k, r, st = s
-    g = torch.Generator().manual_seed(17)
-    d = lc.ConvDesc(n, c, hw, hw, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC)
+def _check(d, seed=17):
+    n, c, k, r, s, st, pad = d.n, d.c, d.k, d.r, d.s, (d.stride_h, d.stride_w), (d.pad_h, d.pad_w)
+    g = torch.Generator().manual_seed(seed)
     p, q = lc.conv2d_out_shape(d)
-    x = torch.randn((n, hw, hw, c), generator=g).to(torch.bfloat16)
-    w = (torch.randn((k, r, r, c), generator=g) / (c * r * r) ** 0.5).to(torch.bfloat16)
+    x = torch.randn((n, d.h, d.w, c), generator=g).to(torch.bfloat16)
+    w = (torch.randn((k, r, s, c), generator=g) / (c * r * s) ** 0.5).to(torch.bfloat16)
     dy = torch.randn((n, p, q, k), generator=g).to(torch.bfloat16)
-    print(f"conv dma {s}", flush=True)
 
     def run(fn, which, a, b, shape):
-        out = torch.full(shape, float("nan"), dtype=torch.bfloat16, device=gu.DEV)
+        out, guard = gu.guarded(shape, torch.bfloat16)
         ws = gu.workspace(lc.conv2d_workspace_bytes(d, which))
         fn(d, a.to(gu.DEV), b.to(gu.DEV), out, ws)
         torch.cuda.synchronize()
+        guard()
         return out.cpu()
 
     def check(got, ref, mag, terms):
@@ -73,18 +88,35 @@ def test_matches_float64(s):
         assert bool(((got.double() - ref).abs() <= bound).all()), float(((got.double() - ref).abs() / (mag + 1e-30)).max())
 
     xn, wn, dyn = (t.double().permute(0, 3, 1, 2) for t in (x, w, dy))
-    fwd = lambda a, b: F.conv2d(a, b, stride=st, padding=r // 2).permute(0, 2, 3, 1)                                             # noqa: E731
-    bwd = lambda a, b: torch.nn.grad.conv2d_input(xn.shape, b, a, stride=st, padding=r // 2).permute(0, 2, 3, 1)                 # noqa: E731
+    fwd = lambda a, b: F.conv2d(a, b, stride=st, padding=pad).permute(0, 2, 3, 1)                                             # noqa: E731
+    bwd = lambda a, b: torch.nn.grad.conv2d_input(xn.shape, b, a, stride=st, padding=pad).permute(0, 2, 3, 1)                 # noqa: E731
     y = run(lc.conv2d_fwd, lc.LC_PASS_FWD, x, w, dy.shape)
-    check(y, fwd(xn, wn), fwd(xn.abs(), wn.abs()), c * r * r)
-    check(run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, w, x.shape), bwd(dyn, wn), bwd(dyn.abs(), wn.abs()), k * r * r)
+    check(y, fwd(xn, wn), fwd(xn.abs(), wn.abs()), c * r * s)
+    check(run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, w, x.shape), bwd(dyn, wn), bwd(dyn.abs(), wn.abs()), k * r * s)
 
     # with statistics: the same bits, and per column the sums of what was stored
     count = lc.conv2d_fwd_stats_count(d)
     assert count > 0
-    stats = torch.full((count, k, 2), float("nan"), device=gu.DEV)
+    stats, guard = gu.guarded((count, k, 2), torch.float32)
     y2 = run(lambda d_, a, b, out, ws: lc.conv2d_fwd_stats(d_, a, b, out, stats, ws), lc.LC_PASS_FWD, x, w, dy.shape)
+    guard()
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
     rows, got = y.double().reshape(-1, k), stats.cpu().double().sum(0)
     assert bool(((got[:, 0] - rows.sum(0)).abs() <= 2e-5 * rows.abs().sum(0) + 1e-30).all())
     assert bool(((got[:, 1] - rows.square().sum(0)).abs() <= 2e-5 * rows.square().sum(0) + 1e-30).all())
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=str)
+def test_matches_float64(s):
+    n, c, hw, k, r, st = s
+    print(f"conv dma {s}", flush=True)
+    _check(lc.ConvDesc(n, c, hw, hw, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC))
+
+
+@pytest.mark.parametrize("case", LARGE_WINDOWS, ids=str)
+def test_windows_of_more_than_32_taps(case):
+    (n, c, h, w, k, r, s, st, ph, pw), fwd, bwd = case
+    d = lc.ConvDesc(n, c, h, w, k, r, s, st, st, ph, pw, lc.LC_BF16, lc.LC_NHWC)
+    assert gu.route(d, lc.LC_PASS_FWD) == fwd and gu.route(d, lc.LC_PASS_BWD_DATA) == bwd
+    print(f"conv dma large window {d}", flush=True)
+    _check(d)
