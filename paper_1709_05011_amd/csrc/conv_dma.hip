@@ -928,15 +928,33 @@ struct WgradRows {
 
 struct WgradDma {
     GemmWgrad g;
-    int chain;                    // stages after which a wave's sums go to a second set
+    int chain;                    // stages (an even number) after which a wave's sums go to a second set
     unsigned q_mul, q_shift, p_mul, p_shift;
 };
 
-// Stages that may go into one running sum: a split's worth in a round of 1024 blocks of 128x128, 256 rows at least.  The error of a sum in fp32 grows with the
-// root of its length, and fewer splits than that would show (1x1, 512 images of 28x28, 512 to 128: 64 splits of 6272 rows 4.0e-7, 256 splits 2.0e-7).
-inline int wgrad_chain(const GemmWgrad& p) {
-    const long long tiles = (long long)((p.K + 127) / 128) * ((p.J + 127) / 128), splits = std::max(1LL, 1024 / tiles);
-    return (int)(std::max(256LL, p.M / splits) / 32);
+// Rows that may go into one running sum: those of a split where the splits fill a round of the staging-register kernels' blocks, or of the slab kernel's where it would
+// take the layer if that had 64 channels and filters.  The error of a sum in fp32 grows with the root of its length, and fewer splits than that would show (1x1, 512 images of 28x28,
+// 512 to 128: 64 splits of 6272 rows 4.0e-7, 256 splits 2.0e-7; 3x3, 440 of 24x24, 448 to 64: sums of 7904 rows 4.6e-7, of 3472 2.9e-7).
+inline int wgrad_former_splits(const GemmWgrad& p) {
+    int splits = lc_wgrad_round_splits(p), positions;
+    const int imgs = (int)(p.M / ((long long)p.P * p.Q));
+    if (p.R == 3 && p.S == 3 && p.sh == 1 && p.sw == 1 && p.ph == 1 && p.pw == 1 && p.C % 64 == 0 && p.K % 64 == 0 && p.W >= kWgradSlabMinW)
+        splits = std::max(splits, lc_wgrad_slab_splits(imgs, p.H, p.W, p.C, p.K, &positions));
+    return splits;
+}
+inline int wgrad_chain_rows(const GemmWgrad& p) { return (p.M + wgrad_former_splits(p) - 1) / wgrad_former_splits(p); }
+// Stages of a running sum, an even number.  Where one split has taken the place of several, their additions (lc_reduce_splits: four interleaved sums) are saved, and the sums may be
+// longer by as much: 48 rows round as often as one addition of everything (measured: 64; 3x3 over 512 channels, 37 images of 7x7, ten stages for eight: 28 -> 26 us, error 0.93 of the seven
+// splits', with eight 0.86).
+inline int wgrad_chain_stages(const GemmWgrad& p) {
+    int rows = wgrad_chain_rows(p);
+    const int parts = wgrad_former_splits(p), each = parts / 4, first = each + parts % 4;
+    if (p.splits == 1 && parts > 2) {
+        int added = first * (first + 1) / 2 - 1;           // how many parts the result of each addition holds
+        if (each > 0) added += 3 * (each * (each + 1) / 2 - 1) + 2 * parts;
+        rows += 48 * (added - parts) / parts;
+    }
+    return std::max(2, rows / 64 * 2);
 }
 
 // Columns of the result: one pixel's channels in 256-wide pieces (or, PLAIN -- a 1x1 window with stride 1 and no padding -- any of the widths).
@@ -1114,14 +1132,26 @@ __global__ void __launch_bounds__(WM* WN * 64, BM * BN <= 64 * 128 ? 3 : 2) wgra
         if (kt + 1 < nkt) step(1);
         if constexpr (TWO) {
             if (kt + 2 >= chain) {
+                // What an addition to the second set rounds away starts the next run of stages, so that many additions lose no more than one.  (Where a sum
+                // is infinite that would be no number: then the whole wave starts from zeros.)
                 chain += pp.chain;
+                float most = 0.f;
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j) {
-                        sum[i][j] += acc[i][j];
-                        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        const f32x4 total = sum[i][j] + acc[i][j];
+                        acc[i][j] -= total - sum[i][j];
+                        sum[i][j] = total;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) most = fmaxf(most, fabsf(total[e]));
                     }
+                if (__builtin_amdgcn_ballot_w64(most > 3.4028234e38f)) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
             }
         }
     }
@@ -1169,7 +1199,7 @@ lc_status launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
     if (!once) return LC_ERR_LAUNCH;
     const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
     if (tiles <= 0 || tiles * p.splits > 0x7fffffffLL) return LC_ERR_UNSUPPORTED;
-    WgradDma q = {p, wgrad_chain(p), 0, 0, 0, 0};
+    WgradDma q = {p, wgrad_chain_stages(p), 0, 0, 0, 0};
     magic_for(p.Q, &q.q_mul, &q.q_shift);
     magic_for(p.P, &q.p_mul, &q.p_shift);
     hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WM, WN, NS, PLAIN>), dim3((unsigned)(tiles * p.splits)), dim3(WM * WN * 64), lds, stream, q);
@@ -1303,7 +1333,7 @@ bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits) {
     const float x_rows = p.R == 1 && p.S == 1 ? (float)p.M : (float)p.M / ((float)p.P * (float)p.Q) * (float)p.H * (float)p.W;
     const float operands = (x_rows * (float)p.C + (float)p.M * (float)p.K) * 2e-6f;      // MB
     auto fourth = [](float x) { return x * x * x * x; };
-    const int chain = wgrad_chain(p);
+    const int chain_rows = wgrad_chain_rows(p);
     float best = 1e30f;
     *bm = 0;
     for (const WgradTile& t : kWgradTiles) {
@@ -1315,7 +1345,7 @@ bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits) {
         auto consider = [&](int s) {
             if (s < 1 || s > most) return;
             const int stages = ((p.M + s - 1) / s + 31) / 32;
-            if (t.bm * t.bn == 256 * 256 && stages > chain + chain / 8) return;      // (it has no second set of sums)
+            if (t.bm * t.bn == 256 * 256 && (p.M + s - 1) / s > chain_rows) return;      // (it has no second set of sums)
             const float steps = (float)stages, blocks = (float)(tiles * s), turns = (float)((tiles * s + cus - 1) / cus);
             if (steps * t.alone >= best || turns * steps * t.shared >= best) return;
             float us = sqrtf(sqrtf(fourth(steps * t.alone) + fourth(turns * steps * t.shared) + fourth(operands / std::min(3.85f, 0.167f * blocks)) +
@@ -1339,6 +1369,10 @@ bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits) {
     const long long spanned = rows / ((long long)p.P * p.Q) + 2;
     const long long x_span = ((spanned * p.H + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.W + p.S + 1) * p.C * 2;
     return rows * std::max(p.K, p.C) * 2 < 0x7fff0000LL && x_span < 0x7fff0000LL && 257LL * p.J * 4 < 0x7fff0000LL;
+}
+
+int lc_wgrad_dma_sum_rows(const GemmWgrad& p) {
+    return p.dma_bm * p.dma_bn == 256 * 256 ? p.m_per_split : std::min(p.m_per_split, wgrad_chain_stages(p) * 32);
 }
 
 lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {

@@ -2164,10 +2164,14 @@ static bool wgrad_by_split(const GemmWgrad& p) {
 }
 
 int lc_wgrad_splits(GemmWgrad* g) {
-    const GemmWgrad& p = *g;
-    int bm, bn, dma_splits;
-    if (lc_wgrad_dma_plan(p, &g->dma_bm, &g->dma_bn, &dma_splits)) return dma_splits;
+    int dma_splits;
+    if (lc_wgrad_dma_plan(*g, &g->dma_bm, &g->dma_bn, &dma_splits)) return dma_splits;
     g->dma_bm = g->dma_bn = 0;
+    return lc_wgrad_round_splits(*g);
+}
+
+int lc_wgrad_round_splits(const GemmWgrad& p) {
+    int bm, bn;
     wgrad_tile(p.K, p.J, &bm, &bn);
     const long long tiles = (long long)((p.K + bm - 1) / bm) * ((p.J + bn - 1) / bn);
     const bool split = wgrad_by_split(p);
@@ -2196,7 +2200,7 @@ bool lc_wgrad_slab_ok(int imgs, int H, int W, int C, int K, int R, int S, int sh
     // there; but 128 -> 128 at 28x28 188 / 113, 64 -> 128 at 56x56 303 / 260, 192 -> 64 at 28x28 135 / 103).  Narrow images spend too many
     // MFMAs on halo positions (2 of every W + 2).  Tests lower the threshold to send small shapes here, of any number of channels.
     const char* e = getenv("LARSCONV_WGRAD_SLAB_MIN_W");
-    if (W < (e ? atoi(e) : 24) || (!e && (C != 64 || K != 64))) return false;
+    if (W < (e ? atoi(e) : kWgradSlabMinW) || (!e && (C != 64 || K != 64))) return false;
     const long long pixels = (long long)imgs * H * W, positions = (long long)imgs * (H + 1) * (W + 2);
     return pixels * (C > K ? C : K) * 2 < 0x7fff0000LL && positions < 0x7ff00000LL;
 }
@@ -2312,7 +2316,7 @@ void lc_wgrad_describe(const GemmWgrad& p, char* text, size_t size) {
     else if (!p.bf16 && wgrad_split_ok(p)) kernel = "wgrad_split";
     else if (wgrad_plain_ok(p)) kernel = "wgrad_plain";
     else if (p.bf16 && p.C % 8 == 0 && p.K % 8 == 0) kernel = "wgrad_bf16";
-    if (p.dma_bm) snprintf(text, size, "%s %dx%d splits %d", kernel, p.dma_bm, p.dma_bn, p.splits);
+    if (p.dma_bm) snprintf(text, size, "%s %dx%d splits %d sums %d", kernel, p.dma_bm, p.dma_bn, p.splits, lc_wgrad_dma_sum_rows(p));
     else snprintf(text, size, "%s splits %d", kernel, p.splits);
 }
 

@@ -176,8 +176,11 @@ int lc_wgrad_splits(GemmWgrad* p);   // fixed function of the shape (determinism
 // bf16 operands straight into LDS (conv_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
 bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits);
 lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream);
+int lc_wgrad_dma_sum_rows(const GemmWgrad& p);     // rows that go into one running sum
 // fp32 operands on the bf16 matrix pipe (conv_split.hip), output tile bm x bn; and how many of its blocks fit on a compute unit
 lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream);
 int lc_wgrad_split_blocks_per_cu(int bm, int bn);
 bool lc_wgrad_slab_ok(int imgs, int H, int W, int C, int K, int R, int S, int sh, int sw, int ph, int pw, int P, int Q, bool bf16);
+constexpr int kWgradSlabMinW = 24;     // columns of an image that the slab kernel takes
+int lc_wgrad_round_splits(const GemmWgrad& p);     // splits that fill one round of blocks of the kernels that stage operands through registers
 int lc_wgrad_slab_splits(int imgs, int H, int W, int C, int K, int* pos_per_split);

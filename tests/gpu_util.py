@@ -82,9 +82,10 @@ def route(d: lc.ConvDesc, which: int, stats: bool = False) -> str:
     return text.value.decode()
 
 
-def guarded(shape, dtype, guard_bytes=4096):
-    """A result filled with NaN between guard bytes, and a function that checks that the guard bytes still hold what they held."""
+def guarded(shape, dtype, guard_bytes=4096, offset=0):
+    """A result filled with NaN between guard bytes, `offset` bytes past a 256-byte boundary, and a function that checks that the guard bytes still hold what they held."""
     size = torch.Size(shape).numel() * torch.empty((), dtype=dtype).element_size()
+    guard_bytes += offset
     raw = torch.full((guard_bytes + (size + 255) // 256 * 256 + guard_bytes,), 0x5A, dtype=torch.uint8, device=DEV)
     out = raw[guard_bytes:guard_bytes + size].view(dtype).view(shape)
     out.fill_(float("nan"))

@@ -1,6 +1,8 @@
 """Which kernel the library sends a layer to, asked on the host (no GPU): every form of a bf16 window that the kernel with operands straight into LDS is built for
-reaches it, in both passes and at every size a call can have."""
+reaches it, in both passes and at every size a call can have, and the running sums of its filter gradients are as short as promised."""
 import itertools
+import random
+import re
 
 import pytest
 
@@ -24,3 +26,47 @@ def test_windows_of_more_than_32_taps(window, stride):
             assert gu.route(d, which).startswith("conv_dma"), (d, which)
         assert gu.route(d, lc.LC_PASS_FWD, stats=True).startswith("conv_dma")
         assert lc.conv2d_fwd_stats_count(d) > 0
+
+
+def _former_splits(d, rows):
+    """The splits of the kernels that staged operands through registers: one round of 256 compute units with 4, 5 or 8 blocks each, 256 rows at least; 3x3 layers
+    over multiples of 64 channels on wide images in two blocks per unit of 64 filters x 64 channels x nine taps."""
+    j = d.r * d.s * d.c
+    tiles = -(-d.k // (128 if d.k > 64 else 64)) * -(-j // (128 if j > 64 else 64))
+    splits = min((4 if d.k > 64 and j > 64 else 8 if d.k <= 64 and j <= 64 else 5) * 256 // tiles, -(-rows // 256))
+    if (d.r, d.s, d.stride_h, d.pad_h) == (3, 3, 1, 1) and d.c % 64 == 0 and d.k % 64 == 0 and d.w >= 24:
+        splits = max(splits, min(512 // (d.c // 64 * (d.k // 64)), -(-d.n * (d.h + 1) * (d.w + 2) // 256)))
+    return max(splits, 1)
+
+
+def _additions(parts):
+    """Adding equal parts in four interleaved sums: the share of the whole that each addition's result holds, summed."""
+    each = parts // 4
+    sums = [each + parts % 4, each, each, each]
+    serial = sum(n * (n + 1) // 2 - 1 for n in sums if n)
+    return (serial + (2 * parts if each else 0)) / parts
+
+
+def test_sums_of_the_filter_gradient_are_no_longer_than_before():
+    """The error of a sum in fp32 grows with the root of its rows.  No running sum holds more rows than a split of the former kernels did; one split in the
+    place of several, whose additions are saved, may hold the 64 rows more per addition of everything that round as often."""
+    rng, seen = random.Random(3), set()
+    for _ in range(4000):
+        unit = rng.choice([8, 32, 64])
+        c, k = (max(unit, int(2 ** rng.uniform(3, 11)) // unit * unit) for _ in range(2))
+        n, hw, r = int(2 ** rng.uniform(0, 9)), int(2 ** rng.uniform(2, 7)), rng.choice([1, 1, 3, 3, 3, 5])
+        stride = rng.choice([1, 1, 1, 2])
+        d = _desc(n, c, hw, hw, k, r, r, stride, r // 2, r // 2)
+        m = re.fullmatch(r"wgrad_dma (\d+x\d+) splits (\d+) sums (\d+)", gu.route(d, lc.LC_PASS_BWD_WEIGHT))
+        if not m:
+            continue
+        splits, sums = int(m[2]), int(m[3])
+        p, q = lc.conv2d_out_shape(d)
+        rows = n * p * q
+        former = _former_splits(d, rows)
+        limit = -(-rows // former)
+        if splits == 1:
+            limit += max(0.0, 64 * (_additions(former) - 1))
+        assert sums <= limit, (d, m[0], former)
+        seen.add(m[1])
+    assert seen == {"256x256", "256x128", "128x256", "128x128", "256x64", "64x256", "128x64", "64x128"}
