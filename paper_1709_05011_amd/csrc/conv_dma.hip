@@ -1364,11 +1364,11 @@ bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits) {
         consider(most);
     }
     if (*bm == 0) return false;
-    // byte offsets of a split's rows and of the images it touches, and of a wave's filters in the result, below 2^31
+    // byte offsets of a split's rows and (but for plain layers, which have no use for them) of the images it touches, and of a wave's filters in the result, below 2^31
     const long long rows = (p.M + *splits - 1) / *splits + 64 + 32 * 6;
     const long long spanned = rows / ((long long)p.P * p.Q) + 2;
     const long long x_span = ((spanned * p.H + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.W + p.S + 1) * p.C * 2;
-    return rows * std::max(p.K, p.C) * 2 < 0x7fff0000LL && x_span < 0x7fff0000LL && 257LL * p.J * 4 < 0x7fff0000LL;
+    return rows * std::max(p.K, p.C) * 2 < 0x7fff0000LL && (wgrad_plain(p) || x_span < 0x7fff0000LL) && 257LL * p.J * 4 < 0x7fff0000LL;
 }
 
 int lc_wgrad_dma_sum_rows(const GemmWgrad& p) {

@@ -28,6 +28,14 @@ def test_windows_of_more_than_32_taps(window, stride):
         assert lc.conv2d_fwd_stats_count(d) > 0
 
 
+@pytest.mark.parametrize("c,k", [(64, 72), (64, 160), (256, 256), (512, 96)])
+def test_filter_gradients_of_plain_layers_on_large_images(c, k):
+    """A 1x1 layer's filter gradient reads rows of pixels, whatever image they are in: images of half a gibibyte and more are like any other."""
+    hw = int((1.2 * 2 ** 29 / c) ** 0.5)
+    for n in (1, 3):
+        assert gu.route(_desc(n, c, hw, hw, k, 1, 1, 1, 0, 0), lc.LC_PASS_BWD_WEIGHT).startswith("wgrad_dma")
+
+
 def _former_splits(d, rows):
     """The splits of the kernels that staged operands through registers: one round of 256 compute units with 4, 5 or 8 blocks each, 256 rows at least; 3x3 layers
     over multiples of 64 channels on wide images in two blocks per unit of 64 filters x 64 channels x nine taps."""

@@ -104,6 +104,17 @@ def test_whole_numbers_are_exact(s, tile):
     assert torch.equal(_dw(d, x, dy).double(), _sums(d, x, dy)[0])
 
 
+def test_plain_layer_on_an_image_of_a_gibibyte():
+    d = _desc((1, 64, 2950, 2950, 72, 1, 1, 0))
+    assert gu.route(d, lc.LC_PASS_BWD_WEIGHT).startswith("wgrad_dma")
+    g = torch.Generator(device=gu.DEV).manual_seed(14)
+    x, dy = (torch.randint(-1, 2, t, generator=g, device=gu.DEV, dtype=torch.int8).to(torch.bfloat16) for t in _shapes(d))
+    ref = torch.zeros((d.k, d.c), dtype=torch.float64, device=gu.DEV)
+    for t, u in zip(dy.view(-1, d.k).split(1 << 20), x.view(-1, d.c).split(1 << 20)):
+        ref += t.t().double().contiguous() @ u.double()
+    assert torch.equal(_dw(d, x, dy).double().view(d.k, d.c), ref.cpu())
+
+
 @pytest.mark.parametrize("s", [SHAPES[0][0], SHAPES[1][0], SHAPES[15][0]], ids=str)
 def test_dw_aligned_to_four_bytes(s):
     d = _desc(s)
