@@ -51,9 +51,9 @@ __device__ __forceinline__ unsigned lds_address(const void* ptr) {
 //
 // kChunks: the channels are a multiple of 64, a k-step is 64 channels of one tap of the window and its place is scalar.  (The taps run fastest: the rows of a tile are read
 // again soon.)  kPadded: the same with the last 64 channels filled up with zeros.  kPieces: the reduction as it lies in the filter, a lane's piece of it has a tap
-// of its own.  Which taps of a row's window lie outside the image is a 32-bit mask.  Windows of more than 32 taps: kRuns is kPadded in runs of at most 32 taps (whole rows of
-// the window, or parts of one that is wider), the masks set up anew for each; kTaps is kPieces with a piece's row and column compared with the image's size, two 16-bit
-// numbers at a time.  us, staging registers with half lines / here, forward, then backward-data: 7x7 over 256 channels, 256 images of 28x28 1462 / 1091 and 1464 / 1100; 11x11 96
+// of its own.  Which taps of a row's window lie outside the image is a 32-bit mask.  Windows of more than 32 taps, and images so large that two of them span 2 GiB: kRuns is kPadded in
+// runs of at most 32 taps (whole rows of the window, or parts of one that is wider), the masks set up anew for each; kTaps is kPieces with a piece's row and column compared with the
+// image's size, two 16-bit numbers at a time; both count a tile's offsets from its first row, the others from its first image.  us, staging registers with half lines / here, forward, then backward-data: 7x7 over 256 channels, 256 images of 28x28 1462 / 1091 and 1464 / 1100; 11x11 96
 // to 128, 64 of 28x28 203 / 146 and 246 / 203; 13x13 with stride 2 64 to 128, 32 of 56x56 113 / 79 and 210 / 180; 7x7 24 to 40, 64 of 56x56 57 / 49 and 83 / 84.
 // ------------------------------------------------------------------------------------------------
 struct ConvDma {
@@ -63,7 +63,7 @@ struct ConvDma {
     int run_rows;                 // kRuns: rows of a window in a run; 0: parts of a row
 };
 
-constexpr unsigned kNoRow = 0x80000000u;                   // row -2^15: outside under every tap's row (below 2^14)
+constexpr unsigned kNoRow = 0x80000000u;                   // row -2^15: outside under every tap's row (below 2^15)
 
 // The sum over the 16 lanes of a row of lanes, in each of them.
 __device__ __forceinline__ float sum_of_16(float x) {
@@ -124,6 +124,11 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
         const int m0 = tm * BM, n0 = (tile - tm * nbn) * BN;
         const int img0 = div_by(div_by(m0, qmul, qsh), pmul, psh);
         const int phb = max(ph_, 0), pwb = max(pw_, 0);
+        int row_base = 0;                                  // the row of the first image that offsets count from: within it, so that the next image's rows lie behind
+        if constexpr (IN == kRuns || IN == kTaps) {
+            const int t0 = div_by(m0, qmul, qsh);
+            row_base = min((t0 - img0 * Po_) * sh_, Hi_);
+        }
         auto place = [&]() __attribute__((always_inline)) {
             if constexpr (by_tap) {
                 const int chunk = k0 / taps;
@@ -150,7 +155,7 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             u_first = run_r * S_ + run_s;
             l_stop = min(l_k1, k0 + (u_first + rows * cols - u_tap));
         }
-        const int run_h = ph_ - run_r, run_w = pw_ - run_s, first_h = phb - run_r, first_w = pwb - run_s;
+        const int run_h = ph_ - run_r, run_w = pw_ - run_s, first_h = phb - run_r - row_base, first_w = pwb - run_s;
         const WindowTaps window(IN != kTaps ? rows : 1, IN != kTaps ? cols : 1);
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
@@ -169,7 +174,7 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             }
             a_voff[i] = ok ? (unsigned)(((((img - img0) * Hi_ + h0 + first_h) * Wi_) + w0 + first_w) * Ci_ * 2 + (by_tap ? piece * 16 : 0)) : 0u;
         }
-        const long long a_first = ((long long)img0 * Hi_ * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
+        const long long a_first = (((long long)img0 * Hi_ + row_base) * Wi_ - ((long long)phb * Wi_ + pwb)) * Ci_;
         a_rsrc = buffer_words(A + a_first, kBufferBytes);
         const long long b_left = (long long)(N_ - n0) * Kg_ * 2;       // rows past N lie past the end of the buffer
         b_rsrc = buffer_words(B + (long long)n0 * Kg_, b_left > 0x7fffffffLL ? 0x7fffffffu : (unsigned)b_left);
@@ -506,8 +511,21 @@ __global__ void __launch_bounds__(2 * WN * 64) conv_dma_fixup_kernel(const GemmC
 // channels of a tap before the next tap, a tile's rows come from beyond L2 once per tap (3x3, us, pieces / padded: 1120 to 64 253 / 175, 1272 to 96 212 / 161,
 // 696 to 1984 439 / 417; but with a ninth of zeros 288 to 1048 380 / 407).
 bool conv_dma_by_tap(const GemmConv& p) { return p.Ci % 64 == 0 || (p.R * p.S > 1 && (p.Ci + 63) / 64 * 64 * 32LL <= p.Ci * 33LL); }
+// Bytes from the first value that a tile of 256 rows (128 of a stride grid) reads to its last: counted from its first image, or -- images of 256 pixels and more, of which it touches two
+// at most -- from its first row.
+long long conv_dma_span(const GemmConv& p, bool from_row) {
+    const int tile = p.scatter ? 128 : 256;
+    long long rows = (tile / ((long long)p.Po * p.Qo) + 2) * p.Hi;
+    if (from_row) {
+        if ((long long)p.Po * p.Qo < tile) return 1LL << 62;
+        rows = (tile / p.Qo + 3LL) * p.sh + std::max(0LL, p.Hi - (p.Po - 1LL) * p.sh) + (p.ph < 0 ? -p.ph : 0);
+    }
+    return ((rows + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.Wi + p.S + 1) * p.Ci * 2;
+}
+constexpr long long kSpanLimit = 0x7fff0000LL;
+bool conv_dma_far(const GemmConv& p) { return conv_dma_span(p, false) >= kSpanLimit; }
 ConvDmaIn conv_dma_in(const GemmConv& p) {
-    if ((long long)p.R * p.S > 32) return conv_dma_by_tap(p) ? kRuns : kTaps;
+    if ((long long)p.R * p.S > 32 || conv_dma_far(p)) return conv_dma_by_tap(p) ? kRuns : kTaps;
     return p.Ci % 64 == 0 ? kChunks : conv_dma_by_tap(p) ? kPadded : kPieces;
 }
 int conv_dma_steps(const GemmConv& p) { return conv_dma_by_tap(p) ? (p.Ci + 63) / 64 * p.R * p.S : (p.Kg + 63) / 64; }
@@ -542,7 +560,7 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
     const float pixels = p.R == 1 && p.S == 1 ? (float)p.M : (float)p.M / ((float)p.Po * (float)p.Qo) * (float)p.Hi * (float)p.Wi;
     const float memory = (pixels * (float)p.Ci + (float)p.M * (float)p.N) * (2e-6f / 4.2f);
     auto fourth = [](float x) { return x * x * x * x; };
-    const bool rows = !p.scatter && p.N % 8 == 0 && p.ldd % 8 == 0, large = (long long)p.R * p.S > 32;
+    const bool rows = !p.scatter && p.N % 8 == 0 && p.ldd % 8 == 0, large = (long long)p.R * p.S > 32 || conv_dma_far(p);
     float best = 1e30f;
     out->nkt = nkt;
     auto tile_cost = [&](int i) {
@@ -574,7 +592,7 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
         };
         consider(rest ? rest : 1, true);
         if (rest == 0 || i == kWide || i >= kOtherRows) return;
-        // (windows of more than 32 taps: every number of parts; 512 to 512 7x7, 64 images of 7x7, 392 k-steps: five parts 85 us, end to end 117, staging registers 111)
+        // (kRuns and kTaps: every number of parts; 512 to 512 7x7, 64 images of 7x7, 392 k-steps: five parts 85 us, end to end 117, staging registers 111)
         for (int s = 2; s <= 16 && rest * s <= resident && nkt >= 2 * s; s += large || s < 4 ? 1 : s < 8 ? 2 : 4) consider(rest * s, true);
         const int all = (int)std::min<long long>(resident, (long long)rest * nkt / 2);
         if (all > rest) consider(all, false);
@@ -1225,12 +1243,11 @@ bool lc_conv_dma_ok(const GemmConv& p) {
     static const bool off = getenv("LARSCONV_NO_CONV_DMA") != nullptr;       // comparison runs
     if (off || !p.bf16 || p.Ci % 8 != 0 || !aligned16(p.a) || !aligned16(p.b) || p.dh > 1 || p.dw > 1) return false;
     if (p.M >= 0x7fff0000) return false;
-    constexpr int k16 = 1 << 14;                           // kTaps: rows, columns and taps in 16 bits
-    if ((long long)p.R * p.S > 32 && !conv_dma_by_tap(p) && (p.Hi >= k16 || p.Wi >= k16 || p.R >= k16 || p.S >= k16)) return false;
-    const long long images = (p.scatter ? 128LL : 256LL) / ((long long)p.Po * p.Qo) + 2;       // (stride grids have tiles of 128 rows)
-    const long long a_span = ((images * p.Hi + (p.ph > 0 ? p.ph : 0) + p.R + 1) * p.Wi + p.S + 1) * p.Ci * 2;
-    const long long d_span = p.scatter ? images * p.Ho * p.Wo * p.ldd * 2 : 288LL * p.ldd * 2;
-    return a_span < 0x7fff0000LL && 257LL * p.Kg * 2 < 0x7fff0000LL && d_span < 0x7fff0000LL;
+    if (conv_dma_in(p) == kTaps && ((long long)p.Hi + p.R > 1 << 15 || (long long)p.Wi + p.S > 1 << 15)) return false;       // (rows and columns in 16 bits)
+    // (large images to at most 64 columns: the main kernel's tile of 256 rows)
+    if (conv_dma_far(p) && ((p.N <= 64 && !p.scatter) || conv_dma_span(p, true) >= kSpanLimit)) return false;
+    const long long d_span = p.scatter ? (128LL / ((long long)p.Po * p.Qo) + 2) * p.Ho * p.Wo * p.ldd * 2 : 288LL * p.ldd * 2;       // (stride grids have tiles of 128 rows)
+    return 257LL * p.Kg * 2 < kSpanLimit && d_span < kSpanLimit;
 }
 
 size_t lc_conv_dma_workspace(const GemmConv& p) {

@@ -235,8 +235,8 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with tensors of spans that conv_dma.hip
-// does not take.
+// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with at most 64 columns out of images of
+// half a gibibyte and more.
 //
 // LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
@@ -1966,10 +1966,13 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     const unsigned grid = pl.dp_tiles > 0 ? (unsigned)resident : (unsigned)pl.sk_blocks;
     const dim3 threads(256);
     const bool whole = pl.sk_blocks == 0 || pl.sk_iters == (long long)pl.sk_blocks * nkt;
-    const bool ut = !SMALLC && uniform_tap_ok<BM, BN>(p);
     if (p.scatter) return LC_ERR_UNSUPPORTED;
-    if (ut) hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true>), dim3(grid), threads, 0, stream, p);
-    else hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false>), dim3(grid), threads, 0, stream, p);
+    bool ut = false;                          // (bf16: what conv_dma.hip leaves has spans that the variant does not take either)
+    if constexpr (!SMALLC && !BF16) {
+        ut = uniform_tap_ok<BM, BN>(p);
+        if (ut) hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true>), dim3(grid), threads, 0, stream, p);
+    }
+    if (!ut) hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, SMALLC, BF16, false>), dim3(grid), threads, 0, stream, p);
     if (!whole && !BF16 && p.stats && !sk_ranges_meet(p, nkt) && tile_stats_vec4(p)) {
         hipLaunchKernelGGL((conv_gemm_fixup_stats_kernel<BN>), dim3((unsigned)(tiles - pl.dp_tiles), 2, 4), dim3(64), 0, stream, p);
     } else if (!whole) {
@@ -2041,10 +2044,12 @@ void lc_tile_stats(const GemmConv& p, int bm, int bn, int first_tile, long long 
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p, bm, bn, first_tile);
 }
 
-// Calls f.template operator()<BM, BN>() for the main kernel's tile.
+// Calls f.template operator()<BM, BN>() for the main kernel's tile.  bf16 results of at most 64 columns take 256 rows where three rounds of such tiles are there: a wave then has as many
+// matrix instructions per load as in 128x128 (3x3 over 64 channels, an image of 3000x3000, 128 rows 1541 us, 256 rows 1296; conv_dma.hip with offsets from a tile's first row 1527).
 template <typename F>
 auto with_main_tile(const GemmConv& p, F&& f) {
     if (p.N > 64) return f.template operator()<128, 128>();
+    if (p.bf16 && p.Ci >= 32 && (p.M + 255) / 256 >= 3 * resident_blocks()) return f.template operator()<256, 64>();
     return f.template operator()<128, 64>();
 }
 
@@ -2066,7 +2071,8 @@ void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t siz
     const ConvKernel k = conv_kernel(p, stats, &lds);
     if (k == ConvKernel::kDma) return lc_conv_dma_describe(p, stats, text, size);
     static const char* const names[] = {"conv3x3_held", "conv3x3_slab", "", "conv_gemm_pk", "conv_gemm_split", "conv_gemm", "none"};
-    snprintf(text, size, "%s", names[(int)k]);
+    if (k == ConvKernel::kMain) with_main_tile(p, [&]<int BM, int BN>() { snprintf(text, size, "%s %dx%d", names[(int)k], BM, BN); });
+    else snprintf(text, size, "%s", names[(int)k]);
 }
 
 // (asked for the call with statistics, which the kernels without partial tiles take no more often than the call without)
@@ -2103,8 +2109,8 @@ size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
     switch (conv_kernel(p, true, &lds)) {
         case ConvKernel::kHeld: return lc_conv_held_stats_tiles(p);
         case ConvKernel::kDma: return lc_conv_dma_stats_tiles(p);
+        case ConvKernel::kMain: return with_main_tile(p, [&]<int BM, int BN>() { return (size_t)2 * ((p.M + BM - 1) / BM); });
         case ConvKernel::kSlab:
-        case ConvKernel::kMain:
         case ConvKernel::kSplit: return (size_t)2 * ((p.M + 127) / 128);
         default: return 0;
     }
@@ -2122,7 +2128,7 @@ lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
         case ConvKernel::kMain:
             if (p.bf16) {
                 if (p.Ci < 32) return p.N > 64 ? launch_conv_sk<128, 128, true, true>(p, stream) : launch_conv_sk<128, 64, true, true>(p, stream);
-                return p.N > 64 ? launch_conv_sk<128, 128, false, true>(p, stream) : launch_conv_sk<128, 64, false, true>(p, stream);
+                return with_main_tile(p, [&]<int BM, int BN>() { return launch_conv_sk<BM, BN, false, true>(p, stream); });
             }
             if (p.Ci < 16) return p.N > 64 ? launch_conv_sk<128, 128, true, false>(p, stream) : launch_conv_sk<128, 64, true, false>(p, stream);
             return p.N > 64 ? launch_conv_sk<128, 128, false, false>(p, stream) : launch_conv_sk<128, 64, false, false>(p, stream);

@@ -28,6 +28,18 @@ def test_windows_of_more_than_32_taps(window, stride):
         assert lc.conv2d_fwd_stats_count(d) > 0
 
 
+@pytest.mark.parametrize("c,k,r,stride", [(256, 256, 1, 1), (64, 72, 1, 1), (64, 64, 3, 1), (128, 256, 3, 1), (40, 40, 3, 1), (64, 128, 3, 2), (40, 24, 5, 1)])
+def test_images_of_half_a_gibibyte_and_more(c, k, r, stride):
+    """Two of them span more than the 2 GiB that a buffer's offsets reach; a tile does not.  At most 64 columns are faster in the main kernel's tile of 256 rows."""
+    kernel = "conv_gemm_pk 256x64" if k <= 64 else "conv_dma"
+    hw = int((1.2 * 2 ** 29 / c) ** 0.5)
+    for n in (1, 3):
+        d = _desc(n, c, hw, hw, k, r, r, stride, r // 2, r // 2)
+        assert gu.route(d, lc.LC_PASS_FWD).startswith(kernel) and gu.route(d, lc.LC_PASS_FWD, stats=True).startswith(kernel)
+        if stride == 1:
+            assert gu.route(_desc(n, k, hw, hw, c, r, r, 1, r // 2, r // 2), lc.LC_PASS_BWD_DATA).startswith(kernel)
+
+
 @pytest.mark.parametrize("c,k", [(64, 72), (64, 160), (256, 256), (512, 96)])
 def test_filter_gradients_of_plain_layers_on_large_images(c, k):
     """A 1x1 layer's filter gradient reads rows of pixels, whatever image they are in: images of half a gibibyte and more are like any other."""

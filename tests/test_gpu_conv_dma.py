@@ -113,6 +113,52 @@ def test_matches_float64(s):
     _check(lc.ConvDesc(n, c, hw, hw, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC))
 
 
+# images of a gibibyte: n, c, h, w, k, window, stride; the kernel of forward and, of the layer with c and k exchanged, of backward-data
+FAR = [
+    ((2, 64, 2950, 2900, 40, 3, 1), "conv_gemm_pk 256x64", "conv_gemm_pk 256x64"),
+    ((2, 64, 2950, 2900, 72, 3, 1), "conv_dma 128x128 runs", "conv_dma 128x128 runs"),
+    ((2, 40, 3300, 4200, 72, 3, 1), "conv_dma 128x128 taps", "conv_dma 128x128 taps"),
+    ((2, 72, 2800, 2700, 264, 1, 1), "conv_dma 256x256 taps", "conv_dma 256x256 taps"),
+    ((2, 128, 2100, 2050, 136, 3, 2), "conv_dma 256x256 runs", None),
+]
+
+
+@pytest.mark.parametrize("case", FAR, ids=str)
+def test_images_of_a_gibibyte(case):
+    """Small whole numbers, whose sums are exact in fp32: the float64 sums, rounded once.  The second image starts inside a tile."""
+    (n, c, h, w, k, r, st), fwd, bwd = case
+    g = torch.Generator(device=gu.DEV).manual_seed(19)
+    numbers = lambda *t: torch.randint(-1, 2, t, generator=g, device=gu.DEV, dtype=torch.int8).to(torch.bfloat16)        # noqa: E731
+
+    def run(d, fn, which, a, b, shape):
+        out, guard = gu.guarded(shape, torch.bfloat16)
+        fn(d, a, b, out, gu.workspace(lc.conv2d_workspace_bytes(d, which)))
+        torch.cuda.synchronize()
+        guard()
+        return out
+
+    def check(got, a, b):                                # b [k, r, s, c]
+        p, q = got.shape[1:3]
+        for i in range(n):
+            pad = F.pad(a[i], (0, 0, r // 2, r // 2, r // 2, r // 2))
+            for p0 in range(0, p, 256):
+                m = min(256, p - p0)
+                ref = sum(pad[u + st * p0:u + st * (p0 + m - 1) + 1:st, v:v + st * (q - 1) + 1:st].reshape(m * q, -1).double() @ b[:, u, v].double().t().contiguous()
+                          for u in range(r) for v in range(r))
+                assert torch.equal(got[i, p0:p0 + m].view(m * q, -1), ref.to(torch.bfloat16)), (i, p0)
+
+    d = lc.ConvDesc(n, c, h, w, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC)
+    print(f"conv dma far {d}", flush=True)
+    assert gu.route(d, lc.LC_PASS_FWD) == fwd
+    x, wt = numbers(n, h, w, c), numbers(k, r, r, c)
+    check(run(d, lc.conv2d_fwd, lc.LC_PASS_FWD, x, wt, (n, *lc.conv2d_out_shape(d), k)), x, wt)
+    if bwd:
+        e = lc.ConvDesc(n, k, h, w, c, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC)
+        assert gu.route(e, lc.LC_PASS_BWD_DATA) == bwd
+        got = run(e, lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, x, wt.permute(3, 1, 2, 0).contiguous(), (n, h, w, k))
+        check(got, x, wt.flip(1, 2).contiguous())
+
+
 @pytest.mark.parametrize("case", LARGE_WINDOWS, ids=str)
 def test_windows_of_more_than_32_taps(case):
     (n, c, h, w, k, r, s, st, ph, pw), fwd, bwd = case
