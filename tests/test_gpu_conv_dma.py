@@ -67,6 +67,55 @@ LARGE_WINDOWS = [
 ]
 
 
+NON_FINITE = [((4, 64, 14, 14, 136, 3, 3, 1, 1, 1), "chunks"), ((2, 504, 7, 7, 72, 3, 3, 1, 1, 1), "padded"), ((3, 40, 9, 9, 72, 3, 3, 1, 1, 1), "pieces"),
+              ((2, 64, 9, 9, 72, 7, 7, 1, 3, 3), "runs"), ((2, 40, 9, 9, 72, 7, 7, 1, 3, 3), "taps"), ((4, 64, 15, 15, 136, 1, 1, 2, 0, 0), "chunks")]
+
+
+@pytest.mark.parametrize("case", NON_FINITE, ids=str)
+def test_infinities_and_nan_stay_where_they_are(case):
+    """In the first and the last channel (beside those filled up with zeros), at corners (beside taps outside the image) and in the last pixel (beside rows past the
+    end): they reach the float64 result's places and no others, and a missing filter value its own filter and that filter's statistics."""
+    (n, c, h, w, k, r, s, st, ph, pw), form = case
+    d = lc.ConvDesc(n, c, h, w, k, r, s, st, st, ph, pw, lc.LC_BF16, lc.LC_NHWC)
+    assert gu.route(d, lc.LC_PASS_FWD).startswith("conv_dma") and form in gu.route(d, lc.LC_PASS_FWD).split()
+    p, q = lc.conv2d_out_shape(d)
+    g = torch.Generator().manual_seed(37)
+    x, dy = torch.randn((n, h, w, c), generator=g).to(torch.bfloat16), torch.randn((n, p, q, k), generator=g).to(torch.bfloat16)
+    wt = (torch.randn((k, r, s, c), generator=g) / (c * r * s) ** 0.5).to(torch.bfloat16)
+    for t in (x, dy):
+        t[0, 0, 0, -1] = t[1, 0, -1, 0] = float("inf")
+        t[-1, -1, -1, -1] = float("nan")
+
+    def run(fn, which, a, b, shape):
+        out, guard = gu.guarded(shape, torch.bfloat16)
+        fn(d, a.to(gu.DEV), b.to(gu.DEV), out, gu.workspace(lc.conv2d_workspace_bytes(d, which)))
+        torch.cuda.synchronize()
+        guard()
+        return out.cpu()
+
+    def check(got, ref):
+        for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(kind(got), kind(ref)), kind
+        ok = torch.isfinite(ref)
+        assert bool(((got.double() - ref).abs()[ok] <= 2.0 ** -7 * ref.abs()[ok] + 1e-4).all())
+
+    nchw = lambda t: t.double().permute(0, 3, 1, 2)                                                                          # noqa: E731
+    check(run(lc.conv2d_fwd, lc.LC_PASS_FWD, x, wt, dy.shape), F.conv2d(nchw(x), nchw(wt), stride=st, padding=(ph, pw)).permute(0, 2, 3, 1))
+    check(run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, wt, x.shape),
+          torch.nn.grad.conv2d_input((n, c, h, w), nchw(wt), nchw(dy), stride=st, padding=(ph, pw)).permute(0, 2, 3, 1))
+
+    x = torch.randn((n, h, w, c), generator=g).to(torch.bfloat16)
+    wt[k // 2, 0, 0, c - 1] = float("nan")
+    stats, guard = gu.guarded((lc.conv2d_fwd_stats_count(d), k, 2), torch.float32)
+    y = run(lambda d_, a, b, out, ws: lc.conv2d_fwd_stats(d_, a, b, out, stats, ws), lc.LC_PASS_FWD, x, wt, dy.shape)
+    guard()
+    others = [i for i in range(k) if i != k // 2]
+    assert torch.isnan(y[..., k // 2]).all() and torch.isfinite(y[..., others]).all()
+    rows, sums = y.double().reshape(-1, k)[:, others], stats.cpu().double().sum(0)
+    assert torch.isnan(sums[k // 2]).all()
+    assert bool(((sums[others, 0] - rows.sum(0)).abs() <= 2e-5 * rows.abs().sum(0) + 1e-30).all())
+
+
 def _check(d, seed=17):
     n, c, k, r, s, st, pad = d.n, d.c, d.k, d.r, d.s, (d.stride_h, d.stride_w), (d.pad_h, d.pad_w)
     g = torch.Generator().manual_seed(seed)
