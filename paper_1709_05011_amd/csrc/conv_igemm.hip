@@ -1,4 +1,4 @@
-// Implicit-GEMM convolution kernels for gfx950: the fp32 forward pass, bf16 layers of 64 channels with a 3x3 window, and the fallbacks of both types
+// Implicit-GEMM convolution kernels for gfx950: the fp32 forward pass, bf16 3x3 layers of at most 64 filters that conv_dma.hip leaves, and the fallbacks of both types
 // (bf16: conv_dma.hip; fp32 backward-data and filter gradients: conv_split.hip).
 //
 // Forward and backward-data run as  D[m][n] = sum_kg A(m,kg) * B[n][kg]  where row m is an output
@@ -235,8 +235,8 @@ __global__ void __launch_bounds__(WGM* WGN * 64) conv_gemm_f32_kernel(const Gemm
 }
 
 // ------------------------------------------------------------------------------------------------
-// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with at most 64 columns out of images of
-// half a gibibyte and more.
+// Main forward kernel of fp32 (channel counts that are multiples of 4, no dilated read); in bf16 it is left with few columns and a short reduction
+// (short_reduction) and at most 64 columns out of images of half a gibibyte and more.
 //
 // LDS tile: [row][16 floats] unpadded; the four 16-byte chunks of a row are permuted by chunk ^ swz(row)
 // so that the b128 fragment reads of 8 or 16 consecutive rows hit distinct banks.  The permutation is
@@ -1967,8 +1967,8 @@ lc_status launch_conv_sk(GemmConv p, hipStream_t stream) {
     const dim3 threads(256);
     const bool whole = pl.sk_blocks == 0 || pl.sk_iters == (long long)pl.sk_blocks * nkt;
     if (p.scatter) return LC_ERR_UNSUPPORTED;
-    bool ut = false;                          // (bf16: what conv_dma.hip leaves has spans that the variant does not take either)
-    if constexpr (!SMALLC && !BF16) {
+    bool ut = false;                          // (bf16 results of more than 64 columns come here for spans that the variant does not take either)
+    if constexpr (!SMALLC && (!BF16 || BN == 64)) {
         ut = uniform_tap_ok<BM, BN>(p);
         if (ut) hipLaunchKernelGGL((conv_gemm_pk_kernel<BM, BN, false, BF16, true>), dim3(grid), threads, 0, stream, p);
     }
@@ -2053,13 +2053,24 @@ auto with_main_tile(const GemmConv& p, F&& f) {
     return f.template operator()<128, 64>();
 }
 
+// bf16 problems of few columns and a short reduction that stay with the main kernel: conv_dma.hip's k-steps of 64 values are zeros in part and its tiles cost more beyond
+// their k-steps than the products.  us, main kernel / conv_dma.hip, forward, with statistics, backward-data: 1x1 32 to 32, 505 images of 63x63 51 / 66, 65 / 80, 55 / 69; 1x1 16 to 48, 31 of
+// 103x103 13 / 19, 15 / 23, 16 / 19; 3x3 16 to 48, 55 of 115x115 40 / 47, 42 / 55; 1x1 16 to 608, 328 of 21x21 34 / 36, 40 / 47; but 3x3 over 16, 25 of 81x81 12.2 / 11.2, and more
+// than 64 columns from 24 values on 0.9 in the mean without statistics.  Multiples of 64 channels: 1x1 over 64, 76 of 58x58 14 / 16, 15 / 19, 18 / 19, 153 of 87x87 64 / 58, 69 / 68, 66 / 62.
+static bool short_reduction(const GemmConv& p) {
+    if (p.scatter || (long long)p.R * p.S > 32) return false;
+    if (p.N > 64) return p.Kg <= 16;
+    if (p.Ci % 64 == 0) return p.Kg == 64 && p.M < 1 << 20;
+    return p.Kg <= (p.N <= 32 ? 128 : 288);
+}
+
 // The kernel that takes a problem; with the statistics (stats) another may.
 enum class ConvKernel { kHeld, kSlab, kDma, kMain, kSplit, kGeneral, kNone };
 static ConvKernel conv_kernel(const GemmConv& p, bool stats, size_t* slab_lds) {
     if (p.bf16) {
         if (lc_conv_held_ok(p, stats)) return ConvKernel::kHeld;
         if (slab_kernel_ok(p, slab_lds)) return ConvKernel::kSlab;
-        if (lc_conv_dma_ok(p)) return ConvKernel::kDma;
+        if (lc_conv_dma_ok(p) && !(short_reduction(p) && use_main_kernel(p))) return ConvKernel::kDma;
         return use_main_kernel(p) ? ConvKernel::kMain : ConvKernel::kNone;       // kNone: the caller converts to fp32 instead
     }
     if (!use_main_kernel(p)) return ConvKernel::kGeneral;

@@ -90,3 +90,13 @@ def test_sums_of_the_filter_gradient_are_no_longer_than_before():
         assert sums <= limit, (d, m[0], former)
         seen.add(m[1])
     assert seen == {"256x256", "256x128", "128x256", "128x128", "256x64", "64x256", "128x64", "64x128"}
+
+
+def test_few_columns_and_short_reductions_stay_with_the_main_kernel():
+    for (n, c, hw, k, r), kernel in (((31, 16, 103, 48, 1), "conv_gemm_pk 128x64"), ((505, 32, 63, 32, 1), "conv_gemm_pk 256x64"), ((55, 16, 115, 48, 3), "conv_gemm_pk 128x64"),
+                                     ((76, 64, 58, 64, 1), "conv_gemm_pk 128x64"), ((153, 64, 87, 64, 1), "conv_dma"), ((512, 64, 56, 64, 1), "conv_dma"),
+                                     ((25, 16, 81, 16, 3), "conv_dma"), ((31, 24, 103, 72, 1), "conv_dma"), ((328, 16, 21, 608, 1), "conv_gemm_pk 128x128")):
+        d = _desc(n, c, hw, hw, k, r, r, 1, r // 2, r // 2)
+        assert gu.route(d, lc.LC_PASS_FWD).startswith(kernel), (d, gu.route(d, lc.LC_PASS_FWD))
+        assert gu.route(d, lc.LC_PASS_FWD, stats=True).startswith(kernel)
+        assert gu.route(_desc(n, k, hw, hw, c, r, r, 1, r // 2, r // 2), lc.LC_PASS_BWD_DATA).startswith(kernel)

@@ -13,40 +13,52 @@ import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-# n, c, hw, k, window, stride
+# n, c, hw, k, window, stride; the tile, addressing and sharing of forward and of backward-data (phases: of the first)
 SHAPES = [
-    (71, 8, 29, 184, 1, 1),        # 256x256
-    (65, 64, 30, 136, 1, 1),
-    (34, 64, 30, 288, 1, 1),       # 240
-    (106, 16, 17, 504, 1, 1),
-    (107, 64, 23, 136, 1, 1),      # 224
-    (106, 8, 16, 312, 1, 1),
-    (64, 64, 20, 264, 1, 1),       # 208
-    (38, 8, 26, 344, 1, 1),
-    (57, 64, 24, 152, 1, 1),       # 192
-    (98, 8, 19, 152, 1, 1),
-    (4, 256, 14, 256, 3, 1),       # 128x128
-    (23, 8, 22, 144, 1, 1),
-    (21, 576, 8, 104, 3, 1),       # tiles shared
-    (76, 296, 6, 72, 3, 1),
-    (2, 504, 7, 72, 3, 1),         # 504 channels as 512
-    (37, 64, 7, 64, 5, 1),         # 128x64
-    (7, 208, 5, 16, 3, 1),
-    (2, 128, 5, 16, 3, 1),
-    (62, 8, 26, 40, 1, 1),         # two waves
-    (57, 64, 24, 16, 1, 1),        # 128x32
-    (40, 32, 31, 32, 3, 1),
-    (112, 544, 30, 56, 1, 1),
-    (3, 64, 1, 1000, 1, 1),        # a fully connected layer of a few rows
-    (5, 72, 9, 33, 3, 1),          # filter counts off the vector stores
-    (3, 64, 10, 130, 1, 1),
-    (2, 64, 13, 35, 3, 1),
-    (6, 64, 15, 136, 1, 2),        # stride grids: one pixel in four, and the four phases of a window
-    (5, 72, 11, 40, 3, 2),
-    (3, 16, 12, 264, 3, 2),
-    (2, 256, 9, 8, 5, 3),
-    (4, 37, 10, 64, 1, 2),         # stride grids of odd and of even counts of channels
-    (3, 38, 9, 64, 3, 2),
+    ((178, 24, 18, 136, 1, 1), "256x256 pieces", "128x32 pieces"),
+    ((65, 64, 30, 136, 1, 1), "256x256 chunks", "conv_gemm_pk 128x64"),
+    ((34, 64, 30, 288, 1, 1), "240x256 chunks", "conv_gemm_pk 128x64"),
+    ((39, 24, 28, 272, 1, 1), "240x256 pieces", "128x32 pieces"),
+    ((107, 64, 23, 136, 1, 1), "224x256 chunks", "conv_gemm_pk 128x64"),
+    ((136, 24, 14, 264, 1, 1), "224x256 pieces", "128x32 pieces"),
+    ((64, 64, 20, 264, 1, 1), "208x256 chunks", "conv_gemm_pk 128x64"),
+    ((148, 24, 13, 264, 1, 1), "208x256 pieces", "128x32 pieces"),
+    ((57, 64, 24, 152, 1, 1), "192x256 chunks", "conv_gemm_pk 128x64"),
+    ((53, 24, 25, 136, 1, 1), "192x256 pieces", "128x32 pieces"),
+    ((4, 256, 14, 256, 3, 1), "128x64 chunks shared", "128x64 chunks shared"),
+    ((91, 24, 11, 136, 1, 1), "128x128 pieces", "128x32 pieces"),
+    ((48, 64, 19, 72, 1, 1), "128x128 chunks", "conv_gemm_pk 128x64"),
+    ((4, 256, 26, 200, 3, 1), "128x128 chunks shared", "128x64 pieces"),
+    ((4, 504, 26, 72, 3, 1), "128x128 padded shared", "128x64 pieces"),
+    ((7, 216, 28, 80, 3, 1), "128x128 pieces shared", "128x64 pieces"),
+    ((9, 216, 25, 68, 3, 1), "128x128 pieces shared", "conv_gemm_split"),
+    ((21, 576, 8, 104, 3, 1), "128x64 chunks shared", "128x64 pieces"),
+    ((76, 296, 6, 72, 3, 1), "128x64 pieces shared", "128x64 pieces"),
+    ((2, 504, 7, 72, 3, 1), "128x64 padded shared", "128x64 pieces"),      # 504 channels as 512
+    ((37, 64, 7, 64, 5, 1), "128x64 chunks shared", "128x64 chunks shared"),
+    ((7, 208, 5, 16, 3, 1), "128x32 pieces shared", "128x64 pieces"),
+    ((2, 128, 5, 16, 3, 1), "128x32 chunks shared", "128x64 pieces"),
+    ((1, 504, 3, 24, 3, 1), "128x32 padded shared", "128x64 pieces"),
+    ((1, 240, 3, 20, 3, 1), "128x32 pieces shared", "conv_gemm_split"),
+    ((9, 312, 30, 134, 3, 1), "128x64 padded", "conv_gemm"),
+    ((40, 24, 41, 40, 5, 1), "128x64 two waves pieces", "128x32 pieces"),
+    ((233, 128, 12, 56, 1, 1), "128x64 two waves chunks", "128x128 pieces"),
+    ((54, 128, 25, 41, 1, 1), "128x64 two waves chunks", "conv_gemm"),
+    ((43, 192, 23, 48, 5, 1), "128x64 two waves chunks shared", "128x128 pieces"),
+    ((13, 496, 29, 33, 5, 1), "128x64 two waves pieces shared", "conv_gemm"),
+    ((57, 128, 24, 16, 1, 1), "128x32 chunks", "conv_gemm_pk 128x128"),
+    ((40, 32, 31, 32, 5, 1), "128x32 pieces", "128x32 pieces"),
+    ((112, 544, 30, 56, 1, 1), "128x64 pieces", "256x256 pieces"),
+    ((3, 64, 1, 1000, 1, 1), "128x64 chunks", "128x64 pieces"),      # a fully connected layer of a few rows
+    ((5, 72, 9, 33, 3, 1), "128x64 pieces", "conv_gemm"),      # filter counts off the vector stores
+    ((3, 64, 10, 130, 1, 1), "128x64 chunks", "conv_gemm"),
+    ((2, 64, 13, 35, 3, 1), "128x64 chunks", "conv_gemm"),
+    ((6, 64, 15, 136, 1, 2), "128x64 chunks", "128x64 pieces"),      # stride grids: one pixel in four, and the four phases of a window
+    ((5, 72, 11, 40, 3, 2), "128x64 pieces", "128x64 pieces"),
+    ((3, 16, 12, 264, 3, 2), "128x64 pieces", "128x32 pieces"),
+    ((2, 256, 9, 8, 5, 3), "128x32 chunks shared", "128x64 pieces"),
+    ((4, 37, 10, 64, 1, 2), "conv_gemm_pk 128x64", "128x64 chunks"),      # stride grids of odd and of even counts of channels
+    ((3, 38, 9, 64, 3, 2), "128x64 pieces", "128x64 chunks"),
 ]
 # windows of more than 32 taps: n, c, h, w, k, r, s, stride, pad_h, pad_w; the kernel of forward and of backward-data
 LARGE_WINDOWS = [
@@ -155,11 +167,13 @@ def _check(d, seed=17):
     assert bool(((got[:, 1] - rows.square().sum(0)).abs() <= 2e-5 * rows.square().sum(0) + 1e-30).all())
 
 
-@pytest.mark.parametrize("s", SHAPES, ids=str)
-def test_matches_float64(s):
+@pytest.mark.parametrize("s,fwd,bwd", SHAPES, ids=str)
+def test_matches_float64(s, fwd, bwd):
     n, c, hw, k, r, st = s
+    d = lc.ConvDesc(n, c, hw, hw, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC)
     print(f"conv dma {s}", flush=True)
-    _check(lc.ConvDesc(n, c, hw, hw, k, r, r, st, st, r // 2, r // 2, lc.LC_BF16, lc.LC_NHWC))
+    assert [gu.route(d, which).removeprefix("conv_dma ") for which in (lc.LC_PASS_FWD, lc.LC_PASS_BWD_DATA)] == [fwd, bwd]
+    _check(d)
 
 
 # images of a gibibyte: n, c, h, w, k, window, stride; the kernel of forward and, of the layer with c and k exchanged, of backward-data
