@@ -466,13 +466,13 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
 }
 
 // Adds the parts of every tile that stream-K blocks share, in k order, and stores the tile: block (t, y) takes piece y of each wave's part.
-template <int TM, int TN, int WN, bool MEET>
+template <int TM, int TN, int WN>
 __global__ void __launch_bounds__(2 * WN * 64) conv_dma_fixup_kernel(const GemmConv p, int nkt) {
     constexpr int BM = 32 * TM, BN = 16 * TN * WN, NW = 2 * WN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nbn = (p.N + BN - 1) / BN;
     int sk_tile, j, j1;
-    if (!sk_shared_tile<MEET>(p, nkt, blockIdx.x, &sk_tile, &j, &j1)) return;  // one block did the whole tile and stored it
+    if (!sk_shared_tile<false>(p, nkt, blockIdx.x, &sk_tile, &j, &j1)) return;  // one block did the whole tile and stored it
     const int tb = sk_tile * nkt;                                        // this tile's first k-step in stream-K positions
     const f32x4* part = reinterpret_cast<const f32x4*>(p.partial) + (blockIdx.y * NW + wave) * 64 + lane;
     constexpr size_t kSlot = BM * BN / 4;
@@ -661,13 +661,10 @@ lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_
             else st = LC_ERR_UNSUPPORTED;
     }
     if (st != LC_OK) return st;
-    if constexpr (TMA == TMB) {
-        if (pl.sk_blocks > 0 && pl.sk_iters != (long long)pl.sk_blocks * nkt) {
-            if (!sk_ranges_meet(p, nkt))
-                hipLaunchKernelGGL((conv_dma_fixup_kernel<TMA, TN, WN, false>), dim3((unsigned)(tiles - pl.dp_tiles), TMA * TN), dim3(threads), 0, stream, p, nkt);
-            else if (pl.sk_blocks > 1)
-                hipLaunchKernelGGL((conv_dma_fixup_kernel<TMA, TN, WN, true>), dim3((unsigned)pl.sk_blocks - 1, TMA * TN), dim3(threads), 0, stream, p, nkt);
-        }
+    // (the plan shares tiles of up to 128 columns, among more blocks than tiles: ranges shorter than a tile)
+    if constexpr (WN != 4) {
+        if (pl.sk_blocks > 0 && pl.sk_iters != (long long)pl.sk_blocks * nkt)
+            hipLaunchKernelGGL((conv_dma_fixup_kernel<TMA, TN, WN>), dim3((unsigned)(tiles - pl.dp_tiles), TMA * TN), dim3(threads), 0, stream, p, nkt);
     }
     return lc_end_call();
 }
