@@ -188,37 +188,35 @@ def run_train_step(args):
     lr = lc.lars_poly_lr(1.0, 1000, T)
 
     def gemm_kernel_of(l, pass_):
-        """Which conv kernel instance a call ends in (mirrors the library's dispatch; labels only)."""
+        """Which conv kernel instance a call ends in (labels only; bf16: as the library says)."""
         cs = l.cs
         if pass_ == "bwd_weight":
             return "wgrad"
+        if bf16:
+            return lc.conv_route(l.desc, lc.LC_PASS_FWD if pass_ == "fwd" else lc.LC_PASS_BWD_DATA).split()[0]
         # ResNet's first layer has a forward kernel of its own
         if ((cs.c, cs.k, cs.r, cs.s, cs.stride, cs.pad) == (3, 64, 7, 7, 2, 3) and cs.p % 16 == 0 and cs.q % 16 == 0
                 and not os.environ.get("LARSCONV_NO_STEM_DIRECT")):
             return "conv_stem"
         n_gemm = cs.k if pass_ == "fwd" else cs.c
-        if pass_ == "bwd_data" and not bf16:
+        if pass_ == "bwd_data":
             return "conv_split_128x64" if n_gemm <= 64 else "conv_split_128x128"
-        k_gemm = cs.c if pass_ == "fwd" else cs.k
-        rows = cs.n * cs.p * cs.q if pass_ == "fwd" or cs.stride > 1 else cs.n * cs.h * cs.w
-        if bf16:
-            # 3x3 stride-1 pad-1 layers of at most 64 columns: the kernel that stages the activation slab once for all nine taps
-            slab = (cs.r == 3 and cs.s == 3 and cs.stride == 1 and cs.pad == 1 and k_gemm % 32 == 0 and n_gemm <= 64
-                    and -(-rows // 128) >= 256)
-            return "conv3x3_slab" if slab else "conv_dma"
         if n_gemm <= 64:
             return "conv_gemm_128x64"
         return "conv_gemm_128x128"
+
+    for l in layers:
+        l.labels = {pass_: gemm_kernel_of(l, pass_) for pass_ in ("fwd", "bwd_data")}
 
     def step(timer=None):
         if timer is not None:
             timer.step_starts.append(len(timer.spans))
         for l in layers:
-            timed(timer, ("fwd", gemm_kernel_of(l, "fwd"), l.cs.flops),
+            timed(timer, ("fwd", l.labels["fwd"], l.cs.flops),
                   lambda l=l: lc.conv2d_fwd(l.desc, l.x, l.w, l.y, ws))
         for l in reversed(layers):
             if not l.first:
-                timed(timer, ("bwd_data", gemm_kernel_of(l, "bwd_data"), l.cs.flops),
+                timed(timer, ("bwd_data", l.labels["bwd_data"], l.cs.flops),
                       lambda l=l: lc.conv2d_bwd_data(l.desc, l.dy, l.w, l.dx, ws))
             if fused_norms:
                 timed(timer, ("bwd_weight", "wgrad", l.cs.flops),

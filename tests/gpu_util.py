@@ -1,7 +1,5 @@
 """Helpers for the GPU parity tests: move seeded numpy inputs to the device, call the C ABI through
 the binding, bring results back.  torch is used for device memory only."""
-import ctypes
-
 import numpy as np
 import torch
 
@@ -76,10 +74,7 @@ def scaled_err(got: np.ndarray, ref: np.ndarray) -> float:
 
 
 def route(d: lc.ConvDesc, which: int, stats: bool = False) -> str:
-    """The kernel a pass of a layer ends in, in the library's words (host only)."""
-    text, c = ctypes.create_string_buffer(96), d.c_struct()
-    assert lc.lib().lc_selftest_conv_route(ctypes.byref(c), ctypes.c_int(which), ctypes.c_int(stats), text, ctypes.c_size_t(96)) == 0
-    return text.value.decode()
+    return lc.conv_route(d, which, stats)
 
 
 def guarded(shape, dtype, guard_bytes=4096, offset=0):
