@@ -174,17 +174,20 @@ def test_bf16_first_layer_full_size_batch512_sampled():
     assert np.max(np.abs(dw[cw[:, 0], cw[:, 2], cw[:, 3], cw[:, 1]] - ref)) <= TOL_DW * np.max(np.abs(ref))
 
 
-def test_bf16_wide_tile_ragged_edges_sampled():
-    """A result wide and tall enough for the 128x256 tile of the main kernel (at least three rounds of tiles), with a
-    ragged last tile in both directions: 103,488 rows (808.5 tiles), 300 columns (256 + 44).  Sampled outputs plus the
-    last rows and columns; forward and backward-data (whose result is 320 wide: 256 + 64)."""
-    n, c, hw, k = 33, 320, 56, 300
-    seed = 7900
+@pytest.mark.parametrize("k", [296, 300])
+def test_bf16_wide_tile_ragged_edges_sampled(k):
+    """Results wide and tall enough for the tiles of 192 to 256 rows by 256 columns, ragged in both directions: 97,216 rows, 296 columns (256 + 40),
+    and backward-data's 320 (256 + 64).  300 filters, which those tiles' whole 16-byte stores do not take, run in 128x128 tiles, and backward in
+    fp32.  Sampled outputs plus the last rows and columns."""
+    n, c, hw = 31, 320, 56
+    seed = 7900 + k
     xb = synth.to_bf16_bits(synth.normal((n, hw, hw, c), seed))
     wb = synth.to_bf16_bits(synth.normal((k, 1, 1, c), seed + 1, std=(2.0 / c) ** 0.5))
     dyb = synth.to_bf16_bits(synth.normal((n, hw, hw, k), seed + 2))
     x, wt, dy = (synth.bf16_bits_to_f32(b) for b in (xb, wb, dyb))
     d = lc.ConvDesc(n, c, hw, hw, k, 1, 1, 1, 1, 0, 0, lc.LC_BF16, lc.LC_NHWC)
+    for which in (lc.LC_PASS_FWD, lc.LC_PASS_BWD_DATA):
+        assert ("x256 " in gu.route(d, which)) == (k == 296)
     xd, wd, dyd = _dev_bf16(xb), _dev_bf16(wb), _dev_bf16(dyb)
     y = torch.empty((n, hw, hw, k), dtype=torch.int16, device=gu.DEV)
     dx = torch.empty((n, hw, hw, c), dtype=torch.int16, device=gu.DEV)

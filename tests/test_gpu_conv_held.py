@@ -49,11 +49,13 @@ def test_matches_float64(s, monkeypatch):
         assert bool(((got.double() - ref(a, b)).abs() <= bound).all())
 
     def run(fn, which, a, shape):
-        out = torch.full(shape, float("nan"), dtype=torch.bfloat16, device=gu.DEV)
+        out, guard = gu.guarded(shape, torch.bfloat16)
         fn(d, a, wt, out, gu.workspace(lc.conv2d_workspace_bytes(d, which)))
         torch.cuda.synchronize()
+        guard()
         return out
 
+    assert (gu.route(d, lc.LC_PASS_FWD) == "conv3x3_held") == (c == 64) and (gu.route(d, lc.LC_PASS_BWD_DATA) == "conv3x3_held") == (k == 64)
     y = run(lc.conv2d_fwd, lc.LC_PASS_FWD, x, dy.shape)
     check(y, x, wt)
     dx = run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, x.shape)
@@ -63,6 +65,7 @@ def test_matches_float64(s, monkeypatch):
     monkeypatch.setenv("LARSCONV_HELD_MIN_TURNS", "1000000000")
     monkeypatch.setenv("LARSCONV_SLAB_MIN_TILES", "1")
     if 1 < w < 100:                                        # (that kernel takes no slabs so narrow or so wide)
+        assert gu.route(d, lc.LC_PASS_FWD if c == 64 else lc.LC_PASS_BWD_DATA) == "conv3x3_slab"
         assert torch.equal(y.view(torch.int16), run(lc.conv2d_fwd, lc.LC_PASS_FWD, x, dy.shape).view(torch.int16))
         assert torch.equal(dx.view(torch.int16), run(lc.conv2d_bwd_data, lc.LC_PASS_BWD_DATA, dy, x.shape).view(torch.int16))
     monkeypatch.setenv("LARSCONV_HELD_MIN_TURNS", "1")
@@ -70,9 +73,44 @@ def test_matches_float64(s, monkeypatch):
     # with statistics: the same bits, and per column the sums of what was stored
     count = lc.conv2d_fwd_stats_count(d)
     assert count > 0
-    stats = torch.full((count, k, 2), float("nan"), device=gu.DEV)
+    stats, guard = gu.guarded((count, k, 2), torch.float32)
     y2 = run(lambda d_, a, b, out, ws: lc.conv2d_fwd_stats(d_, a, b, out, stats, ws), lc.LC_PASS_FWD, x, dy.shape)
+    guard()
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
     rows, got = y.double().reshape(-1, k), stats.double().sum(0)
     assert bool(((got[:, 0] - rows.sum(0)).abs() <= 2e-5 * rows.abs().sum(0) + 1e-30).all())
     assert bool(((got[:, 1] - rows.square().sum(0)).abs() <= 2e-5 * rows.square().sum(0) + 1e-30).all())
+
+
+def test_infinities_and_nan_stay_where_they_are(monkeypatch):
+    """An infinite or missing pixel reaches the outputs whose window holds it -- not those of the next image, whose halo it would be -- and a missing filter
+    value its own filter and that filter's statistics."""
+    monkeypatch.setenv("LARSCONV_HELD_MIN_TURNS", "1")
+    n, h, w = 256, 16, 16
+    d = lc.ConvDesc(n, 64, h, w, 64, 3, 3, 1, 1, 1, 1, lc.LC_BF16, lc.LC_NHWC)
+    assert gu.route(d, lc.LC_PASS_FWD) == "conv3x3_held" and gu.route(d, lc.LC_PASS_FWD, stats=True) == "conv3x3_held"
+    gen = torch.Generator(device=gu.DEV).manual_seed(29)
+    x = torch.randn((n, h, w, 64), generator=gen, device=gu.DEV).to(torch.bfloat16)
+    wt = (torch.randn((64, 3, 3, 64), generator=gen, device=gu.DEV) / 24).to(torch.bfloat16)
+    bad = x.clone()
+    bad[3, 0, 0, 63] = bad[7, h - 1, w - 1, 0] = float("inf")
+    bad[9, h - 1, 5, 31] = bad[11, 4, w - 1, 32] = float("nan")
+    want = torch.zeros((n, h, w), dtype=torch.bool, device=gu.DEV)
+    for i, p, q in ((3, 0, 0), (7, h - 1, w - 1), (9, h - 1, 5), (11, 4, w - 1)):
+        want[i, max(p - 1, 0):p + 2, max(q - 1, 0):q + 2] = True
+    y, clean = torch.empty_like(x), torch.empty_like(x)
+    lc.conv2d_fwd(d, x, wt, clean, None)
+    lc.conv2d_fwd(d, bad, wt, y, None)
+    torch.cuda.synchronize()
+    assert torch.equal(~torch.isfinite(y), want[..., None].expand_as(y))
+    assert torch.equal(y[~want].view(torch.int16), clean[~want].view(torch.int16))
+    assert not torch.isnan(y[3]).any() and torch.isnan(y[9][want[9]]).all()
+
+    filt = wt.clone()
+    filt[5, 2, 0, 40] = float("nan")
+    stats = torch.empty((lc.conv2d_fwd_stats_count(d), 64, 2), device=gu.DEV)
+    lc.conv2d_fwd_stats(d, x, filt, y, stats, None)
+    torch.cuda.synchronize()
+    others = [i for i in range(64) if i != 5]
+    assert torch.isnan(y[..., 5]).all() and torch.equal(y[..., others].view(torch.int16), clean[..., others].view(torch.int16))
+    assert torch.isnan(stats[:, 5].sum(0)).all() and torch.isfinite(stats[:, others]).all()

@@ -10,7 +10,7 @@ What is checked, per shape:
     output within the batch-norm tolerances (1e-4 tensor-scaled in fp32; one bf16 step in bf16).
 Shapes cover tiles the stream-K blocks share (their sums come from a read-back kernel), ragged last tiles in both
 directions, the few-channel first layer over 2x2 pixel blocks, the 256x256 tile of the bf16 kernel, and -- with the
-tile threshold lowered -- the slab kernel of the bf16 3x3 layers."""
+tile threshold lowered -- the slab kernel of the bf16 3x3 layers of at most 64 filters; the library is asked that the last two take theirs."""
 import numpy as np
 import pytest
 import torch
@@ -146,18 +146,32 @@ def test_statistics_with_the_fixup(name):
     _case(name, SHAPES_F32_ONLY[name], False)
 
 
+def _route(shape):
+    n, c, h, w, k, r, s, stride, pad = shape
+    return gu.route(lc.ConvDesc(n, c, h, w, k, r, s, stride, stride, pad, pad, lc.LC_BF16, NHWC), lc.LC_PASS_FWD, stats=True)
+
+
 @pytest.mark.parametrize("name", list(SHAPES_BF16_ONLY))
 def test_statistics_out_of_the_big_tile(name):
+    assert _route(SHAPES_BF16_ONLY[name]).startswith("conv_dma 256x256")
     _case(name, SHAPES_BF16_ONLY[name], True)
 
 
-@pytest.mark.parametrize("name", ["3x3_multi_tile", "ragged_rows_and_columns", "resnet_14_stage"])
+SLAB_SHAPES = {
+    "ragged_rows_and_columns": SHAPES["ragged_rows_and_columns"],      # 297 rows: two tiles and a ragged one; 40 columns
+    "slab_many_tiles": (8, 64, 28, 28, 64, 3, 3, 1, 1),                # 49 tiles
+    "slab_four_chunks": (5, 128, 15, 13, 48, 3, 3, 1, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(SLAB_SHAPES))
 def test_statistics_out_of_the_slab_kernel(name):
     import os
     old = os.environ.get("LARSCONV_SLAB_MIN_TILES")
     os.environ["LARSCONV_SLAB_MIN_TILES"] = "1"
     try:
-        _case(name, SHAPES[name], True)
+        assert _route(SLAB_SHAPES[name]) == "conv3x3_slab"
+        _case(name, SLAB_SHAPES[name], True)
     finally:
         if old is None:
             del os.environ["LARSCONV_SLAB_MIN_TILES"]
