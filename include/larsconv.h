@@ -316,7 +316,7 @@ lc_status relu_add_bwd_bnsums_grid_t(lc_dtype dtype, const void* y, const void* 
  * piece of the output's pixels, of the values written to y (as written: after rounding where y is bf16).  Every pixel
  * (n, p, q) lies in exactly one piece: 64 or 128 consecutive pixels in (n, p, q) order, or -- ResNet's first layer in
  * fp32, which has a kernel of its own -- a block of 4 x 16 pixels of one image, or -- bf16 3x3 layers from 64 channels to 33
- * to 64 filters -- every fourth 16 pixels of up to 590 consecutive ones.  They come out of the output tile's registers: 1/16 (fp32) or 1/8 (bf16) of y's bytes instead of a pass over y.
+ * to 64 filters -- every fourth 16 pixels of up to 494 consecutive ones.  They come out of the output tile's registers: 1/16 (fp32) or 1/8 (bf16) of y's bytes instead of a pass over y.
  * The count is 0 -- and conv2d_fwd_stats returns LC_ERR_UNSUPPORTED -- for layers whose plan has no such epilogue: NCHW,
  * groups > 1, and operands the MFMA kernels do not take (fp32 tensors off a 16-byte boundary, channel counts not a
  * multiple of 4 resp. 8); callers then use conv2d_fwd and batchnorm_fwd_t.  stats: DEVICE, 8-byte aligned, written in full.

@@ -1,4 +1,4 @@
-// What the implicit-GEMM kernels of conv_igemm.hip and conv_split.hip share: tile numbering, guarded loads, buffer descriptors, division by
+// What the implicit-GEMM kernels of conv_igemm.hip, conv_split.hip and conv_dma.hip share: tile numbering, guarded loads, buffer descriptors, division by
 // host constants, and the host-side work split.  Everything is local to the including file.
 #pragma once
 
@@ -87,14 +87,13 @@ inline SkPlan sk_plan(long long tiles, int nkt, int resident_blocks, bool allow_
 }
 
 // The same with the number of blocks for the tiles beyond the whole rounds chosen by what they cost.  Candidates: every such tile to S blocks in
-// equal parts -- S = 1 needs no fix-up at all -- or the k-steps end to end over the resident blocks.  The model, in us, fitted to
-// bf16 and fp32 layers of 1 to 512 images on a chip that does nothing else (beside a second stream `alone` is too short; whole training steps with
+// equal parts -- S = 1 needs no fix-up at all -- or the k-steps end to end over the resident blocks.  For fp32 backward-data (conv_split.hip) and what bf16 leaves the main
+// kernel; conv_dma.hip has a model of its own.  In us, fitted to layers of 1 to 512 images on a chip that does nothing else (beside a second stream `alone` is too short; whole training steps with
 // their filter gradients on one are 2 to 18 % faster than with the plain form all the same): a k-step takes `alone` where a block has its compute unit
 // to itself, `shared` per block where blocks take turns, see the callers; tiles that several blocks share cost 5 for the fix-up launch and
 // 0.018 per 128x128 part written and read again.  Before, every problem took
 // the last form with 8 k-steps per block or more, which splits tiles that the idle chip could take whole and joins tiles while compute units
-// stand idle (bf16: 1x1 over 512 channels, 16 images of 7x7 20.2 -> 10.4 us; over 64 channels, two of 56x56 22 -> 7.5; backward of 512 to 2048, 64 of
-// 7x7 39 -> 28; 3x3 over 256, 64 of 14x14 46 -> 30).
+// stand idle (fp32 backward-data, 3x3 over 128 channels, 32 images of 28x28 87 -> 60 us).
 struct StepCost {
     double alone, shared, tile;      // us, us, what a part costs in parts of 128x128
     int min_steps;                   // k-steps a block takes of a shared tile at least
