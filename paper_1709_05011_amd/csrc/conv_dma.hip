@@ -44,8 +44,10 @@ __device__ __forceinline__ unsigned lds_address(const void* ptr) {
 // pixel.  TMA and TMB: rows of pieces of the first and the second row of waves; each SIMD runs one wave of either kind, so a tile may have any
 // multiple of 16 rows.
 //
-// Bound: windows by the matrix pipe and power (3x3 over 256 channels, 512 images of 14x14: 98 to 106 us by the card's temperature, 1,110 to 1,200 TFLOP/s where a large
-// product reaches 1,377), 1x1 layers by memory (512 to 128 at 28x28 131 -> 108 us, 4.8 TB/s; 64 to 256 at 56x56 225 -> 197, 5.2).  With staging registers and k-steps of 32, half
+// Bound: windows of many columns by power (3x3 over 256 channels, 512 images of 14x14: 98 to 106 us by the card's temperature, 1,110 to 1,200 TFLOP/s where a large
+// product reaches 1,377; the pipe is busy in 57 % of the cycles at 1.87 to 1.97 GHz), 1x1 layers of few or of 256 and more columns on large images by memory (512 to 128 at 28x28
+// 131 -> 108 us, 4.8 TB/s; 64 to 256 at 56x56 225 -> 197, 5.2).  The 1x1 layers between (128 to 512, 256 to 1024) by neither: 3.0 to 3.5 TB/s and 30 to 40 % of the pipe.
+//  With staging registers and k-steps of 32, half
 // a line of a row per load, the same layers took 147, 131 and 225.  Measured and left out: the loads spread over the following step, wave priorities around
 // the matrix instructions (both equal or slower).
 //
@@ -675,11 +677,13 @@ lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_
 //
 // With so few columns a wave of a tile kernel reads as many bytes of LDS as it multiplies, and fetches its pixels nine times: 512 images of 56x56 took 174 us (slab
 // kernel of conv_igemm.hip, half of its fragment reads the filter's) to 189 (conv_dma_kernel) of the 86 its products take.  Here 1 KB of pixels feeds four matrix instructions, half of
-// what LDS gives.  Bound by the matrix pipe's power and memory together; us against the slab kernel in the same run: 512 images of 56x56 to 64 153 / 218 (with
+// what LDS gives.  Bound by its one wave per SIMD, beside which nothing hides a wait: the matrix pipe is busy in 42 % of the cycles at 2.03 GHz, LDS in 30 % (half of that bank conflicts), memory
+// moves 3.1 TB/s.  us against the slab kernel in the same run: 512 images of 56x56 to 64 153 / 218 (with
 // statistics 162 / 203), to 48 123 / 182, 256 images 66 / 90, 128 images of 112x112 149 / 200.
 //
 // A block is persistent; its tile is `tr` whole rows of an image, whose pixels with their halo go straight into LDS, one tile ahead: two planes of 32 channels (64
-// bytes a pixel), so that a half is an immediate offset, 16-byte pieces at piece ^ (column / 4 % 4), so that sixteen neighbouring pixels meet every bank once.  A tap is a
+// bytes a pixel), so that a half is an immediate offset, 16-byte pieces at piece ^ (column / 4 % 4), so that a piece of sixteen neighbouring pixels meets every bank once (by the counters half
+// of the cycles LDS is busy are conflicts all the same, against 2 to 7 % in conv_dma_kernel's windows: not explained yet).  A tap is a
 // displacement of the lane's address; rows above the image are masked and rows below it lie past the end of the buffer.  The four waves take 16 pixels at a time in turn;
 // a group's results leave while the next one is multiplied.  The sums run over the taps of 32 channels and then of the others, as in the slab kernel: the same bits.
 // ------------------------------------------------------------------------------------------------
@@ -916,7 +920,7 @@ bool conv_held_plan(const GemmConv& p, bool stats, ConvHeld* c) {
 // 8g + 0..3 (then 8g + 4..7) for g = 0..3, and LDS serves the lanes of two g at a time: those eight rows are spread over loads 1056 bytes apart (and, with
 // W = 64, over the halves of a load), which puts their pieces on eight distinct eighths of the banks.
 //
-// Bound: wide tiles by the matrix pipe and the transposing reads (96 bytes a clock with 128x64 per wave, of the 82 to 128 LDS gives), 1x1 layers by
+// Bound: wide tiles by power (256x256: the matrix pipe busy in 67 % of the cycles at 1.71 GHz, 128x256 on windows 56 % at 1.89; LDS 36 %), 1x1 layers by
 // memory.  Whole calls at batch 512, us, gathering / plain / slab kernel with staging registers before -> now: 3x3 over 256 channels at 14x14 174 -> 108 (1,090 TFLOP/s),
 // 3x3 over 128 at 28x28 188 -> 127, 1x1 stride 2 512 to 1024 at 28x28 177 -> 110, 512 to 128 1x1 at 28x28 130 -> 102 (5.0 TB/s), 256 to 64 at 56x56 209 -> 181.
 // ------------------------------------------------------------------------------------------------

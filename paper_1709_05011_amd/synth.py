@@ -6,7 +6,7 @@ norm, no update rule): only
 
 * a counter-based random generator (splitmix64 finaliser over a 64-bit
   counter, Box-Muller for normals) whose output depends on nothing but
-  ``(seed, index)``, so the same bytes are produced here, on the GPU machine and in
+  ``(seed, index)``, so the same bytes are produced on every machine and in
   any process;
 * rounding of fp32 draws to bf16-representable values (input preparation for
   the bf16 workload);
