@@ -22,8 +22,10 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "../../include/larsconv.h"
+#include "conv_common.h"
 #include "internal.h"
 
 namespace {
@@ -57,6 +59,21 @@ __device__ __forceinline__ void scale_shift(float gamma, float beta, float mean,
 
 // VEC consecutive elements of a tensor of fp32 values (T = float) or bf16 bit patterns (T = uint16_t) as floats and back
 // (bf16 -> fp32 is exact; fp32 -> bf16 rounds to nearest even).  One 16-byte access where VEC elements fill it.
+// NT: past the caches' usual keeping (streams that nothing reads again soon).
+typedef unsigned lc_u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT, typename R>
+__device__ __forceinline__ R fetch16(const void* p) {
+    static_assert(sizeof(R) == 16, "16-byte access");
+    if constexpr (NT) return __builtin_bit_cast(R, __builtin_nontemporal_load(static_cast<const lc_u32x4*>(p)));
+    else return *static_cast<const R*>(p);
+}
+template <bool NT, typename R>
+__device__ __forceinline__ void put16(void* p, const R& v) {
+    static_assert(sizeof(R) == 16, "16-byte access");
+    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(lc_u32x4, v), static_cast<lc_u32x4*>(p));
+    else *static_cast<R*>(p) = v;
+}
+
 template <typename T, int VEC>
 struct Pack;
 template <>
@@ -105,6 +122,11 @@ struct Pack<uint16_t, 8> {
         *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 };
+template <bool NT, typename T, int VEC>
+__device__ __forceinline__ typename Pack<T, VEC>::raw fetch_v(const T* p) {
+    if constexpr (sizeof(typename Pack<T, VEC>::raw) == 16) return fetch16<NT, typename Pack<T, VEC>::raw>(p);
+    else return Pack<T, VEC>::fetch(p);
+}
 template <typename T>
 __device__ __forceinline__ float widen(T v);
 template <>
@@ -141,14 +163,16 @@ template <typename T, int VEC, int MODE, int JOIN = 0>
 __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __restrict__ x, const T* __restrict__ dy,
                                                                   const float* __restrict__ mean, const float* __restrict__ inv_std,
                                                                   const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                                  BnGeom g, BnWorkspace ws, BnJoin<T> join = BnJoin<T>{}) {
+                                                                  BnGeom g, BnWorkspace ws, BnJoin<T> join, long long nt_rows) {
     constexpr bool STATS = MODE == kStats;
     constexpr int TU = 4;                                 // a tile is TU rows of the block's threads (the same for every form: equal sums)
     constexpr int U = JOIN ? 2 : 4;                       // rows a thread has in flight
     static_assert(JOIN == 0 || MODE == kSums, "the joined form makes an unmasked dy");
     __shared__ float red[kThreads * 2 * VEC];
     const int tx = threadIdx.x % g.tx, ty = threadIdx.x / g.tx;
-    const int c0 = (blockIdx.y * g.tx + tx) * VEC;
+    // blocks that share the rows of a slab are neighbours: together they read whole rows at about the same time
+    const unsigned bx = blockIdx.x / (unsigned)g.cblocks, by = blockIdx.x - bx * (unsigned)g.cblocks;
+    const int c0 = (by * g.tx + tx) * VEC;
     const bool live = c0 < g.C;
     float s0[VEC], s1[VEC], mu[VEC], is[VEC], sc[VEC], sh[VEC];
 #pragma unroll
@@ -178,30 +202,32 @@ __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __res
     // stretch of the tensor (a block that kept to a region of its own would make as many scattered streams as blocks).
     if (live) {
         const long long tile = (long long)g.ty * TU;
-        for (long long base = (long long)blockIdx.x * tile; base < g.M; base += (long long)gridDim.x * tile) {
-            if (base + tile <= g.M) {                                             // U loads per tensor, then U rows in order
+        for (long long base = (long long)bx * tile; base < g.M; base += (long long)g.slabs * tile) {
+            // U loads per tensor, then U rows in order.  NT: x (and out) go past the caches; NTJ: the tensors that the pass behind does not read
+            auto whole = [&](auto nt, auto ntj) {
+              constexpr bool NT = decltype(nt)::value, NTJ = decltype(ntj)::value;
               for (int part = 0; part < TU; part += U) {
                 const long long r = base + ty + (long long)part * g.ty;
                 typename Pack<T, VEC>::raw ra[U], rb[U], ry[JOIN ? U : 1], rc[JOIN == 2 ? U : 1];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const long long at = (r + (long long)u * g.ty) * g.C + c0;
-                    ra[u] = Pack<T, VEC>::fetch(x + at);
+                    ra[u] = fetch_v<NT, T, VEC>(x + at);
                     if constexpr (JOIN) {
-                        ry[u] = Pack<T, VEC>::fetch(join.y + at);
+                        ry[u] = fetch_v<NTJ, T, VEC>(join.y + at);
                         long long gat = at;
                         if (join.stride > 1) {
                             const long long gr = join.grid_row(r + (long long)u * g.ty);
                             gat = gr < 0 ? -1 : gr * g.C + c0;
                         }
                         rb[u] = typename Pack<T, VEC>::raw{};
-                        if (gat >= 0) rb[u] = Pack<T, VEC>::fetch(join.da + gat);
+                        if (gat >= 0) rb[u] = fetch_v<NTJ, T, VEC>(join.da + gat);
                         if constexpr (JOIN == 2) {
                             rc[u] = typename Pack<T, VEC>::raw{};
-                            if (gat >= 0) rc[u] = Pack<T, VEC>::fetch(join.db + gat);
+                            if (gat >= 0) rc[u] = fetch_v<NTJ, T, VEC>(join.db + gat);
                         }
                     } else if constexpr (!STATS) {
-                        rb[u] = Pack<T, VEC>::fetch(dy + at);
+                        rb[u] = fetch_v<NT, T, VEC>(dy + at);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);        // all loads are issued before the first is waited for
@@ -220,7 +246,7 @@ __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __res
                             if (!(yv[e] > 0.f)) b[e] = 0.f;
                         }
                         const typename Pack<T, VEC>::raw stored = Pack<T, VEC>::pack(b);
-                        *reinterpret_cast<typename Pack<T, VEC>::raw*>(join.out + (r + (long long)u * g.ty) * g.C + c0) = stored;
+                        put16<NT>(join.out + (r + (long long)u * g.ty) * g.C + c0, stored);
                         Pack<T, VEC>::unpack(stored, b);                           // the sums are those of the stored values
                     } else if constexpr (!STATS) {
                         Pack<T, VEC>::unpack(rb[u], b);
@@ -228,6 +254,11 @@ __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __res
                     add_row(a, b);
                 }
               }
+            };
+            if (base + tile <= g.M) {
+                if (base < nt_rows) whole(std::true_type{}, std::true_type{});
+                else if (JOIN && nt_rows > 0) whole(std::false_type{}, std::true_type{});
+                else whole(std::false_type{}, std::false_type{});
             } else {                                                              // the tensor's last, partial tile
                 for (long long q = base + ty; q < g.M; q += g.ty) {
                     float a[VEC], b[VEC];
@@ -272,11 +303,11 @@ __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __res
     // one thread per column adds the block's rows in order (double); columns of the channels beyond c are left out
     const int ncols = g.tx * 2 * VEC;
     for (int j = threadIdx.x; j < ncols; j += kThreads) {
-        const int ch2 = blockIdx.y * ncols + j;           // 2 * channel + which sum
+        const int ch2 = by * ncols + j;           // 2 * channel + which sum
         if (ch2 >= 2 * g.C) continue;
         double t = 0.0;
         for (int k = 0; k < g.ty; ++k) t += (double)red[k * ncols + j];
-        ws.partial[(size_t)blockIdx.x * g.C * 2 + ch2] = t;
+        ws.partial[(size_t)bx * g.C * 2 + ch2] = t;
     }
 }
 
@@ -298,29 +329,21 @@ __device__ __forceinline__ void load_coef(const float* __restrict__ p, float (&v
     }
 }
 
-// INV: the launch makes (threads in the grid) * VEC a multiple of c, so a thread meets the same channels on every
-// trip of its loop and keeps their coefficients in registers.
-template <typename T, int VEC, bool TWO, bool RELU, bool MASK, bool INV>
-__global__ void __launch_bounds__(kThreads) bn_apply_nhwc_kernel(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ out,
-                                                                 const float* __restrict__ coef, BnGeom g) {
-    const size_t total = (size_t)g.M * g.C / VEC;
-    const size_t first = blockIdx.x * (size_t)blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+// The coefficients of VEC channels and what they do to VEC values.
+template <int VEC, bool TWO, bool MASK>
+struct Coef {
     float p[VEC], r[VEC], q[TWO ? VEC : 1], ms[MASK ? VEC : 1], mh[MASK ? VEC : 1];
-    auto coefficients = [&](int c0) {
+    __device__ __forceinline__ void load(const float* __restrict__ coef, int c, int c0) {
         load_coef<VEC>(coef + c0, p);
-        load_coef<VEC>(coef + 2 * g.C + c0, r);
-        if constexpr (TWO) load_coef<VEC>(coef + g.C + c0, q);
+        load_coef<VEC>(coef + 2 * c + c0, r);
+        if constexpr (TWO) load_coef<VEC>(coef + c + c0, q);
         if constexpr (MASK) {
-            load_coef<VEC>(coef + 3 * g.C + c0, ms);
-            load_coef<VEC>(coef + 4 * g.C + c0, mh);
+            load_coef<VEC>(coef + 3 * c + c0, ms);
+            load_coef<VEC>(coef + 4 * c + c0, mh);
         }
-    };
-    if constexpr (INV) coefficients((int)((first * VEC) % g.C));
-    for (size_t i = first; i < total; i += stride) {
-        if constexpr (!INV) coefficients((int)((i * VEC) % g.C));
-        float va[VEC], vb[VEC], o[VEC];
-        Pack<T, VEC>::load(a + i * VEC, va);
-        if constexpr (TWO) Pack<T, VEC>::load(b + i * VEC, vb);
+    }
+    template <bool RELU>
+    __device__ __forceinline__ void apply(const float (&va)[VEC], const float (&vb)[VEC], float (&o)[VEC]) const {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             o[e] = fmaf(p[e], va[e], r[e]);
@@ -332,8 +355,61 @@ __global__ void __launch_bounds__(kThreads) bn_apply_nhwc_kernel(const T* __rest
             }
             if constexpr (RELU) o[e] = fmaxf(o[e], 0.f);
         }
+    }
+};
+
+// Whatever the vector path does not take: one group of channels a turn of a loop over the grid.
+template <typename T, int VEC, bool TWO, bool RELU, bool MASK>
+__global__ void __launch_bounds__(kThreads) bn_apply_nhwc_kernel(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ out,
+                                                                 const float* __restrict__ coef, BnGeom g) {
+    const size_t total = (size_t)g.M * g.C / VEC;
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+        Coef<VEC, TWO, MASK> k;
+        k.load(coef, g.C, (int)((i * VEC) % g.C));
+        float va[VEC], vb[VEC], o[VEC];
+        Pack<T, VEC>::load(a + i * VEC, va);
+        if constexpr (TWO) Pack<T, VEC>::load(b + i * VEC, vb);
+        k.template apply<RELU>(va, vb, o);
         Pack<T, VEC>::store(out + i * VEC, o);
     }
+}
+
+struct BnSpan {
+    size_t total;                // vectors in the tensor
+    unsigned groups;             // vectors in a pixel: c / VEC
+    unsigned step;               // threads of a block % groups
+    unsigned mul, shift;         // n / groups for n < 2^31
+};
+
+// The vector path.  Bound by memory, so by how the accesses meet there: one vector a thread and one wave a block, so that blocks start in the order of
+// their addresses and the chip works on one narrow stretch of each tensor at a time.  Blocks that go round a grid (16,384 of 256 threads) drift apart:
+// 822 MB read and 822 written took 331 us that way, 269 with a thread per vector, 254 with non-temporal accesses; two read and one written
+// 539, 412, 387.  More vectors a thread or more waves a block are 1 to 8 % slower.  The walk is from the end to the start, where the pass before (or the
+// convolution) left the last stretch in the memory-side cache.  Coefficients come from the first-level cache on every vector: holding them cost the order.
+// Forward and backward with these and the reduce pass's loads: fp32 411 MB 294 -> 254 and 373 -> 317 us, bf16 206 MB 122 -> 97 and 230 -> 174, 822 MB 568 -> 507
+// and 715 -> 638 (6.4 to 6.5 TB/s).
+constexpr int kApplyThreads = 64;
+template <typename T, int VEC, bool TWO, bool RELU, bool MASK, bool NTL, bool NTS>
+__global__ void __launch_bounds__(kApplyThreads) bn_apply_vec_kernel(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ out,
+                                                                     const float* __restrict__ coef, int c, BnSpan s) {
+    typedef typename Pack<T, VEC>::raw raw;
+    const unsigned block = gridDim.x - 1 - blockIdx.x;
+    const size_t base = (size_t)block * kApplyThreads;
+    if (base + threadIdx.x >= s.total) return;
+    const raw ra = fetch16<NTL, raw>(a + base * VEC + threadIdx.x * VEC);
+    raw rb{};
+    if constexpr (TWO) rb = fetch16<NTL, raw>(b + base * VEC + threadIdx.x * VEC);
+    // the channel group of the block's first vector, (block * threads) % groups, then the thread's
+    const unsigned turn = block - (unsigned)div_by((int)block, s.mul, s.shift) * s.groups;
+    const unsigned at = turn * s.step, first = at - (unsigned)div_by((int)at, s.mul, s.shift) * s.groups;
+    const unsigned mine = first + threadIdx.x, group = mine - (unsigned)div_by((int)mine, s.mul, s.shift) * s.groups;
+    Coef<VEC, TWO, MASK> k;
+    k.load(coef, c, (int)(group * VEC));
+    float va[VEC], vb[VEC], o[VEC];
+    Pack<T, VEC>::unpack(ra, va);
+    if constexpr (TWO) Pack<T, VEC>::unpack(rb, vb);
+    k.template apply<RELU>(va, vb, o);
+    put16<NTS>(out + base * VEC + threadIdx.x * VEC, Pack<T, VEC>::pack(o));
 }
 
 // ---------------- NCHW ----------------
@@ -586,16 +662,47 @@ inline unsigned stream_blocks(size_t items) {
     return (unsigned)(b ? b : 1);
 }
 
-// grid of the NHWC apply pass over `items` threads' worth of work; *inv: the grid was sized so that every thread stays on
-// one group of channels (grid * kThreads * vec is a multiple of c)
-inline unsigned apply_blocks(size_t items, int c, int vec, bool* inv) {
-    unsigned b = stream_blocks(items);
-    long long x = (long long)kThreads * vec, y = c;
-    while (y) { const long long t = x % y; x = y; y = t; }            // x = gcd(kThreads * vec, c)
-    const long long m = c / x;
-    *inv = m <= 64;
-    if (*inv) b = (unsigned)((b + m - 1) / m * m);
-    return b;
+static int knob(const char* n, int d) { const char* e = getenv(n); return e ? atoi(e) : d; }
+// The memory-side cache holds 256 MB.  A pass that another one reads behind streams all but the last kKeepBytes past it (non-temporal loads) and
+// leaves those there, where the next pass, which walks the other way, finds them (bf16, two tensors of 206 MB: 182 us for the backward pass with ordinary
+// loads throughout, 197 with none, 174 to 177 so; read alone, 822 MB come at 6.1 TB/s with ordinary loads and 6.8 without keeping).
+constexpr size_t kKeepBytes = (size_t)200 << 20;
+// Apply pass, tensors of this size and more: non-temporal loads, and stores.  Below, the data is in the caches or is wanted there: whole fp32 step at 32
+// images (tensors to 103 MB) 10.98 ms with loads from 64 MB and no such stores, 11.00 with stores from 64, 11.12 from 20; whole bf16 step at 512 images
+// 36.43 without either, 36.08 with the loads, 35.90 with the stores from 128 MB (35.94 from 20, 35.84 from 300, but then the 64-channel layer at 56x56,
+// whose tensors have 205 MB, takes 745 us instead of 712).
+constexpr size_t kStreamLoadBytes = (size_t)64 << 20, kStreamStoreBytes = (size_t)128 << 20;
+
+template <typename T, int VEC, int MODE, int JOIN = 0>
+void launch_reduce(const T* x, const T* dy, const float* mean, const float* inv_std, const float* gamma, const float* beta, const BnGeom& g,
+                   const BnWorkspace& ws, const BnJoin<T>& join, hipStream_t stream) {
+    const long long keep = (long long)(kKeepBytes / ((MODE == kStats ? 1 : 2) * sizeof(T) * (size_t)g.C));    // rows of the tensors the apply pass reads
+    hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, MODE, JOIN>), dim3((unsigned)(g.slabs * g.cblocks)), dim3(kThreads), 0, stream, x, dy, mean, inv_std,
+                       gamma, beta, g, ws, join, g.M > keep ? g.M - keep : 0);
+}
+
+template <typename T, int VEC, bool TWO, bool RELU, bool MASK>
+void launch_apply(const T* a, const T* b, T* out, const float* coef, const BnGeom& g, hipStream_t stream) {
+    const size_t total = (size_t)g.M * g.C / VEC, bytes = (size_t)g.M * g.C * sizeof(T);
+    if constexpr (VEC > 1) {
+        BnSpan s;
+        s.total = total;
+        s.groups = (unsigned)(g.C / VEC);
+        s.step = kApplyThreads % s.groups;
+        magic_for((int)s.groups, &s.mul, &s.shift);
+        // (the group's arithmetic is 31-bit and the grid's threads are a 32-bit number: more than 4 million channels or 64 GiB take the loop)
+        if (s.groups <= 1u << 20 && total <= 0xffffffffull - kApplyThreads) {
+            const dim3 grid((unsigned)((total + kApplyThreads - 1) / kApplyThreads));
+#define LC_BN_GO(L, S) \
+    hipLaunchKernelGGL((bn_apply_vec_kernel<T, VEC, TWO, RELU, MASK, L, S>), grid, dim3(kApplyThreads), 0, stream, a, b, out, coef, g.C, s)
+            if (bytes >= kStreamStoreBytes) LC_BN_GO(true, true);
+            else if (bytes >= kStreamLoadBytes) LC_BN_GO(true, false);
+            else LC_BN_GO(false, false);
+#undef LC_BN_GO
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bn_apply_nhwc_kernel<T, VEC, TWO, RELU, MASK>), dim3(stream_blocks(total)), dim3(kThreads), 0, stream, a, b, out, coef, g);
 }
 
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -656,18 +763,7 @@ lc_status bn_fwd_impl(const T* x, const float* gamma, const float* beta, const T
     // our own; the pieces are first folded into this pass's slab partials, piece t into slab t mod slabs, in order
     const size_t pivot_stride = layout == LC_NHWC ? 1 : (size_t)g.HW;       // the first pixel's value of channel ch sits at x[ch * stride]
     if (layout == LC_NHWC) {
-        const dim3 grid((unsigned)g.slabs, (unsigned)g.cblocks);
-        bool inv;
-        const dim3 agrid(apply_blocks(total / g.vec, c, g.vec, &inv));
-#define LC_BN_APPLY(VEC, TWO, RELU)                                                                                                   \
-    do {                                                                                                                              \
-        if (inv)                                                                                                                      \
-            hipLaunchKernelGGL((bn_apply_nhwc_kernel<T, VEC, TWO, RELU, false, true>), agrid, dim3(kThreads), 0, stream, x, residual, y, \
-                               ws.coef, g);                                                                                           \
-        else                                                                                                                          \
-            hipLaunchKernelGGL((bn_apply_nhwc_kernel<T, VEC, TWO, RELU, false, false>), agrid, dim3(kThreads), 0, stream, x, residual, y, \
-                               ws.coef, g);                                                                                           \
-    } while (0)
+#define LC_BN_APPLY(VEC, TWO, RELU) launch_apply<T, VEC, TWO, RELU, false>(x, residual, y, ws.coef, g, stream)
 #define LC_BN_FWD(VEC)                                                                                                                  \
     do {                                                                                                                                \
         if (stats && stats_tiles <= (size_t)kFusedPieces) {                                                                             \
@@ -679,8 +775,7 @@ lc_status bn_fwd_impl(const T* x, const float* gamma, const float* beta, const T
             hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, false>), fin_grid, fin_block, 0, stream, ws, nonef, 0, none, pivot_stride,    \
                                gamma, beta, save_mean, save_invstd, g, eps, second);                                                    \
         } else {                                                                                                                        \
-            hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, kStats>), grid, dim3(kThreads), 0, stream, x, none, nonef, nonef, nonef,  \
-                               nonef, g, ws);                                                                                           \
+            launch_reduce<T, VEC, kStats>(x, none, nonef, nonef, nonef, nonef, g, ws, BnJoin<T>{}, stream);  \
             hipLaunchKernelGGL((bn_finalize_fwd_kernel<T, false>), fin_grid, fin_block, 0, stream, ws, nonef, 0, x, pivot_stride,       \
                                gamma, beta, save_mean, save_invstd, g, eps, second);                                                    \
         }                                                                                                                               \
@@ -765,22 +860,13 @@ lc_status bn_bwd_impl(const T* x, const T* dy, const float* gamma, const float* 
     const bool mask = relu != 0;
     const float* mask_beta = mask ? beta : nullptr;
     if (layout == LC_NHWC) {
-        const dim3 grid((unsigned)g.slabs, (unsigned)g.cblocks);
-        bool inv;
-        const dim3 agrid(apply_blocks(total / g.vec, c, g.vec, &inv));
 #define LC_BN_BWD(VEC, MODE, MASK)                                                                                                       \
     do {                                                                                                                                \
         if (!presummed)                                                                                                                 \
-            hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, MODE>), grid, dim3(kThreads), 0, stream, x, dy, save_mean, save_invstd,    \
-                               gamma, mask_beta, g, ws, BnJoin<T>{});                                                                   \
+            launch_reduce<T, VEC, MODE>(x, dy, save_mean, save_invstd, gamma, mask_beta, g, ws, BnJoin<T>{}, stream); \
         hipLaunchKernelGGL(bn_finalize_bwd_kernel, fin_grid, fin_block, 0, stream, ws, gamma, mask_beta, save_mean, save_invstd, dgamma, \
                            dbeta, g);                                                                                                   \
-        if (inv)                                                                                                                        \
-            hipLaunchKernelGGL((bn_apply_nhwc_kernel<T, VEC, true, false, MASK, true>), agrid, dim3(kThreads), 0, stream, x, dy, dx,     \
-                               ws.coef, g);                                                                                             \
-        else                                                                                                                            \
-            hipLaunchKernelGGL((bn_apply_nhwc_kernel<T, VEC, true, false, MASK, false>), agrid, dim3(kThreads), 0, stream, x, dy, dx,    \
-                               ws.coef, g);                                                                                             \
+        launch_apply<T, VEC, true, false, MASK>(x, dy, dx, ws.coef, g, stream);                                                          \
     } while (0)
         if constexpr (kF32) {
             if (g.vec == 4) { if (mask) LC_BN_BWD(4, kMaskedSums, true); else LC_BN_BWD(4, kSums, false); }
@@ -827,7 +913,6 @@ lc_status bn_join_impl(const T* y, const T* da, const T* db, T* dx, const T* x_b
     ws.coef = reinterpret_cast<float*>(static_cast<char*>(workspace) + coef_off);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     lc_begin_call();
-    const dim3 grid((unsigned)g.slabs, (unsigned)g.cblocks);
     const float* nonef = nullptr;
     const T* none = nullptr;
     BnJoin<T> join{y, da, db, dx};
@@ -839,11 +924,9 @@ lc_status bn_join_impl(const T* y, const T* da, const T* db, T* dx, const T* x_b
         join.hwq = ((h + stride - 1) / stride) * join.wq;
     }
     if (db)
-        hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, kWide<T>, kSums, 2>), grid, dim3(kThreads), 0, stream, x_bn, none, save_mean, save_invstd,
-                           nonef, nonef, g, ws, join);
+        launch_reduce<T, kWide<T>, kSums, 2>(x_bn, none, save_mean, save_invstd, nonef, nonef, g, ws, join, stream);
     else
-        hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, kWide<T>, kSums, 1>), grid, dim3(kThreads), 0, stream, x_bn, none, save_mean, save_invstd,
-                           nonef, nonef, g, ws, join);
+        launch_reduce<T, kWide<T>, kSums, 1>(x_bn, none, save_mean, save_invstd, nonef, nonef, g, ws, join, stream);
     return lc_end_call();
 }
 
