@@ -59,21 +59,6 @@ __device__ __forceinline__ void scale_shift(float gamma, float beta, float mean,
 
 // VEC consecutive elements of a tensor of fp32 values (T = float) or bf16 bit patterns (T = uint16_t) as floats and back
 // (bf16 -> fp32 is exact; fp32 -> bf16 rounds to nearest even).  One 16-byte access where VEC elements fill it.
-// NT: past the caches' usual keeping (streams that nothing reads again soon).
-typedef unsigned lc_u32x4 __attribute__((ext_vector_type(4)));
-template <bool NT, typename R>
-__device__ __forceinline__ R fetch16(const void* p) {
-    static_assert(sizeof(R) == 16, "16-byte access");
-    if constexpr (NT) return __builtin_bit_cast(R, __builtin_nontemporal_load(static_cast<const lc_u32x4*>(p)));
-    else return *static_cast<const R*>(p);
-}
-template <bool NT, typename R>
-__device__ __forceinline__ void put16(void* p, const R& v) {
-    static_assert(sizeof(R) == 16, "16-byte access");
-    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(lc_u32x4, v), static_cast<lc_u32x4*>(p));
-    else *static_cast<R*>(p) = v;
-}
-
 template <typename T, int VEC>
 struct Pack;
 template <>
@@ -124,7 +109,7 @@ struct Pack<uint16_t, 8> {
 };
 template <bool NT, typename T, int VEC>
 __device__ __forceinline__ typename Pack<T, VEC>::raw fetch_v(const T* p) {
-    if constexpr (sizeof(typename Pack<T, VEC>::raw) == 16) return fetch16<NT, typename Pack<T, VEC>::raw>(p);
+    if constexpr (sizeof(typename Pack<T, VEC>::raw) == 16) return lc_fetch16<NT, typename Pack<T, VEC>::raw>(p);
     else return Pack<T, VEC>::fetch(p);
 }
 template <typename T>
@@ -246,7 +231,7 @@ __global__ void __launch_bounds__(kThreads) bn_reduce_nhwc_kernel(const T* __res
                             if (!(yv[e] > 0.f)) b[e] = 0.f;
                         }
                         const typename Pack<T, VEC>::raw stored = Pack<T, VEC>::pack(b);
-                        put16<NT>(join.out + (r + (long long)u * g.ty) * g.C + c0, stored);
+                        lc_put16<NT>(join.out + (r + (long long)u * g.ty) * g.C + c0, stored);
                         Pack<T, VEC>::unpack(stored, b);                           // the sums are those of the stored values
                     } else if constexpr (!STATS) {
                         Pack<T, VEC>::unpack(rb[u], b);
@@ -396,9 +381,9 @@ __global__ void __launch_bounds__(kApplyThreads) bn_apply_vec_kernel(const T* __
     const unsigned block = gridDim.x - 1 - blockIdx.x;
     const size_t base = (size_t)block * kApplyThreads;
     if (base + threadIdx.x >= s.total) return;
-    const raw ra = fetch16<NTL, raw>(a + base * VEC + threadIdx.x * VEC);
+    const raw ra = lc_fetch16<NTL, raw>(a + base * VEC + threadIdx.x * VEC);
     raw rb{};
-    if constexpr (TWO) rb = fetch16<NTL, raw>(b + base * VEC + threadIdx.x * VEC);
+    if constexpr (TWO) rb = lc_fetch16<NTL, raw>(b + base * VEC + threadIdx.x * VEC);
     // the channel group of the block's first vector, (block * threads) % groups, then the thread's
     const unsigned turn = block - (unsigned)div_by((int)block, s.mul, s.shift) * s.groups;
     const unsigned at = turn * s.step, first = at - (unsigned)div_by((int)at, s.mul, s.shift) * s.groups;
@@ -409,7 +394,7 @@ __global__ void __launch_bounds__(kApplyThreads) bn_apply_vec_kernel(const T* __
     Pack<T, VEC>::unpack(ra, va);
     if constexpr (TWO) Pack<T, VEC>::unpack(rb, vb);
     k.template apply<RELU>(va, vb, o);
-    put16<NTS>(out + base * VEC + threadIdx.x * VEC, Pack<T, VEC>::pack(o));
+    lc_put16<NTS>(out + base * VEC + threadIdx.x * VEC, Pack<T, VEC>::pack(o));
 }
 
 // ---------------- NCHW ----------------

@@ -23,6 +23,21 @@ __device__ __forceinline__ uint32_t lc_bf16x2_rne(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, lc_bf16x2));
 }
 
+// 16-byte accesses.  NT: non-temporal, for streams that nothing reads again soon; a line that the caches hold is still found there.
+typedef unsigned lc_u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT, typename R>
+__device__ __forceinline__ R lc_fetch16(const void* p) {
+    static_assert(sizeof(R) == 16, "16-byte access");
+    if constexpr (NT) return __builtin_bit_cast(R, __builtin_nontemporal_load(static_cast<const lc_u32x4*>(p)));
+    else return *static_cast<const R*>(p);
+}
+template <bool NT, typename R>
+__device__ __forceinline__ void lc_put16(void* p, const R& v) {
+    static_assert(sizeof(R) == 16, "16-byte access");
+    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(lc_u32x4, v), static_cast<lc_u32x4*>(p));
+    else *static_cast<R*>(p) = v;
+}
+
 // ---- small device-side utilities (layout.hip) ----
 void lc_bf16_to_f32(const void* src, float* dst, size_t count, hipStream_t stream);
 void lc_f32_to_bf16(const float* src, void* dst, size_t count, hipStream_t stream);
