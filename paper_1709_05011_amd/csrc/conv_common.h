@@ -14,6 +14,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kBufferWords3 = 0x00020000u;       // raw buffer, 32-bit data format
+constexpr int kNonTemporal = 2;                       // policy operand of the buffer instructions: the nt bit
 constexpr unsigned kBufferBytes = 0x80000000u;        // buffer size given to the hardware; offsets with bit 31 set read zeros
 
 // Blocks are dealt round-robin to the 8 XCDs, each with its own L2.  Re-number them so that every

@@ -21,6 +21,9 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ void load_to_lds(const u32x4& rsrc, unsigned voff, int soff, unsigned lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
+__device__ __forceinline__ void load_to_lds_nt(const u32x4& rsrc, unsigned voff, int soff, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" : : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
 __device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(base);
     return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a), (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32)),
@@ -70,7 +73,7 @@ constexpr unsigned kNoRow = 0x80000000u;                   // row -2^15: outside
 // What leaves with a tile: whole 16-byte pieces of rows (columns a multiple of 8); any number of columns and the statistics; any number of columns; the pixels
 // of a stride grid.
 enum ConvDmaOut { kRows, kStats, kAny, kGrid };
-enum ConvDmaIn { kChunks, kPadded, kPieces, kRuns, kTaps };
+enum ConvDmaIn { kChunks, kPadded, kPieces, kRuns, kTaps, kOnce };
 
 template <int TMA, int TMB, int TN, int WN, ConvDmaIn IN, ConvDmaOut OUT>
 __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma pp) {
@@ -106,7 +109,7 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
     const int piece = (lane & 7) ^ (((wave & 1) * 4 + (lrow >> 1)) & 7);     // row / 2 % 8 of every row this lane loads: 8 * (i * NW + wave) + lrow
     unsigned a_voff[LA], a_inv[LA];                        // kTaps: a_inv is the place of the window's first tap in the image, row in the upper half
     u32x4 a_rsrc = {0, 0, 0, 0}, b_rsrc = a_rsrc;
-    constexpr bool by_tap = IN == kChunks || IN == kPadded || IN == kRuns;
+    constexpr bool by_tap = IN == kChunks || IN == kPadded || IN == kRuns || IN == kOnce;
     const unsigned b_voff = (unsigned)((wave * 8 + lrow) * Kg_ * 2 + piece * 16);
     int u_c = 0, u_tap = 0, u_r = 0, u_s = 0;              // first channel and tap; kPieces, kTaps: u_c is the k-step
     int u_first = 0, l_stop = 0;                           // kRuns: the run's first tap; the k-step behind the run or the segment
@@ -208,7 +211,8 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             if (NA % NW != 0 && load >= NA) return;
             if constexpr (by_tap) {
                 const unsigned vo = (((a_inv[l] << (31 - (u_tap - u_first))) & kBufferBytes) | a_voff[l]) | v_bad;
-                load_to_lds(a_rsrc, vo, ((u_r * Wi_ + u_s) * Ci_ + u_c) * 2, l_lds + load * 1024);
+                if constexpr (IN == kOnce) load_to_lds_nt(a_rsrc, vo, ((u_r * Wi_ + u_s) * Ci_ + u_c) * 2, l_lds + load * 1024);
+                else load_to_lds(a_rsrc, vo, ((u_r * Wi_ + u_s) * Ci_ + u_c) * 2, l_lds + load * 1024);
             } else if constexpr (IN == kTaps) {            // a sign bit of the place, or of what is left to the last row and column: outside
                 const s16x2 at = __builtin_bit_cast(s16x2, a_inv[l]) + v_rs;
                 const unsigned out = __builtin_bit_cast(unsigned, at) | __builtin_bit_cast(unsigned, last - at);
@@ -346,10 +350,12 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
 #pragma unroll
                     for (int e = 0; e < 16 / RPI; ++e) {
                         if constexpr (!scatter) {
-                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
+                            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, kNonTemporal);
+                            else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
                         } else {
                             const unsigned off = row_off(mw + i * 16 + e * RPI + lr);
-                            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, 0);
+                            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, kNonTemporal);
+                            else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, 0);
                         }
                     }
                 } else {
@@ -612,6 +618,11 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
 }
 bool conv_dma_shares(const ConvDmaPlan& c) { return c.sk.sk_iters != (long long)c.sk.sk_blocks * c.nkt; }
 
+// kOnce: kChunks with the rows past the caches.  Each is read once -- a 1x1 window, one tile of columns -- and the memory-side cache does not hold the image (us, 512 to 128
+// at 28x28, 512 images 105 / 102, 256 to 64 at 56x56 188 / 182).  Windows and further tiles of columns read them again: 3x3 over 128 channels 130 / 167, 256 to 1024 at 14x14 72 / 82.
+// (An instance of its own: the choice within the loop cost windows 1 to 2 %.)
+bool conv_dma_once(const GemmConv& p, int bn) { return p.N <= bn && p.R * p.S == 1 && !p.scatter && ((p.N | p.ldd) & 7) == 0 && (double)p.M * p.Ci * 2 >= 256e6; }
+
 template <int TMA, int TMB, int TN, int WN>
 lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_t stream) {
     constexpr int BM = 16 * (TMA + TMB), BN = 16 * TN * WN, threads = 2 * WN * 64;
@@ -648,14 +659,22 @@ lc_status launch_conv_dma(const GemmConv& q, const ConvDmaPlan& plan, hipStream_
         if constexpr (WN != 4 || (TMA == 8 && TMB == 8)) {
             if (p.stats) return launch.template operator()<IN, kStats>();
         }
-        if constexpr (WN != 4) {
+        if constexpr (WN != 4 && IN != kOnce) {
             if (p.scatter) return launch.template operator()<IN, kGrid>();
             if (((p.N | p.ldd) & 7) != 0) return launch.template operator()<IN, kAny>();
         }
         launch.template operator()<IN, kRows>();
     };
     switch (conv_dma_in(p)) {
-        case kChunks: out.template operator()<kChunks>(); break;
+        case kChunks:
+            if constexpr (TMA == TMB && TMA != 7 && TMA != 6) {
+                if (conv_dma_once(p, BN)) {
+                    out.template operator()<kOnce>();
+                    break;
+                }
+            }
+            out.template operator()<kChunks>();
+            break;
         case kPadded: out.template operator()<kPadded>(); break;
         case kPieces: out.template operator()<kPieces>(); break;
         default:
@@ -788,7 +807,8 @@ __global__ void __launch_bounds__(256, 1) conv3x3_held_kernel(const ConvHeld pp)
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int m = (turn * 4 + wave) * 16 + e * 8;
-            __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, 0);
+            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, kNonTemporal);
+            else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, 0);
             if (STATS) {
                 const unsigned in = m + lane / 8 < valid ? ~0u : 0u;
 #pragma unroll
@@ -977,8 +997,9 @@ inline int wgrad_chain_stages(const GemmWgrad& p) {
     return std::max(2, rows / 64 * 2);
 }
 
-// Columns of the result: one pixel's channels in 256-wide pieces (or, PLAIN -- a 1x1 window with stride 1 and no padding -- any of the widths).
-template <int BM, int BN, int WM, int WN, int NS, bool PLAIN>
+// Columns of the result: one pixel's channels in 256-wide pieces (or, kPlain -- a 1x1 window with stride 1 and no padding -- any of the widths).
+enum WgradIn { kWindow, kPlain, kAround };
+template <int BM, int BN, int WM, int WN, int NS, WgradIn IN>
 __global__ void __launch_bounds__(WM* WN * 64, BM * BN <= 64 * 128 ? 3 : 2) wgrad_dma_kernel(const WgradDma pp) {
     const GemmWgrad& p = pp.g;
     using RA = WgradRows<BM>;
@@ -1006,14 +1027,15 @@ __global__ void __launch_bounds__(WM* WN * 64, BM * BN <= 64 * 128 ? 3 : 2) wgra
     // dY: rows past the end of the split lie past the end of the buffer
     const uint16_t* const DY = static_cast<const uint16_t*>(p.dy);
     const uint16_t* const X = static_cast<const uint16_t*>(p.x);
-    const int rows = max(m_end - m_begin, 0);
-    const u32x4 a_rsrc = buffer_words(DY + (long long)m_begin * K_, (unsigned)rows * (unsigned)K_ * 2u);
+    constexpr bool PLAIN = IN != kWindow, AROUND = IN == kAround;      // AROUND: stage t of split z is rows 32 * (t * splits + z) and on
+    const int rows = AROUND ? max(((p.M + 31) / 32 - z + p.splits - 1) / p.splits, 0) * 32 : max(m_end - m_begin, 0);
+    u32x4 a_rsrc = buffer_words(DY + (long long)m_begin * K_, (unsigned)rows * (unsigned)K_ * 2u);
     const int a_col = k0 + RA::lane_col(lane);
     const unsigned a_voff = a_col < K_ ? (unsigned)(RA::lane_row(lane) * K_ + a_col) * 2u : kBufferBytes;
     // X
     const int img_first = PLAIN ? 0 : m_begin / (P_ * Q_);
     const int phb = max(ph_, 0), pwb = max(pw_, 0);
-    const u32x4 b_rsrc = PLAIN ? buffer_words(X + (long long)m_begin * C_, (unsigned)rows * (unsigned)C_ * 2u)
+    u32x4 b_rsrc = PLAIN ? buffer_words(X + (long long)m_begin * C_, (unsigned)rows * (unsigned)C_ * 2u)
                                : buffer_words(X + ((long long)img_first * H_ * W_ - ((long long)phb * W_ + pwb)) * C_, kBufferBytes);
     const int b_col = j0 + RB::lane_col(lane);
     unsigned b_voff = kBufferBytes, b_up = 0;
@@ -1060,16 +1082,28 @@ __global__ void __launch_bounds__(WM* WN * 64, BM * BN <= 64 * 128 ? 3 : 2) wgra
     auto load_one = [&](int l) __attribute__((always_inline)) {       // load l of this wave's LPW for the stage at mt
         if (l < LA) {
             const int load = l * NW + wave;
-            load_to_lds(a_rsrc, a_voff, (mt + RA::first_row(load)) * K_ * 2, l_lds + load * RA::kPitch);
+            if constexpr (AROUND) load_to_lds_nt(a_rsrc, a_voff, RA::first_row(load) * K_ * 2, l_lds + load * RA::kPitch);
+            else load_to_lds(a_rsrc, a_voff, (mt + RA::first_row(load)) * K_ * 2, l_lds + load * RA::kPitch);
         } else {
             const int load = (l - LA) * NW + wave;
             const unsigned dst = l_lds + RA::kBytes + load * RB::kPitch;
-            if constexpr (PLAIN) load_to_lds(b_rsrc, b_voff, (mt + RB::first_row(load)) * C_ * 2, dst);
+            if constexpr (AROUND) load_to_lds_nt(b_rsrc, b_voff, RB::first_row(load) * C_ * 2, dst);
+            else if constexpr (PLAIN) load_to_lds(b_rsrc, b_voff, (mt + RB::first_row(load)) * C_ * 2, dst);
             else load_to_lds(b_rsrc, ((px[l - LA].y << b_up) & kBufferBytes) | (b_voff + px[l - LA].x), 0, dst);
         }
     };
+    auto place_stage = [&]() __attribute__((always_inline)) {
+        if constexpr (AROUND) {
+            const long long first = ((long long)(mt / 32) * p.splits + z) * 32;
+            const int left = (int)max(0ll, min(32ll, (long long)p.M - first));
+            a_rsrc = buffer_words(DY + first * K_, (unsigned)left * (unsigned)K_ * 2u);
+            b_rsrc = buffer_words(X + first * C_, (unsigned)left * (unsigned)C_ * 2u);
+        }
+    };
+    place_stage();
     auto next_stage = [&]() __attribute__((always_inline)) {
         mt += 32;
+        place_stage();
         l_lds += STAGE;
         if (l_lds == lds0 + NS * STAGE) l_lds = lds0;
     };
@@ -1210,11 +1244,11 @@ __global__ void __launch_bounds__(WM* WN * 64, BM * BN <= 64 * 128 ? 3 : 2) wgra
     }
 }
 
-template <int BM, int BN, int WM, int WN, int NS, bool PLAIN>
+template <int BM, int BN, int WM, int WN, int NS, WgradIn IN>
 lc_status launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
-    constexpr int lds = NS * (WgradRows<BM>::kBytes + WgradRows<BN>::kBytes) + (PLAIN ? 0 : WM * WN * 512);
+    constexpr int lds = NS * (WgradRows<BM>::kBytes + WgradRows<BN>::kBytes) + (IN != kWindow ? 0 : WM * WN * 512);
     static const bool once =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_dma_kernel<BM, BN, WM, WN, NS, PLAIN>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) ==
+        hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_dma_kernel<BM, BN, WM, WN, NS, IN>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) ==
         hipSuccess;
     if (!once) return LC_ERR_LAUNCH;
     const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
@@ -1222,7 +1256,7 @@ lc_status launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
     WgradDma q = {p, wgrad_chain_stages(p), 0, 0, 0, 0};
     magic_for(p.Q, &q.q_mul, &q.q_shift);
     magic_for(p.P, &q.p_mul, &q.p_shift);
-    hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WM, WN, NS, PLAIN>), dim3((unsigned)(tiles * p.splits)), dim3(WM * WN * 64), lds, stream, q);
+    hipLaunchKernelGGL((wgrad_dma_kernel<BM, BN, WM, WN, NS, IN>), dim3((unsigned)(tiles * p.splits)), dim3(WM * WN * 64), lds, stream, q);
     return lc_end_call();
 }
 
@@ -1398,7 +1432,11 @@ lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
     if (!aligned16(p.dy) || !aligned16(p.x)) return LC_ERR_ALIGN;
     const bool plain = wgrad_plain(p);
     auto go = [&]<int BM, int BN, int WM, int WN, int NS>() {
-        return plain ? launch_wgrad_dma<BM, BN, WM, WN, NS, true>(p, stream) : launch_wgrad_dma<BM, BN, WM, WN, NS, false>(p, stream);
+        // One tile of large operands, bound by memory: all blocks work on one narrow stretch of both (and past the caches: nothing reads them again) instead of each
+        // on rows of its own.  64 to 256 1x1, 512 images of 56x56 173 -> 150 us (6.8 TB/s), 256 to 64 172 -> 152.  Several tiles read the same rows, and the L2s
+        // hold them better in one place: 512 to 128 at 28x28 104 / 108, 512 to 2048 at 7x7 64 / 73.
+        if (plain && p.K <= BM && p.J <= BN && (double)p.M * (p.K + p.C) * 2 >= 128e6) return launch_wgrad_dma<BM, BN, WM, WN, NS, kAround>(p, stream);
+        return plain ? launch_wgrad_dma<BM, BN, WM, WN, NS, kPlain>(p, stream) : launch_wgrad_dma<BM, BN, WM, WN, NS, kWindow>(p, stream);
     };
     switch (p.dma_bm * 1000 + p.dma_bn) {
         case 256256: return go.template operator()<256, 256, 2, 4, 4>();

@@ -529,6 +529,8 @@ __global__ void __launch_bounds__(256, kPkBlocksPerCu) conv_gemm_pk_kernel(const
                 // byte selectors of v_perm_b32 over {received, own}: even lanes keep their low half and take the
                 // neighbour's low half above it; odd lanes take the neighbour's high half below their own high half
                 const unsigned perm_sel = odd ? 0x03020706u : 0x05040100u;
+                auto store = [&](auto policy) __attribute__((always_inline)) {
+                constexpr int kPolicy = decltype(policy)::value;
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -546,17 +548,20 @@ __global__ void __launch_bounds__(256, kPkBlocksPerCu) conv_gemm_pk_kernel(const
                                 if (pairs) {
                                     // u = {row r0 | row r0 + 1} of this lane's column; swap with the neighbouring lane
                                     const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, kPolicy);
                                 } else {
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
-                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, kPolicy);
+                                    __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, kPolicy);
                                 }
                             } else {
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)d_voff[j], soff, 0);
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v + 1]), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, 0);
+                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), d_rsrc, (int)d_voff[j], soff, kPolicy);
+                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v + 1]), d_rsrc, (int)d_voff[j], soff + ldd_ * ES, kPolicy);
                             }
                         }
                     }
+                };
+                if (p.stream_d) store(std::integral_constant<int, kNonTemporal>{});
+                else store(std::integral_constant<int, 0>{});
             }
             {
                 if (p.stats) {
@@ -1037,6 +1042,8 @@ __global__ void __launch_bounds__(256, 2) conv3x3_slab_kernel(const GemmConv p) 
             if (pairs && col < N_) d_voff[j] = (unsigned)(((4 * fhalf + odd) * ldd_ + (col & ~1)) * 2);
         }
         const unsigned perm_sel = odd ? 0x03020706u : 0x05040100u;
+        auto store = [&](auto policy) __attribute__((always_inline)) {
+        constexpr int kPolicy = decltype(policy)::value;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1048,13 +1055,16 @@ __global__ void __launch_bounds__(256, 2) conv3x3_slab_kernel(const GemmConv p) 
                     const unsigned u = lc_bf16x2_rne(acc[i][j][v], acc[i][j][v + 1]);
                     if (pairs) {
                         const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(got, u, perm_sel), d_rsrc, (int)d_voff[j], soff, kPolicy);
                     } else {
-                        __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, 0);
-                        __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * 2, 0);
+                        __builtin_amdgcn_raw_buffer_store_b16((short)(u & 0xffffu), d_rsrc, (int)d_voff[j], soff, kPolicy);
+                        __builtin_amdgcn_raw_buffer_store_b16((short)(u >> 16), d_rsrc, (int)d_voff[j], soff + ldd_ * 2, kPolicy);
                     }
                 }
             }
+        };
+        if (p.stream_d) store(std::integral_constant<int, kNonTemporal>{});
+        else store(std::integral_constant<int, 0>{});
     }
     if (p.stats) {
         // per column, the sum and the sum of squares of the stored (rounded) values over this wave's 64 rows, as in the main kernel
@@ -2127,7 +2137,9 @@ size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
     }
 }
 
-lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream) {
+lc_status lc_launch_conv_gemm(const GemmConv& q, hipStream_t stream) {
+    GemmConv p = q;
+    p.stream_d = lc_stream_out((double)p.M * p.N * (p.bf16 ? 2 : 4), p.d, (size_t)p.ldd * (p.bf16 ? 2 : 4));
     if (p.stats && lc_conv_gemm_stats_tiles(p) == 0) return LC_ERR_UNSUPPORTED;
     size_t lds;
     switch (conv_kernel(p, p.stats != nullptr, &lds)) {

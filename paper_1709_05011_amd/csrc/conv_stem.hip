@@ -126,14 +126,22 @@ __global__ void __launch_bounds__(256, 2) conv_stem_f32_kernel(const StemConv p)
         // the wave's 4 rows x 16 columns of output pixels, 64 channels
         const int tx = tile % tiles_x, t2 = tile / tiles_x, ty = t2 % tiles_y, img = t2 / tiles_y;
         float* yo = p.y + (((long long)img * p.P + ty * TH + 4 * wave) * p.Q + tx * TW) * N + 4 * half * N + m;
+        auto store = [&](auto past) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = 2 * i + (v >> 3), col = 8 * ((v >> 2) & 1) + (v & 3);
+                for (int v = 0; v < 16; ++v) {
+                    const int row = 2 * i + (v >> 3), col = 8 * ((v >> 2) & 1) + (v & 3);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) yo[(row * p.Q + col) * N + 32 * j] = acc[i][j][v];
-            }
+                    for (int j = 0; j < 2; ++j) {
+                        float* const at = yo + (row * p.Q + col) * N + 32 * j;
+                        if constexpr (decltype(past)::value) __builtin_nontemporal_store(acc[i][j][v], at);
+                        else *at = acc[i][j][v];
+                    }
+                }
+        };
+        if (p.stream_y) store(std::true_type{});
+        else store(std::false_type{});
         if (p.stats) {
             typedef float flt2 __attribute__((ext_vector_type(2)));
             flt2* st = reinterpret_cast<flt2*>(p.stats) + ((size_t)tile * 4 + wave) * N;
@@ -377,6 +385,7 @@ __global__ void __launch_bounds__(256, 2) conv_stem_bf16_kernel(const StemConvBf
         uint16_t* yo = p.y + (((long long)img * p.P + ty * TH + 4 * wave) * p.Q + tx * TW) * N + (4 * kb + odd) * N + (m & ~1);
         const unsigned perm_sel = odd ? 0x03020706u : 0x05040100u;
         float sum[2] = {0.f, 0.f}, sq[2] = {0.f, 0.f};
+        auto store = [&](auto past) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -389,7 +398,9 @@ __global__ void __launch_bounds__(256, 2) conv_stem_bf16_kernel(const StemConvBf
                     const f32x2 pr = {acc[i][j][v], acc[i][j][v + 1]};
                     const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
                     const unsigned got = (unsigned)__builtin_amdgcn_mov_dpp((int)u, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-                    *reinterpret_cast<unsigned*>(yo + (row * p.Q + col) * N + 32 * j) = __builtin_amdgcn_perm(got, u, perm_sel);
+                    unsigned* const at = reinterpret_cast<unsigned*>(yo + (row * p.Q + col) * N + 32 * j);
+                    if constexpr (decltype(past)::value) __builtin_nontemporal_store(__builtin_amdgcn_perm(got, u, perm_sel), at);
+                    else *at = __builtin_amdgcn_perm(got, u, perm_sel);
                     const float f0 = __uint_as_float(u << 16), f1 = __uint_as_float(u & 0xffff0000u);
                     sum[j] += f0;
                     sq[j] = fmaf(f0, f0, sq[j]);
@@ -397,6 +408,9 @@ __global__ void __launch_bounds__(256, 2) conv_stem_bf16_kernel(const StemConvBf
                     sq[j] = fmaf(f1, f1, sq[j]);
                 }
             }
+        };
+        if (p.stream_y) store(std::true_type{});
+        else store(std::false_type{});
         if (p.stats) {
             typedef float flt2 __attribute__((ext_vector_type(2)));
             flt2* st = reinterpret_cast<flt2*>(p.stats) + ((size_t)tile * 4 + wave) * N;
@@ -576,8 +590,10 @@ lc_status lc_launch_conv_stem_wgrad_bf16(const StemWgradBf16& p, int blocks, hip
     return lc_end_call();
 }
 
-lc_status lc_launch_conv_stem_bf16(const StemConvBf16& p, hipStream_t stream) {
+lc_status lc_launch_conv_stem_bf16(const StemConvBf16& q, hipStream_t stream) {
     using namespace stemb;
+    StemConvBf16 p = q;
+    p.stream_y = lc_stream_out((double)p.imgs * p.P * p.Q * N * 2, p.y, N * 2);
     constexpr size_t lds = (size_t)(N * BP + 2 * SLAB) * 2;
     if (p.P % TH != 0 || p.Q % TW != 0) return LC_ERR_UNSUPPORTED;
     if ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.w)) & 1 || reinterpret_cast<uintptr_t>(p.y) & 3) return LC_ERR_ALIGN;
@@ -586,8 +602,10 @@ lc_status lc_launch_conv_stem_bf16(const StemConvBf16& p, hipStream_t stream) {
     return lc_end_call();
 }
 
-lc_status lc_launch_conv_stem_f32(const StemConv& p, hipStream_t stream) {
+lc_status lc_launch_conv_stem_f32(const StemConv& q, hipStream_t stream) {
     using namespace stem;
+    StemConv p = q;
+    p.stream_y = lc_stream_out((double)p.imgs * p.P * p.Q * N * 4, p.y, N * 4);
     constexpr size_t lds = (size_t)(KP * N + 2 * SLAB) * 4;
     static bool once = [] {
         return hipFuncSetAttribute(reinterpret_cast<const void*>(conv_stem_f32_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) ==

@@ -110,7 +110,17 @@ struct GemmConv {
     // not null (main and slab kernels, no scatter): [lc_conv_gemm_stats_tiles()][N][2] floats -- per half tile of rows and
     // per column, the sum and the sum of squares of the values stored to d (as stored: after rounding to bf16)
     float* stats;
+    int stream_d;       // d is stored past the caches (lc_stream_out()): set by lc_launch_conv_gemm()
 };
+// Whether a convolution's result of so many bytes is stored with non-temporal stores.  They do not push the operands out of the caches, and they go to memory in
+// order: us, 512 images in bf16, ordinary / so: 64 to 256 1x1 at 56x56 200 / 190, 512 to 128 at 28x28 111 / 105 and its backward-data 135 / 127, 256 to 1024 at
+// 14x14 89 / 72, 3x3 over 256 channels at 14x14 108 / 99.  A result that the caches hold until the next layer reads it is worth more there: whole bf16
+// step at 512 images 35.69 ms without, 34.98 from 128 MB, 34.83 from 64 MB, no better below.  Only where every row is whole lines of 128 bytes: a line
+// that two stores fill goes to memory twice (64 to 104 1x1 at 56x56 122 / 159, to 200 187 / 309; fp32, 64 to 100 170 / 201).
+constexpr double kStreamOutBytes = 64e6;
+inline int lc_stream_out(double bytes, const void* d, size_t row_bytes) {
+    return bytes >= kStreamOutBytes && row_bytes % 128 == 0 && (reinterpret_cast<uintptr_t>(d) & 127) == 0;
+}
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream);
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` for this problem; 0: the kernel that takes it has none
 extern "C" int lc_selftest_stream_k(int max_blocks);   // host check of the work split's 32-bit form (0 = all good)
@@ -143,6 +153,7 @@ struct StemConv {
     float* y;           // [imgs][P][Q][64]
     float* stats;       // [pieces][64][2] (sum, sum of squares per piece of 64 pixels) or null
     int imgs, H, W, P, Q;
+    int stream_y;       // lc_stream_out(): set by the launcher
 };
 struct StemConvBf16 {
     const uint16_t* x;  // [imgs][H][W][3]
@@ -150,6 +161,7 @@ struct StemConvBf16 {
     uint16_t* y;        // [imgs][P][Q][64]
     float* stats;       // as StemConv
     int imgs, H, W, P, Q;
+    int stream_y;       // as StemConv
 };
 lc_status lc_launch_conv_stem_bf16(const StemConvBf16& p, hipStream_t stream);
 struct StemWgrad {
