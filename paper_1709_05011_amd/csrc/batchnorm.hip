@@ -662,8 +662,10 @@ template <typename T, int VEC, int MODE, int JOIN = 0>
 void launch_reduce(const T* x, const T* dy, const float* mean, const float* inv_std, const float* gamma, const float* beta, const BnGeom& g,
                    const BnWorkspace& ws, const BnJoin<T>& join, hipStream_t stream) {
     const long long keep = (long long)(kKeepBytes / ((MODE == kStats ? 1 : 2) * sizeof(T) * (size_t)g.C));    // rows of the tensors the apply pass reads
+    // (what the joined form writes goes past the caches too: only where its rows are whole lines)
+    const bool lines = JOIN == 0 || ((g.C * sizeof(T)) % 128 == 0 && (reinterpret_cast<uintptr_t>(join.out) & 127) == 0);
     hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, MODE, JOIN>), dim3((unsigned)(g.slabs * g.cblocks)), dim3(kThreads), 0, stream, x, dy, mean, inv_std,
-                       gamma, beta, g, ws, join, g.M > keep ? g.M - keep : 0);
+                       gamma, beta, g, ws, join, lines && g.M > keep ? g.M - keep : 0);
 }
 
 template <typename T, int VEC, bool TWO, bool RELU, bool MASK>
@@ -680,7 +682,8 @@ void launch_apply(const T* a, const T* b, T* out, const float* coef, const BnGeo
             const dim3 grid((unsigned)((total + kApplyThreads - 1) / kApplyThreads));
 #define LC_BN_GO(L, S) \
     hipLaunchKernelGGL((bn_apply_vec_kernel<T, VEC, TWO, RELU, MASK, L, S>), grid, dim3(kApplyThreads), 0, stream, a, b, out, coef, g.C, s)
-            if (bytes >= kStreamStoreBytes) LC_BN_GO(true, true);
+            // (a line that two blocks fill would go to memory twice)
+            if (bytes >= kStreamStoreBytes && (reinterpret_cast<uintptr_t>(out) & 127) == 0) LC_BN_GO(true, true);
             else if (bytes >= kStreamLoadBytes) LC_BN_GO(true, false);
             else LC_BN_GO(false, false);
 #undef LC_BN_GO

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -225,9 +226,8 @@ lars_finalize_kernel(LarsWorkspace ws, float lr, float* __restrict__ trust_out) 
 // 250 -> 207.  Lists whose arrays fit the caches together are indifferent (5.8 million parameters 39.7 and 40.6 us) and keep the ordinary form.
 constexpr int kUpdateThreads = 64, kPart = kUpdateThreads * 4, kParts = kChunk / kPart;
 constexpr long long kStreamParams = 12 << 20;                // three arrays of 48 MB
-template <bool NT>
 __global__ void __launch_bounds__(kUpdateThreads)
-lars_update_kernel(LarsWorkspace ws, int n_chunks, float momentum) {
+lars_update_kernel(LarsWorkspace ws, int n_chunks, float momentum, bool stream) {
     const int chunk = n_chunks - 1 - (int)(blockIdx.x / kParts), part = kParts - 1 - (int)(blockIdx.x % kParts);
     const int l = ws.chunk_tensor[chunk];
     const LarsTensor t = ws.table[l];
@@ -244,26 +244,32 @@ lars_update_kernel(LarsWorkspace ws, int n_chunks, float momentum) {
 
     const bool vec = ((((uintptr_t)w) | ((uintptr_t)g) | ((uintptr_t)v)) & 15) == 0 && (((uintptr_t)lp) & 7) == 0;
     if (vec && len == kPart) {
-        const float4 a = lc_fetch16<NT, float4>(w + threadIdx.x * 4), b = lc_fetch16<NT, float4>(g + threadIdx.x * 4), m = lc_fetch16<NT, float4>(v + threadIdx.x * 4);
-        float4 nv, nw;
-        nv.x = fmaf(momentum, m.x, scale * fmaf(weight_decay, a.x, b.x));
-        nv.y = fmaf(momentum, m.y, scale * fmaf(weight_decay, a.y, b.y));
-        nv.z = fmaf(momentum, m.z, scale * fmaf(weight_decay, a.z, b.z));
-        nv.w = fmaf(momentum, m.w, scale * fmaf(weight_decay, a.w, b.w));
-        nw.x = a.x - nv.x;
-        nw.y = a.y - nv.y;
-        nw.z = a.z - nv.z;
-        nw.w = a.w - nv.w;
-        lc_put16<NT>(v + threadIdx.x * 4, nv);
-        lc_put16<NT>(w + threadIdx.x * 4, nw);
-        if (lp) {
-            ushort4 h;
-            h.x = lc_bf16_rne(nw.x);
-            h.y = lc_bf16_rne(nw.y);
-            h.z = lc_bf16_rne(nw.z);
-            h.w = lc_bf16_rne(nw.w);
-            reinterpret_cast<ushort4*>(lp)[threadIdx.x] = h;                 // read by the next step's convolutions
-        }
+        auto update = [&](auto past) __attribute__((always_inline)) {
+            constexpr bool NT = decltype(past)::value;
+            const float4 a = lc_fetch16<NT, float4>(w + threadIdx.x * 4), b = lc_fetch16<NT, float4>(g + threadIdx.x * 4), m = lc_fetch16<NT, float4>(v + threadIdx.x * 4);
+            float4 nv, nw;
+            nv.x = fmaf(momentum, m.x, scale * fmaf(weight_decay, a.x, b.x));
+            nv.y = fmaf(momentum, m.y, scale * fmaf(weight_decay, a.y, b.y));
+            nv.z = fmaf(momentum, m.z, scale * fmaf(weight_decay, a.z, b.z));
+            nv.w = fmaf(momentum, m.w, scale * fmaf(weight_decay, a.w, b.w));
+            nw.x = a.x - nv.x;
+            nw.y = a.y - nv.y;
+            nw.z = a.z - nv.z;
+            nw.w = a.w - nv.w;
+            lc_put16<NT>(v + threadIdx.x * 4, nv);
+            lc_put16<NT>(w + threadIdx.x * 4, nw);
+            if (lp) {
+                ushort4 h;
+                h.x = lc_bf16_rne(nw.x);
+                h.y = lc_bf16_rne(nw.y);
+                h.z = lc_bf16_rne(nw.z);
+                h.w = lc_bf16_rne(nw.w);
+                reinterpret_cast<ushort4*>(lp)[threadIdx.x] = h;                 // read by the next step's convolutions
+            }
+        };
+        // (a line that two waves fill would go to memory twice)
+        if (stream && ((((uintptr_t)w) | ((uintptr_t)v)) & 127) == 0) update(std::true_type{});
+        else update(std::false_type{});
     } else {
         for (int i = threadIdx.x; i < len; i += kUpdateThreads) {
             const float x = w[i];
@@ -377,10 +383,7 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
         constexpr int kMost = 1 << 22;
         for (int last = (int)lay.n_chunks; last > 0; last -= kMost) {
             const dim3 grid((unsigned)(last < kMost ? last : kMost) * kParts);
-            if (lay.n_chunks >= kStreamParams / kChunk)
-                hipLaunchKernelGGL(lars_update_kernel<true>, grid, dim3(kUpdateThreads), 0, stream, ws, last, momentum);
-            else
-                hipLaunchKernelGGL(lars_update_kernel<false>, grid, dim3(kUpdateThreads), 0, stream, ws, last, momentum);
+            hipLaunchKernelGGL(lars_update_kernel, grid, dim3(kUpdateThreads), 0, stream, ws, last, momentum, lay.n_chunks >= kStreamParams / kChunk);
         }
     }
     return lc_end_call();
