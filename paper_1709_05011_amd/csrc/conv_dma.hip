@@ -350,11 +350,11 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
 #pragma unroll
                     for (int e = 0; e < 16 / RPI; ++e) {
                         if constexpr (!scatter) {
-                            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, kNonTemporal);
+                            if (__builtin_expect(p.stream_d, 0)) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, kNonTemporal);
                             else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, (i * 16 + e * RPI) * ldd_ * 2, 0);
                         } else {
                             const unsigned off = row_off(mw + i * 16 + e * RPI + lr);
-                            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, kNonTemporal);
+                            if (__builtin_expect(p.stream_d, 0)) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, kNonTemporal);
                             else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)(col < N_ ? off + (unsigned)col * 2u : kBufferBytes), 0, 0);
                         }
                     }
@@ -807,7 +807,7 @@ __global__ void __launch_bounds__(256, 1) conv3x3_held_kernel(const ConvHeld pp)
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int m = (turn * 4 + wave) * 16 + e * 8;
-            if (p.stream_d) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, kNonTemporal);
+            if (__builtin_expect(p.stream_d, 0)) __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, kNonTemporal);
             else __builtin_amdgcn_raw_buffer_store_b128(out[e], d_rsrc, (int)d_voff, m * ldd_ * 2, 0);
             if (STATS) {
                 const unsigned in = m + lane / 8 < valid ? ~0u : 0u;

@@ -560,7 +560,7 @@ __global__ void __launch_bounds__(256, kPkBlocksPerCu) conv_gemm_pk_kernel(const
                         }
                     }
                 };
-                if (p.stream_d) store(std::integral_constant<int, kNonTemporal>{});
+                if (__builtin_expect(p.stream_d, 0)) store(std::integral_constant<int, kNonTemporal>{});
                 else store(std::integral_constant<int, 0>{});
             }
             {
@@ -1063,7 +1063,7 @@ __global__ void __launch_bounds__(256, 2) conv3x3_slab_kernel(const GemmConv p) 
                 }
             }
         };
-        if (p.stream_d) store(std::integral_constant<int, kNonTemporal>{});
+        if (__builtin_expect(p.stream_d, 0)) store(std::integral_constant<int, kNonTemporal>{});
         else store(std::integral_constant<int, 0>{});
     }
     if (p.stats) {

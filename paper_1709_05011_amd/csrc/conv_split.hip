@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
                     px = m - m0;
                 }
                 const unsigned off = m < M_ ? (unsigned)(px * ldd_ + col) * 4u : kBufferBytes;
-                if (quads && p.stream_d) {
+                if (quads && __builtin_expect(p.stream_d, 0)) {
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[e]), d_rsrc, (int)(col < N_ ? off : kBufferBytes), 0, kNonTemporal);
                 } else if (quads) {
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[e]), d_rsrc, (int)(col < N_ ? off : kBufferBytes), 0, 0);
