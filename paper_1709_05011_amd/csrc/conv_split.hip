@@ -489,8 +489,11 @@ __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p)
 //
 // LDS: per 16 columns [plane][row group of 8][16 columns][8 rows]; with two columns per lane a block holds the even columns first, then the odd
 // ones, so that eight lanes store 128 consecutive bytes; the epilogue undoes that.
-// A load covers one output pixel, so its (image, p, q), its byte offset and the set of its taps inside the image are wave-uniform (scalar); a lane
-// holds its column's tap offset and bit, and a tap outside the image moves its offset past the end of the buffer.
+// A load covers one output pixel, so its byte offset and the set of its taps inside the image are wave-uniform; a lane holds its column's tap offset and bit, and
+// a tap outside the image moves its offset past the end of the buffer.  Offsets and sets are worked out for the wave's rows of eight steps at once, a row per
+// lane, and read lane by lane.  (Row by row on the scalar unit a step's loads took 2.3 us to issue, half of a step where a block has its compute unit to itself, and three
+// blocks did not hide it.  us, before / now: 3x3 over 128 channels, 256 images of 28x28 401 / 353, over 256, 256 of 14x14 409 / 343, 32 images 75 / 66, two images 27 / 22; over 64, 32 of
+// 56x56 95 / 73; 1x1 stride 2 512 to 1024, 32 of 28x28 71 / 63.)
 // PLAIN: a 1x1 window with stride 1 and no padding -- pixel m reads pixel m.
 // Three 128x128 blocks per compute unit (168 registers, 48 KB of LDS): 364 us with two of them on the 3x3 layer above, 320 with three.
 // ------------------------------------------------------------------------------------------------
@@ -545,18 +548,22 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
                                                   (int)kBufferWords3)
               : __builtin_amdgcn_make_buffer_rsrc((void*)(X + ((long long)img_first * H_ * W_ - ((long long)phb * W_ + pwb)) * C_), 0,
                                                   (int)kBufferBytes, (int)kBufferWords3);
-    // (image - img_first, p, q) of this wave's first row of the step being loaded; 32 rows further: 32 = (d_img * P + d_p) * Q + d_q
-    int mt = m_begin + wave * 8;
-    int s_q, s_p, s_img;
-    {
-        const int t = mt / Q_;
-        s_q = mt - t * Q_;
-        const int im = t / P_;
-        s_p = t - im * P_;
-        s_img = im - img_first;
-    }
-    const int d_q = BK % Q_, d_t = BK / Q_, d_p = d_t % P_, d_img = d_t / P_;
+    int mt = m_begin + wave * 8;                           // this wave's first row of the step being loaded
     const WindowTaps window(R_, S_);
+    // pixel offset and taps outside the image of row lane % 8 of step lane / 8 of the eight steps from pix_step on
+    int pix_off = 0, pix_step = 8;
+    unsigned pix_inv = 0;
+    auto pixels_of_steps = [&]() __attribute__((always_inline)) {
+        const int m = mt + (lane >> 3) * BK + (lane & 7);
+        const int t = div_by(m, p.q_mul, p.q_shift), q = m - t * Q_;
+        const int im = div_by(t, p.p_mul, p.p_shift), pp = t - im * P_;
+        const int h0 = pp * sh_ - ph_, w0 = q * sw_ - pw_;
+        const unsigned inv = window.outside(h0, w0, H_, W_, R_, S_);
+        const bool ok = ((unsigned)m < (unsigned)m_end) & (inv != ~0u);      // (m may lie past 2^31)
+        pix_inv = ok ? inv : ~0u;
+        pix_off = ok ? (((im - img_first) * H_ + h0 + phb) * W_ + w0 + pwb) * C_ * 4 : 0;
+        pix_step = 0;
+    };
 
     typename RowVec<VA>::type ga[8];
     typename RowVec<VB>::type gb[8];
@@ -574,33 +581,13 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
 #pragma unroll
             for (int i = 0; i < 8; ++i) load_row(gb[i], b_rsrc, b_voff, (row0 + i) * C_ * 4);
         } else {
-            int q = s_q, pp = s_p, im = s_img;
+            if (pix_step == 8) pixels_of_steps();
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const int h0 = pp * sh_ - ph_, w0 = q * sw_ - pw_;
-                unsigned inv = 0;                                 // taps outside the image for this pixel
-                if (mt + i >= m_end) {
-                    inv = ~0u;
-                } else if ((h0 < 0) | (w0 < 0) | (h0 + R_ > H_) | (w0 + S_ > W_)) {
-                    inv = window.outside(h0, w0, H_, W_, R_, S_);
-                }
-                const int soff = inv == ~0u ? 0 : ((im * H_ + h0 + phb) * W_ + w0 + pwb) * C_ * 4;
-                load_row(gb[i], b_rsrc, ((inv << b_up) & kBufferBytes) | b_voff, soff);
-                if (++q == Q_) {
-                    q = 0;
-                    if (++pp == P_) {
-                        pp = 0;
-                        ++im;
-                    }
-                }
+                const unsigned inv = (unsigned)__builtin_amdgcn_readlane((int)pix_inv, pix_step * 8 + i);
+                load_row(gb[i], b_rsrc, ((inv << b_up) & kBufferBytes) | b_voff, __builtin_amdgcn_readlane(pix_off, pix_step * 8 + i));
             }
-            s_q += d_q;
-            const bool cq = s_q >= Q_;
-            s_q -= cq ? Q_ : 0;
-            s_p += d_p + (cq ? 1 : 0);
-            const bool cp = s_p >= P_;
-            s_p -= cp ? P_ : 0;
-            s_img += d_img + (cp ? 1 : 0);
+            ++pix_step;
         }
         mt += BK;
     };
@@ -746,7 +733,10 @@ __global__ void __launch_bounds__(256, wgrad_split_blocks_per_cu(BM, BN)) wgrad_
 }
 
 template <int BM, int BN>
-lc_status launch_wgrad_split(const GemmWgrad& p, hipStream_t stream) {
+lc_status launch_wgrad_split(const GemmWgrad& q, hipStream_t stream) {
+    GemmWgrad p = q;
+    magic_for(p.Q, &p.q_mul, &p.q_shift);
+    magic_for(p.P, &p.p_mul, &p.p_shift);
     const long long tiles = (long long)((p.K + BM - 1) / BM) * ((p.J + BN - 1) / BN);
     if (tiles <= 0 || tiles * p.splits > 0x7fffffffLL) return LC_ERR_UNSUPPORTED;
     const bool plain = p.R == 1 && p.S == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 && p.pw == 0 && p.H == p.P && p.W == p.Q;

@@ -195,6 +195,7 @@ struct GemmWgrad {
     int splits, m_per_split;
     int bf16;           // dy and x are bf16 (widened on the fly; the sums and d stay fp32)
     int slab;           // 3x3 stride-1 pad-1 bf16 layer for wgrad3x3_slab_kernel: m_per_split counts padded positions
+    unsigned q_mul, q_shift, p_mul, p_shift;       // multiply-high division constants for Q and P (filled in by the launcher that needs them)
     int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (conv_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
