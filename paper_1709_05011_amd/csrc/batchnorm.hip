@@ -647,7 +647,6 @@ inline unsigned stream_blocks(size_t items) {
     return (unsigned)(b ? b : 1);
 }
 
-static int knob(const char* n, int d) { const char* e = getenv(n); return e ? atoi(e) : d; }
 // The memory-side cache holds 256 MB.  A pass that another one reads behind streams all but the last kKeepBytes past it (non-temporal loads) and
 // leaves those there, where the next pass, which walks the other way, finds them (bf16, two tensors of 206 MB: 182 us for the backward pass with ordinary
 // loads throughout, 197 with none, 174 to 177 so; read alone, 822 MB come at 6.1 TB/s with ordinary loads and 6.8 without keeping).

@@ -135,6 +135,8 @@ bool lc_conv_dma_ok(const GemmConv& p);
 size_t lc_conv_dma_workspace(const GemmConv& p);
 size_t lc_conv_dma_stats_tiles(const GemmConv& p);
 lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream);
+// its tiles of 256 columns, with the plan that conv_dma_plan() made
+lc_status lc_launch_conv_dma_wide(const GemmConv& p, int tile, int nkt, long long tiles, int dp_tiles, int sk_blocks, long long sk_iters, hipStream_t stream);
 // the kernel (tile, addressing, whether blocks share tiles) that takes a problem, in words
 void lc_conv_dma_describe(const GemmConv& p, bool stats, char* text, size_t size);
 void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t size);
