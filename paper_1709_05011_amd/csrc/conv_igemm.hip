@@ -669,8 +669,8 @@ __global__ void __launch_bounds__(256) conv_gemm_fixup_kernel(const GemmConv p) 
     const int tb = sk_tile * nkt;                                        // this tile's first k-step in stream-K positions
 
     // The first block's piece is the last of its range unless its range starts here (slot 0 or 1); all others start their ranges in this tile.
-    // Four parts are fetched at a time and added one after the other: a chain of dependent loads, and a division per part, made this kernel
-    // a third of the call on small problems (3x3 over 256 channels, two images of 14x14 in fp32: 26.8 -> 23.3 us).
+    // Eight parts are fetched at a time and added one after the other: a chain of dependent loads, and a division per part, made this kernel
+    // a third of the call on small problems (3x3 over 256 channels, two images of 14x14 in fp32, this kernel: 7.0 us with four parts, 5.7 with eight).
     const int skip = sk_begin(p, j) >= tb ? 0 : 1;
     const float* first = p.partial + (size_t)2 * j * (BM * BN) + (size_t)skip * (BM * BN) + partial_index<TM, TN>(wave, 0, 0, v, lane);
     const float* rest = p.partial + (size_t)2 * (j + 1) * (BM * BN) + partial_index<TM, TN>(wave, 0, 0, v, lane);
@@ -681,25 +681,25 @@ __global__ void __launch_bounds__(256) conv_gemm_fixup_kernel(const GemmConv p) 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] = 0.f + first[(i * TN + jj) * kTile];
-    auto add_parts = [&](int t, auto count) __attribute__((always_inline)) {
-        constexpr int U = decltype(count)::value;
-        float part[U][TM][TN];
+    for (int t = 0; t < more; t += 8) {
+        float part[8][TM][TN];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < 8; ++u)
+            if (t + u < more) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int jj = 0; jj < TN; ++jj) part[u][i][jj] = rest[(size_t)2 * (t + u) * (BM * BN) + (i * TN + jj) * kTile];
+                    for (int jj = 0; jj < TN; ++jj) part[u][i][jj] = rest[(size_t)2 * (t + u) * (BM * BN) + (i * TN + jj) * kTile];
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < 8; ++u)
+            if (t + u < more) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] += part[u][i][jj];
-    };
-    int t = 0;
-    for (; t + 4 <= more; t += 4) add_parts(t, std::integral_constant<int, 4>{});
-    for (; t < more; ++t) add_parts(t, std::integral_constant<int, 1>{});
+                    for (int jj = 0; jj < TN; ++jj) acc[i][jj][0] += part[u][i][jj];
+            }
+    }
     // move the sums to register position v, where store_tile expects them
     f32x16 out[TM][TN];
 #pragma unroll

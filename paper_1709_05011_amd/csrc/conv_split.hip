@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(256, split_blocks_per_cu(BN, UT)) conv_gemm_sp
 }
 
 // Adds the parts of every tile that stream-K blocks split between them, in k order, and stores the tile: block (t, y) handles the 16x16
-// tile y of each of the four waves of stream-K tile t.  Four parts are fetched at a time.
+// tile y of each of the four waves of stream-K tile t.  Eight parts are fetched at a time.
 template <int BM, int BN, bool MEET>
 __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p) {
     constexpr int TN = BN / 32;
@@ -452,14 +452,15 @@ __global__ void __launch_bounds__(256) conv_split_fixup_kernel(const GemmConv p)
     constexpr size_t kSlot = BM * BN / 4;
     // the first block's piece is the last of its range unless its range starts here; all others start their ranges in this tile
     f32x4 sum = part[((size_t)2 * j + (sk_begin(p, j) >= tb ? 0 : 1)) * kSlot];
-    for (++j; j + 4 <= j1; j += 4) {
-        f32x4 v[4];
+    for (++j; j < j1; j += 8) {
+        f32x4 v[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = part[(size_t)2 * (j + u) * kSlot];
+        for (int u = 0; u < 8; ++u)
+            if (j + u < j1) v[u] = part[(size_t)2 * (j + u) * kSlot];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) sum += v[u];
+        for (int u = 0; u < 8; ++u)
+            if (j + u < j1) sum += v[u];
     }
-    for (; j < j1; ++j) sum += part[(size_t)2 * j * kSlot];
     const int tile = p.dp_tiles + sk_tile, tm = tile / nbn;
     const int ti = blockIdx.y / TN, tj = blockIdx.y - ti * TN;
     const int m = tm * BM + (wave >> 1) * (BM / 2) + ti * 16 + (lane & 15);
