@@ -374,16 +374,16 @@ struct BnSpan {
 // Forward and backward with these and the reduce pass's loads: fp32 411 MB 294 -> 254 and 373 -> 317 us, bf16 206 MB 122 -> 97 and 230 -> 174, 822 MB 568 -> 507
 // and 715 -> 638 (6.4 to 6.5 TB/s).
 constexpr int kApplyThreads = 64;
-template <typename T, int VEC, bool TWO, bool RELU, bool MASK, bool NTL, bool NTS>
+template <typename T, int VEC, bool TWO, bool RELU, bool MASK, bool PAST>
 __global__ void __launch_bounds__(kApplyThreads) bn_apply_vec_kernel(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ out,
                                                                      const float* __restrict__ coef, int c, BnSpan s) {
     typedef typename Pack<T, VEC>::raw raw;
     const unsigned block = gridDim.x - 1 - blockIdx.x;
     const size_t base = (size_t)block * kApplyThreads;
     if (base + threadIdx.x >= s.total) return;
-    const raw ra = lc_fetch16<NTL, raw>(a + base * VEC + threadIdx.x * VEC);
+    const raw ra = lc_fetch16<PAST, raw>(a + base * VEC + threadIdx.x * VEC);
     raw rb{};
-    if constexpr (TWO) rb = lc_fetch16<NTL, raw>(b + base * VEC + threadIdx.x * VEC);
+    if constexpr (TWO) rb = lc_fetch16<PAST, raw>(b + base * VEC + threadIdx.x * VEC);
     // the channel group of the block's first vector, (block * threads) % groups, then the thread's
     const unsigned turn = block - (unsigned)div_by((int)block, s.mul, s.shift) * s.groups;
     const unsigned at = turn * s.step, first = at - (unsigned)div_by((int)at, s.mul, s.shift) * s.groups;
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(kApplyThreads) bn_apply_vec_kernel(const T* __
     Pack<T, VEC>::unpack(ra, va);
     if constexpr (TWO) Pack<T, VEC>::unpack(rb, vb);
     k.template apply<RELU>(va, vb, o);
-    lc_put16<NTS>(out + base * VEC + threadIdx.x * VEC, Pack<T, VEC>::pack(o));
+    lc_put16<PAST>(out + base * VEC + threadIdx.x * VEC, Pack<T, VEC>::pack(o));
 }
 
 // ---------------- NCHW ----------------
@@ -651,11 +651,11 @@ inline unsigned stream_blocks(size_t items) {
 // leaves those there, where the next pass, which walks the other way, finds them (bf16, two tensors of 206 MB: 182 us for the backward pass with ordinary
 // loads throughout, 197 with none, 174 to 177 so; read alone, 822 MB come at 6.1 TB/s with ordinary loads and 6.8 without keeping).
 constexpr size_t kKeepBytes = (size_t)200 << 20;
-// Apply pass, tensors of this size and more: non-temporal loads, and stores.  Below, the data is in the caches or is wanted there: whole fp32 step at 32
-// images (tensors to 103 MB) 10.98 ms with loads from 64 MB and no such stores, 11.00 with stores from 64, 11.12 from 20; whole bf16 step at 512 images
-// 36.43 without either, 36.08 with the loads, 35.90 with the stores from 128 MB (35.94 from 20, 35.84 from 300, but then the 64-channel layer at 56x56,
-// whose tensors have 205 MB, takes 745 us instead of 712).
-constexpr size_t kStreamLoadBytes = (size_t)64 << 20, kStreamStoreBytes = (size_t)128 << 20;
+// Apply pass, tensors of this size and more: non-temporal loads and stores.  Below, the data is in the caches or is wanted there: whole fp32 step at 32
+// images (tensors to 103 MB) 10.98 ms with ordinary stores, 11.02 with such stores from 64 MB, 11.12 from 20 MB; whole bf16 step at 512 images 36.43 without either,
+// 35.90 with both.  Such loads beside ordinary stores are the worst of the four (103 MB in fp32, a layer's two passes by themselves: 189 us; both ordinary 173).
+// The line is just above that step's 103 MB: bf16, 120 MB of cold data take 175 us with ordinary accesses, 165 with these; 140 MB 229 and 206.
+constexpr size_t kStreamBytes = 112000000;
 
 template <typename T, int VEC, int MODE, int JOIN = 0>
 void launch_reduce(const T* x, const T* dy, const float* mean, const float* inv_std, const float* gamma, const float* beta, const BnGeom& g,
@@ -679,12 +679,11 @@ void launch_apply(const T* a, const T* b, T* out, const float* coef, const BnGeo
         // (the group's arithmetic is 31-bit and the grid's threads are a 32-bit number: more than 4 million channels or 64 GiB take the loop)
         if (s.groups <= 1u << 20 && total <= 0xffffffffull - kApplyThreads) {
             const dim3 grid((unsigned)((total + kApplyThreads - 1) / kApplyThreads));
-#define LC_BN_GO(L, S) \
-    hipLaunchKernelGGL((bn_apply_vec_kernel<T, VEC, TWO, RELU, MASK, L, S>), grid, dim3(kApplyThreads), 0, stream, a, b, out, coef, g.C, s)
+#define LC_BN_GO(PAST) \
+    hipLaunchKernelGGL((bn_apply_vec_kernel<T, VEC, TWO, RELU, MASK, PAST>), grid, dim3(kApplyThreads), 0, stream, a, b, out, coef, g.C, s)
             // (a line that two blocks fill would go to memory twice)
-            if (bytes >= kStreamStoreBytes && (reinterpret_cast<uintptr_t>(out) & 127) == 0) LC_BN_GO(true, true);
-            else if (bytes >= kStreamLoadBytes) LC_BN_GO(true, false);
-            else LC_BN_GO(false, false);
+            if (bytes >= kStreamBytes && (reinterpret_cast<uintptr_t>(out) & 127) == 0) LC_BN_GO(true);
+            else LC_BN_GO(false);
 #undef LC_BN_GO
             return;
         }
