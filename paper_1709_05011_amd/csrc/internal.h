@@ -44,6 +44,7 @@ void lc_f32_to_bf16(const float* src, void* dst, size_t count, hipStream_t strea
 void lc_fill_f32(float* dst, float value, size_t count, hipStream_t stream);
 void lc_fill_u32x4(void* dst, size_t bytes16, hipStream_t stream);   // zero `bytes16` * 16 bytes
 void lc_zero_bytes(void* dst, size_t bytes, hipStream_t stream);      // zero an even number of bytes at a 2-byte aligned address
+void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh, int sw, hipStream_t stream);   // [n][h][w] pixels but those on the stride grid
 
 // rows x width_bytes bytes from src (row pitch src_pitch bytes) to dst (row pitch dst_pitch); every size a multiple of 2
 void lc_copy2d(const void* src, size_t src_pitch, void* dst, size_t dst_pitch, size_t width_bytes, size_t rows, hipStream_t stream);
@@ -91,8 +92,8 @@ struct GemmConv {
     int ph, pw;
     int dh, dw;         // > 1: "dilated" read, valid only where h % dh == 0, then h /= dh
     int ldd;
-    // scatter epilogue (0 = off): row (img,po,qo) is pixel (po*esh, qo*esw) of an [imgs][Ho][Wo][ldd] tensor that
-    // the caller has cleared; the pixels between the stride grid stay zero.
+    // scatter epilogue (0 = off): row (img,po,qo) is pixel (po*esh, qo*esw) of an [imgs][Ho][Wo][ldd] tensor;
+    // the pixels between the stride grid are the caller's, every value on it is written.
     int scatter, Ho, Wo, esh, esw;
     // stream-K split, filled in by the launcher: whole-tile blocks, blocks sharing the k-steps of the
     // remaining tiles, their total k-steps, and the workspace for partial tiles (2 slots per such block)
