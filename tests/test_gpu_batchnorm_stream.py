@@ -1,6 +1,6 @@
 """GPU parity of the batch-norm passes where their streaming choices change: channel counts that a block of 64 vectors does not divide,
 a last block that is partly past the end, tensors just below and above the size from which the stream pass goes past the caches
-(128 MB) and from which the reduce pass does (200 MB over the tensors that are read again), and a channel count that takes the
+(112 MB) and from which the reduce pass does (200 MB over the tensors that are read again), and a channel count that takes the
 loop kernel.  Reference: the same formulas in float64 on the device.
 
 Bounds: an fp32 value carries at most a handful of roundings of its terms (scale*x, shift, residual; in the backward pass dy and the two
