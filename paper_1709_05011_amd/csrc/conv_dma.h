@@ -195,8 +195,9 @@ __global__ void __launch_bounds__(2 * WN * 64, 2) conv_dma_kernel(const ConvDma 
             const int load = (l - LA) * NW + wave;
             const int rows = (l - LA) * NW * 8 * Kg_ * 2;
             int place = rows + (by_tap ? (u_tap * Ci_ + u_c) * 2 : u_c * 128);
-            if constexpr (NS > 2 && !by_tap) place = __builtin_amdgcn_readfirstlane(place);
-            load_to_lds(b_rsrc, b_voff | v_bad, place, l_lds + BM * 128 + load * 1024);
+            constexpr bool vector = NS > 2 && !by_tap;     // (the compiler counts u_c in a vector register there)
+            if constexpr (vector) place = __builtin_amdgcn_readfirstlane(place);
+            load_to_lds<vector>(b_rsrc, b_voff | v_bad, place, l_lds + BM * 128 + load * 1024);
         }
     };
     auto load_end = [&]() __attribute__((always_inline)) {
