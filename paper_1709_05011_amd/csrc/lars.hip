@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -335,6 +336,13 @@ lc_status lars_check(int n_tensors, float* const* w, const float* const* g, floa
     return LC_OK;
 }
 
+// The update pass's launches, each with fewer than 2^32 threads (the runtime takes no more): go(last, blocks) for the chunks last - 1, last - 2, ...
+constexpr int kMostChunks = (int)(0xffffffffull / (kParts * kUpdateThreads));
+template <typename F>
+void for_update_launches(int n_chunks, F&& go) {
+    for (int last = n_chunks; last > 0; last -= kMostChunks) go(last, (unsigned)(last < kMostChunks ? last : kMostChunks) * kParts);
+}
+
 // The launches of one step on scratch memory at `base` (device, 256-byte aligned, lay.total bytes).
 lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float* const* v, const int64_t* numel, float eta,
                    float momentum, float weight_decay, float lr, const float* eta_per_tensor,
@@ -379,17 +387,24 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
     }
     hipLaunchKernelGGL(lars_finalize_kernel, dim3(n_tensors), dim3(kThreads), 0, stream, ws, lr, trust_out);
     if (lay.n_chunks > 0) {
-        // a launch holds fewer than 2^32 threads: the parts of 2^22 chunks (2^34 parameters) at a time
-        constexpr int kMost = 1 << 22;
-        for (int last = (int)lay.n_chunks; last > 0; last -= kMost) {
-            const dim3 grid((unsigned)(last < kMost ? last : kMost) * kParts);
-            hipLaunchKernelGGL(lars_update_kernel, grid, dim3(kUpdateThreads), 0, stream, ws, last, momentum, lay.n_chunks >= kStreamParams / kChunk);
-        }
+        for_update_launches((int)lay.n_chunks, [&](int last, unsigned blocks) {
+            hipLaunchKernelGGL(lars_update_kernel, dim3(blocks), dim3(kUpdateThreads), 0, stream, ws, last, momentum, lay.n_chunks >= kStreamParams / kChunk);
+        });
     }
     return lc_end_call();
 }
 
 }  // namespace
+
+// Host check of the update pass's launches for a list of so many chunks: the threads of the largest, or -1 where they do not take every chunk once.
+extern "C" long long lc_selftest_lars_launches(int n_chunks) {
+    long long most = 0, next = n_chunks;
+    for_update_launches(n_chunks, [&](int last, unsigned blocks) {
+        next = last == next && blocks % kParts == 0 ? next - blocks / kParts : -1;
+        most = std::max(most, (long long)blocks * kUpdateThreads);
+    });
+    return next == 0 ? most : -1;
+}
 
 extern "C" lc_status lars_step_ex(int n_tensors, float* const* w, const float* const* g, float* const* v,
                                   const int64_t* numel, float eta, float momentum, float weight_decay, float lr,

@@ -151,6 +151,15 @@ def test_work_split_in_32_bits_matches_the_plain_quotients():
     assert L.lc_selftest_stream_k(2048) == 0
 
 
+def test_lars_update_launches_hold_fewer_than_2_to_the_32_threads():
+    # the runtime refuses a larger launch; a list of 2^34 parameters (2^22 chunks of 4096) fits the card, the layout takes up to 2^31 - 1 chunks
+    L = lc.lib()
+    L.lc_selftest_lars_launches.restype = ctypes.c_longlong
+    L.lc_selftest_lars_launches.argtypes = [ctypes.c_int]
+    for chunks in (1, 2, 1000, (1 << 22) - 2, (1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 23) - 3, 1 << 23, 3 << 23, (1 << 31) - 1):
+        assert 0 < L.lc_selftest_lars_launches(chunks) < 1 << 32, chunks
+
+
 def test_filter_gradients_bound_by_memory_or_latency_plan_for_the_fp32_kernels():
     # the plan's partial sums tell the kernel: one round of blocks with 256 rows each at least for the fp32 kernels, two rounds with 128 rows for
     # the kernel with split operands (no GPU in sight: the plan counts 256 compute units)
