@@ -661,10 +661,11 @@ template <typename T, int VEC, int MODE, int JOIN = 0>
 void launch_reduce(const T* x, const T* dy, const float* mean, const float* inv_std, const float* gamma, const float* beta, const BnGeom& g,
                    const BnWorkspace& ws, const BnJoin<T>& join, hipStream_t stream) {
     const long long keep = (long long)(kKeepBytes / ((MODE == kStats ? 1 : 2) * sizeof(T) * (size_t)g.C));    // rows of the tensors the apply pass reads
-    // (what the joined form writes goes past the caches too: only where its rows are whole lines)
-    const bool lines = JOIN == 0 || ((g.C * sizeof(T)) % 128 == 0 && (reinterpret_cast<uintptr_t>(join.out) & 127) == 0);
+    // (What the joined form writes goes past the caches too.  Its rows need not be whole lines: a block's rows are one stretch, and a line that two blocks fill is the exception.
+    // This pass, then with the apply pass behind it, us, ordinary accesses / so: 72 channels, 217 MB, fp32 165 / 142 and 259 / 250, bf16 187 / 164 and 290 / 276; 2056 channels in fp32,
+    // 493 MB, 417 / 368 and 667 / 632; 520 in bf16, 499 MB, 519 / 496 and 766 / 750; at the worst 1032 in bf16, 413 MB, 374 / 354 and 580 / 599.)
     hipLaunchKernelGGL((bn_reduce_nhwc_kernel<T, VEC, MODE, JOIN>), dim3((unsigned)(g.slabs * g.cblocks)), dim3(kThreads), 0, stream, x, dy, mean, inv_std,
-                       gamma, beta, g, ws, join, lines && g.M > keep ? g.M - keep : 0);
+                       gamma, beta, g, ws, join, g.M > keep ? g.M - keep : 0);
 }
 
 template <typename T, int VEC, bool TWO, bool RELU, bool MASK>
