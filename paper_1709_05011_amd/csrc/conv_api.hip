@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <stdint.h>
 #include <stdlib.h>
+#include <string.h>
 
 #include "internal.h"
 
@@ -642,6 +643,7 @@ lc_status fwd_impl(const lc_conv_desc* d, const void* x, const void* w, void* y,
     g.a = xs;
     g.b = wsrc;
     g.d = ydst;
+    g.copied = pl.nchw;
     g.partial = pl.sk_bytes ? reinterpret_cast<float*>(at(workspace, pl.sk)) : nullptr;
     g.stats = stats;
     st = lc_launch_conv_gemm(g, stream);
@@ -687,6 +689,16 @@ extern "C" lc_status conv2d_fwd_stats(const lc_conv_desc* d, const void* x, cons
     if (reinterpret_cast<uintptr_t>(stats) & 7) return LC_ERR_ALIGN;
     return fwd_impl(d, x, w, y, stats, workspace, workspace_bytes, hip_stream);
 }
+
+namespace {
+// Whether the zeros between a stride grid leave past the caches, as a large result would.  Not before a long fp32 product: bound by its pipe, it hides what the caches still have to write (us, ordinary
+// zeros / past the caches: 512 to 1024, 256 images of 28x28 334 / 344, 256 to 512 of 56x56 392 / 413; but 512 to 256, 128 of 28x28 87 / 81, 64 to 64, 512 of 56x56 128 / 104; bf16, 512 to 1024, 512 of
+// 28x28 220 / 202, 256 to 512 of 56x56 282 / 275).
+bool zeros_stream(const lc_conv_desc* d, const Plan& pl, const void* dx) {
+    const size_t pixel = (size_t)d->c * pl.esize;
+    return (pl.bf16 || d->k < 512) && lc_stream_out((double)d->n * d->h * d->w * pixel, dx, pixel, pl.nchw ? kStreamCopyBytes : kStreamOutBytes);
+}
+}  // namespace
 
 extern "C" lc_status conv2d_bwd_data(const lc_conv_desc* d, const void* dy, const void* w, void* dx,
                                      void* workspace, size_t workspace_bytes, void* hip_stream) {
@@ -740,6 +752,7 @@ extern "C" lc_status conv2d_bwd_data(const lc_conv_desc* d, const void* dy, cons
             g.a = dys;
             g.b = wp;
             g.d = static_cast<char*>(dxdst) + ph[i].d_off * pl.esize;
+            g.copied = pl.nchw;
             g.partial = pl.sk_bytes ? reinterpret_cast<float*>(at(workspace, pl.sk)) : nullptr;
             st = lc_launch_conv_gemm(g, stream);
             if (st != LC_OK) return st;
@@ -754,8 +767,9 @@ extern "C" lc_status conv2d_bwd_data(const lc_conv_desc* d, const void* dy, cons
     g.a = dys;
     g.b = wt;
     g.d = dxdst;
+    g.copied = pl.nchw;
     // a strided 1x1 window touches only the stride grid of dx: clear the rest, the kernels write the grid
-    if (g.scatter) lc_zero_off_grid(dxdst, d->n, d->h, d->w, (size_t)d->c * pl.esize, d->stride_h, d->stride_w, stream);
+    if (g.scatter) lc_zero_off_grid(dxdst, d->n, d->h, d->w, (size_t)d->c * pl.esize, d->stride_h, d->stride_w, zeros_stream(d, pl, dxdst), stream);
     g.partial = pl.sk_bytes ? reinterpret_cast<float*>(at(workspace, pl.sk)) : nullptr;
     st = lc_launch_conv_gemm(g, stream);
     if (st != LC_OK) return st;
@@ -880,8 +894,8 @@ extern "C" lc_status conv2d_bwd_weight_sq(const lc_conv_desc* d, const void* x, 
 }
 
 
-// Which kernel a pass of a layer ends in, in words (tests and the benchmark's labels); 0 and the text, or an error.  stats: conv2d_fwd_stats.  A layer
-// with groups: that of one group; backward-data by stride phases: that of the first phase.
+// Which kernel a pass of a layer ends in, in words (tests and the benchmark's labels); 0 and the text, or an error.  stats: 1 for conv2d_fwd_stats, and
+// 2 for the kernel's form as well.  A layer with groups: that of one group; backward-data by stride phases: that of the first phase.
 extern "C" int lc_selftest_conv_route(const lc_conv_desc* d, int pass, int stats, char* text, size_t size) {
     lc_conv_desc canon, one;
     if (!d || !text || size < 8) return LC_ERR_NULL;
@@ -910,14 +924,18 @@ extern "C" int lc_selftest_conv_route(const lc_conv_desc* d, int pass, int stats
         g.slab = pl.wgrad_slab;
         g.dma_bm = pl.wgrad_bm;
         g.dma_bn = pl.wgrad_bn;
-        lc_wgrad_describe(g, text, size);
+        lc_wgrad_describe(g, (stats & 2) != 0, text, size);
     } else if (pl.phases) {
         Phase ph[kMaxPhases];
         bool covered;
         plan_phases(d, pl.P, pl.Q, ph, &covered);
-        lc_conv_gemm_describe(ph[0].g, false, text, size);
+        ph[0].g.copied = pl.nchw;
+        lc_conv_gemm_describe(ph[0].g, false, (stats & 2) != 0, text, size);
     } else {
-        lc_conv_gemm_describe(pass == LC_PASS_FWD ? gemm_fwd(d, pl.P, pl.Q, pl.cpad) : gemm_bwd_data(d, pl.P, pl.Q), stats != 0, text, size);
+        GemmConv g = pass == LC_PASS_FWD ? gemm_fwd(d, pl.P, pl.Q, pl.cpad) : gemm_bwd_data(d, pl.P, pl.Q);
+        g.copied = pl.nchw;
+        lc_conv_gemm_describe(g, (stats & 1) != 0, (stats & 2) != 0, text, size);
+        if ((stats & 2) && g.scatter && zeros_stream(d, pl, nullptr)) snprintf(text + strlen(text), size - strlen(text), ", zeros past");
     }
     return LC_OK;
 }

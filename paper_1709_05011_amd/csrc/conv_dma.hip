@@ -273,13 +273,14 @@ size_t lc_conv_dma_stats_tiles(const GemmConv& p) {
     return (size_t)2 * ((p.M + bm - 1) / bm);
 }
 
-void lc_conv_dma_describe(const GemmConv& p, bool stats, char* text, size_t size) {
+void lc_conv_dma_describe(const GemmConv& p, bool stats, bool form, char* text, size_t size) {
     ConvDmaPlan c;
     static const char* const in[] = {"chunks", "padded", "pieces", "runs", "taps"};
     if (!conv_dma_plan(p, !stats, &c)) snprintf(text, size, "none");
     else
-        snprintf(text, size, "conv_dma %dx%d%s %s%s", kConvTiles[c.tile].bm, kConvTiles[c.tile].bn, c.tile == kNarrowTwoWaves ? " two waves" : "",
-                 in[conv_dma_in(p)], conv_dma_shares(c) ? " shared" : "");
+        snprintf(text, size, "conv_dma %dx%d%s %s%s%s", kConvTiles[c.tile].bm, kConvTiles[c.tile].bn, c.tile == kNarrowTwoWaves ? " two waves" : "",
+                 in[conv_dma_in(p)], conv_dma_shares(c) ? " shared" : "",
+                 !form ? "" : conv_dma_deep(p, c) ? " four stages" : conv_dma_in(p) == kChunks && conv_dma_once(p, kConvTiles[c.tile].bn) ? " once" : "");
 }
 
 lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream) {

@@ -2064,13 +2064,22 @@ static ConvKernel conv_kernel(const GemmConv& p, bool stats, size_t* slab_lds) {
     return p.split ? ConvKernel::kSplit : ConvKernel::kMain;
 }
 
-void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t size) {
+// Whether the kernel stores the result past the caches: lc_stream_out(), but for the main kernel's 128 columns in bf16, which are left with reductions of at most 16 values, products that
+// end before the stores have left (us, ordinary / past the caches: 16 to 128 1x1, 512 images of 28x28 25 / 37, of 56x56 127 / 130, 16 to 640 at 28x28 123 / 170, 8 to 256 56 / 68).
+static int conv_streams(const GemmConv& p, ConvKernel kernel) {
+    if (kernel == ConvKernel::kMain && p.bf16 && p.N > 64) return 0;
+    const int es = p.bf16 ? 2 : 4;
+    return lc_stream_out((double)p.M * p.N * es, p.d, (size_t)p.ldd * es, p.copied ? kStreamCopyBytes : kStreamOutBytes);
+}
+
+void lc_conv_gemm_describe(const GemmConv& p, bool stats, bool form, char* text, size_t size) {
     size_t lds;
     const ConvKernel k = conv_kernel(p, stats, &lds);
-    if (k == ConvKernel::kDma) return lc_conv_dma_describe(p, stats, text, size);
     static const char* const names[] = {"conv3x3_held", "conv3x3_slab", "", "conv_gemm_pk", "conv_gemm_split", "conv_gemm", "none"};
-    if (k == ConvKernel::kMain) with_main_tile(p, [&]<int BM, int BN>() { snprintf(text, size, "%s %dx%d", names[(int)k], BM, BN); });
+    if (k == ConvKernel::kDma) lc_conv_dma_describe(p, stats, form, text, size);
+    else if (k == ConvKernel::kMain) with_main_tile(p, [&]<int BM, int BN>() { snprintf(text, size, "%s %dx%d", names[(int)k], BM, BN); });
     else snprintf(text, size, "%s", names[(int)k]);
+    if (form && conv_streams(p, k) && k != ConvKernel::kGeneral) snprintf(text + strlen(text), size - strlen(text), " past");
 }
 
 // (asked for the call with statistics, which the kernels without partial tiles take no more often than the call without)
@@ -2116,10 +2125,11 @@ size_t lc_conv_gemm_stats_tiles(const GemmConv& p) {
 
 lc_status lc_launch_conv_gemm(const GemmConv& q, hipStream_t stream) {
     GemmConv p = q;
-    p.stream_d = lc_stream_out((double)p.M * p.N * (p.bf16 ? 2 : 4), p.d, (size_t)p.ldd * (p.bf16 ? 2 : 4));
     if (p.stats && lc_conv_gemm_stats_tiles(p) == 0) return LC_ERR_UNSUPPORTED;
     size_t lds;
-    switch (conv_kernel(p, p.stats != nullptr, &lds)) {
+    const ConvKernel kernel = conv_kernel(p, p.stats != nullptr, &lds);
+    p.stream_d = conv_streams(p, kernel);
+    switch (kernel) {
         case ConvKernel::kHeld: return lc_launch_conv_held(p, stream);
         case ConvKernel::kSlab: return launch_slab(p, lds, stream);
         case ConvKernel::kDma: return lc_launch_conv_dma(p, stream);
@@ -2318,14 +2328,14 @@ static lc_status dispatch_wgrad(const GemmWgrad& p, hipStream_t stream) {
 }
 
 // (mirrors dispatch_wgrad)
-void lc_wgrad_describe(const GemmWgrad& p, char* text, size_t size) {
+void lc_wgrad_describe(const GemmWgrad& p, bool form, char* text, size_t size) {
     const char* kernel = "wgrad";
     if (p.slab) kernel = "wgrad3x3_slab";
     else if (p.bf16 && p.dma_bm) kernel = "wgrad_dma";
     else if (!p.bf16 && wgrad_split_ok(p)) kernel = "wgrad_split";
     else if (wgrad_plain_ok(p)) kernel = "wgrad_plain";
     else if (p.bf16 && p.C % 8 == 0 && p.K % 8 == 0) kernel = "wgrad_bf16";
-    if (p.dma_bm) snprintf(text, size, "%s %dx%d splits %d sums %d", kernel, p.dma_bm, p.dma_bn, p.splits, lc_wgrad_dma_sum_rows(p));
+    if (p.dma_bm) snprintf(text, size, "%s %dx%d splits %d sums %d%s", kernel, p.dma_bm, p.dma_bn, p.splits, lc_wgrad_dma_sum_rows(p), form ? lc_wgrad_dma_form(p) : "");
     else snprintf(text, size, "%s splits %d", kernel, p.splits);
 }
 

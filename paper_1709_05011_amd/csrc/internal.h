@@ -44,7 +44,8 @@ void lc_f32_to_bf16(const float* src, void* dst, size_t count, hipStream_t strea
 void lc_fill_f32(float* dst, float value, size_t count, hipStream_t stream);
 void lc_fill_u32x4(void* dst, size_t bytes16, hipStream_t stream);   // zero `bytes16` * 16 bytes
 void lc_zero_bytes(void* dst, size_t bytes, hipStream_t stream);      // zero an even number of bytes at a 2-byte aligned address
-void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh, int sw, hipStream_t stream);   // [n][h][w] pixels but those on the stride grid
+void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh, int sw, bool past,
+                      hipStream_t stream);   // [n][h][w] pixels but those on the stride grid; past: past the caches
 
 // rows x width_bytes bytes from src (row pitch src_pitch bytes) to dst (row pitch dst_pitch); every size a multiple of 2
 void lc_copy2d(const void* src, size_t src_pitch, void* dst, size_t dst_pitch, size_t width_bytes, size_t rows, hipStream_t stream);
@@ -111,16 +112,22 @@ struct GemmConv {
     // not null (main and slab kernels, no scatter): [lc_conv_gemm_stats_tiles()][N][2] floats -- per half tile of rows and
     // per column, the sum and the sum of squares of the values stored to d (as stored: after rounding to bf16)
     float* stats;
+    int copied;         // d is copied to another layout next
     int stream_d;       // d is stored past the caches (lc_stream_out()): set by lc_launch_conv_gemm()
 };
 // Whether a convolution's result of so many bytes is stored with non-temporal stores.  They do not push the operands out of the caches, and they go to memory in
-// order: us, 512 images in bf16, ordinary / so: 64 to 256 1x1 at 56x56 200 / 190, 512 to 128 at 28x28 111 / 105 and its backward-data 135 / 127, 256 to 1024 at
-// 14x14 89 / 72, 3x3 over 256 channels at 14x14 108 / 99.  A result that the caches hold until the next layer reads it is worth more there: whole bf16
-// step at 512 images 35.69 ms without, 34.98 from 128 MB, 34.83 from 64 MB, no better below.  Only where every row is whole lines of 128 bytes: a line
-// that two stores fill goes to memory twice (64 to 104 1x1 at 56x56 122 / 159, to 200 187 / 309; fp32, 64 to 100 170 / 201).
+// order: us, 512 images in bf16, ordinary / so, alternating: 128 to 512 1x1 at 28x28 128 / 86, 256 to 1024 at 14x14 87 / 65, 64 to 256 at 56x56 200 / 195 and its
+// backward-data 198 / 187, 3x3 over 128 channels at 28x28 130 / 121 and 134 / 127; also where two stores fill a line between them (64 columns: 256 to 64 at 56x56 193 / 184, 3x3 32 to 64 at
+// 56x56 128 / 114).  fp32, 256 images: 128 to 512 at 28x28 230 / 224, its backward-data 174 / 173, 512 to 128 216 / 217 and 199 / 191, 3x3 over 128 435 / 433 and 314 / 318, 16 to 128 1x1 at 56x56
+// 107 / 91; most others within 1 %.  A result that the caches hold until the next layer reads it is worth more there: whole bf16 step at 512 images 35.24 ms without, 34.80 from 64 MB,
+// 34.73 to 34.79 from 30, 50, 90 or 120 MB; fp32 at 32 images 10.44 with and without.  Results below the line gain as much by themselves (128 to 64 1x1 at 28x28, 51 MB 31 / 27) or nothing (3x3 over 256 at
+// 14x14, 51 MB 94.0 / 93.2).  Only where every row is whole lines of 128 bytes: a line that two tiles fill goes to memory twice (64 to 104 1x1 at 56x56 122 / 159, to 200 187 / 309; fp32, 64 to 100 170 / 201).
 constexpr double kStreamOutBytes = 64e6;
-inline int lc_stream_out(double bytes, const void* d, size_t row_bytes) {
-    return bytes >= kStreamOutBytes && row_bytes % 128 == 0 && (reinterpret_cast<uintptr_t>(d) & 127) == 0;
+// A copy that another layout is made of at once is left to the caches as long as the memory-side cache can hold it (NCHW, the pass and its transposes, us: bf16 3x3 over 128, 103 MB 310 / 318 and 313 / 321,
+// 512 to 128 562 / 586; fp32 103 and 206 MB no difference; 128 to 512, 411 MB, bf16 603 / 547, fp32 506 / 490).  (Copies of a group's channels gain from 64 MB on: 3x3 over 128 392 / 374 and 398 / 376.)
+constexpr double kStreamCopyBytes = 256e6;
+inline int lc_stream_out(double bytes, const void* d, size_t row_bytes, double least = kStreamOutBytes) {
+    return bytes >= least && row_bytes % 128 == 0 && (reinterpret_cast<uintptr_t>(d) & 127) == 0;
 }
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream);
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` for this problem; 0: the kernel that takes it has none
@@ -140,8 +147,9 @@ lc_status lc_launch_conv_dma(const GemmConv& p, hipStream_t stream);
 // its tiles of 256 columns, with the plan that conv_dma_plan() made
 lc_status lc_launch_conv_dma_wide(const GemmConv& p, int tile, int nkt, long long tiles, int dp_tiles, int sk_blocks, long long sk_iters, hipStream_t stream);
 // the kernel (tile, addressing, whether blocks share tiles) that takes a problem, in words
-void lc_conv_dma_describe(const GemmConv& p, bool stats, char* text, size_t size);
-void lc_conv_gemm_describe(const GemmConv& p, bool stats, char* text, size_t size);
+// (`form`: also its form, where the plan has a choice of several that give the same sums)
+void lc_conv_dma_describe(const GemmConv& p, bool stats, bool form, char* text, size_t size);
+void lc_conv_gemm_describe(const GemmConv& p, bool stats, bool form, char* text, size_t size);
 // bf16 3x3 layers from 64 channels to 33 to 64 filters whose filter a wave holds in registers (conv_dma.hip)
 bool lc_conv_held_ok(const GemmConv& p, bool stats);
 size_t lc_conv_held_stats_tiles(const GemmConv& p);
@@ -203,11 +211,12 @@ struct GemmWgrad {
     int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (conv_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
-void lc_wgrad_describe(const GemmWgrad& p, char* text, size_t size);     // the kernel that takes a planned problem, in words
+void lc_wgrad_describe(const GemmWgrad& p, bool form, char* text, size_t size);     // the kernel that takes a planned problem, in words
 int lc_wgrad_splits(GemmWgrad* p);   // fixed function of the shape (determinism); chooses the tile of wgrad_dma_kernel where that takes the layer
 // bf16 operands straight into LDS (conv_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
 bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits);
 lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream);
+const char* lc_wgrad_dma_form(const GemmWgrad& p);      // which of its forms, in words behind a space, or nothing
 int lc_wgrad_dma_sum_rows(const GemmWgrad& p);     // rows that go into one running sum
 // fp32 operands on the bf16 matrix pipe (conv_split.hip), output tile bm x bn; and how many of its blocks fit on a compute unit
 lc_status lc_launch_wgrad_split(const GemmWgrad& p, int bm, int bn, hipStream_t stream);

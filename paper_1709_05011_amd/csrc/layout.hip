@@ -395,7 +395,7 @@ void lc_zero_bytes(void* dst, size_t bytes, hipStream_t stream) {
 
 // Zeros between the stride grid of [n][h][w][pixel_bytes]: what the caller's kernel does not write.  Cleared as a whole are pixels that are not whole aligned
 // vectors, rows that leave most of a block idle, and tensors whose threads a 32-bit number does not hold (64 GiB).
-void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh, int sw, hipStream_t stream) {
+void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh, int sw, bool past, hipStream_t stream) {
     const size_t bytes = (size_t)n * h * w * pixel_bytes, vecs = (size_t)w * (pixel_bytes / 16);
     const size_t chunks = (vecs + kZeroThreads - 1) / kZeroThreads;
     if (pixel_bytes % 16 != 0 || !aligned16(dst) || vecs < kZeroThreads / 2 || (double)n * h * (double)chunks * kZeroThreads > 4294967295.0) {
@@ -416,7 +416,7 @@ void lc_zero_off_grid(void* dst, int n, int h, int w, size_t pixel_bytes, int sh
     magic_for(sw, &s.sw_mul, &s.sw_shift);
     magic_for(s.groups, &s.g_mul, &s.g_shift);
     const dim3 grid((unsigned)((size_t)n * h * chunks));
-    if (lc_stream_out((double)bytes, dst, pixel_bytes)) hipLaunchKernelGGL((zero_off_grid_kernel<true>), grid, dim3(kZeroThreads), 0, stream, static_cast<uint4*>(dst), s);
+    if (past) hipLaunchKernelGGL((zero_off_grid_kernel<true>), grid, dim3(kZeroThreads), 0, stream, static_cast<uint4*>(dst), s);
     else hipLaunchKernelGGL((zero_off_grid_kernel<false>), grid, dim3(kZeroThreads), 0, stream, static_cast<uint4*>(dst), s);
 }
 

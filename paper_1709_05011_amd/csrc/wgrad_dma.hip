@@ -403,14 +403,24 @@ int lc_wgrad_dma_sum_rows(const GemmWgrad& p) {
     return p.dma_bm * p.dma_bn == 256 * 256 ? p.m_per_split : std::min(p.m_per_split, wgrad_chain_stages(p) * 32);
 }
 
+// One tile of large operands, bound by memory: all blocks work on one narrow stretch of both (and past the caches: nothing reads them again) instead of each
+// on rows of its own.  64 to 256 1x1, 512 images of 56x56 173 -> 150 us (6.8 TB/s), 256 to 64 172 -> 152.  Several tiles read the same rows, and the L2s
+// hold them better in one place: 512 to 128 at 28x28 104 / 108, 512 to 2048 at 7x7 64 / 73.
+static bool wgrad_around(const GemmWgrad& p, int bm, int bn) { return wgrad_plain(p) && p.K <= bm && p.J <= bn && (double)p.M * (p.K + p.C) * 2 >= 128e6; }
+// 128x128 tiles whose blocks have a compute unit each: eight waves, which hide each other's reads of LDS (3x3 over 512 channels, 37 images of 7x7 26.3 -> 23.1 us,
+// one image of 28x28 15.7 -> 13.9).
+static bool wgrad_eight_waves(const GemmWgrad& p) { return (long long)((p.K + 127) / 128) * ((p.J + 127) / 128) * p.splits <= device_cu_count(); }
+
+const char* lc_wgrad_dma_form(const GemmWgrad& p) {
+    const bool eight = p.dma_bm == 128 && p.dma_bn == 128 && wgrad_eight_waves(p);
+    return wgrad_around(p, p.dma_bm, p.dma_bn) ? (eight ? " eight waves around" : " around") : eight ? " eight waves" : "";
+}
+
 lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
     if (!aligned16(p.dy) || !aligned16(p.x)) return LC_ERR_ALIGN;
     const bool plain = wgrad_plain(p);
     auto go = [&]<int BM, int BN, int WM, int WN, int NS>() {
-        // One tile of large operands, bound by memory: all blocks work on one narrow stretch of both (and past the caches: nothing reads them again) instead of each
-        // on rows of its own.  64 to 256 1x1, 512 images of 56x56 173 -> 150 us (6.8 TB/s), 256 to 64 172 -> 152.  Several tiles read the same rows, and the L2s
-        // hold them better in one place: 512 to 128 at 28x28 104 / 108, 512 to 2048 at 7x7 64 / 73.
-        if (plain && p.K <= BM && p.J <= BN && (double)p.M * (p.K + p.C) * 2 >= 128e6) return launch_wgrad_dma<BM, BN, WM, WN, NS, kAround>(p, stream);
+        if (wgrad_around(p, BM, BN)) return launch_wgrad_dma<BM, BN, WM, WN, NS, kAround>(p, stream);
         return plain ? launch_wgrad_dma<BM, BN, WM, WN, NS, kPlain>(p, stream) : launch_wgrad_dma<BM, BN, WM, WN, NS, kWindow>(p, stream);
     };
     switch (p.dma_bm * 1000 + p.dma_bn) {
@@ -418,8 +428,7 @@ lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream) {
         case 256128: return go.template operator()<256, 128, 4, 2, 5>();
         case 128256: return go.template operator()<128, 256, 2, 4, 5>();
         case 128128:
-            // (blocks that have a compute unit each: eight waves, which hide each other's reads of LDS; 3x3 over 512 channels, 37 images of 7x7 26.3 -> 23.1 us, one image of 28x28 15.7 -> 13.9)
-            if ((long long)((p.K + 127) / 128) * ((p.J + 127) / 128) * p.splits <= device_cu_count()) return go.template operator()<128, 128, 2, 4, 5>();
+            if (wgrad_eight_waves(p)) return go.template operator()<128, 128, 2, 4, 5>();
             return go.template operator()<128, 128, 2, 2, 4>();
         case 256064: return go.template operator()<256, 64, 4, 1, 3>();
         case 64256: return go.template operator()<64, 256, 1, 4, 3>();

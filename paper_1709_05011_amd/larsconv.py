@@ -487,12 +487,12 @@ def batchnorm_bwd_presummed_t(dtype: int, x, dy, gamma, save_mean, save_invstd, 
                                            _stream(stream)), "batchnorm_bwd_presummed_t")
 # ---- batch-norm statistics out of the convolution's epilogue ----
 
-def conv_route(desc, which: int, stats: bool = False) -> str:
+def conv_route(desc, which: int, stats: bool = False, form: bool = False) -> str:
     """The kernel a pass of a layer ends in, in the library's words (host only; for tests and labels, not part of the C ABI)."""
     fn = lib().lc_selftest_conv_route
     fn.restype, fn.argtypes = ctypes.c_int, [ctypes.POINTER(lc_conv_desc), ctypes.c_int, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]
     text = ctypes.create_string_buffer(96)
-    _check(fn(ctypes.byref(_desc(desc)), which, int(stats), text, 96), "conv_route")
+    _check(fn(ctypes.byref(_desc(desc)), which, int(stats) + 2 * form, text, 96), "conv_route")
     return text.value.decode()
 
 

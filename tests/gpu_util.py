@@ -73,8 +73,8 @@ def scaled_err(got: np.ndarray, ref: np.ndarray) -> float:
     return float(np.max(np.abs(got - ref))) / (scale if scale > 0 else 1.0) if ref.size else 0.0
 
 
-def route(d: lc.ConvDesc, which: int, stats: bool = False) -> str:
-    return lc.conv_route(d, which, stats)
+def route(d: lc.ConvDesc, which: int, stats: bool = False, form: bool = False) -> str:
+    return lc.conv_route(d, which, stats, form)
 
 
 def guarded(shape, dtype, guard_bytes=4096, offset=0):

@@ -100,3 +100,33 @@ def test_few_columns_and_short_reductions_stay_with_the_main_kernel():
         assert gu.route(d, lc.LC_PASS_FWD).startswith(kernel), (d, gu.route(d, lc.LC_PASS_FWD))
         assert gu.route(d, lc.LC_PASS_FWD, stats=True).startswith(kernel)
         assert gu.route(_desc(n, k, hw, hw, c, r, r, 1, r // 2, r // 2), lc.LC_PASS_BWD_DATA).startswith(kernel)
+
+
+def _layer(n, c, hw, k, r=1, stride=1, dtype=lc.LC_BF16, layout=lc.LC_NHWC):
+    return lc.ConvDesc(n, c, hw, hw, k, r, r, stride, stride, r // 2, r // 2, dtype, layout)
+
+
+@pytest.mark.parametrize("d,fwd,bwd", [
+    (_layer(512, 128, 28, 512), True, True),
+    (_layer(512, 256, 14, 256, 3), False, False),                       # 51 MB
+    (_layer(512, 64, 56, 104), False, True),                            # rows of 208 bytes
+    (_layer(512, 16, 56, 64), True, False),                             # two waves fill a line; rows of 32 bytes
+    (_layer(512, 16, 28, 128), False, False),                           # reductions of 16 values to 128 columns: products that end before their stores
+    (_layer(512, 8, 28, 256), False, False),
+    (_layer(512, 16, 28, 640), False, False),
+    (_layer(512, 128, 28, 128, 3, layout=lc.LC_NCHW), False, False),    # 103 MB that a transpose reads next
+    (_layer(512, 128, 28, 512, layout=lc.LC_NCHW), True, False),        # 411 MB, 103 MB
+    (_layer(256, 128, 28, 512, dtype=lc.LC_F32, layout=lc.LC_NCHW), True, False),
+    (_layer(256, 128, 28, 512, dtype=lc.LC_F32), True, True),
+], ids=str)
+def test_results_that_go_past_the_caches(d, fwd, bwd):
+    assert gu.route(d, lc.LC_PASS_FWD, form=True).endswith(" past") == fwd
+    assert gu.route(d, lc.LC_PASS_BWD_DATA, form=True).endswith(" past") == bwd
+
+
+@pytest.mark.parametrize("d,past", [(_layer(512, 512, 28, 1024, 1, 2), True), (_layer(256, 512, 28, 1024, 1, 2, lc.LC_F32), False),
+                                    (_layer(256, 256, 56, 512, 1, 2, lc.LC_F32), False), (_layer(128, 512, 28, 256, 1, 2, lc.LC_F32), True),
+                                    (_layer(64, 64, 56, 128, 1, 2, lc.LC_F32), False), (_layer(512, 64, 56, 64, 1, 2, lc.LC_F32), True)], ids=str)
+def test_zeros_between_a_stride_grid_that_go_past_the_caches(d, past):
+    """Not before a long fp32 product, nor where the caches hold them."""
+    assert gu.route(d, lc.LC_PASS_BWD_DATA, form=True).endswith(", zeros past") == past
