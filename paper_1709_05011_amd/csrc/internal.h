@@ -133,7 +133,7 @@ lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream);
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` for this problem; 0: the kernel that takes it has none
 extern "C" int lc_selftest_stream_k(int max_blocks);   // host check of the work split's 32-bit form (0 = all good)
 extern "C" int lc_selftest_division(int max_d);   // host check of the multiply-high division constants (0 = all good)
-extern "C" long long lc_selftest_lars_launches(int n_chunks);   // host check of the update pass's launches (lars.hip)
+extern "C" long long lc_selftest_lars_launches(int n_chunks, long long longest);   // host check of the update pass's launches (lars.hip)
 bool lc_conv_gemm_bf16_native(const GemmConv& p);   // can the bf16 MFMA kernel take this problem (shape and alignment)?
 bool lc_conv_gemm_scatter_ok(const GemmConv& p);    // can the main kernel's scatter epilogue take this problem?
 // fp32 backward-data on the bf16 matrix pipe (conv_split.hip), and the partial-tile bytes they need

@@ -223,13 +223,16 @@ lars_finalize_kernel(LarsWorkspace ws, float lr, float* __restrict__ trust_out) 
 
 // One vector a thread and one wave a block: the chip works on one narrow stretch of the three arrays at a time.  NT: every access past the caches' usual
 // keeping; what the norm pass left of w and g in the memory-side cache is still found there, and the new values push nothing out that is read sooner.
-// ResNet-50's list (102 MB an array), whole call: 138 us with ordinary accesses, 128 with such stores alone, 115 with both; 8 million parameters in 60 tensors
-// 250 -> 207.  Lists whose arrays fit the caches together are indifferent (5.8 million parameters 39.7 and 40.6 us) and keep the ordinary form.
+// ResNet-50's list (102 MB an array), whole call: 138 us with ordinary accesses, 128 with such stores alone, 115 with both; 47 million parameters in 60 tensors
+// 250 -> 207.
+// From 12 million parameters on, by what a list meets between two steps (us, ordinary / so, 20 tensors): four lists in turn, none of which the caches still hold, 4 million 27.5 / 31.1, 8 million
+// 51 / 47, 12 million 69 / 61, 25 million 132 / 113, 40 million 208 / 175; one list again at once 27.6 / 29.8, 42 / 47, 57 / 62, 108 / 113, 188 / 174.  A training step passes gigabytes
+// between two calls, as the first; at the line that gains more than the second loses.
 constexpr int kUpdateThreads = 64, kPart = kUpdateThreads * 4, kParts = kChunk / kPart;
 constexpr long long kStreamParams = 12 << 20;                // three arrays of 48 MB
 __global__ void __launch_bounds__(kUpdateThreads)
-lars_update_kernel(LarsWorkspace ws, int n_chunks, float momentum, bool stream) {
-    const int chunk = n_chunks - 1 - (int)(blockIdx.x / kParts), part = kParts - 1 - (int)(blockIdx.x % kParts);
+lars_update_kernel(LarsWorkspace ws, int n_chunks, int parts_log2, float momentum, bool stream) {
+    const int chunk = n_chunks - 1 - (int)(blockIdx.x >> parts_log2), part = (1 << parts_log2) - 1 - (int)(blockIdx.x & ((1u << parts_log2) - 1));
     const int l = ws.chunk_tensor[chunk];
     const LarsTensor t = ws.table[l];
     const float weight_decay = t.weight_decay;
@@ -336,11 +339,20 @@ lc_status lars_check(int n_tensors, float* const* w, const float* const* g, floa
     return LC_OK;
 }
 
+// Parts of a chunk that the update pass has blocks for, a power of two: no more than the longest tensor fills (1000 tensors of 1000 elements: sixteen parts, twelve of them empty, 8.6 us for this kernel,
+// 4.8 in blocks of a whole chunk; four parts 5.2).
+constexpr int kPartsLog2 = 4;
+static_assert(1 << kPartsLog2 == kParts);
+int update_parts_log2(long long longest) {
+    int p = 0;
+    while (p < kPartsLog2 && (long long)kPart << p < longest) ++p;
+    return p;
+}
 // The update pass's launches, each with fewer than 2^32 threads (the runtime takes no more): go(last, blocks) for the chunks last - 1, last - 2, ...
-constexpr int kMostChunks = (int)(0xffffffffull / (kParts * kUpdateThreads));
 template <typename F>
-void for_update_launches(int n_chunks, F&& go) {
-    for (int last = n_chunks; last > 0; last -= kMostChunks) go(last, (unsigned)(last < kMostChunks ? last : kMostChunks) * kParts);
+void for_update_launches(int n_chunks, int parts_log2, F&& go) {
+    const int most = (int)std::min(0x7fffffffull, 0xffffffffull / ((unsigned long long)kUpdateThreads << parts_log2));
+    for (int last = n_chunks; last > 0; last -= std::min(last, most)) go(last, (unsigned)std::min(last, most) << parts_log2);
 }
 
 // The launches of one step on scratch memory at `base` (device, 256-byte aligned, lay.total bytes).
@@ -358,6 +370,7 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
 
     LarsGroupArgs args;
     int chunk_cursor = 0;
+    int64_t longest = 0;
     for (int first = 0; first < n_tensors; first += kTablePerLaunch) {
         const int count = (n_tensors - first) < kTablePerLaunch ? (n_tensors - first) : kTablePerLaunch;
         args.chunk_begin = chunk_cursor;
@@ -369,6 +382,7 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
             t.v = v[l];
             t.w_lowp = w_lowp_out ? static_cast<uint16_t*>(w_lowp_out[l]) : nullptr;
             t.numel = numel[l];
+            longest = std::max(longest, numel[l]);
             t.eta = eta_per_tensor ? eta_per_tensor[l] : eta;
             t.weight_decay = weight_decay_per_tensor ? weight_decay_per_tensor[l] : weight_decay;
             t.skip = skip ? (int)skip[l] : 0;
@@ -387,8 +401,9 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
     }
     hipLaunchKernelGGL(lars_finalize_kernel, dim3(n_tensors), dim3(kThreads), 0, stream, ws, lr, trust_out);
     if (lay.n_chunks > 0) {
-        for_update_launches((int)lay.n_chunks, [&](int last, unsigned blocks) {
-            hipLaunchKernelGGL(lars_update_kernel, dim3(blocks), dim3(kUpdateThreads), 0, stream, ws, last, momentum, lay.n_chunks >= kStreamParams / kChunk);
+        const int parts_log2 = update_parts_log2(longest);
+        for_update_launches((int)lay.n_chunks, parts_log2, [&](int last, unsigned blocks) {
+            hipLaunchKernelGGL(lars_update_kernel, dim3(blocks), dim3(kUpdateThreads), 0, stream, ws, last, parts_log2, momentum, lay.n_chunks >= kStreamParams / kChunk);
         });
     }
     return lc_end_call();
@@ -396,11 +411,14 @@ lc_status lars_run(int n_tensors, float* const* w, const float* const* g, float*
 
 }  // namespace
 
-// Host check of the update pass's launches for a list of so many chunks: the threads of the largest, or -1 where they do not take every chunk once.
-extern "C" long long lc_selftest_lars_launches(int n_chunks) {
+// Host check of the update pass's launches for a list of so many chunks whose longest tensor has so many elements: the threads of the largest, or -1 where
+// they do not take every part of every chunk once.
+extern "C" long long lc_selftest_lars_launches(int n_chunks, long long longest) {
+    const int parts_log2 = update_parts_log2(longest);
     long long most = 0, next = n_chunks;
-    for_update_launches(n_chunks, [&](int last, unsigned blocks) {
-        next = last == next && blocks % kParts == 0 ? next - blocks / kParts : -1;
+    if ((long long)kPart << parts_log2 < std::min<long long>(longest, kChunk)) return -1;
+    for_update_launches(n_chunks, parts_log2, [&](int last, unsigned blocks) {
+        next = last == next && blocks % (1u << parts_log2) == 0 ? next - (blocks >> parts_log2) : -1;
         most = std::max(most, (long long)blocks * kUpdateThreads);
     });
     return next == 0 ? most : -1;

@@ -155,9 +155,12 @@ def test_lars_update_launches_hold_fewer_than_2_to_the_32_threads():
     # the runtime refuses a larger launch; a list of 2^34 parameters (2^22 chunks of 4096) fits the card, the layout takes up to 2^31 - 1 chunks
     L = lc.lib()
     L.lc_selftest_lars_launches.restype = ctypes.c_longlong
-    L.lc_selftest_lars_launches.argtypes = [ctypes.c_int]
+    L.lc_selftest_lars_launches.argtypes = [ctypes.c_int, ctypes.c_longlong]
     for chunks in (1, 2, 1000, (1 << 22) - 2, (1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 23) - 3, 1 << 23, 3 << 23, (1 << 31) - 1):
-        assert 0 < L.lc_selftest_lars_launches(chunks) < 1 << 32, chunks
+        for longest in (1, 255, 256, 257, 511, 513, 1000, 1024, 1025, 2048, 2049, 4096, 4097, 1 << 34):
+            assert 0 < L.lc_selftest_lars_launches(chunks, longest) < 1 << 32, (chunks, longest)
+    # no blocks for parts that no tensor fills
+    assert [L.lc_selftest_lars_launches(1000, n) // 64000 for n in (256, 257, 600, 1000, 2000, 2049, 1 << 20)] == [1, 2, 4, 4, 8, 16, 16]
 
 
 def test_filter_gradients_bound_by_memory_or_latency_plan_for_the_fp32_kernels():
