@@ -651,10 +651,12 @@ inline unsigned stream_blocks(size_t items) {
 // leaves those there, where the next pass, which walks the other way, finds them (bf16, two tensors of 206 MB: 182 us for the backward pass with ordinary
 // loads throughout, 197 with none, 174 to 177 so; read alone, 822 MB come at 6.1 TB/s with ordinary loads and 6.8 without keeping).
 constexpr size_t kKeepBytes = (size_t)200 << 20;
-// Apply pass, tensors of this size and more: non-temporal loads and stores.  Below, the data is in the caches or is wanted there: whole fp32 step at 32
-// images (tensors to 103 MB) 10.98 ms with ordinary stores, 11.02 with such stores from 64 MB, 11.12 from 20 MB; whole bf16 step at 512 images 36.43 without either,
-// 35.90 with both.  Such loads beside ordinary stores are the worst of the four (103 MB in fp32, a layer's two passes by themselves: 189 us; both ordinary 173).
-// The line is just above that step's 103 MB: bf16, 120 MB of cold data take 175 us with ordinary accesses, 165 with these; 140 MB 229 and 206.
+// Apply pass, tensors of this size and more: non-temporal loads and stores.  Where the caches hold none of a call's tensors these gain at any size, where they hold all of them these lose until
+// the tensors outgrow the caches; the line is where they cost at most 2 % even then.  Whole passes, us, ordinary accesses / so, tensors not held, then held: fp32 forward 52 MB 36 / 32 and
+// 32 / 33, 103 MB 65 / 55 and 54.0 / 54.6, 120 MB 74 / 62 and 60.6 / 61.7; with a residual 103 MB 77 / 71 and 70.5 / 71.0, 120 MB 89 / 80 and 80.5 / 80.6; backward (three tensors) 52 MB 55 / 49 and
+// 47 / 50, 103 MB 99 / 90 and 87 / 89, 120 MB 112 / 103 and 100.5 / 101.0; bf16 the same within 2 % but for the backward pass, 52 MB 57 / 52 and 49 / 53, 103 MB 105 / 92 and 91 / 92.  From 140 MB on
+// nothing loses.  Between the layers of a step tensors are neither: a line at 50, 99, 112 or 210 MB gives 10.42, 10.41, 10.44 and 10.43 ms in fp32 at 32 images, 11.69, 11.77, 11.79 and
+// 11.86 in bf16 at 128, 34.70, 34.68, 34.77 and 34.93 at 512.  Such loads beside ordinary stores are the slowest of the four (103 MB in fp32, a layer's two passes 189 us; both ordinary 173).
 constexpr size_t kStreamBytes = 112000000;
 
 template <typename T, int VEC, int MODE, int JOIN = 0>

@@ -8,7 +8,7 @@ namespace {
 // ------------------------------------------------------------------------------------------------
 // Forward and backward-data.  A k-step is 64 values of the reduction: 128 bytes of a row, so that a load of 64 lanes covers eight whole lines.  LDS holds a
 // stage as [row][128 bytes] with the 16-byte pieces of a row at piece ^ (row / 2 % 8) -- the lanes fetch them in that order -- and a fragment of sixteen rows then
-// meets every bank once.  Two stages; while one is multiplied the other arrives, across tile boundaries (persistent blocks, segments as in SkWalk).
+// meets every bank once.  NS stages, two or four; while one is multiplied the others arrive, across tile boundaries (persistent blocks, segments as in SkWalk).
 //
 // A wave owns 16 TM x 16 TN of the tile in 16x16 pieces, the filter being the matrix instruction's first operand: a lane holds four neighbouring columns of a
 // pixel.  TMA and TMB: rows of pieces of the first and the second row of waves; each SIMD runs one wave of either kind, so a tile may have any
@@ -633,10 +633,14 @@ bool conv_dma_shares(const ConvDmaPlan& c) { return c.sk.sk_iters != (long long)
 // (An instance of its own: the choice within the loop cost windows 1 to 2 %.)
 bool conv_dma_once(const GemmConv& p, int bn) { return p.N <= bn && p.R * p.S == 1 && !p.scatter && ((p.N | p.ldd) & 7) == 0 && (double)p.M * p.Ci * 2 >= 256e6; }
 
-// Blocks that have a compute unit each, and eight k-steps and more: four stages in flight, and 128x128 tiles by eight waves.  One block alone waits for its own loads -- they take longer than a k-step's
-// products -- and with one wave a SIMD for every read of LDS.  The same sums.  us, forward and backward-data before / so (ragged: 72 k-steps of 60 tiles in four parts): 512 to 512 3x3, 37
-// images of 7x7 27.9 / 23.3 and 34.0 / 29.6 (four stages with four waves 27.4 and 33.1), one image of 28x28 20.5 / 19.0 and 27.1 / 25.7; 128 to 128 3x3, 16 of 28x28 14.4 / 12.7 and 17.6 / 16.1; 1024 to 256 1x1, 16 of
-// 14x14 13.4 / 11.1.  Fewer k-steps gain nothing: 256 to 256 3x3, 8 of 14x14 17.3 / 18.1.
+// Blocks that have a compute unit each, and eight k-steps and more: four stages in flight, and 128x128 tiles by eight waves.  One block alone waits for its own loads, which take longer than a k-step's
+// products where they come from beyond its L2, and with one wave a SIMD for every read of LDS.  The same sums.  us, two stages / four, forward and backward-data, 24 sets of tensors in turn: 512 to 512
+// 3x3, 37 images of 7x7 27.7 / 22.9 and 31.6 / 30.6, one image of 28x28 21.9 / 16.7 and 25.8 / 24.2; 128 to 128 3x3, 16 of 28x28 13.7 / 11.8 and 17.0 / 15.1; 1024 to 256 1x1, 16 of 14x14 12.8 / 10.6; at eight
+// and nine k-steps 512 to 512 1x1, four of 14x14 7.8 / 7.5 and 10.9 / 10.5, 64 to 192 3x3, eight of 28x28 8.7 / 8.2 and 15.9 / 15.6.  Of 110 such passes none is slower but 512 to 128 1x1 of one
+// image of 5x5, whose sets the L2s hold, 6.0 / 6.9.  So do all forward passes that run again on tensors that the L2s still hold: 0.9 us more at eight k-steps, 1.2 at eighteen (6.4 / 7.2, 10.3 / 11.5), while
+// their backward passes, whose filter has just been re-ordered on other units, gain (15.7 / 14.3).
+// The ragged layer's times depend on where its tensors lie: 24 or 25 / 26 to 32 and 32 / 28 to 32 over eight places of one set, 26.4 / 27.6 and 33.3 / 28.3 at another; its three passes
+// in turn 78.3 -> 68.7 to 69.0 us on three cards and 77.0 on one, with the filter gradient's eight waves.
 bool conv_dma_deep(const GemmConv& p, const ConvDmaPlan& c) {
     if ((c.tile != kSquare && c.tile != kNarrow) || c.sk.dp_tiles > 0 || c.sk.sk_blocks > device_cu_count() || conv_dma_in(p) > kPieces) return false;
     return c.sk.sk_blocks > 0 && c.sk.sk_iters >= 8LL * c.sk.sk_blocks;

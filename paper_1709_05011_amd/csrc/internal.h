@@ -208,12 +208,12 @@ struct GemmWgrad {
     int bf16;           // dy and x are bf16 (widened on the fly; the sums and d stay fp32)
     int slab;           // 3x3 stride-1 pad-1 bf16 layer for wgrad3x3_slab_kernel: m_per_split counts padded positions
     unsigned q_mul, q_shift, p_mul, p_shift;       // multiply-high division constants for Q and P (filled in by the launcher that needs them)
-    int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (conv_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
+    int dma_bm, dma_bn; // bf16 layer for wgrad_dma_kernel (wgrad_dma.hip): its tile, chosen by lc_wgrad_splits() (0: another kernel)
 };
 lc_status lc_launch_wgrad_f32(const GemmWgrad& p, hipStream_t stream);
 void lc_wgrad_describe(const GemmWgrad& p, bool form, char* text, size_t size);     // the kernel that takes a planned problem, in words
 int lc_wgrad_splits(GemmWgrad* p);   // fixed function of the shape (determinism); chooses the tile of wgrad_dma_kernel where that takes the layer
-// bf16 operands straight into LDS (conv_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
+// bf16 operands straight into LDS (wgrad_dma.hip): tile and number of splits for a shape, false where another kernel takes it; and the launch
 bool lc_wgrad_dma_plan(const GemmWgrad& p, int* bm, int* bn, int* splits);
 lc_status lc_launch_wgrad_dma(const GemmWgrad& p, hipStream_t stream);
 const char* lc_wgrad_dma_form(const GemmWgrad& p);      // which of its forms, in words behind a space, or nothing

@@ -403,13 +403,19 @@ int lc_wgrad_dma_sum_rows(const GemmWgrad& p) {
     return p.dma_bm * p.dma_bn == 256 * 256 ? p.m_per_split : std::min(p.m_per_split, wgrad_chain_stages(p) * 32);
 }
 
-// One tile of large operands, bound by memory: all blocks work on one narrow stretch of both (and past the caches: nothing reads them again) instead of each
-// on rows of its own.  64 to 256 1x1, 512 images of 56x56 173 -> 150 us (6.8 TB/s), 256 to 64 172 -> 152.  Several tiles read the same rows, and the L2s
-// hold them better in one place: 512 to 128 at 28x28 104 / 108, 512 to 2048 at 7x7 64 / 73.
-static bool wgrad_around(const GemmWgrad& p, int bm, int bn) { return wgrad_plain(p) && p.K <= bm && p.J <= bn && (double)p.M * (p.K + p.C) * 2 >= 128e6; }
-// 128x128 tiles whose blocks have a compute unit each: eight waves, which hide each other's reads of LDS (3x3 over 512 channels, 37 images of 7x7 26.3 -> 23.1 us,
-// one image of 28x28 15.7 -> 13.9).
-static bool wgrad_eight_waves(const GemmWgrad& p) { return (long long)((p.K + 127) / 128) * ((p.J + 127) / 128) * p.splits <= device_cu_count(); }
+// One tile of large operands, bound by memory: all blocks work on one narrow stretch of both (and past the caches: nothing reads them again) instead of each on rows of its own.  us, each on its own / so, two
+// sets in turn, images of 56x56: 128 to 64, 319 images 74.3 / 64.3, 205 49.8 / 43.5, 160 39.8 / 36.5; 64 to 128, 512 images 110 / 98, 200 to 72 160 / 141, 72 to 160 137 / 124, 128 to 32 88 / 78, 16 to 128 83 / 75.
+// From 160 MB on: 128 to 64, 154 MB 38.1 / 37.9, 96 to 64, 128 MB 26.4 / 30.6.  Where the operands fill three fifths of the tile's rows and columns: 72 to 72 82 / 89, 72 to 32 62 / 66, 8 to 96 64 / 65, though 8 to 160
+// 99 / 96.  Several tiles read the same rows, and the L2s hold them better in one place: 512 to 128 at 28x28 104 / 108, 512 to 2048 at 7x7 64 / 73.
+static bool wgrad_around(const GemmWgrad& p, int bm, int bn) {
+    return wgrad_plain(p) && p.K <= bm && p.J <= bn && 5 * (p.K + p.J) >= 3 * (bm + bn) && (double)p.M * (p.K + p.C) * 2 >= 160e6;
+}
+// 128x128 tiles whose blocks have a compute unit each: eight waves, which hide each other's reads of LDS.  us, four / eight: 3x3 over 512 channels, 37 images of 7x7 24.8 / 22.3, one image of 28x28 14.9 / 13.2,
+// 512 to 256, 16 of 14x14 23.4 / 21.7; 1x1 256 to 448, 96 of 21x21 27.3 / 25.9.  Splits of up to 100 stages gain, 1 to 12 % (twenty-six layers, the worst 1.015); longer ones are bound by memory: 196
+// stages, 512 to 128, 512 of 28x28 102 / 103, 200 to 72, 256 of 56x56 84 / 96.
+static bool wgrad_eight_waves(const GemmWgrad& p) {
+    return (long long)((p.K + 127) / 128) * ((p.J + 127) / 128) * p.splits <= device_cu_count() && p.m_per_split <= 128 * 32;
+}
 
 const char* lc_wgrad_dma_form(const GemmWgrad& p) {
     const bool eight = p.dma_bm == 128 && p.dma_bn == 128 && wgrad_eight_waves(p);

@@ -130,3 +130,59 @@ def test_results_that_go_past_the_caches(d, fwd, bwd):
 def test_zeros_between_a_stride_grid_that_go_past_the_caches(d, past):
     """Not before a long fp32 product, nor where the caches hold them."""
     assert gu.route(d, lc.LC_PASS_BWD_DATA, form=True).endswith(", zeros past") == past
+
+
+def test_shapes_of_few_blocks_meet_every_form():
+    import test_gpu_conv_deep as deep
+
+    seen = set()
+    for n, h, w, c, k, r, s in deep.LAYERS:
+        d = _desc(n, c, h, w, k, r, r, s, r // 2, r // 2)
+        for which, out, columns, stats in ((lc.LC_PASS_FWD, "rows", k, False), (lc.LC_PASS_FWD, "stats", k, True), (lc.LC_PASS_BWD_DATA, "rows" if s == 1 else "grid", c, False)):
+            m = re.fullmatch(r"conv_dma (128x\d+) (\w+)( shared)? four stages", gu.route(d, which, stats, form=True))
+            if m:
+                seen.add((m[1], m[2], out if columns % 8 == 0 or out != "rows" else "any", bool(m[3])))
+        if "eight waves" in gu.route(d, lc.LC_PASS_BWD_WEIGHT, form=True):
+            seen.add("eight waves")
+    want = {"eight waves"} | {(t, i, o, True) for t in ("128x64", "128x128") for i in ("chunks", "padded") for o in ("rows", "stats")}
+    want |= {(t, i, o, False) for t in ("128x64", "128x128") for i, o in (("chunks", "rows"), ("chunks", "stats"), ("chunks", "any"), ("pieces", "rows"), ("pieces", "stats"), ("chunks", "grid"))}
+    want |= {("128x128", "pieces", "rows", True), ("128x128", "chunks", "any", True)}
+    assert not want - seen, want - seen
+
+
+def test_shapes_past_the_caches_meet_every_form():
+    import test_gpu_conv_stream as stream
+
+    seen = {lc.LC_BF16: set(), lc.LC_F32: set()}
+    for dtype, forms in seen.items():
+        for n, h, w, c, k in stream.POINTWISE:
+            d = lc.ConvDesc(n, c, h, w, k, 1, 1, 1, 1, 0, 0, dtype, lc.LC_NHWC)
+            forms |= {("fwd", gu.route(d, lc.LC_PASS_FWD, form=True)), ("bwd", gu.route(d, lc.LC_PASS_BWD_DATA, form=True)),
+                      ("dw", re.sub(r" splits.*sums \d+", "", gu.route(d, lc.LC_PASS_BWD_WEIGHT, form=True)))}
+        for n, h, w, c, k, r, s in stream.WINDOWS:
+            if s == 2 and r == 1:
+                c, k = k, c
+            d = lc.ConvDesc(n, c, h, w, k, r, r, s, s, r // 2, r // 2, dtype, lc.LC_NHWC)
+            forms |= {("fwd", gu.route(d, lc.LC_PASS_FWD, form=True)), ("bwd", gu.route(d, lc.LC_PASS_BWD_DATA, form=True))}
+            if s == 2 and r > 1 and r < 7:
+                forms.add(("phases", gu.route(d, lc.LC_PASS_BWD_DATA, form=True)))
+    want = {("dw", f"wgrad_dma {t} around") for t in ("64x128", "128x64", "256x64", "64x256", "256x128", "128x256", "128x128", "256x256", "128x128 eight waves")}
+    want |= {("dw", "wgrad_dma 128x128 eight waves")}
+    want |= {("fwd", f"conv_dma {t} chunks once{p}") for t, p in (("128x64 two waves", ""), ("128x128", ""), ("128x32", ""), ("256x256", " past"))}
+    want |= {("bwd", "conv_dma 128x32 chunks once"), ("bwd", "conv_dma 128x128 chunks once past")}
+    want |= {("fwd", f"{f} past") for f in ("conv3x3_held", "conv3x3_slab", "conv_gemm_pk 256x64", "conv_gemm_pk 128x64", "conv_dma 128x64 two waves chunks", "conv_dma 128x128 chunks",
+                                            "conv_dma 128x128 pieces", "conv_dma 256x256 chunks", "conv_dma 224x256 chunks", "conv_dma 240x256 chunks", "conv_dma 224x256 pieces")}
+    want |= {("bwd", "conv3x3_held past"), ("bwd", "conv_dma 128x128 chunks past, zeros past"), ("phases", "conv_dma 128x128 chunks past")}
+    assert not want - seen[lc.LC_BF16], want - seen[lc.LC_BF16]
+    want = {("fwd", "conv_gemm_pk 128x64 past"), ("fwd", "conv_gemm_pk 128x128 past"), ("bwd", "conv_gemm_split past"), ("bwd", "conv_gemm_split past, zeros past"),
+            ("phases", "conv_gemm_split past")}
+    assert not want - seen[lc.LC_F32], want - seen[lc.LC_F32]
+
+
+def test_filter_gradients_round_the_splits():
+    """Large operands, one tile of which they fill three fifths; eight waves where a split is short."""
+    for (n, hw, c, k, r), form in (((319, 56, 128, 64, 1), "around"), ((160, 56, 128, 64, 1), "around"), ((512, 28, 128, 64, 1), ""), ((512, 28, 96, 64, 1), ""), ((512, 56, 72, 72, 1), ""),
+                                   ((512, 56, 72, 32, 1), ""), ((512, 56, 64, 256, 1), ""), ((37, 7, 512, 512, 3), "eight waves"), ((96, 21, 256, 448, 1), "eight waves"),
+                                   ((256, 56, 200, 72, 1), ""), ((512, 28, 512, 128, 1), "")):
+        m = re.fullmatch(r"wgrad_dma (\d+x\d+) splits \d+ sums \d+ ?(.*)", gu.route(_layer(n, c, hw, k, r), lc.LC_PASS_BWD_WEIGHT, form=True))
+        assert m and m[2] == form, (n, hw, c, k, r, m and m[0])

@@ -1,7 +1,7 @@
 """GPU parity of the bf16 kernels that few blocks run on: forward and backward-data with four stages in flight (at most one block a compute unit,
 eight k-steps and more: counts around the four stages' wrap, one tile to many, shared tiles and whole ones, whole and padded channel
-chunks, pieces, ragged rows and columns, stride grids, statistics) and filter gradients of 128x128 tiles by eight waves.  Reference: float64 on
-the CPU.
+chunks, pieces, ragged rows and columns, stride grids, statistics; 128x64 and 128x128 tiles) and filter gradients of 128x128 tiles by eight waves; and
+shapes of the same kind just below eight k-steps a block.  test_conv_routes.py asks the library whether every form is met.  Reference: float64 on the CPU.
 
 Bounds: as products are exact in fp32, a sum of n of them is off by n * 2^-24 of the sum of their sizes at most, in practice by its square
 root: four times that; y and dx are rounded once more to bf16, 2^-8 of the value."""
@@ -29,6 +29,18 @@ LAYERS = [
     (4, 10, 10, 640, 512, 1, 2),      # stride grid
     (1, 28, 28, 512, 512, 3, 1),      # 72
     (1, 6, 6, 1032, 48, 1, 1),        # narrow tiles, pieces
+    (1, 5, 7, 512, 97, 1, 1),         # odd columns
+    (2, 8, 8, 504, 64, 3, 1),         # channels filled up to 512, shared tiles
+    # 128x128 tiles
+    (37, 7, 7, 512, 512, 3, 1),       # 72, shared
+    (4, 28, 28, 256, 256, 3, 1),      # 36, shared
+    (16, 14, 14, 504, 256, 3, 1),     # filled up, shared
+    (37, 7, 7, 88, 512, 5, 1),        # pieces, shared
+    (32, 7, 7, 1032, 2048, 1, 1),     # pieces, whole
+    (32, 7, 7, 1024, 2044, 1, 1),     # columns in pairs, whole
+    (37, 7, 7, 512, 500, 3, 1),       # columns in pairs, shared
+    (32, 14, 14, 512, 2048, 1, 2),    # stride grid, shared
+    (37, 14, 14, 1024, 2048, 1, 2),   # stride grid, whole
 ]
 
 

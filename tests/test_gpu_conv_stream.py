@@ -1,7 +1,8 @@
 """GPU parity of the convolution passes where their large operands and results go past the caches: results of 64 MB and more (every kernel
-that stores one: whole rows, ragged columns, stride grids, fp32 and bf16, the first layer), rows of 256 MB and more that are read once (1x1
-forward and backward-data to one tile of columns) and filter gradients of one tile, whose stages go round the splits.  Row counts are
-no multiple of any tile.  Reference: plain products in float64 (1x1) or float32 (windows, by torch) of the same values, on the device.
+that stores one so: tiles of conv_dma, held, slab, main and fp32 kernels, stride grids and the zeros between them, phases of a strided window, the first layer;
+and results that do not: ragged columns, copies), rows of 256 MB and more that are read once (1x1 forward and backward-data to one tile of columns) and
+filter gradients of one tile, whose stages go round the splits.  Row counts are no multiple of any tile.  Which form each shape is for stands beside it, and
+test_conv_routes.py asks the library whether all of them are met.  Reference: plain products in float64 (1x1) or float32 (windows, by torch) of the same values, on the device.
 
 Bounds: a sum of n products in fp32 is off by at most n * 2^-24 of the sum of their sizes, in practice by its square root: four times
 that; a bf16 result is rounded once more, 2^-8 of the value."""
@@ -31,9 +32,14 @@ def _close(got, ref, size, n, bf16):
     assert bad.max().item() <= 0.0
 
 
-# (images, h, w, c, k): rows * k (and rows * c) around the limits; 40, 100 and 97 columns end within a tile, 97 within a line
-POINTWISE = [(1, 500, 503, 512, 40), (1, 500, 503, 512, 104), (1, 500, 503, 512, 256), (1, 1021, 979, 128, 64), (1, 601, 601, 64, 100), (1, 601, 601, 64, 97),
-             (1, 331, 333, 24, 512), (1, 401, 403, 64, 256), (1, 401, 403, 256, 64)]
+# (images, h, w, c, k); 40, 100 and 97 columns end within a tile, 97 within a line
+POINTWISE = [(1, 500, 503, 512, 40), (1, 500, 503, 512, 104), (1, 500, 503, 512, 256),                 # rows read once: 128x64, 128x128 and 256x256 tiles
+             (1, 500, 503, 512, 32), (1, 500, 503, 32, 512), (1, 500, 503, 128, 512),                  # 128x32; backward-data to 32 and 128 columns
+             (1, 1021, 979, 128, 64), (1, 801, 803, 120, 8), (1, 801, 803, 24, 104), (1, 801, 803, 8, 184), (1, 801, 803, 184, 8),   # gradients of one tile: 64x128 twice, 128x64, 256x64, 64x256
+             (1, 801, 803, 72, 88), (1, 1281, 1283, 80, 80), (1, 801, 803, 96, 136), (1, 1001, 1003, 200, 72),      # 128x128 by eight waves and by four, 256x128, 128x256
+             (1, 1281, 1283, 200, 136), (1, 801, 803, 72, 72),                                         # 256x256; a tile less than three fifths full
+             (1, 801, 803, 64, 64),                                                                    # the main kernel's 256x64 tile
+             (1, 601, 601, 64, 100), (1, 601, 601, 64, 97), (1, 331, 333, 24, 512), (1, 401, 403, 64, 256), (1, 401, 403, 256, 64)]
 
 
 @pytest.mark.parametrize("dtype", [lc.LC_BF16, lc.LC_F32])
@@ -63,8 +69,10 @@ def test_pointwise(dtype, n, h, w, c, k):
     assert ((st.double().sum(0) - want).abs() <= 1e-5 * scale).all()
 
 
-# windows: main, slab, held and window kernels, a stride grid, the first layer
-WINDOWS = [(3, 211, 213, 64, 64, 3, 1), (5, 211, 213, 32, 64, 3, 1), (2, 301, 299, 64, 320, 3, 1), (2, 301, 299, 12, 200, 3, 1), (9, 130, 122, 128, 256, 1, 2),
+WINDOWS = [(160, 56, 56, 64, 64, 3, 1), (200, 56, 56, 32, 64, 3, 1), (3, 601, 603, 32, 64, 3, 1), (12, 211, 213, 32, 64, 3, 1),     # held, slab, main 256x64 and 128x64
+           (12, 211, 213, 64, 64, 3, 1), (5, 301, 299, 64, 128, 3, 1), (3, 301, 299, 136, 128, 3, 1),                            # 128x64, 128x128, pieces
+           (32, 130, 122, 128, 512, 1, 2), (64, 130, 122, 128, 128, 3, 2), (41, 224, 224, 3, 64, 7, 2),                          # stride grid, phases, the first layer
+           (3, 211, 213, 64, 64, 3, 1), (5, 211, 213, 32, 64, 3, 1), (2, 301, 299, 64, 320, 3, 1), (2, 301, 299, 12, 200, 3, 1), (9, 130, 122, 128, 256, 1, 2),
            (9, 130, 122, 40, 264, 1, 2), (11, 224, 224, 3, 64, 7, 2)]
 
 
