@@ -30,8 +30,8 @@ __global__ void zero16_kernel(uint4* __restrict__ dst, size_t count) {
 // Zeros in the pixels of [images * h][w] that are not on a stride grid (row % sh == 0 and column % sw == 0), one 16-byte vector a thread in address
 // order; `chunks` blocks take a row of `vecs` vectors, `groups` vectors a pixel.  Bound by how fast blocks start: the three stride grids of the ResNet-50 step
 // at 512 images (822, 411 and 206 MB) take 59 us in the mean with blocks of 256, 101 with 64, 70 with 512, 74 with four vectors a thread.  Clearing them whole
-// takes 61, but leaves lines in the caches that go to memory while the product's kernel runs, a quarter of them to be written again: the three passes of
-// 512 to 1024 1x1 over every other pixel of 256 fp32 images of 28x28 1081 -> 1012 and 1070 -> 1024 us on two cards, of which other changes are 26.
+// takes 61, but leaves lines in the caches that go to memory while the product's kernel runs, a quarter of them to be written again: the three passes of 512 to 1024 1x1 over
+// every other pixel of 256 fp32 images of 28x28 1054 to 1072 -> 1001 to 1010 us, of which 34 are the filter gradient's.  Past the caches (where the caller says: zeros_stream() of conv_api.hip).
 struct OffGrid {
     int h, sh, sw, vecs, groups;
     unsigned chunks, c_mul, c_shift, h_mul, h_shift, sh_mul, sh_shift, sw_mul, sw_shift, g_mul, g_shift;
