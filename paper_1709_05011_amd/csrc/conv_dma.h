@@ -628,10 +628,11 @@ bool conv_dma_plan(const GemmConv& p, bool any_rows, ConvDmaPlan* out) {
 }
 bool conv_dma_shares(const ConvDmaPlan& c) { return c.sk.sk_iters != (long long)c.sk.sk_blocks * c.nkt; }
 
-// kOnce: kChunks with the rows past the caches.  Each is read once -- a 1x1 window, one tile of columns -- and the memory-side cache does not hold the image (us, 512 to 128
-// at 28x28, 512 images 105 / 102, 256 to 64 at 56x56 188 / 182).  Windows and further tiles of columns read them again: 3x3 over 128 channels 130 / 167, 256 to 1024 at 14x14 72 / 82.
+// kOnce: kChunks with the rows past the caches.  Each is read once -- a 1x1 window, one tile of columns -- and the memory-side cache does not hold the image (us, ordinary loads / so: 512 to 128
+// at 28x28, 512 images 105 / 102, 256 to 64 at 56x56 192 / 184, 512 to 64 at 28x28 99 / 90, 1024 to 128, 2048 images of 14x14 186 / 175; tiles of 256 columns within 1 %).  Windows and further tiles of columns read them
+// again: 3x3 over 128 channels 130 / 167, 256 to 1024 at 14x14 72 / 82.  A single k-step has nothing to be ahead of: 64 to 32, 512 of 112x112 241 / 249, to 64, 800 of 56x56 127.4 / 126.3, to 256 292 / 295.
 // (An instance of its own: the choice within the loop cost windows 1 to 2 %.)
-bool conv_dma_once(const GemmConv& p, int bn) { return p.N <= bn && p.R * p.S == 1 && !p.scatter && ((p.N | p.ldd) & 7) == 0 && (double)p.M * p.Ci * 2 >= 256e6; }
+bool conv_dma_once(const GemmConv& p, int bn) { return p.N <= bn && p.R * p.S == 1 && p.Ci > 64 && !p.scatter && ((p.N | p.ldd) & 7) == 0 && (double)p.M * p.Ci * 2 >= 256e6; }
 
 // Blocks that have a compute unit each, and eight k-steps and more: four stages in flight, and 128x128 tiles by eight waves.  One block alone waits for its own loads, which take longer than a k-step's
 // products where they come from beyond its L2, and with one wave a SIMD for every read of LDS.  The same sums.  us, two stages / four, forward and backward-data, 24 sets of tensors in turn: 512 to 512

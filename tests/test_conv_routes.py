@@ -186,3 +186,10 @@ def test_filter_gradients_round_the_splits():
                                    ((256, 56, 200, 72, 1), ""), ((512, 28, 512, 128, 1), "")):
         m = re.fullmatch(r"wgrad_dma (\d+x\d+) splits \d+ sums \d+ ?(.*)", gu.route(_layer(n, c, hw, k, r), lc.LC_PASS_BWD_WEIGHT, form=True))
         assert m and m[2] == form, (n, hw, c, k, r, m and m[0])
+
+
+@pytest.mark.parametrize("d,once", [(_layer(512, 512, 28, 128), True), (_layer(512, 256, 56, 64), True), (_layer(512, 64, 112, 32), False), (_layer(800, 64, 56, 64), False),
+                                    (_layer(512, 128, 28, 128, 3), False), (_layer(256, 512, 28, 128), False), (_layer(512, 512, 28, 512), False)], ids=str)
+def test_rows_read_once_come_past_the_caches(d, once):
+    """Images of 256 MB and more under a 1x1 window of two k-steps and more, one tile of columns."""
+    assert (" once" in gu.route(d, lc.LC_PASS_FWD, form=True)) == once
