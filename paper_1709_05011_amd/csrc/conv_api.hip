@@ -916,7 +916,9 @@ extern "C" int lc_selftest_conv_route(const lc_conv_desc* d, int pass, int stats
         return lc_selftest_conv_route(&f, pass, stats, text, size);
     }
     if (stem_direct(d, pl, (lc_pass)pass)) {
-        snprintf(text, size, pass == LC_PASS_FWD ? "conv_stem" : "conv_stem_wgrad");
+        const double x = (double)d->n * d->h * d->w * d->c * pl.esize, y = (double)d->n * pl.P * pl.Q * d->k * pl.esize;
+        const bool past = (stats & 2) && pass == LC_PASS_FWD && lc_stream_first_layer(y, x, nullptr, (size_t)d->k * pl.esize);
+        snprintf(text, size, "%s%s", pass == LC_PASS_FWD ? "conv_stem" : "conv_stem_wgrad", past ? " past" : "");
     } else if (pass == LC_PASS_BWD_WEIGHT) {
         GemmWgrad g = gemm_wgrad(d, pl);
         g.splits = pl.splits;

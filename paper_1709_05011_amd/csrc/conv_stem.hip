@@ -593,7 +593,7 @@ lc_status lc_launch_conv_stem_wgrad_bf16(const StemWgradBf16& p, int blocks, hip
 lc_status lc_launch_conv_stem_bf16(const StemConvBf16& q, hipStream_t stream) {
     using namespace stemb;
     StemConvBf16 p = q;
-    p.stream_y = lc_stream_out((double)p.imgs * p.P * p.Q * N * 2, p.y, N * 2);
+    p.stream_y = lc_stream_first_layer((double)p.imgs * p.P * p.Q * N * 2, (double)p.imgs * p.H * p.W * 6, p.y, N * 2);
     constexpr size_t lds = (size_t)(N * BP + 2 * SLAB) * 2;
     if (p.P % TH != 0 || p.Q % TW != 0) return LC_ERR_UNSUPPORTED;
     if ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.w)) & 1 || reinterpret_cast<uintptr_t>(p.y) & 3) return LC_ERR_ALIGN;
@@ -605,7 +605,7 @@ lc_status lc_launch_conv_stem_bf16(const StemConvBf16& q, hipStream_t stream) {
 lc_status lc_launch_conv_stem_f32(const StemConv& q, hipStream_t stream) {
     using namespace stem;
     StemConv p = q;
-    p.stream_y = lc_stream_out((double)p.imgs * p.P * p.Q * N * 4, p.y, N * 4);
+    p.stream_y = lc_stream_first_layer((double)p.imgs * p.P * p.Q * N * 4, (double)p.imgs * p.H * p.W * 12, p.y, N * 4);
     constexpr size_t lds = (size_t)(KP * N + 2 * SLAB) * 4;
     static bool once = [] {
         return hipFuncSetAttribute(reinterpret_cast<const void*>(conv_stem_f32_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) ==

@@ -129,6 +129,9 @@ constexpr double kStreamCopyBytes = 256e6;
 inline int lc_stream_out(double bytes, const void* d, size_t row_bytes, double least = kStreamOutBytes) {
     return bytes >= least && row_bytes % 128 == 0 && (reinterpret_cast<uintptr_t>(d) & 127) == 0;
 }
+// The same for the first layer, as long as its images leave room in the memory-side cache: they are what gains by staying there (bf16, us, ordinary / past the caches, two sets in turn, then five: 64 images
+// 39 / 38 and 46 / 38, 128 86 / 67 and 86 / 66, 256 169 / 125 and 161 / 160, 512, 154 MB, 318 / 321 and 315 / 322; fp32 within 1 % from 16 to 256 images; whole steps the same either way).
+inline int lc_stream_first_layer(double y_bytes, double x_bytes, const void* y, size_t row_bytes) { return x_bytes <= 128e6 && lc_stream_out(y_bytes, y, row_bytes); }
 lc_status lc_launch_conv_gemm(const GemmConv& p, hipStream_t stream);
 size_t lc_conv_gemm_stats_tiles(const GemmConv& p);   // row pieces of `stats` for this problem; 0: the kernel that takes it has none
 extern "C" int lc_selftest_stream_k(int max_blocks);   // host check of the work split's 32-bit form (0 = all good)
@@ -165,7 +168,7 @@ struct StemConv {
     float* y;           // [imgs][P][Q][64]
     float* stats;       // [pieces][64][2] (sum, sum of squares per piece of 64 pixels) or null
     int imgs, H, W, P, Q;
-    int stream_y;       // lc_stream_out(): set by the launcher
+    int stream_y;       // lc_stream_first_layer(): set by the launcher
 };
 struct StemConvBf16 {
     const uint16_t* x;  // [imgs][H][W][3]

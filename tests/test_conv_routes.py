@@ -118,6 +118,9 @@ def _layer(n, c, hw, k, r=1, stride=1, dtype=lc.LC_BF16, layout=lc.LC_NHWC):
     (_layer(512, 128, 28, 512, layout=lc.LC_NCHW), True, False),        # 411 MB, 103 MB
     (_layer(256, 128, 28, 512, dtype=lc.LC_F32, layout=lc.LC_NCHW), True, False),
     (_layer(256, 128, 28, 512, dtype=lc.LC_F32), True, True),
+    (_layer(256, 3, 224, 64, 7, 2), True, False),                       # the first layer, images of 77, 154 and 5 MB
+    (_layer(512, 3, 224, 64, 7, 2), False, False),
+    (_layer(16, 3, 224, 64, 7, 2), False, False),
 ], ids=str)
 def test_results_that_go_past_the_caches(d, fwd, bwd):
     assert gu.route(d, lc.LC_PASS_FWD, form=True).endswith(" past") == fwd
@@ -171,10 +174,10 @@ def test_shapes_past_the_caches_meet_every_form():
     want |= {("fwd", f"conv_dma {t} chunks once{p}") for t, p in (("128x64 two waves", ""), ("128x128", ""), ("128x32", ""), ("256x256", " past"))}
     want |= {("bwd", "conv_dma 128x32 chunks once"), ("bwd", "conv_dma 128x128 chunks once past")}
     want |= {("fwd", f"{f} past") for f in ("conv3x3_held", "conv3x3_slab", "conv_gemm_pk 256x64", "conv_gemm_pk 128x64", "conv_dma 128x64 two waves chunks", "conv_dma 128x128 chunks",
-                                            "conv_dma 128x128 pieces", "conv_dma 256x256 chunks", "conv_dma 224x256 chunks", "conv_dma 240x256 chunks", "conv_dma 224x256 pieces")}
+                                            "conv_dma 128x128 pieces", "conv_dma 256x256 chunks", "conv_dma 224x256 chunks", "conv_dma 240x256 chunks", "conv_dma 224x256 pieces", "conv_stem")}
     want |= {("bwd", "conv3x3_held past"), ("bwd", "conv_dma 128x128 chunks past, zeros past"), ("phases", "conv_dma 128x128 chunks past")}
     assert not want - seen[lc.LC_BF16], want - seen[lc.LC_BF16]
-    want = {("fwd", "conv_gemm_pk 128x64 past"), ("fwd", "conv_gemm_pk 128x128 past"), ("bwd", "conv_gemm_split past"), ("bwd", "conv_gemm_split past, zeros past"),
+    want = {("fwd", "conv_stem past"), ("fwd", "conv_gemm_pk 128x64 past"), ("fwd", "conv_gemm_pk 128x128 past"), ("bwd", "conv_gemm_split past"), ("bwd", "conv_gemm_split past, zeros past"),
             ("phases", "conv_gemm_split past")}
     assert not want - seen[lc.LC_F32], want - seen[lc.LC_F32]
 
